@@ -73,10 +73,11 @@ typedef struct {
                                 2: own masks up to 3 tokens, the union from 4 tokens on (there the union is ~90 % of the
                                 channels anyway, its columns are loaded either way, and using them for every token is
                                 strictly more accurate at the same bytes) */
-    int32_t dense_rowmajor;  /* 1: also keep W row-major on the device (doubles the weight footprint).  Needed by
-                                the row-dot kernel of rsparse_dense_ref and by the matrix-core path that
-                                rsparse_linear takes from 5 tokens on (see mfma_min_batch); without it those
-                                batches run in tiles of up to 8 tokens on the vector ALU */
+    int32_t dense_rowmajor;  /* 1: also keep W row by row on the device, in the matrix cores' operand layout (doubles the
+                                weight footprint; layers under 2^22 weights keep a plain row-major copy besides).  Needed by
+                                the matrix-core path that rsparse_linear takes from 5 tokens on and rsparse_dense_ref at
+                                any batch (see mfma_min_batch), and by the row-dot kernel; without it batches from 5 tokens on
+                                run in tiles of up to 8 tokens on the vector ALU */
     int32_t strip_cols;      /* layout of W on the device for the vector path (up to 8 tokens per batch tile).  0: column-major
                                 (Sec. 3.4), run by the column-tile kernel: tiles of 512 outputs x channel splits whose partial
                                 sums meet in fp32 atomics.  32, 64, 128, 256 or 512: the columns are cut into strips of that
@@ -108,7 +109,8 @@ typedef struct {
     int32_t splits;          /* channel splits per column tile of the gather / dense-axpy kernels */
     int32_t waves;           /* waves (of 64 lanes) per workgroup in those kernels: 1, 2, 4 or 8 */
     int32_t lowrank_rows;    /* rows of S_r V_r^T per stage-1 workgroup */
-    int32_t dense_kernel;    /* rsparse_dense_ref: 0 auto, 1 axpy over column-major W, 2 row-dot */
+    int32_t dense_kernel;    /* rsparse_dense_ref: 0 auto, 1 axpy over column-major W, 2 row-dot (matrix cores on layers of
+                                2^22 weights or more) */
     int32_t nontemporal;     /* weight loads of the vector-path kernels: 0 default (non-temporal), 1 non-temporal,
                                 2 ordinary (temporal) loads */
     int32_t stages;          /* rsparse_linear, two-launch form: 0 the whole layer, 1 first launch only, 2 second
@@ -116,10 +118,12 @@ typedef struct {
     int32_t tile_map;        /* workgroup -> (column tile, split) mapping: 0 default, 1 tile-fastest (plain),
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix-core path (needs dense_rowmajor = 1):
-                                0 = default (5 for rsparse_linear; 2 for rsparse_dense_ref, 4 on layers of 2^25 weights or more), 33 = never (all batches
+                                0 = default (5 for rsparse_linear; for rsparse_dense_ref 1, 2 on layers under 2^22 weights, and
+                                with dense_kernel set 2, 4 on layers of 2^25 weights or more), 33 = never (all batches
                                 then run in tiles of up to 8 tokens on the vector ALU) */
-    int32_t mfma_rows;       /* output rows per workgroup of the matrix-core kernels: 0 default, or 64, 128, 256 */
-    int32_t launches;        /* rsparse_linear up to 8 tokens (and beyond without the row-major copy): 0 default
+    int32_t mfma_rows;       /* output rows per workgroup of the matrix-core kernels: 0 default (16; 32 above 16 tokens where
+                                that still fills the chip), or 64, 128, 256 (32 above 16 tokens whatever the layer) */
+    int32_t launches;        /* rsparse_linear: 0 default
                                 (one launch; two on 4-bit weights), 1 one launch, 2 two launches (stage 2 and the
                                 rounding in a second kernel).  stages != 0 implies two launches */
     int32_t lowrank_wgs;     /* stage-1 workgroups of the channel-major form (cfg.lowrank_channel_major): 0 default (64, or 128

@@ -121,6 +121,22 @@ void transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst)
     });
 }
 
+// The smallest 16-bit pattern p in [0, infinity's] with value(p) >= bound, 0x7fff if there is none (NaN bound); for a
+// signed threshold the smallest such x as a two's complement number (x = -p for the pattern p of a negative value).
+// Values order like these numbers, so `value >= bound` is exactly `number >= result` for everything but NaN.
+int16_t smallest_kept_pattern(float bound, int dtype, bool keep_signed)
+{
+    const int inf = dtype == RSPARSE_F16 ? 0x7c00 : 0x7f80;
+    auto kept = [&](int v) { return (v < 0 ? -widen16((uint16_t)-v, dtype) : widen16((uint16_t)v, dtype)) >= bound; };
+    int lo = keep_signed ? -inf : 0, hi = inf;
+    if (!kept(hi)) return 0x7fff;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (kept(mid)) hi = mid; else lo = mid + 1;
+    }
+    return (int16_t)lo;
+}
+
 }  // namespace
 
 struct rsparse_layer {
@@ -129,6 +145,7 @@ struct rsparse_layer {
     int device = 0;
     int cus = 256;
     uint16_t *M = nullptr, *SVt = nullptr, *U = nullptr, *Wrow = nullptr;
+    uint16_t *Wtile = nullptr, *SVtile = nullptr, *Utile = nullptr;   // matrix-core operands (dense_rowmajor = 1)
     uint16_t *Ms = nullptr;                // strip-major W + U_r^T: [strips][d_in + rank][strip_w]
     int strip_w = 0, strips = 0;
     long long strip_stride = 0;
@@ -140,12 +157,12 @@ struct rsparse_layer {
     float *t = nullptr, *yacc = nullptr;
     uint16_t *SVc = nullptr;               // [d_in][rank] channel-major copy of S_r V_r^T (cfg.lowrank_channel_major)
     float *t_sum = nullptr;                // [rank] fp32 sums of the stage 1 that reads it (zero between calls)
-    float *t_acc = nullptr;                // [rank][32] accumulated t of the matrix-core path (zero between calls)
-    uint16_t *t16 = nullptr;               // [2][32][rank] its two 16-bit halves
+    float *t_acc = nullptr;                // fp32 sums of t of the matrix-core path (zero between calls)
+    void *t16 = nullptr;                   // t of the matrix-core path: two 16-bit halves in operand layout
     uint32_t *act_bits = nullptr, *chan_bits = nullptr;
     bool last_mfma = false;
     int32_t *act_list = nullptr, *act_count = nullptr;
-    int *sync = nullptr;
+    int *sync = nullptr, *t_flags = nullptr;   // t_flags: inside sync
     uint32_t *t_pub = nullptr;
     ScratchView last_scratch{};            // the per-call scratch the last call used: the handle's own, or the static one
     uint16_t *hy = nullptr;                // [max_batch][d_out] 16-bit output scratch (gate / up results of rsparse_mlp_gate_up's fallback)
@@ -176,13 +193,19 @@ struct rsparse_layer {
         return sp;
     }
 
+    MatrixView matrix(const LayerView &v) const
+    {
+        if (!Wtile) return MatrixView{};
+        return MatrixView{Wtile, SVtile, Utile, t16, t_acc, t_flags, smallest_kept_pattern(v.tau_ge, cfg.dtype, v.keep_signed != 0)};
+    }
+
     // The view of one call: `batch` decides the mask mode when the configuration leaves it to the library; the dense
     // baseline gets no bias and no fixed-count rules.
     LayerView view(const ScratchView *ov = nullptr, int batch = 1, bool dense = false) const
     {
         const ScratchView sp = ov ? *ov : own_scratch();
         LayerView v{};
-        v.M = M; v.SVt = SVt; v.U = U; v.Wrow = Wrow; v.t = sp.t; v.yacc = sp.yacc; v.t_acc = ov ? nullptr : t_acc; v.SVc = SVc; v.t_sum = ov ? nullptr : t_sum; v.t16 = ov ? nullptr : t16;
+        v.M = M; v.SVt = SVt; v.U = U; v.Wrow = Wrow; v.t = sp.t; v.yacc = sp.yacc; v.SVc = SVc; v.t_sum = ov ? nullptr : t_sum;
         v.act_list = sp.act_list; v.act_bits = sp.act_bits; v.act_count = sp.act_count; v.sync = sp.sync; v.t_pub = sp.t_pub;
         v.d_in = cfg.d_in; v.d_out = cfg.d_out; v.rank = cfg.rank;
         v.dtype = cfg.dtype; v.out_dtype = cfg.out_dtype; v.cmp_mode = cfg.cmp_mode;
@@ -202,6 +225,10 @@ struct rsparse_layer {
 };
 
 namespace {
+
+// Layers below this many weights keep W row-major beside the operand layout (dense_rowmajor = 1): the row-dot kernel is
+// the faster dense kernel there at one token (rsparse_dense_ref_group).
+constexpr size_t kRowdotWeights = (size_t)1 << 22;
 
 int batch_tile_of(int batch) { return batch <= 1 ? 1 : batch <= 2 ? 2 : batch <= 4 ? 4 : 8; }
 
@@ -365,10 +392,19 @@ void free_layer(rsparse_layer *L)
     (void)hipFree(L->M); (void)hipFree(L->SVt); (void)hipFree(L->U); (void)hipFree(L->Wrow); (void)hipFree(L->t);
     (void)hipFree(L->yacc); (void)hipFree(L->act_bits); (void)hipFree(L->chan_bits);
     (void)hipFree(L->act_list); (void)hipFree(L->act_count); (void)hipFree(L->sync); (void)hipFree(L->t_pub); (void)hipFree(L->xg); (void)hipFree(L->hy);
-    (void)hipFree(L->Ms); (void)hipFree(L->t_tag); (void)hipFree(L->act_seg); (void)hipFree(L->bias); (void)hipFree(L->rules); (void)hipFree(L->t_acc); (void)hipFree(L->SVc); (void)hipFree(L->t_sum); (void)hipFree(L->t16);
+    (void)hipFree(L->Wtile); (void)hipFree(L->SVtile); (void)hipFree(L->Utile);
+    (void)hipFree(L->Ms); (void)hipFree(L->t_tag); (void)hipFree(L->act_seg); (void)hipFree(L->bias); (void)hipFree(L->rules); (void)hipFree(L->SVc); (void)hipFree(L->t_sum); (void)hipFree(L->t16); (void)hipFree(L->t_acc);
     (void)hipFree(L->Mq); (void)hipFree(L->qs); (void)hipFree(L->qz); (void)hipFree(L->Ut);
     (void)hipFree(L->Qrow); (void)hipFree(L->Srow); (void)hipFree(L->Zrow);
     delete L;
+}
+
+// A row-major 16-bit matrix (device) in the matrix cores' operand layout; rows padded to a multiple of row_pad (16 or 32).
+rsparse_status make_operand(const uint16_t *src_dev, size_t rows, size_t cols, size_t row_pad, uint16_t **out)
+{
+    RS_HIP(hipMalloc((void **)out, mfma_operand_bytes(rows, cols, row_pad)));
+    RS_HIP(launch_pack_operand(src_dev, rows, cols, row_pad, *out, nullptr));
+    return RSPARSE_OK;
 }
 
 // 4-bit weights as the caller hands them over (rsparse_prepare_q4); all host pointers.
@@ -399,12 +435,16 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
 
         // pack W column-major: row c of M = W[:, c]; rows d_in.. = U_r^T (row d_in + j = U_r[:, j]), which the
         // one-launch kernel streams as r more channels
+        // (with dense_rowmajor W is uploaded row by row anyway, and M is transposed from there on the device)
+        const bool on_device = !q4 && cfg->dense_rowmajor && cfg->strip_cols == 0 && (d_out + 63) / 64 <= 65535;
         std::vector<uint16_t> host;
         try {
-            if (!q4) host.resize((d_in + r) * d_out);
+            if (!q4 && !on_device) host.resize((d_in + r) * d_out);
             if (r) { L->U16.assign(U16, U16 + d_out * r); L->SV16.assign(SV16, SV16 + r * d_in); }
         } catch (const std::bad_alloc &) { return fail(RSPARSE_ENOMEM, "host allocation failed"); }
-        if (!q4) {
+        if (on_device) {
+            RS_HIP(hipMalloc((void **)&L->M, (d_in + r) * d_out * 2));
+        } else if (!q4) {
             transpose16(W, d_out, d_in, host.data());
             if (r) transpose16(U16, d_out, r, host.data() + d_in * d_out);
             if (cfg->strip_cols == 0) {
@@ -502,20 +542,31 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         if (cfg->dense_rowmajor && !q4) {
             RS_HIP(hipMalloc((void **)&L->Wrow, d_in * d_out * 2));
             RS_HIP(hipMemcpy(L->Wrow, W, d_in * d_out * 2, hipMemcpyHostToDevice));
+            rsparse_status ts = make_operand(L->Wrow, d_out, d_in, 16, &L->Wtile);
+            if (ts == RSPARSE_OK && r) ts = make_operand(L->SVt, r, d_in, 32, &L->SVtile);
+            if (ts == RSPARSE_OK && r) ts = make_operand(L->U, d_out, r, 16, &L->Utile);
+            if (ts != RSPARSE_OK) return ts;
+            if (on_device) {
+                RS_HIP(launch_transpose16(L->Wrow, d_out, d_in, L->M, nullptr));
+                if (r) RS_HIP(launch_transpose16(L->U, d_out, r, L->M + d_in * d_out, nullptr));
+            }
+            if (d_in * d_out >= kRowdotWeights) {
+                RS_HIP(hipDeviceSynchronize());
+                RS_HIP(hipFree(L->Wrow));
+                L->Wrow = nullptr;
+            }
         }
         if (cfg->dense_rowmajor && !q4 && r) {
-            RS_HIP(hipMalloc((void **)&L->t_acc, (size_t)32 * r * 4));
-            RS_HIP(hipMemset(L->t_acc, 0, (size_t)32 * r * 4));
-            RS_HIP(hipMalloc((void **)&L->t16, (size_t)2 * 32 * r * 2));
-            RS_HIP(hipMemset(L->t16, 0, (size_t)2 * 32 * r * 2));
+            RS_HIP(hipMalloc(&L->t16, mfma_t_bytes((int)r)));
+            RS_HIP(hipMemset(L->t16, 0, mfma_t_bytes((int)r)));
+            RS_HIP(hipMalloc((void **)&L->t_acc, (r + 31) / 32 * 32 * 32 * 4));
+            RS_HIP(hipMemset(L->t_acc, 0, (r + 31) / 32 * 32 * 32 * 4));
         }
         RS_HIP(hipMalloc((void **)&L->xg, (size_t)cfg->max_batch * d_in * 2));
         RS_HIP(hipMalloc((void **)&L->hy, (size_t)cfg->max_batch * d_out * 2));
         const size_t bpad = (size_t)L->nz_max * kMaxBT;
         const size_t n_t = std::max<size_t>(1, r * bpad);
-        // the matrix-core kernels keep these accumulators as [d_out][16 or 32 tokens]
-        const size_t n_y = (size_t)(cfg->dense_rowmajor ? std::max(cfg->max_batch, cfg->max_batch > 16 ? 32 : 16)
-                                                          : cfg->max_batch) * d_out;
+        const size_t n_y = (size_t)cfg->max_batch * d_out;
         L->n_y = n_y;
         const size_t n_list = (size_t)L->nz_max * d_in;
         RS_HIP(hipMalloc((void **)&L->t, n_t * 4));
@@ -526,9 +577,11 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->chan_bits, d_in * 4));
         RS_HIP(hipMalloc((void **)&L->rules, (size_t)cfg->max_batch * sizeof(KeepRule)));
         RS_HIP(hipMemset(L->rules, 0, (size_t)cfg->max_batch * sizeof(KeepRule)));
-        L->sync_n = sync_words(std::max(L->tiles, L->strips));
+        const size_t flags_at = (sync_words(std::max(L->tiles, L->strips)) + 31) / 32 * 32;
+        L->sync_n = flags_at + (cfg->dense_rowmajor && !q4 && r ? t_flag_words((int)r) : 0);
         RS_HIP(hipMalloc((void **)&L->sync, L->sync_n * 4));
         RS_HIP(hipMemset(L->sync, 0, L->sync_n * 4));
+        L->t_flags = L->sync + flags_at;
         {
             const int one = 1;                        // generation 1: no entry of t_tag (all zero) carries it
             RS_HIP(hipMemcpy(L->sync + kSyncGen, &one, 4, hipMemcpyHostToDevice));
@@ -800,8 +853,10 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         lc[i] = resolve_launch(layers[i], batch, false, n_layers, i ? lc[0].waves : 0, fused, launch_weights);
         layers[i]->last_scratch = ov ? *ov : layers[i]->own_scratch();
     }
+    MatrixView mv[RSPARSE_MAX_GROUP];
+    for (int i = 0; i < n_layers; ++i) mv[i] = layers[i]->matrix(v[i]);
     bool mfma = !ov && batch >= (layers[0]->tuning.mfma_min_batch > 0 ? layers[0]->tuning.mfma_min_batch : kMfmaDefaultMinBatch);
-    for (int i = 0; i < n_layers; ++i) mfma = mfma && mfma_path_supported(v[i], batch) && layers[i]->cfg.topk == 0;
+    for (int i = 0; i < n_layers; ++i) mfma = mfma && mfma_path_supported(mv[i], batch) && layers[i]->cfg.topk == 0;
     // a gated input is written out once first (one small launch), then the layer runs on it
     if (G_dev) {
         RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
@@ -847,9 +902,15 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         return RSPARSE_OK;
     }
     if (mfma) {
-        // matrix-core path, one layer at a time (each is already a full-chip launch)
-        for (int i = 0; i < n_layers; ++i)
-            RS_HIP(launch_mfma_linear(v[i], X_dev, batch, Y_devs[i], layers[i]->chan_bits, layers[i]->cus, stages, false, layers[0]->tuning.mfma_rows, s));
+        uint32_t *bits[RSPARSE_MAX_GROUP];
+        for (int i = 0; i < n_layers; ++i) bits[i] = layers[i]->chan_bits;
+        const rsparse_tuning &t = layers[0]->tuning;
+        if (fused) {
+            RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 3, false, t.mfma_rows, t.debug_wait_polls, t.debug_skip_stage1, s));
+        } else {
+            if (stages != 2) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 1, false, t.mfma_rows, 0, 0, s));
+            if (stages != 1) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, false, t.mfma_rows, 0, 0, s));
+        }
     } else if (fused) {
         RS_HIP(launch_fused(v, lc, n_layers, X_dev, batch, Y_devs, s));
     } else {
@@ -860,7 +921,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         layers[i]->last_stream = s;
         layers[i]->last_batch = batch;
         layers[i]->last_mfma = mfma;
-        layers[i]->last_fused = !mfma && fused;
+        layers[i]->last_fused = fused;
         layers[i]->last_bt = 0;
         layers[i]->last_strip = false;
     }
@@ -889,7 +950,7 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
                                (size_t)pair[0]->cfg.d_in * pair[0]->cfg.d_out + (size_t)pair[1]->cfg.d_in * pair[1]->cfg.d_out);
     }
     bool mfma = batch >= (gate->tuning.mfma_min_batch > 0 ? gate->tuning.mfma_min_batch : kMfmaDefaultMinBatch);
-    for (int i = 0; i < 2; ++i) mfma = mfma && mfma_path_supported(v[i], batch) && pair[i]->cfg.topk == 0;
+    for (int i = 0; i < 2; ++i) mfma = mfma && mfma_path_supported(pair[i]->matrix(v[i]), batch) && pair[i]->cfg.topk == 0;
     const int bt = batch_tile_of(batch);
     const bool one_tile = (batch + bt - 1) / bt == 1;
     if (fused && !mfma && one_tile && lc[0].tile_map != 2 && lc[1].tile_map != 2 && gate->M && up->M) {
@@ -968,24 +1029,36 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     for (int i = 0; i < n_layers; ++i) {
         v[i] = layers[i]->view(nullptr, batch, true);
         lc[i] = resolve_launch(layers[i], batch, true, n_layers, i ? lc[0].waves : 0);
-        can_rowdot = can_rowdot && layers[i]->Wrow != nullptr && rowdot_supported(layers[i]->cfg.d_in, batch);
+        can_rowdot = can_rowdot && layers[i]->Wtile != nullptr && rowdot_supported(layers[i]->cfg.d_in, batch);
     }
-    // the dense baseline moves to the matrix cores from 2 tokens on small layers and from 4 on large ones
-    // (measured: 4096 x 11008 and 8192 x 8192 are still faster on the vector path at 2-3 tokens)
+    // The dense product runs on the matrix cores at every batch (measured, us, vector ALU -> matrix cores: 4096 x 4096 9.2
+    // -> 8.7 at one token and 15.0 -> 8.7 at two, 8192 x 8192 25.8 -> 24.1 and 32.9 -> 24.2, 28672 -> 8192 86 -> 75 and 90
+    // -> 76; errors against 64 bits alike), except one token on layers that keep the row-major copy for the row-dot
+    // kernel (1024 x 1024 3.5 against 4.3, 2048 x 2048 both 5.2).  A kernel asked for by name gets the batches it had.
     const bool large = (size_t)layers[0]->cfg.d_in * layers[0]->cfg.d_out >= ((size_t)1 << 25);
+    bool all_rowdot = can_rowdot;
+    for (int i = 0; i < n_layers; ++i) all_rowdot = all_rowdot && layers[i]->Wrow != nullptr;
+    const int asked = layers[0]->tuning.dense_kernel;
     bool mfma = batch >= (layers[0]->tuning.mfma_min_batch > 0 ? layers[0]->tuning.mfma_min_batch
-                                                                 : (large ? 4 : kMfmaDefaultMinBatchDense));
-    for (int i = 0; i < n_layers; ++i) mfma = mfma && mfma_path_supported(v[i], batch);
+                          : asked != 0                         ? (large ? 4 : kMfmaDefaultMinBatchDense)
+                          : all_rowdot                         ? 2
+                                                               : 1);
+    // (the row-dot kernel reads rows: on layers without the row-major copy the matrix cores stand in for it)
+    if (asked == 2 && can_rowdot && !all_rowdot) mfma = true;
+    MatrixView mv[RSPARSE_MAX_GROUP];
+    for (int i = 0; i < n_layers; ++i) {
+        mv[i] = layers[i]->matrix(v[i]);
+        mfma = mfma && mfma_path_supported(mv[i], batch);
+    }
     if (mfma) {
-        for (int i = 0; i < n_layers; ++i)
-            RS_HIP(launch_mfma_linear(v[i], X_dev, batch, Y_devs[i], layers[i]->chan_bits, layers[i]->cus, 0, true, layers[0]->tuning.mfma_rows, s));
+        RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, nullptr, layers[0]->cus, 3, true, layers[0]->tuning.mfma_rows, 0, 0, s));
         return RSPARSE_OK;
     }
     int kernel = layers[0]->tuning.dense_kernel;
     if (kernel == 2 && !can_rowdot)
         return fail(RSPARSE_EINVAL, "row-dot dense kernel needs dense_rowmajor=1 and batch_tile*d_in*2 <= 64 KiB");
     // row dots win for short rows; for long rows (and for more than one token) the axpy form streams better
-    if (kernel == 0) kernel = (can_rowdot && layers[0]->cfg.d_in <= 8192 && batch == 1) ? 2 : 1;
+    if (kernel == 0) kernel = (all_rowdot && layers[0]->cfg.d_in <= 8192 && batch == 1) ? 2 : 1;
     bool strip = true, colmajor = true;
     for (int i = 0; i < n_layers; ++i) {
         strip = strip && layers[i]->Ms != nullptr && layers[i]->strip_w == layers[0]->strip_w;

@@ -33,8 +33,6 @@ struct LayerView {
     float *t_sum;           // [nz][BT][rank] fp32 sums of the stage 1 that reads SVc; zero between calls (or nullptr)
     const uint16_t *Wrow;   // [d_out][d_in] row-major copy of W, or nullptr
     float *t;               // [nz][BT][rank] stage-1 result, fp32
-    float *t_acc;           // [rank][16 or 32 tokens] matrix-core path: t summed over the K slices; zero between calls (or nullptr)
-    uint16_t *t16;          // [2][32][rank] matrix-core path: t split into two 16-bit halves, [token][rank] each (or nullptr)
     float *yacc;            // [max_batch][d_out] fp32 accumulators; zero between calls
     int32_t *act_list;      // [nz][d_in] ascending kept channels of batch tile z (union over its tokens)
     uint32_t *act_bits;     // [nz][d_in] per list entry: bit b = token b of the tile keeps it
@@ -76,6 +74,17 @@ hipError_t launch_q4_dense_rowdot(const uint8_t *Qrow, const uint16_t *Srow, con
 // Fixed-count activation: per token of X [batch][d_in] the KeepRule that keeps exactly min(k, non-NaN channels)
 // channels of largest magnitude (ties: lower channel first).  One workgroup per token.
 hipError_t launch_topk_rules(const void *X, int dtype, int batch, int d_in, int k, KeepRule *rules, hipStream_t stream);
+
+// What the matrix-core path holds of a layer beside LayerView (all null without it).  Operand layout of a matrix: [block of
+// 16 rows][step of 32 columns][64 lanes][16 bytes], lane l of a tile = columns 8 (l / 16) .. + 7 of row l % 16; rows and
+// columns past the matrix are zero.
+struct MatrixView {
+    const uint16_t *W, *SVt, *U;   // W [d_out][d_in], S_r V_r^T [rank rounded up to 32][d_in], U_r [d_out][rank]
+    void *t;                       // t as two 16-bit halves, mfma_t_bytes(rank)
+    float *t_acc;                  // fp32 sums of t, [32 tokens][rank rounded up to 32]; zero between calls
+    int *t_flags;                  // [t_flag_words(rank)]; zero between calls
+    int16_t keep_min;              // LayerView::tau_ge as the smallest kept 16-bit pattern of |x| (keep_signed: of x, as a two's complement number)
+};
 
 // Per-call scratch of a layer: what the kernels write besides Y.  Normally owned by the handle (allocated when the
 // layer is prepared); rsparse_linear_static points it into a file-scope device array instead.
@@ -122,6 +131,12 @@ constexpr int kSyncStartedN = 256;
 constexpr int kSyncMaxZ = 4;        // batch tiles per launch
 constexpr int kSyncTile = kSyncStarted + kSyncStartedN;   // [nz][tiles] channel splits of the tile that have added their sums
 inline size_t sync_words(int tiles) { return (size_t)kSyncTile + (size_t)kSyncMaxZ * tiles; }
+// Matrix-core path, MatrixView::t_flags (32-bit words; every part starts a 128-byte line of its own): a flag per block of 16
+// rank indices (its t is stored), an arrival counter per block (K slices), kTReadSubs counters a line apart of the units of
+// W that have read all of t, and how many of those counters are complete.
+constexpr int kTReadSubs = 32;
+__host__ __device__ inline int t_flag_pitch(int rank) { return (rank + 511) / 512 * 32; }
+inline size_t t_flag_words(int rank) { return 2 * (size_t)t_flag_pitch(rank) + 32 * kTReadSubs + 32; }
 
 // All launchers take a group of n <= kMaxGroupLayers layers that read the same input X (same d_in and
 // dtype); cfg[0].waves and cfg[0].nontemporal apply to the whole launch.
@@ -154,13 +169,19 @@ hipError_t launch_dense_axpy(const LayerView *L, const Launch *cfg, int n, const
                              hipStream_t stream);
 hipError_t launch_dense_rowdot(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
                                hipStream_t stream);
-// Matrix-core path for 2 <= batch <= 32 (needs the row-major copy of W): both launches of one layer.
-// chan_bits [d_in] receives, per channel, the bit mask of the tokens that keep it.  stages as in
-// rsparse_tuning.  Zeroes L.t with a fill kernel first (its stage-1 partial sums meet in atomics).
-// dense = the dense baseline Y = X W^T through the same kernels (no masks, no low-rank part).
-bool mfma_path_supported(const LayerView &L, int batch);
-hipError_t launch_mfma_linear(const LayerView &L, const void *X, int batch, void *Y, uint32_t *chan_bits, int cus,
-                              int stages, bool dense, int rows_per_wg_hint, hipStream_t stream);
+// Matrix-core path for up to 32 tokens over the row-major copy of W: n layers that read the same input in one launch.
+// chan_bits[i] [d_in] receives, per channel, the bit mask of the tokens that keep it.  phases: 3 = the whole call (t is
+// handed over inside the launch through t_flags); 1 = t only, 2 = the rest, as launches of their own.
+// dense = the dense product Y = X W^T through the same kernel (no masks, no low-rank part).
+bool mfma_path_supported(const MatrixView &M, int batch);
+size_t mfma_t_bytes(int rank);
+// A row-major matrix [rows][cols] (device; cols a multiple of 8) in operand layout, rows padded to row_pad (16 or 32).
+size_t mfma_operand_bytes(size_t rows, size_t cols, size_t row_pad);
+hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, size_t row_pad, uint16_t *dst, hipStream_t stream);
+// dst [cols][rows] = transpose of src [rows][cols], 16-bit, both multiples of 8 (device).
+hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream);
+hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
+                       int phases, bool dense, int rows_per_wg_hint, int wait_polls, int skip_stage1, hipStream_t stream);
 // The whole layer over strip-major weights (LayerView::Ms), up to 8 tokens per batch tile: one workgroup per strip
 // of strip_w output columns streams all kept rows of the strip and stores its slice of Y (cfg[i].splits == 1), or
 // `splits` workgroups per strip meet in yacc.  fused: stage 1 runs in the same launch and hands t over through
@@ -178,9 +199,6 @@ int strip_list_cap(int d_in, int rank, int splits, int waves, int bt, int strip_
 bool strip_width_ok(int w);
 // out[0:n) = round16(silu(G) * Up), n a multiple of 8, all 16-byte aligned.
 hipError_t launch_gated_input(const void *G, const void *Up, void *out, size_t n, int dtype, hipStream_t stream);
-// Zero `n` 32-bit words (a fill kernel, safe to record into a HIP graph).
-hipError_t launch_zero(void *p, size_t n_words, hipStream_t stream);
-
 size_t gather_lds_bytes(int d_in, int splits, int waves, int bt, int fused_rank = 0);
 size_t lowrank_lds_bytes(int d_in, int bt);
 bool rowdot_supported(int d_in, int batch);

@@ -1153,13 +1153,6 @@ __global__ __launch_bounds__(256) void k_dense_rowdot(const RowdotGroupArgs ga)
     }
 }
 
-__global__ void k_zero(uint32_t *p, size_t n)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = 0u;
-}
-
 int batch_tile(int batch)
 {
     if (batch <= 1) return 1;
@@ -1505,15 +1498,6 @@ hipError_t launch_gated_input(const void *G, const void *Up, void *out, size_t n
     else
         hipLaunchKernelGGL(k_gated_input<BF16>, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint16_t *)G,
                            (const uint16_t *)Up, (uint16_t *)out, n8);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero(void *p, size_t n_words, hipStream_t stream)
-{
-    if (n_words == 0) return hipSuccess;
-    size_t blocks = (n_words + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, stream, (uint32_t *)p, n_words);
     return hipGetLastError();
 }
 

@@ -1,31 +1,35 @@
-// gfx950 matrix-core path of the R-Sparse linear layer for batch > 8 (R-Sparse, Sec. 3.4).
+// gfx950 matrix-core path of the R-Sparse linear layer (R-Sparse, Sec. 3.4) for 5 to 32 tokens, and of the dense product
+// for 1 to 32, over a copy of W in operand layout (dense_rowmajor = 1).
 //
-// At 16-32 tokens the union of kept channels is ~all of them (measured 99.5 % at 16 tokens with
-// 50 % per-token sparsity), and 2*B flops per weight byte is more than the vector ALU sustains
-// at HBM speed, so all three products become skinny GEMMs on MFMA, still one pass over the
-// weights:
+// At 5 tokens and more the union of kept channels is nearly all of them and 2*B flops per weight byte is more than the
+// vector ALU sustains at HBM speed, so all three products are skinny GEMMs on MFMA, still one pass over the weights:
 //
 //   Y_s = (X (.) m)  W^T            rows of W   [d_out][d_in] row-major  (dense, per-token masks in X)
 //   t   = (X (.) !m) (S_r V_r^T)^T  rows of SVt [r][d_in]
 //   Y   = round(Y_s + t U_r^T)      rows of U   [d_out][r]
 //
-// All three weight matrices are stored "output row major, contraction index contiguous", which is
-// exactly the operand layout of v_mfma_f32_16x16x32_{bf16,f16}: lane l supplies 8 consecutive k
+// Operands of v_mfma_f32_16x16x32_{bf16,f16}: lane l supplies 8 consecutive k
 // (one 16-byte load) of row l%16 at k-group l/16.  A = 16 weight rows x 32 k, B = 32 k x 16
-// tokens (from LDS), D[row][token] fp32: lane l, register j holds row 4*(l/16)+j, token l%16.
+// tokens, D[row][token] fp32: lane l, register j holds row 4*(l/16)+j, token l%16.
 //
-// Launch 1 (k_mfma_sparse_and_t): grid = (row groups of W + row groups of SVt) x K slices; a row group is a balanced
-// share of the matrix's 16-row blocks, the number of groups such that the grid is two rounds of one workgroup per
-// compute unit.  A workgroup stages the masked tokens of ITS K slice once (kept part for W rows, dropped part for SVt
-// rows; the slice is sized to fill the 64 KiB of LDS a workgroup may use) and then streams all its 16-row blocks
-// against it with no further barrier: eight 16-byte weight loads per lane and batch, two batches in flight, a block's
-// D tile in registers until its slice is done, then added to yacc / t_acc (both [row][16 or 32 tokens]) with fp32
-// atomics (one add per K slice and output; stored directly when there is one slice).
-// Between the launches (k_mfma_split_t): t_acc -> two 16-bit halves hi + lo (so the contraction keeps ~16 mantissa
-// bits of the fp32 t), [token][rank]; t_acc re-zeroed.
-// Launch 2 (k_mfma_finish): D = U_r t from the staged halves, Y = round(yacc + D + bias), yacc re-zeroed.
+// ONE launch per call (a group of layers that read the same input shares it).  The matrices are kept in that operand
+// layout (MatrixView), so that a wave's load is 1 KiB of consecutive bytes; from row-major rows it is 16 pieces of
+// 64 bytes a row pitch apart, which the first-level cache drops half-used (8192 x 8192, 32 tokens: 74 us against 51).
+// A unit is 16 * NB rows of W over the WHOLE contraction, owned by one workgroup whose waves take its batches of loads in
+// turn: no sum of outputs crosses workgroups, so there are no atomics on outputs, no accumulators in memory, no second
+// launch.  Bound by HBM: the tokens come from L2, change to the operand layout through the wave's own LDS and are masked
+// there in their 16-bit patterns (five packed integer operations per two values); the waves' D tiles meet in LDS once.
+// The first workgroups of the grid take t, a (block of 16 rank indices, K slice) each, and wait for nothing; the last
+// slice of a block splits the sums into two 16-bit halves (hi + lo, ~16 mantissa bits of the fp32 t) and stores them in
+// operand layout with write-through stores, waits for these to be acknowledged and sets the block's flag.  A unit of W
+// waits for the flags (bounded) when its rows are done and adds U_r t.  The t buffer is read with ordinary loads: its
+// lines are first touched in a launch by readers that have seen the flags, so no older copy of them is in a cache.
+// Measured (us per call, before: a first launch with sums over K slices in fp32 atomics, a split launch and a finish
+// launch): 8192 x 8192 r 1024 60.3 -> 41.7 at 32 tokens, 53.1 -> 34.7 at 8; 4096 x 4096 r 256 23.1 -> 14.6 at 8; dense
+// 4096 -> 14336 (two) and back 93.1 -> 71.1 at 16.
 #include "kernels.h"
 #include "device_common.h"
+#include "device_stage1.h"
 
 #include <algorithm>
 
@@ -35,10 +39,13 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kMfmaK = 32;        // contraction depth of one MFMA
-constexpr int kMfmaUnroll = 8;    // weight loads in flight per lane
-constexpr int kRowsPerBlock = 16;
+// MFMA steps of one batch of loads, for units of NB blocks.  Measured on plain streams of this shape (512 workgroups of
+// 8 waves, 134 MB): two batches of 4 KiB per wave in flight 6.3 TB/s, of 8 KiB 5.6, of 16 KiB 4.5 -- more requests than
+// the memory system takes only push each other out.
+template <int NB> struct StepsOf { static constexpr int value = NB == 1 ? 4 : 2; };
 
 template <int DT>
 __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
@@ -50,440 +57,605 @@ __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x
 
 template <int DT>
 __device__ __forceinline__ uint16_t narrow(float f) { return DT == F16 ? to_f16(f) : to_bf16(f); }
-template <int DT>
-__device__ __forceinline__ float widen(uint16_t h)
-{
-    return DT == F16 ? (float)__builtin_bit_cast(_Float16, h) : as_f((uint32_t)h << 16);
-}
-
-struct MfmaArgs {
-    LayerView L;
-    const uint16_t *X;
-    int batch, tok_pad;          // tokens, padded to 16 or 32
-    int ks;                      // K slice staged in LDS, multiple of 32 * kMfmaUnroll
-    int k_slices;
-    int w_chunks, t_chunks;      // row groups of W and of SVt (balanced shares of their 16-row blocks);
-                                 // grid.x = (w_chunks + t_chunks) * k_slices
-    uint32_t *chan_bits;         // [d_in] bit b = token b keeps the channel (read-back)
-    int dense;                   // 1: dense baseline -- every channel kept, no masks, no stage 1
-};
-
-constexpr int kStageBatch = 8;      // 16-byte token loads in flight per thread while staging
-
-// One batch of weight loads of a 16-row block: kMfmaUnroll steps of 32 k, starting at step s0.
-__device__ __forceinline__ void load_a_batch(const uint16_t *__restrict__ rowptr, bool row_ok, int klen, int s0, int kg,
-                                             u32x4 (&v)[kMfmaUnroll])
-{
-#pragma unroll
-    for (int u = 0; u < kMfmaUnroll; ++u) {
-        const int k = (s0 + u) * kMfmaK + kg;
-        v[u] = (row_ok && k < klen) ? *reinterpret_cast<const u32x4 *>(rowptr + k) : u32x4{0, 0, 0, 0};
-    }
-}
-
-template <int DT>
-__device__ __forceinline__ void mfma_a_batch(const u32x4 (&v)[kMfmaUnroll], int s0, const unsigned char *b_lo,
-                                             const unsigned char *b_hi, bool two, f32x4 &acc0, f32x4 &acc1)
-{
-#pragma unroll
-    for (int u = 0; u < kMfmaUnroll; ++u) {
-        const size_t off = (size_t)(s0 + u) * kMfmaK * 2;
-        acc0 = mfma16<DT>(v[u], *reinterpret_cast<const u32x4 *>(b_lo + off), acc0);
-        if (two) acc1 = mfma16<DT>(v[u], *reinterpret_cast<const u32x4 *>(b_hi + off), acc1);
-    }
-}
-
-template <int DT>
-__global__ __launch_bounds__(256) void k_mfma_sparse_and_t(const MfmaArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const LayerView &L = a.L;
-    const int d_in = L.d_in;
-    const int ksl = blockIdx.x % a.k_slices;
-    int rc = blockIdx.x / a.k_slices;
-    const bool is_t = rc >= a.w_chunks;
-    if (is_t) rc -= a.w_chunks;
-    const int nq = a.ks / 8;                            // 16-byte pieces per token in the slice
-    const int pitch = a.ks * 2 + 16;                    // odd multiple of 16 bytes: conflict-free B reads
-    unsigned char *s_act = smem;                        // [tok_pad][pitch]
-    const bool union_all = L.batch_mask_mode == 1 && !a.dense;
-    const bool publish = !is_t && rc == 0 && !a.dense;  // these workgroups cover every channel once
-    const int k0 = ksl * a.ks;
-    const int klen = min(a.ks, d_in - k0);              // > 0 by construction of k_slices
-    const uint32_t all_tokens = a.batch >= 32 ? 0xffffffffu : ((1u << a.batch) - 1u);
-    // the layer's threshold as a rule (the fixed-count activation never takes this path: its rules are per token)
-    const KeepRule thr = {L.tau_ge, __builtin_nanf(""), -1, 0};
-
-    // ---- per-channel keep bits of every token: needed for the union mask and for read-back
-    uint32_t *s_bits = reinterpret_cast<uint32_t *>(smem + (size_t)a.tok_pad * pitch);   // [ks]
-    if (union_all || publish) {
-        for (int i = tid; i < a.ks; i += 256) s_bits[i] = 0u;
-        __syncthreads();
-        for (int q = tid; q < a.tok_pad * nq; q += 256) {
-            const int tok = q / nq, kq = q % nq;
-            if (tok < a.batch && kq * 8 < klen) {
-                float f[8];
-                unpack8<DT>(*reinterpret_cast<const u32x4 *>(a.X + (size_t)tok * d_in + k0 + kq * 8), f);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (keep(f[e], k0 + kq * 8 + e, thr, L.keep_signed != 0)) atomicOr(&s_bits[kq * 8 + e], 1u << tok);
-            }
-        }
-        __syncthreads();
-        if (publish)
-            for (int i = tid; i < klen; i += 256) a.chan_bits[k0 + i] = union_all && s_bits[i] ? all_tokens : s_bits[i];
-    }
-
-    // ---- stage the kept part (W rows) or the dropped part (SVt rows) of every token, once.
-    //      All of a round's loads are issued before the first is used (one L2 round trip per round).
-    const int total = a.tok_pad * nq;
-    for (int q0 = tid; q0 < total; q0 += 256 * kStageBatch) {
-        u32x4 raw[kStageBatch];
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int q = q0 + u * 256;
-            const int tok = q / nq, kq = q % nq;
-            raw[u] = (q < total && tok < a.batch && kq * 8 < klen)
-                         ? *reinterpret_cast<const u32x4 *>(a.X + (size_t)tok * d_in + k0 + kq * 8)
-                         : u32x4{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int u = 0; u < kStageBatch; ++u) {
-            const int q = q0 + u * 256;
-            if (q < total) {
-                const int tok = q / nq, kq = q % nq;
-                u32x4 o = raw[u];
-                if (!a.dense) {
-                    float f[8];
-                    unpack8<DT>(o, f);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const bool kept = union_all ? s_bits[kq * 8 + e] != 0u : keep(f[e], k0 + kq * 8 + e, thr, L.keep_signed != 0);
-                        if (kept == is_t) o[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;   // not this part's
-                    }
-                }
-                *reinterpret_cast<u32x4 *>(s_act + (size_t)tok * pitch + kq * 16) = o;
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- stream my 16-row blocks against the staged slice: no barrier from here on
-    const uint16_t *Mat = is_t ? L.SVt : L.Wrow;
-    const int nrows = is_t ? L.rank : L.d_out;
-    float *out = is_t ? L.t_acc : L.yacc;               // both [row][tok_pad]
-    const int kg = (lane >> 4) * 8;
-    const unsigned char *b_lo = s_act + (size_t)(lane & 15) * pitch + kg * 2;
-    const unsigned char *b_hi = b_lo + (size_t)16 * pitch;
-    const bool two = a.tok_pad > 16;
-    const bool direct = a.k_slices == 1;
-    const int tok = lane & 15;
-    const int bpb = a.ks / (kMfmaK * kMfmaUnroll);      // batches per block
-    // my balanced share of the matrix's 16-row blocks: the first (blocks % groups) groups hold one block more
-    const int nblk = (nrows + kRowsPerBlock - 1) / kRowsPerBlock, ngrp = is_t ? a.t_chunks : a.w_chunks;
-    const int bbase = nblk / ngrp, brem = nblk % ngrp;
-    const int blk_lo = rc * bbase + min(rc, brem);
-    const int blocks = bbase + (rc < brem ? 1 : 0);     // >= 1: the host keeps groups <= blocks
-    const int row_base = blk_lo * kRowsPerBlock;
-    const int my_blocks = blocks > w ? (blocks - w + 3) / 4 : 0;                                     // blocks w, w+4, ...
-    const int n_batches = my_blocks * bpb;
-
-    auto row_of = [&](int batch_i, const uint16_t *&rowptr, bool &row_ok) {
-        const int row = row_base + (w + 4 * (batch_i / bpb)) * kRowsPerBlock + (lane & 15);
-        row_ok = row < nrows;
-        rowptr = Mat + (size_t)(row_ok ? row : 0) * d_in + k0;
-    };
-    auto flush = [&](int batch_i, f32x4 &acc0, f32x4 &acc1) {
-        const int row0 = row_base + (w + 4 * (batch_i / bpb)) * kRowsPerBlock;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int orow = row0 + 4 * (lane >> 4) + j;
-            if (orow < nrows) {
-                // the accumulators of Y and of t are [row][tok_pad], so that the 16 lanes of one D register hit one
-                // 64-byte run instead of 16 lines (t used to be [token][rank]: 64 separate lines per atomic
-                // instruction, and the few workgroups that own the rows of S_r V_r^T finished last)
-                float *p0 = out + (size_t)orow * a.tok_pad + tok;
-                float *p1 = p0 + 16;
-                if (direct) {
-                    if (tok < a.batch) *p0 = acc0[j];
-                    if (tok + 16 < a.batch) *p1 = acc1[j];
-                } else {
-                    if (tok < a.batch) __hip_atomic_fetch_add(p0, acc0[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (tok + 16 < a.batch) __hip_atomic_fetch_add(p1, acc1[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-        }
-        acc0 = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-    };
-
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    u32x4 va[kMfmaUnroll], vb[kMfmaUnroll];
-    const uint16_t *rowptr;
-    bool row_ok;
-    if (n_batches > 0) {
-        row_of(0, rowptr, row_ok);
-        load_a_batch(rowptr, row_ok, klen, 0, kg, va);
-    }
-    for (int i = 0; i < n_batches; i += 2) {
-        if (i + 1 < n_batches) {
-            row_of(i + 1, rowptr, row_ok);
-            load_a_batch(rowptr, row_ok, klen, ((i + 1) % bpb) * kMfmaUnroll, kg, vb);
-        }
-        mfma_a_batch<DT>(va, (i % bpb) * kMfmaUnroll, b_lo, b_hi, two, acc0, acc1);
-        if (i % bpb == bpb - 1) flush(i, acc0, acc1);
-        if (i + 1 >= n_batches) break;
-        if (i + 2 < n_batches) {
-            row_of(i + 2, rowptr, row_ok);
-            load_a_batch(rowptr, row_ok, klen, ((i + 2) % bpb) * kMfmaUnroll, kg, va);
-        }
-        mfma_a_batch<DT>(vb, ((i + 1) % bpb) * kMfmaUnroll, b_lo, b_hi, two, acc0, acc1);
-        if ((i + 1) % bpb == bpb - 1) flush(i + 1, acc0, acc1);
-    }
-}
 
 // The lo half of t is stored scaled by a power of two (exact): in fp16 the remainder t - hi would otherwise fall into
 // the subnormals for |t| below ~0.1 and lose the bits it is there to keep.
 template <int DT> struct LoScale { static constexpr float value = DT == F16 ? 2048.0f : 1.0f; };
 
-// Between the two launches: t_acc [rank][tok_pad] fp32 (complete now: the launch that summed it has ended) ->
-// t_hi, t_lo [tok_pad][rank] in the storage type, t = hi + lo / scale, so that the contraction with U_r keeps ~16
-// mantissa bits of t; puts t_acc back to zero for the next call.  One thread per (rank index, four tokens).
-template <int DT>
-__global__ __launch_bounds__(256) void k_mfma_split_t(float *t_acc, int rank, int tok_pad, uint16_t *t_hi, uint16_t *t_lo)
-{
-    const int q = tok_pad / 4;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= rank * q) return;
-    const int k = i / q, tok0 = (i % q) * 4;
-    float4 *src = reinterpret_cast<float4 *>(t_acc + (size_t)k * tok_pad + tok0);
-    const float4 v4 = *src;
-    *src = float4{0.f, 0.f, 0.f, 0.f};
-    const float v[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint16_t hi = narrow<DT>(v[e]);
-        const uint16_t lo = narrow<DT>((v[e] - widen<DT>(hi)) * LoScale<DT>::value);
-        t_hi[(size_t)(tok0 + e) * rank + k] = hi;
-        t_lo[(size_t)(tok0 + e) * rank + k] = lo;
-    }
-}
-
-struct MfmaFinishArgs {
-    LayerView L;
-    void *Y;
-    int batch, tok_pad;
-    int use_rank;
-    const uint16_t *t_hi, *t_lo; // [tok_pad][rank] each: t = hi + lo / kLoScale in the storage type (k_mfma_split_t)
+// ---------------------------------------------------------------------------------------------
+// The sparsification function on packed 16-bit patterns.  Magnitudes order like their patterns, so |x| >= t is
+// pattern(|x|) >= pattern_min (host-computed, exact), signed thresholds compare the sign-magnitude pattern as a two's
+// complement number, and NaN patterns lie above infinity's.
+// ---------------------------------------------------------------------------------------------
+struct KeepPattern {
+    uint32_t min2, inf2;       // smallest kept pattern and infinity's, each twice
 };
 
-// Second launch: Y = round(yacc + U_r t + bias).  One wave = one 16-row block of U_r, a workgroup = 64 output rows.
-// t arrives already split into its two 16-bit halves (k_mfma_split_t) and is staged through LDS in chunks of 256 rank
-// indices (the MFMA B operand of all four waves); nothing a chunk needs depends on what the kernel computes, so the
-// U_r loads run three chunks ahead and the t loads one chunk ahead, the latter issued BEFORE the former so that they
-// do not queue behind them (loads return in order).
-// Tried and dropped: both operands straight from memory, no LDS -- the 128 KiB of t do not stay in the first-level
-// cache and every workgroup's re-reads went to L2: 20 us instead of 14 us at 8192 x 1024, 60 instead of 23 us at
-// 28672 x 1024 (32 tokens).
-template <int DT>
-__global__ __launch_bounds__(256) void k_mfma_finish(const MfmaFinishArgs a)
+// 0xffff in every half of x that the token DROPS.
+template <bool SIGNED>
+__device__ __forceinline__ uint32_t dropped2(uint32_t x, const KeepPattern &kp)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const LayerView &L = a.L;
-    const int d_out = L.d_out, r = a.use_rank;
-    constexpr int RC = kMfmaK * kMfmaUnroll;                         // rank indices per chunk: one batch of U loads per lane
-    const int pitch = RC * 2 + 16;
-    unsigned char *s_hi = smem, *s_lo = smem + (size_t)a.tok_pad * pitch;
-    const int row0 = (blockIdx.x * 4 + w) * kRowsPerBlock;
-    const int row = row0 + (lane & 15);
-    const bool row_ok = row < d_out;
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};    // the lo halves' products, scaled by kLoScale
-    constexpr float kLoScale = LoScale<DT>::value;
-    const int kg = (lane >> 4) * 8;
-    const size_t lane_off = (size_t)(lane & 15) * pitch + kg * 2;
-    const bool two = a.tok_pad > 16;
-    const uint16_t *urow = L.U + (size_t)(row_ok ? row : 0) * r;
-    const int rc8 = RC / 8, total8 = a.tok_pad * rc8;                // 16-byte pieces of one staged chunk (per half)
-    constexpr int kTV = 4;                                           // pieces per thread and half: 32 tokens x 256 / 8 / 256 threads
-    u32x4 th[kTV], tl[kTV];
-    auto request_t = [&](int c0) {
-        const int clen = min(RC, r - c0);
-#pragma unroll
-        for (int u = 0; u < kTV; ++u) {
-            const int i = tid + u * 256;
-            const int tok = i / rc8, k = (i % rc8) * 8;
-            const bool ok = i < total8 && k < clen;                  // rows of tokens past the batch hold zeros
-            th[u] = ok ? *reinterpret_cast<const u32x4 *>(a.t_hi + (size_t)tok * r + c0 + k) : u32x4{0, 0, 0, 0};
-            tl[u] = ok ? *reinterpret_cast<const u32x4 *>(a.t_lo + (size_t)tok * r + c0 + k) : u32x4{0, 0, 0, 0};
-        }
-    };
-    auto stage_t = [&]() {
-#pragma unroll
-        for (int u = 0; u < kTV; ++u) {
-            const int i = tid + u * 256;
-            if (i < total8) {
-                const int tok = i / rc8, k = (i % rc8) * 8;
-                *reinterpret_cast<u32x4 *>(s_hi + (size_t)tok * pitch + k * 2) = th[u];
-                *reinterpret_cast<u32x4 *>(s_lo + (size_t)tok * pitch + k * 2) = tl[u];
-            }
-        }
-    };
-    auto both_halves = [&](const u32x4 (&v)[kMfmaUnroll]) {
-        mfma_a_batch<DT>(v, 0, s_hi + lane_off, s_hi + lane_off + (size_t)16 * pitch, two, acc0, acc1);
-        mfma_a_batch<DT>(v, 0, s_lo + lane_off, s_lo + lane_off + (size_t)16 * pitch, two, lo0, lo1);
-    };
-    // the epilogue's inputs do not depend on the products either: requested first
-    const int orow = row0 + 4 * (lane >> 4);
-    float ya[2][4];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int tok = (lane & 15) + 16 * half;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            ya[half][j] = (orow + j < d_out && tok < a.batch) ? L.yacc[(size_t)(orow + j) * a.tok_pad + tok] : 0.f;
+    const s16x2 mag = __builtin_bit_cast(s16x2, x & 0x7fff7fffu);
+    s16x2 key = mag;
+    if (SIGNED) {
+        const s16x2 sgn = __builtin_bit_cast(s16x2, x) >> 15;
+        key = (mag ^ sgn) - sgn;
     }
-    const int nch = (r + RC - 1) / RC;
-    u32x4 ua[4][kMfmaUnroll];                                        // ring of U batches, chunk c in slot c % 4
+    const s16x2 below = __builtin_elementwise_sub_sat(key, __builtin_bit_cast(s16x2, kp.min2));
+    const s16x2 nan = __builtin_bit_cast(s16x2, kp.inf2) - mag;
+    return __builtin_bit_cast(uint32_t, (s16x2)((below | nan) >> 15));
+}
+
+__device__ __forceinline__ uint32_t and_over_16_lanes(uint32_t v)
+{
+    constexpr int kRowRor = 0x120;
+    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 8, 0xf, 0xf, false);
+    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 4, 0xf, 0xf, false);
+    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 2, 0xf, 0xf, false);
+    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 1, 0xf, 0xf, false);
+    return v;
+}
+
+// All of this wave's earlier atomics and stores have been performed.
+__device__ __forceinline__ void wait_own_writes()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
+constexpr int kMaskNone = 0, kMaskOwn = 1, kMaskUnion = 2;   // MfmaJob::mask_mode
+constexpr int kMaskSigned = 4;                               // ... + the rule applies to x itself
+
+// The part of the tokens a unit works on: kept values (want = 0) or dropped ones (want = ~0), the others zeroed.
+// Frags of one step: NF token tiles of 16; with the union mask a channel counts as kept if any token keeps it (lanes
+// past the batch hold a copy of its last token).
+template <int NF, int MODE>
+__device__ __forceinline__ void mask_step(u32x4 (&b)[NF], const KeepPattern &kp, uint32_t want)
+{
+    if (MODE == kMaskNone) return;
+    uint32_t d[NF][4];
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        if (c < nch) load_a_batch(urow + c * RC, row_ok, min(RC, r - c * RC), 0, kg, ua[c]);
-    if (nch > 0) request_t(0);
-    for (int c0 = 0; c0 < nch; c0 += 4) {
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[f][i] = dropped2<(MODE & kMaskSigned) != 0>(b[f][i], kp);
+    if (MODE & kMaskUnion) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int c = c0 + i;
-            if (c < nch) {                                           // wave-uniform
-                if (c > 0) __syncthreads();                          // every wave has read the chunk before
-                stage_t();
-                __syncthreads();
-                if (c + 1 < nch) request_t((c + 1) * RC);
-                if (c + 3 < nch) load_a_batch(urow + (c + 3) * RC, row_ok, min(RC, r - (c + 3) * RC), 0, kg, ua[(i + 3) & 3]);
-                both_halves(ua[i]);
-            }
+            uint32_t all = d[0][i];
+#pragma unroll
+            for (int f = 1; f < NF; ++f) all &= d[f][i];
+            all = and_over_16_lanes(all);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) d[f][i] = all;
         }
     }
-    // lane l holds rows row0 + 4*(l/16) + 0..3 of token l%16 (and l%16 + 16): 4 consecutive outputs
-    if (orow < d_out) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int tok = (lane & 15) + 16 * half;
-            if (tok < a.batch) {
-                const f32x4 acc = half ? acc1 : acc0, lo = half ? lo1 : lo0;
-                float *yp = L.yacc + (size_t)orow * a.tok_pad + tok;          // [row][tok_pad], see launch 1
-                float o[4];
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    o[j] = ya[half][j] + acc[j] + lo[j] * (1.0f / kLoScale) + (orow + j < d_out ? bias_at(L, orow + j) : 0.f);
-                const size_t oi = (size_t)tok * d_out + orow;
-                if (L.out_dtype == F32) {
-                    *reinterpret_cast<float4 *>((float *)a.Y + oi) = float4{o[0], o[1], o[2], o[3]};
-                } else {
-                    uint2 pk;
-                    pk.x = (uint32_t)narrow<DT>(o[0]) | ((uint32_t)narrow<DT>(o[1]) << 16);
-                    pk.y = (uint32_t)narrow<DT>(o[2]) | ((uint32_t)narrow<DT>(o[3]) << 16);
-                    *reinterpret_cast<uint2 *>((uint16_t *)a.Y + oi) = pk;
+        for (int i = 0; i < 4; ++i) b[f][i] &= ~(d[f][i] ^ want);
+}
+
+struct MfmaJob {
+    const uint16_t *W, *SVt, *U; // operand layout (MatrixView)
+    unsigned char *t;            // t in operand layout: [step of 32 rank indices][token tile][hi, lo][64 lanes][16 bytes]
+    float *t_acc;                // [block of 16 rank indices][token tile][4][64] fp32 sums of t's K slices, zero between calls
+    int *t_flags;                // a flag per block of t, zero between calls; then an arrival counter per block
+    void *Y;
+    const float *bias;
+    uint32_t *chan_bits;         // [d_in] bit b = token b keeps the channel (read-back), or nullptr
+    int *sync;
+    int d_out, rank;
+    int out_dtype, mask_mode;
+    KeepPattern kp;
+    int t_blocks, w_units;       // blocks of S_r V_r^T (0: no low-rank part), units of W
+};
+struct MfmaArgs {
+    MfmaJob job[kMaxGroupLayers];
+    int t_end[kMaxGroupLayers];  // t tasks (block, K slice) of jobs 0..i
+    int w_end[kMaxGroupLayers];  // units of W of jobs 0..i
+    const uint16_t *X;
+    int n, batch, d_in, t_slices;
+    int phases;                  // 1: t, 2: the units of W, 3: both in this launch (the units of W wait for t)
+    int wait_polls, skip_stage1;
+};
+
+// One batch of a wave: S steps of NB weight tiles (1 KiB each) and the same 32 * S channels of all tokens, 4 * S lanes to
+// a token.
+template <int NB, int NF>
+struct Batch {
+    static constexpr int S = StepsOf<NB>::value, K = kMfmaK * S, kLanes = 4 * S, kX = NF * S;
+    static constexpr int kPitch = K * 2 + 16;   // bytes of a token in LDS: the 16 tokens of a read hit 16 bank groups
+    u32x4 a[S][NB], x[kX];
+};
+
+// Weights are read once: non-temporal (8192 x 8192 at 32 tokens 51.7 against 54.7 us with ordinary loads).
+__device__ __forceinline__ u32x4 ld16(const unsigned char *p)
+{
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+}
+
+// Batch `bi` of the contraction (past its end: its last values again).
+template <int NB, int NF>
+__device__ __forceinline__ void load_batch(const unsigned char *__restrict__ mat, const size_t (&aoff)[NB], const unsigned char *__restrict__ x,
+                                           const uint32_t (&xoff)[Batch<NB, NF>::kX], int lane, int d_in, int steps, int bi,
+                                           Batch<NB, NF> &v)
+{
+    using B = Batch<NB, NF>;
+    const uint32_t k = (uint32_t)min(bi * B::K + lane % B::kLanes * 8, d_in - 8) * 2u;
+#pragma unroll
+    for (int j = 0; j < B::kX; ++j) v.x[j] = *reinterpret_cast<const u32x4 *>(x + (size_t)(xoff[j] + k));
+#pragma unroll
+    for (int u = 0; u < B::S; ++u) {
+        const int s = min(bi * B::S + u, steps - 1);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) v.a[u][i] = ld16(mat + aoff[i] + (size_t)s * 1024 + lane * 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);      // all of them are issued here, ahead of the batch that is used next
+}
+
+template <int DT, int NB, int NF, int MODE>
+__device__ __forceinline__ void use_batch(Batch<NB, NF> &v, unsigned char *sx, const KeepPattern &kp, uint32_t want, int lane,
+                                          int k_end, int bi, f32x4 (&acc)[NB][NF])
+{
+    using B = Batch<NB, NF>;
+    // the tokens change from kLanes lanes a token to the operand layout through this wave's own LDS
+    const bool in = bi * B::K + lane % B::kLanes * 8 < k_end;
+#pragma unroll
+    for (int j = 0; j < B::kX; ++j)
+        *reinterpret_cast<u32x4 *>(sx + (j * (64 / B::kLanes) + lane / B::kLanes) * B::kPitch + lane % B::kLanes * 16) =
+            in ? v.x[j] : u32x4{0, 0, 0, 0};
+    __builtin_amdgcn_wave_barrier();
+    f32x4 sum[NB][NF];
+#pragma unroll
+    for (int u = 0; u < B::S; ++u) {
+        u32x4 b[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            b[f] = *reinterpret_cast<const u32x4 *>(sx + (f * 16 + (lane & 15)) * B::kPitch + u * 64 + (lane >> 4) * 16);
+        mask_step<NF, MODE>(b, kp, want);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) sum[i][f] = mfma16<DT>(v.a[u][i], b[f], u ? sum[i][f] : f32x4{0.f, 0.f, 0.f, 0.f});
+    }
+    // a batch's sums are added to the task's with the vector ALU: the matrix cores' own long chains of sums lose bits
+    // (28672 channels: 3.8e-7 from the 64-bit result in one chain)
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[i][f] += sum[i][f];
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// A wave's batches bi, bi + nw, ... below `end`, two in flight: every load is unconditional (past the end it re-reads the
+// last values, against tokens of zeros), so that the compiler counts the outstanding ones exactly and waits for the
+// current batch alone.  The first batch is in va already.
+template <int DT, int NB, int NF, int MODE>
+__device__ __forceinline__ void stream_rows(const unsigned char *__restrict__ mat, const size_t (&aoff)[NB],
+                                            const unsigned char *__restrict__ x, const uint32_t (&xoff)[Batch<NB, NF>::kX], unsigned char *sx,
+                                            const KeepPattern &kp, uint32_t want, int lane, int d_in, int bi, int end, int nw,
+                                            Batch<NB, NF> &va, f32x4 (&acc)[NB][NF])
+{
+    const int steps = (d_in + kMfmaK - 1) / kMfmaK;
+    Batch<NB, NF> vb;
+    const int k_end = min(end * Batch<NB, NF>::K, d_in);
+    for (; bi < end; bi += 2 * nw) {
+        load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, bi + nw, vb);
+        use_batch<DT, NB, NF, MODE>(va, sx, kp, want, lane, k_end, bi, acc);
+        load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, bi + 2 * nw, va);
+        use_batch<DT, NB, NF, MODE>(vb, sx, kp, want, lane, k_end, bi + nw, acc);
+    }
+}
+
+template <int DT, int NB, int NF>
+__global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaArgs ga)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = uniform(tid >> 6), nw = uniform(nthr >> 6);
+    const int d_in = ga.d_in, batch = ga.batch;
+    using B = Batch<NB, NF>;
+    const int steps = (d_in + kMfmaK - 1) / kMfmaK, n_batches = (steps + B::S - 1) / B::S;
+    const size_t block_bytes = (size_t)steps * 1024;
+    const unsigned char *x = reinterpret_cast<const unsigned char *>(ga.X);
+    // tokens past the batch repeat its last one; their results are not used
+    uint32_t xoff[B::kX];
+#pragma unroll
+    for (int j = 0; j < B::kX; ++j) xoff[j] = (uint32_t)min(j * (64 / B::kLanes) + lane / B::kLanes, batch - 1) * (uint32_t)d_in * 2u;
+    constexpr int kTiles = NB * NF;
+    // a wave's LDS: its tokens' staging, and its D tiles when the waves meet
+    constexpr int kWaveLds = NF * 16 * B::kPitch > kTiles * 1024 ? NF * 16 * B::kPitch : kTiles * 1024;
+    unsigned char *sx = smem + (size_t)w * kWaveLds;
+
+    // the first t_wgs workgroups take a (block, K slice) of t each and wait for nothing; the others a unit of W each
+    const int t_wgs = ga.t_end[kMaxGroupLayers - 1] * (ga.phases & 1);
+    const bool is_t = (int)blockIdx.x < t_wgs;
+    const int first = is_t ? (int)blockIdx.x : (int)blockIdx.x - t_wgs;
+    int job = 0, begin = 0;
+#pragma unroll
+    for (int j = 0; j < kMaxGroupLayers - 1; ++j) {
+        const int e = is_t ? ga.t_end[j] : ga.w_end[j];
+        if (first >= e) { job = j + 1; begin = e; }
+    }
+    const MfmaJob &jb = ga.job[job];
+    const KeepPattern kp = jb.kp;
+    const int t_slices = ga.t_slices, slice = is_t ? (first - begin) % t_slices : 0;
+    const int unit = is_t ? (first - begin) / t_slices : first - begin;
+    const int lo = is_t ? (int)((unsigned)(n_batches * slice) / (unsigned)t_slices) : 0;
+    const int hi = is_t ? (int)((unsigned)(n_batches * (slice + 1)) / (unsigned)t_slices) : n_batches;
+    const int block0 = is_t ? unit : unit * NB, n_blocks = (jb.d_out + 15) / 16;
+    const unsigned char *mat = reinterpret_cast<const unsigned char *>(is_t ? jb.SVt : jb.W) + (size_t)block0 * block_bytes;
+    size_t aoff[NB];                                            // (blocks past the matrix: the last one again)
+#pragma unroll
+    for (int k = 0; k < NB; ++k) aoff[k] = is_t ? 0 : (size_t)min(k, n_blocks - 1 - block0) * block_bytes;
+
+    Batch<NB, NF> va;
+    load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, lo + w, va);
+
+    // ---- which tokens keep a channel, for read-back: the last wave, 16 channels at a time (a lane = a token)
+    if (!is_t && w == nw - 1) {
+        for (int j = 0; j < ga.n; ++j) {
+            const MfmaJob &pj = ga.job[j];
+            if (!pj.chan_bits) continue;
+            const KeepPattern pk = pj.kp;
+            const bool sgn = (pj.mask_mode & kMaskSigned) != 0;
+            for (int c0 = first * 16; c0 < d_in; c0 += ((int)gridDim.x - t_wgs) * 16) {
+                const int c = c0 + (lane >> 5) * 8, tok = lane & 31;
+                u32x4 v = u32x4{0, 0, 0, 0};
+                const bool in = c < d_in && tok < batch;
+                if (in) v = *reinterpret_cast<const u32x4 *>(ga.X + (size_t)tok * d_in + c);
+                const uint32_t all_tokens = batch >= 32 ? 0xffffffffu : (1u << batch) - 1u;
+                uint32_t mine = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t d = sgn ? dropped2<true>(v[i], pk) : dropped2<false>(v[i], pk);
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const unsigned long long m = __ballot(in && !((d >> (16 * e)) & 1u));
+                        const uint32_t half = lane < 32 ? (uint32_t)m : (uint32_t)(m >> 32);
+                        if ((lane & 31) == 2 * i + e) mine = half;
+                    }
                 }
+                if ((pj.mask_mode & kMaskUnion) && mine) mine = all_tokens;
+                if ((lane & 31) < 8 && c < d_in) pj.chan_bits[c + (lane & 31)] = mine;
+            }
+        }
+    }
+
+    f32x4 acc[NB][NF];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (orow + j < d_out) yp[(size_t)j * a.tok_pad] = 0.f;
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t want = is_t ? 0xffffffffu : 0u;
+#define RS_STREAM(MODE) stream_rows<DT, NB, NF, MODE>(mat, aoff, x, xoff, sx, kp, want, lane, d_in, lo + w, hi, nw, va, acc)
+    switch (jb.mask_mode) {
+    case kMaskNone: RS_STREAM(kMaskNone); break;
+    case kMaskOwn: RS_STREAM(kMaskOwn); break;
+    case kMaskUnion: RS_STREAM(kMaskUnion); break;
+    case kMaskOwn | kMaskSigned: RS_STREAM(kMaskOwn | kMaskSigned); break;
+    default: RS_STREAM(kMaskUnion | kMaskSigned); break;
+    }
+#undef RS_STREAM
+    const bool lowrank = !is_t && jb.t_blocks > 0, hand_off = lowrank && ga.phases == 3;
+
+    // the waves meet in LDS; sum_up adds up item (tile, lane)
+    auto meet = [&]() {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) *reinterpret_cast<f32x4 *>(sx + (i * NF + f) * 1024 + lane * 16) = acc[i][f];
+        __syncthreads();
+    };
+    auto sum_up = [&](int item) {
+        f32x4 s = *reinterpret_cast<const f32x4 *>(smem + item * 16);
+        for (int ww = 1; ww < nw; ++ww) s += *reinterpret_cast<const f32x4 *>(smem + (size_t)ww * kWaveLds + item * 16);
+        return s;
+    };
+
+    if (is_t) {
+        // ---- t: one wave sums the waves up; with several slices it adds to t_acc, and the last slice to arrive takes the
+        //      sums out again (which leaves zeros); they are split and published
+        meet();
+        if (w == 0) {
+            f32x4 s[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) s[f] = sum_up(f * 64 + lane);
+            bool mine = true;
+            if (ga.t_slices > 1) {
+                float *ta = jb.t_acc + (size_t)unit * NF * 256 + lane;
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        __hip_atomic_fetch_add(ta + f * 256 + j * 64, s[f][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                wait_own_writes();
+                int *ctr = jb.t_flags + t_flag_pitch(jb.rank) + unit;
+                int arrived = 0;
+                if (lane == 0) arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                mine = uniform(arrived) == ga.t_slices - 1;
+                if (mine) {
+                    if (lane == 0) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            s[f][j] = __hip_atomic_exchange(ta + f * 256 + j * 64, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
+            if (mine) {
+                const int row = unit * 16 + 4 * (lane >> 4);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    // rank indices row..row+3 of a token, in operand layout; entries past the rank are zero
+                    uint32_t hi[2] = {0, 0}, lw[2] = {0, 0};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float v = row < jb.rank ? s[f][e] : 0.f;
+                        const uint16_t hb = narrow<DT>(v);
+                        hi[e >> 1] |= (uint32_t)hb << (16 * (e & 1));
+                        lw[e >> 1] |= (uint32_t)narrow<DT>((v - widen16<DT>(hb)) * LoScale<DT>::value) << (16 * (e & 1));
+                    }
+                    const int r = row % kMfmaK;
+                    unsigned char *p = jb.t + (size_t)(row / kMfmaK * NF + f) * 2048 + (size_t)((r / 8) * 16 + (lane & 15)) * 16 + (r % 8) * 2;
+                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)hi[0] | ((unsigned long long)hi[1] << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p + 1024), (unsigned long long)lw[0] | ((unsigned long long)lw[1] << 32),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (ga.phases == 3) {
+                    wait_own_writes();                           // performed: now the block counts as ready
+                    if (lane == 0 && !ga.skip_stage1)
+                        __hip_atomic_store(jb.t_flags + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        return;
+    }
+
+    // ---- U_r t: the rank's steps of 32, one per wave in turn; the rows of U_r are requested before t is waited for
+    if (lowrank) {
+        f32x4 ah[NB][NF], al[NB][NF];                          // the products with t's hi and lo halves
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) ah[i][f] = al[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int usteps = (jb.rank + kMfmaK - 1) / kMfmaK;
+        const size_t ublock = (size_t)usteps * 1024;
+        const unsigned char *um = reinterpret_cast<const unsigned char *>(jb.U) + (size_t)block0 * ublock + lane * 16;
+        constexpr int US = NB * NF == 1 ? 4 : 2;
+        u32x4 ua[US][NB];
+        auto request_u = [&](int s0) {
+#pragma unroll
+            for (int u = 0; u < US; ++u) {
+                const int s = min(s0 + u * nw, usteps - 1);
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    ua[u][i] = ld16(um + min(i, n_blocks - 1 - block0) * ublock + (size_t)s * 1024);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request_u(w);
+        if (hand_off) {
+            // one wave looks at the flags (every block of t has one of its own: no read-modify-write, so nothing
+            // queues up on them), the others wait for it at the barrier
+            if (w == 0) {
+                const long long t0 = wall_clock64();
+                bool ok = false;
+                for (int polls = 0; polls < ga.wait_polls && !ok; ++polls) {
+                    ok = true;
+                    for (int i = lane; i < jb.t_blocks; i += 64)
+                        ok = ok && __hip_atomic_load(jb.t_flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                    ok = __all(ok);
+                    if (!ok) {
+                        __builtin_amdgcn_s_sleep(16);
+                        if (wall_clock64() - t0 > kWaitLimitTicks) break;
+                    }
+                }
+                if (!ok && lane == 0) __hip_atomic_store(jb.sync + kSyncError, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            __atomic_signal_fence(__ATOMIC_ACQUIRE);           // no load of t moves up here
+        }
+        for (int s0 = w; s0 < usteps; s0 += nw * US) {
+            u32x4 th[US][NF], tl[US][NF];
+#pragma unroll
+            for (int u = 0; u < US; ++u) {
+                const int s = min(s0 + u * nw, usteps - 1);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    const unsigned char *p = jb.t + (size_t)(s * NF + f) * 2048 + lane * 16;
+                    th[u][f] = *reinterpret_cast<const u32x4 *>(p);
+                    tl[u][f] = *reinterpret_cast<const u32x4 *>(p + 1024);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < US; ++u) {
+                if (s0 + u * nw < usteps) {
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) {
+                            ah[i][f] = mfma16<DT>(ua[u][i], th[u][f], ah[i][f]);
+                            al[i][f] = mfma16<DT>(ua[u][i], tl[u][f], al[i][f]);
+                        }
+                }
+            }
+            if (s0 + nw * US < usteps) request_u(s0 + nw * US);
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][f][j] += ah[i][f][j] + al[i][f][j] * (1.0f / LoScale<DT>::value);
+    }
+
+    meet();
+    // every wave of this workgroup has read t: count the unit, over kTReadSubs counters first, so that the units, which end
+    // together, do not queue up on one address (the answer is looked at after the stores)
+    const bool counted = hand_off && tid == 0;
+    const int sub = unit % kTReadSubs;
+    int *const t_read = jb.t_flags + 2 * t_flag_pitch(jb.rank);
+    int arrived = -1;
+    if (counted) arrived = __hip_atomic_fetch_add(t_read + sub * 32, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int item = tid; item < kTiles * 64; item += nthr) {
+        const int l = item & 63, tile = item >> 6, i = tile / NF, f = tile % NF;
+        const f32x4 s = sum_up(item);
+        const int tok = f * 16 + (l & 15);
+        const int row = (block0 + i) * 16 + 4 * (l >> 4);       // four consecutive rows (d_out is a multiple of 8)
+        if (tok < batch && row < jb.d_out) {
+            float o[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = jb.bias ? s[j] + jb.bias[row + j] : s[j];
+            const size_t oi = (size_t)tok * jb.d_out + row;
+            if (jb.out_dtype == F32) {
+                *reinterpret_cast<float4 *>((float *)jb.Y + oi) = float4{o[0], o[1], o[2], o[3]};
+            } else {
+                uint2 pk;
+                pk.x = (uint32_t)narrow<DT>(o[0]) | ((uint32_t)narrow<DT>(o[1]) << 16);
+                pk.y = (uint32_t)narrow<DT>(o[2]) | ((uint32_t)narrow<DT>(o[3]) << 16);
+                *reinterpret_cast<uint2 *>((uint16_t *)jb.Y + oi) = pk;
+            }
+        }
+    }
+    if (counted && arrived == (jb.w_units - sub + kTReadSubs - 1) / kTReadSubs - 1) {
+        // the last of its counter; the last of the counters puts the flags back for the next call
+        __hip_atomic_store(t_read + sub * 32, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_fetch_add(t_read + 32 * kTReadSubs, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == min(jb.w_units, kTReadSubs) - 1) {
+            __hip_atomic_store(t_read + 32 * kTReadSubs, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < jb.t_blocks; ++i) __hip_atomic_store(jb.t_flags + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
 
 }  // namespace
 
-namespace {
-// K slice: a few load batches (256 k each) of every token in LDS next to the keep-bit words, so that 3-4 workgroups
-// fit a compute unit; slices are evened out over d_in (measured: 768 k for 17-32 tokens, 1024 k for up to 16; larger
-// slices cost occupancy).  Returns the number of slices, ks = their length.
-int mfma_k_slices(int d_in, int tok_pad, int &ks)
-{
-    constexpr int kStep = kMfmaK * kMfmaUnroll;
-    const int ks_max = tok_pad > 16 ? 3 * kStep : 4 * kStep;
-    int n = (d_in + ks_max - 1) / ks_max;
-    ks = (((d_in + n - 1) / n + kStep - 1) / kStep) * kStep;
-    return (d_in + ks - 1) / ks;
-}
-}  // namespace
+bool mfma_path_supported(const MatrixView &M, int batch) { return batch >= 1 && batch <= 32 && M.W != nullptr; }
 
-bool mfma_path_supported(const LayerView &L, int batch)
+size_t mfma_operand_bytes(size_t rows, size_t cols, size_t row_pad)
 {
-    return batch >= 1 && batch <= 32 && L.Wrow != nullptr && (L.d_in % 8) == 0 && (L.d_out % 8) == 0;
+    return (rows + row_pad - 1) / row_pad * (row_pad / 16) * ((cols + kMfmaK - 1) / kMfmaK) * 1024;
 }
 
-hipError_t launch_mfma_linear(const LayerView &L, const void *X, int batch, void *Y, uint32_t *chan_bits, int cus,
-                              int stages, bool dense, int rows_per_wg_hint, hipStream_t stream)
+// One thread per 16 bytes of the result.
+__global__ void k_pack_operand(const uint16_t *src, size_t rows, size_t cols, size_t steps, uint16_t *dst, size_t n)
 {
-    const int tok_pad = batch > 16 ? 32 : 16;
-    const int rank = dense ? 0 : L.rank;
-    if (stages != 2) {
-        MfmaArgs a{};
-        a.L = L; a.X = (const uint16_t *)X; a.batch = batch; a.tok_pad = tok_pad; a.chan_bits = chan_bits;
-        a.dense = dense ? 1 : 0;
-        a.k_slices = mfma_k_slices(L.d_in, tok_pad, a.ks);
-        // row groups: the 16-row blocks of W and of S_r V_r^T dealt out evenly to as many workgroups as two rounds of
-        // one per compute unit (measured: with whole 64-row units the busiest compute unit carried 3 workgroups of 192
-        // rows against an average of 2.1 -- 48.7 us against 32.6 us for the dense layer on 8192 x 8192 at 32 tokens,
-        // for 12 % more rows)
-        const int blk_w = (L.d_out + kRowsPerBlock - 1) / kRowsPerBlock, blk_t = (rank + kRowsPerBlock - 1) / kRowsPerBlock;
-        int groups = std::max(1, (2 * cus) / a.k_slices);
-        groups = std::max(1, std::min(groups, (blk_w + blk_t) / 4));        // at least one block per wave
-        if (rows_per_wg_hint == 64 || rows_per_wg_hint == 128 || rows_per_wg_hint == 256)
-            groups = std::max(1, (blk_w + blk_t) * kRowsPerBlock / rows_per_wg_hint);
-        // the split of the groups between W and S_r V_r^T that keeps the largest share of blocks smallest
-        int g_t = 0;
-        if (rank > 0) {
-            int best = 1 << 30;
-            for (int t = 1; t < std::max(2, groups) && t <= blk_t; ++t) {
-                const int w = std::max(1, std::min(blk_w, groups - t));
-                const int worst = std::max((blk_t + t - 1) / t, (blk_w + w - 1) / w);
-                if (worst < best) { best = worst; g_t = t; }
-            }
-        }
-        const int g_w = std::max(1, std::min(blk_w, groups - g_t));
-        a.w_chunks = g_w;
-        a.t_chunks = g_t;
-        const size_t lds = (size_t)tok_pad * (a.ks * 2 + 16) + (size_t)a.ks * 4;
-        if (lds > 64 * 1024) return hipErrorInvalidValue;
-        // stage 1 goes to t_acc (summed over the K slices with atomics, or stored when there is one slice), which the
-        // split launch of the second stage leaves at zero; a first launch timed alone (stages = 1) clears it itself
-        if (rank > 0 && (!L.t_acc || !L.t16)) return hipErrorInvalidValue;
-        if (rank > 0 && stages != 0) {
-            hipError_t e = launch_zero(L.t_acc, (size_t)tok_pad * L.rank, stream);
-            if (e != hipSuccess) return e;
-        }
-        dim3 grid((a.w_chunks + a.t_chunks) * a.k_slices), block(256);
-        if (L.dtype == F16) hipLaunchKernelGGL(k_mfma_sparse_and_t<F16>, grid, block, lds, stream, a);
-        else hipLaunchKernelGGL(k_mfma_sparse_and_t<BF16>, grid, block, lds, stream, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t l = i % 64, tile = i / 64, row = tile / steps * 16 + l % 16, col = tile % steps * kMfmaK + l / 16 * 8;
+        u32x4 v = u32x4{0, 0, 0, 0};
+        if (row < rows && col < cols) v = *reinterpret_cast<const u32x4 *>(src + row * cols + col);
+        *reinterpret_cast<u32x4 *>(dst + i * 8) = v;
     }
-    if (stages != 1) {
-        MfmaFinishArgs f{};
-        f.L = L; f.Y = Y; f.batch = batch; f.tok_pad = tok_pad; f.use_rank = rank;
-        if (rank > 0) {
-            if (!L.t_acc || !L.t16) return hipErrorInvalidValue;
-            f.t_hi = L.t16;
-            f.t_lo = L.t16 + (size_t)32 * L.rank;
-            const int items = rank * (tok_pad / 4);
-            dim3 sgrid((items + 255) / 256), sblock(256);
-            if (L.dtype == F16) hipLaunchKernelGGL(k_mfma_split_t<F16>, sgrid, sblock, 0, stream, L.t_acc, rank, tok_pad, L.t16, L.t16 + (size_t)32 * L.rank);
-            else hipLaunchKernelGGL(k_mfma_split_t<BF16>, sgrid, sblock, 0, stream, L.t_acc, rank, tok_pad, L.t16, L.t16 + (size_t)32 * L.rank);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+}
+
+hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, size_t row_pad, uint16_t *dst, hipStream_t stream)
+{
+    const size_t n = mfma_operand_bytes(rows, cols, row_pad) / 16, steps = (cols + kMfmaK - 1) / kMfmaK;
+    hipLaunchKernelGGL(k_pack_operand, dim3((unsigned)std::min<size_t>((n + 255) / 256, 16384)), dim3(256), 0, stream, src, rows, cols, steps, dst, n);
+    return hipGetLastError();
+}
+
+size_t mfma_t_bytes(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 2048; }
+
+// 64 x 64 tiles through LDS, 16 bytes per access on both sides.
+__global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst)
+{
+    __shared__ uint16_t tile[64][66];
+    const size_t c0 = (size_t)blockIdx.x * 64, r0 = (size_t)blockIdx.y * 64;
+    for (int i = threadIdx.x; i < 512; i += 256) {
+        const size_t r = r0 + i / 8, c = c0 + i % 8 * 8;
+        if (r < rows && c < cols) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(src + r * cols + c);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) tile[i / 8][i % 8 * 8 + e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
         }
-        const size_t lds = 2 * (size_t)tok_pad * (kMfmaK * kMfmaUnroll * 2 + 16);
-        dim3 grid((L.d_out + 63) / 64), block(256);
-        if (L.dtype == F16) hipLaunchKernelGGL(k_mfma_finish<F16>, grid, block, lds, stream, f);
-        else hipLaunchKernelGGL(k_mfma_finish<BF16>, grid, block, lds, stream, f);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    __syncthreads();
+    for (int i = threadIdx.x; i < 512; i += 256) {
+        const size_t c = c0 + i / 8, r = r0 + i % 8 * 8;
+        if (c < cols && r < rows) {
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (uint32_t)tile[i % 8 * 8 + 2 * e][i / 8] | ((uint32_t)tile[i % 8 * 8 + 2 * e + 1][i / 8] << 16);
+            *reinterpret_cast<u32x4 *>(dst + c * rows + r) = v;
+        }
+    }
+}
+
+hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream)
+{
+    if (rows == 0 || cols == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_transpose16, dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)), dim3(256), 0, stream, src, rows, cols, dst);
+    return hipGetLastError();
+}
+
+hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
+                       int phases, bool dense, int rows_per_wg_hint, int wait_polls, int skip_stage1, hipStream_t stream)
+{
+    if (n < 1 || n > kMaxGroupLayers || batch < 1 || batch > 32 || phases < 1 || phases > 3) return hipErrorInvalidValue;
+    const int nf = batch > 16 ? 2 : 1;
+    MfmaArgs a{};
+    a.n = n; a.X = (const uint16_t *)X; a.batch = batch; a.d_in = L[0].d_in; a.phases = phases;
+    a.wait_polls = wait_polls > 0 ? wait_polls : kWaitLimitPolls;
+    a.skip_stage1 = skip_stage1;
+    // Units of one block for up to 16 tokens, of two for more (a unit reads all tokens, from L2, beside its rows: at 32
+    // tokens and one block twice the bytes of the rows; measured at 8192 x 8192, 32 tokens: dense 33.7 us with one block,
+    // 27.0 with two; at 8 tokens 23.2 and 22.9, at 4096 -> 14336 with 16 tokens 70.9 and 78.1) -- unless that leaves
+    // compute units without a unit.  Four waves a unit: with eight the same bytes are in flight in half the workgroups
+    // (8192 x 8192, 8 tokens: 24.7 against 25.8 us).
+    int nb = 1, nw = 4;
+    if (nf == 2) {
+        int blocks = 0;
+        for (int i = 0; i < n; ++i) blocks += (L[i].d_out + 15) / 16;
+        if (blocks >= 2 * cus || rows_per_wg_hint > 0) nb = 2;
+    }
+    int w_total = 0, t_blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        MfmaJob &jb = a.job[i];
+        const LayerView &v = L[i];
+        const MatrixView &m = M[i];
+        if (v.d_in != a.d_in || v.dtype != L[0].dtype || !mfma_path_supported(m, batch) || !Y[i]) return hipErrorInvalidValue;
+        jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.Y = Y[i]; jb.bias = v.bias;
+        jb.t_acc = m.t_acc; jb.t_flags = m.t_flags;
+        jb.chan_bits = dense ? nullptr : chan_bits[i];
+        jb.sync = v.sync; jb.d_out = v.d_out; jb.rank = dense ? 0 : v.rank; jb.out_dtype = v.out_dtype;
+        jb.mask_mode = dense ? kMaskNone : (v.batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (v.keep_signed ? kMaskSigned : 0);
+        jb.kp = KeepPattern{(uint32_t)(uint16_t)m.keep_min * 0x10001u, (v.dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
+        if (jb.rank > 0 && (!m.t || !m.t_acc || !v.sync || !m.t_flags || !m.SVt || !m.U)) return hipErrorInvalidValue;
+        jb.t_blocks = (jb.rank + 31) / 32 * 2;
+        jb.w_units = ((v.d_out + 15) / 16 + nb - 1) / nb;
+        w_total += jb.w_units;
+        t_blocks += jb.t_blocks;
+        a.w_end[i] = w_total;
+    }
+    const int batch_k = kMfmaK * (nb == 1 ? 4 : 2), n_batches = (a.d_in + batch_k - 1) / batch_k;
+    // K slices of t: enough workgroups for the chip, a batch of loads for every wave, and at most four, whose sums meet in
+    // atomics (8192 x 8192, rank 1024, 8 tokens: 43.5 us with one slice, 39.0 with two, 34.5 with four; 4096 x 4096, rank
+    // 256: 16.1 with one, 14.6 with four, 15.4 with sixteen)
+    a.t_slices = t_blocks > 0 ? std::max(1, std::min({4, cus / t_blocks, n_batches / nw})) : 1;
+    int t_total = 0;
+    for (int i = 0; i < kMaxGroupLayers; ++i) {
+        if (i < n) t_total += a.job[i].t_blocks * a.t_slices;
+        else a.w_end[i] = w_total;
+        a.t_end[i] = t_total;
+    }
+    if (phases == 1 && t_total == 0) return hipSuccess;
+    const size_t lds = (size_t)nw * std::max(nf * 16 * (batch_k * 2 + 16), nb * nf * 1024);
+    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    dim3 grid((phases & 1 ? t_total : 0) + (phases & 2 ? w_total : 0)), block(64 * nw);
+#define RS_M(DT, NBV, NFV) hipLaunchKernelGGL((k_mfma_rows<DT, NBV, NFV>), grid, block, lds, stream, a)
+#define RS_MD(DT)                                                                               \
+    do {                                                                                        \
+        if (nf == 1) RS_M(DT, 1, 1);                                                            \
+        else if (nb == 1) RS_M(DT, 1, 2);                                                       \
+        else RS_M(DT, 2, 2);                                                                    \
+    } while (0)
+    if (L[0].dtype == F16) RS_MD(F16); else RS_MD(BF16);
+#undef RS_MD
+#undef RS_M
+    return hipGetLastError();
 }
 
 }  // namespace rsparse

@@ -1,0 +1,108 @@
+"""GPU tests of the matrix-core path where its units end: rows and ranks that leave part of a 16-row block, contractions
+that leave part of a step or batch, token tiles, K slices of t, groups of layers, both launch forms, the dense product at
+every batch, and the bounded wait for t.  Same oracle and tolerances as the other parity tests (gpu_util)."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+import oracle
+import paper_2504_19449_amd as rs
+from paper_2504_19449_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _parity(layer, L, X16, tau, **kw):
+    got = gu.run_linear(layer, X16)
+    want = gu.oracle_linear(L, X16, tau, **kw)
+    gu.check_lists(got, want)
+    gu.check_outputs(got["Y"], want["Y"], rs.F32)
+
+
+@pytest.mark.parametrize("d_in,d_out,rank", [(8, 8, 8), (24, 40, 0), (136, 24, 24), (520, 1000, 40), (1032, 264, 136), (4104, 520, 72)])
+@pytest.mark.parametrize("dt", [synth.F16, synth.BF16])
+def test_ragged_units(d_in, d_out, rank, dt):
+    L = synth.random_layer(d_in, d_out, rank, dt, seed=41 + d_in + rank)
+    for B, mode in ((5, 0), (16, 1), (17, 0), (32, 1)):
+        X16, src = gu.tokens_for(L, B, linear=B)
+        tau = gu.calibrated_tau(L, src, 0.5)
+        layer = gu.prepare(L, tau, max_batch=32, out_dtype=rs.F32, dense_rowmajor=1, batch_mask_mode=mode)
+        for launches in (1, 2, 1):
+            rs.rsparse_set_tuning(layer, launches=launches)
+            _parity(layer, L, X16, tau, batch_mask_mode=mode)
+        # the same handle at the other number of token tiles: nothing of the last call shows
+        other = X16[:7] if B > 16 else np.concatenate([X16, X16, X16, X16])[:20]
+        _parity(layer, L, other, tau, batch_mask_mode=mode)
+        layer.destroy()
+
+
+@pytest.mark.parametrize("cmp_mode", [1, 2])
+def test_strict_and_signed_thresholds_on_patterns(cmp_mode):
+    """Thresholds on, between and beyond representable values, zeros of both signs, subnormals, infinities and NaN: the
+    pattern comparison keeps exactly what the definition keeps."""
+    for dt in (synth.F16, synth.BF16):
+        L = synth.random_layer(136, 64, 16, dt, seed=7)
+        rng = np.random.default_rng(3)
+        X16 = synth.encode16(rng.standard_normal((6, 136)), dt)
+        inf = 0x7C00 if dt == synth.F16 else 0x7F80
+        X16[:, :12] = np.array([0, 0x8000, 1, 0x8001, inf, inf | 0x8000, inf + 1, (inf + 1) | 0x8000, inf - 1, (inf - 1) | 0x8000, 2, 0x8002],
+                               dtype=np.uint16)
+        vals = synth.decode16(np.abs(X16.view(np.int16)[0, 20:24]).view(np.uint16), dt)
+        taus = [0.0, float(np.float32(vals[0])), float(np.nextafter(np.float32(vals[1]), np.float32(9))),
+                float(np.nextafter(np.float32(vals[2]), np.float32(0))), 1e-30, 1e30, np.inf, -np.inf] + ([-0.25, -1e30] if cmp_mode == 2 else [])
+        layer = gu.prepare(L, 0.0, max_batch=8, out_dtype=rs.F32, dense_rowmajor=1, cmp_mode=cmp_mode)
+        for tau in taus:
+            rs.rsparse_set_tau(layer, tau)
+            got = gu.run_linear(layer, X16)
+            want = gu.oracle_linear(L, X16, tau, cmp_mode=cmp_mode)
+            gu.check_lists(got, want)
+        layer.destroy()
+
+
+def test_grouped_layers_share_one_launch_and_a_bias():
+    """Four layers of different sizes and ranks (one without a low-rank part) on one input, several calls in a row."""
+    shapes = [(528, 200), (528, 8), (528, 1032), (528, 16)]
+    ranks = [40, 8, 0, 16]
+    Ls = [synth.random_layer(a, b, r, synth.BF16, seed=90 + i) for i, ((a, b), r) in enumerate(zip(shapes, ranks))]
+    X16, src = gu.tokens_for(Ls[0], 9, linear=3)
+    tau = gu.calibrated_tau(Ls[0], src, 0.5)
+    layers = [gu.prepare(L, tau, max_batch=16, out_dtype=rs.F32, dense_rowmajor=1) for L in Ls]
+    bias = np.linspace(-1, 1, 1032).astype(np.float32)
+    rs.rsparse_set_bias(layers[2], bias)
+    Xd = gu.to_dev16(X16)
+    for _ in range(3):
+        Ys = [gu._alloc_out(l, 9) for l in layers]
+        rs.rsparse_linear_group(layers, Xd.data_ptr(), 9, [y.data_ptr() for y in Ys], gu.stream_ptr())
+        for i, (l, L, y) in enumerate(zip(layers, Ls, Ys)):
+            want = gu.oracle_linear(L, X16, tau)["Y"] + (bias if i == 2 else 0)
+            gu.check_outputs(gu._read_out(l, y), want, rs.F32)
+            rs.rsparse_synchronize(l)
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 5, 16, 17, 32])
+def test_dense_product_at_every_batch(B):
+    for d_in, d_out in ((8, 24), (1032, 1096), (2056, 2056)):        # below and above the row-dot limit
+        L = synth.random_layer(d_in, d_out, 8, synth.F16, seed=d_in)
+        X16, _ = gu.tokens_for(L, B, linear=B)
+        layer = gu.prepare(L, 0.5, max_batch=32, out_dtype=rs.F32, dense_rowmajor=1)
+        want = oracle.dense_linear(L.W16, X16, L.dtype, L.dtype, nthreads=8)
+        for kernel in (0, 1, 2):
+            rs.rsparse_set_tuning(layer, dense_kernel=kernel)
+            gu.check_outputs(gu.run_dense(layer, X16), want, rs.F32)
+        layer.destroy()
+
+
+def test_bounded_wait_for_t_runs_out_and_the_handle_recovers():
+    """Stage 1 sets no flag (test hook) and the wait is bounded to a few polls: the kernel ends, the call is reported
+    as failed once, and the next calls are right again."""
+    L = synth.random_layer(520, 328, 40, synth.BF16, seed=5)
+    X16, src = gu.tokens_for(L, 12, linear=1)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    layer = gu.prepare(L, tau, max_batch=16, out_dtype=rs.F32, dense_rowmajor=1)
+    _parity(layer, L, X16, tau)
+    rs.rsparse_set_tuning(layer, debug_skip_stage1=1, debug_wait_polls=4)
+    with pytest.raises(rs.RSparseError):
+        gu.run_linear(layer, X16)
+    rs.rsparse_set_tuning(layer)
+    for _ in range(2):
+        _parity(layer, L, X16, tau)
