@@ -117,12 +117,13 @@ typedef struct {
                                 only -- for timing one kernel in isolation; results are only valid with 0 */
     int32_t tile_map;        /* workgroup -> (column tile, split) mapping: 0 default, 1 tile-fastest (plain),
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
-    int32_t mfma_min_batch;  /* smallest batch that takes the matrix-core path (needs dense_rowmajor = 1):
-                                0 = default (5 for rsparse_linear; for rsparse_dense_ref 1, 2 on layers under 2^22 weights, and
-                                with dense_kernel set 2, 4 on layers of 2^25 weights or more), 33 = never (all batches
-                                then run in tiles of up to 8 tokens on the vector ALU) */
-    int32_t mfma_rows;       /* output rows per workgroup of the matrix-core kernels: 0 default (16; 32 above 16 tokens where
-                                that still fills the chip), or 64, 128, 256 (32 above 16 tokens whatever the layer) */
+    int32_t mfma_min_batch;  /* smallest batch that takes the matrix-core path (16-bit weights: needs dense_rowmajor = 1; 4-bit
+                                weights: needs max_batch >= 2): 0 = default (5 for rsparse_linear, 2 on 4-bit weights; for
+                                rsparse_dense_ref 1, 2 on layers under 2^22 weights, and with dense_kernel set 2, 4 on layers
+                                of 2^25 weights or more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on
+                                4-bit weights, on the vector ALU) */
+    int32_t mfma_rows;       /* 0, 64, 128 or 256; without effect (rows per workgroup of earlier matrix-core kernels: now 16, and
+                                32 above 16 tokens) */
     int32_t launches;        /* rsparse_linear: 0 default
                                 (one launch; two on 4-bit weights), 1 one launch, 2 two launches (stage 2 and the
                                 rounding in a second kernel).  stages != 0 implies two launches */
@@ -173,9 +174,10 @@ rsparse_status rsparse_prepare_factors(const rsparse_config *cfg, const void *W_
  * U16_host / SV16_host stay 16-bit and are the caller's (of the unquantised W, or of W~).  group_size: a power
  * of two in [32, 1024] that divides d_in.  The library packs the codes channel-major (one kept channel = one
  * contiguous run of d_out / 2 bytes) and dequantises in registers: per quantisation group it accumulates
- * sum x_c q_c and sum x_c and applies scale and zero point once.  Limits of this path: no matrix-core path
- * (batches above 4 tokens run as tiles of 4, the codes streamed once per tile); rsparse_linear and friends run it as
- * two launches per layer by default (tuning launches = 1 selects a one-launch form, measured no faster); grouped
+ * sum x_c q_c and sum x_c and applies scale and zero point once.  From 2 tokens on (max_batch >= 2) the
+ * products run on the matrix cores, codes converted exactly; rsparse_linear and friends run this path as two launches per
+ * layer (tuning launches = 1 selects a one-launch form of the vector kernel, which takes batches above 4 tokens as tiles of
+ * 4, the codes streamed once per tile; measured no faster at one token); grouped
  * calls and rsparse_mlp_gate_up take such layers one at a time.  rsparse_dense_ref gives the dense product with W~:
  * with dense_rowmajor = 1 (a second, row-major copy of the codes, scales and zero points: + d_in * d_out / 2 bytes)
  * as a row-dot GEMV over row-major codes, the form a dense 4-bit decoder would use (tuning dense_kernel = 1 forces the

@@ -158,7 +158,9 @@ struct rsparse_layer {
     uint16_t *SVc = nullptr;               // [d_in][rank] channel-major copy of S_r V_r^T (cfg.lowrank_channel_major)
     float *t_sum = nullptr;                // [rank] fp32 sums of the stage 1 that reads it (zero between calls)
     float *t_acc = nullptr;                // fp32 sums of t of the matrix-core path (zero between calls)
-    void *t16 = nullptr;                   // t of the matrix-core path: two 16-bit halves in operand layout
+    void *t16 = nullptr;                   // t of the matrix-core path: its 16-bit parts in operand layout
+    float *yc = nullptr;                   // 4-bit weights on the matrix cores: sums of the W part (zero between calls)
+    int yc_rows = 0;
     uint32_t *act_bits = nullptr, *chan_bits = nullptr;
     bool last_mfma = false;
     int32_t *act_list = nullptr, *act_count = nullptr;
@@ -195,8 +197,8 @@ struct rsparse_layer {
 
     MatrixView matrix(const LayerView &v) const
     {
-        if (!Wtile) return MatrixView{};
-        return MatrixView{Wtile, SVtile, Utile, t16, t_acc, t_flags, smallest_kept_pattern(v.tau_ge, cfg.dtype, v.keep_signed != 0)};
+        if (!Wtile && !yc) return MatrixView{};
+        return MatrixView{Wtile, SVtile, Utile, t16, t_acc, t_flags, yc, yc_rows, smallest_kept_pattern(v.tau_ge, cfg.dtype, v.keep_signed != 0)};
     }
 
     // The view of one call: `batch` decides the mask mode when the configuration leaves it to the library; the dense
@@ -229,6 +231,10 @@ namespace {
 // Layers below this many weights keep W row-major beside the operand layout (dense_rowmajor = 1): the row-dot kernel is
 // the faster dense kernel there at one token (rsparse_dense_ref_group).
 constexpr size_t kRowdotWeights = (size_t)1 << 22;
+// Smallest batch that 4-bit layers run on the matrix cores
+// (measured, us for gate, up and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 60 -> 65 at one token, 106 -> 66
+// at two, 226 -> 66 at four, 717 -> 68 at sixteen, 1342 -> 96 at 32).
+constexpr int kMfmaMinBatchQ4 = 2;
 
 int batch_tile_of(int batch) { return batch <= 1 ? 1 : batch <= 2 ? 2 : batch <= 4 ? 4 : 8; }
 
@@ -393,7 +399,7 @@ void free_layer(rsparse_layer *L)
     (void)hipFree(L->yacc); (void)hipFree(L->act_bits); (void)hipFree(L->chan_bits);
     (void)hipFree(L->act_list); (void)hipFree(L->act_count); (void)hipFree(L->sync); (void)hipFree(L->t_pub); (void)hipFree(L->xg); (void)hipFree(L->hy);
     (void)hipFree(L->Wtile); (void)hipFree(L->SVtile); (void)hipFree(L->Utile);
-    (void)hipFree(L->Ms); (void)hipFree(L->t_tag); (void)hipFree(L->act_seg); (void)hipFree(L->bias); (void)hipFree(L->rules); (void)hipFree(L->SVc); (void)hipFree(L->t_sum); (void)hipFree(L->t16); (void)hipFree(L->t_acc);
+    (void)hipFree(L->Ms); (void)hipFree(L->t_tag); (void)hipFree(L->act_seg); (void)hipFree(L->bias); (void)hipFree(L->rules); (void)hipFree(L->SVc); (void)hipFree(L->t_sum); (void)hipFree(L->t16); (void)hipFree(L->t_acc); (void)hipFree(L->yc);
     (void)hipFree(L->Mq); (void)hipFree(L->qs); (void)hipFree(L->qz); (void)hipFree(L->Ut);
     (void)hipFree(L->Qrow); (void)hipFree(L->Srow); (void)hipFree(L->Zrow);
     delete L;
@@ -556,7 +562,19 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
                 L->Wrow = nullptr;
             }
         }
-        if (cfg->dense_rowmajor && !q4 && r) {
+        // 4-bit layers take the matrix cores from their own threshold on
+        const bool q4_mm = q4 && cfg->max_batch >= kMfmaMinBatchQ4;
+        if (q4_mm) {
+            const size_t words = mfma_q4_words(L->qtiles, cfg->max_batch);
+            L->yc_rows = L->qtiles * kQ4Tile;
+            RS_HIP(hipMalloc((void **)&L->yc, words * 4));
+            RS_HIP(hipMemset(L->yc, 0, words * 4));
+            rsparse_status ts = RSPARSE_OK;
+            if (r) ts = make_operand(L->SVt, r, d_in, 32, &L->SVtile);
+            if (ts == RSPARSE_OK && r) ts = make_operand(L->U, d_out, r, 16, &L->Utile);
+            if (ts != RSPARSE_OK) return ts;
+        }
+        if (((cfg->dense_rowmajor && !q4) || q4_mm) && r) {
             RS_HIP(hipMalloc(&L->t16, mfma_t_bytes((int)r)));
             RS_HIP(hipMemset(L->t16, 0, mfma_t_bytes((int)r)));
             RS_HIP(hipMalloc((void **)&L->t_acc, (r + 31) / 32 * 32 * 32 * 4));
@@ -578,7 +596,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->rules, (size_t)cfg->max_batch * sizeof(KeepRule)));
         RS_HIP(hipMemset(L->rules, 0, (size_t)cfg->max_batch * sizeof(KeepRule)));
         const size_t flags_at = (sync_words(std::max(L->tiles, L->strips)) + 31) / 32 * 32;
-        L->sync_n = flags_at + (cfg->dense_rowmajor && !q4 && r ? t_flag_words((int)r) : 0);
+        L->sync_n = flags_at + (r ? t_flag_words((int)r) : 0);     // (matrix-core path)
         RS_HIP(hipMalloc((void **)&L->sync, L->sync_n * 4));
         RS_HIP(hipMemset(L->sync, 0, L->sync_n * 4));
         L->t_flags = L->sync + flags_at;
@@ -750,6 +768,18 @@ rsparse_status linear_q4(rsparse_layer *L, const void *X_dev, int32_t batch, voi
 {
     const LayerView v = L->view(nullptr, batch, dense);
     const int stages = L->tuning.stages;
+    const int mm_min = L->tuning.mfma_min_batch > 0 ? L->tuning.mfma_min_batch : kMfmaMinBatchQ4;
+    if (L->yc && batch >= mm_min && L->tuning.launches != 1) {
+        const MatrixView mv = L->matrix(v);
+        uint32_t *bits = L->chan_bits;
+        if (stages != 2) RS_HIP(launch_mfma_q4(v, mv, true, X_dev, batch, dense, L->cus, s));
+        if (stages != 1) RS_HIP(launch_mfma(&v, &mv, 1, X_dev, batch, &Y_dev, &bits, L->cus, 2, dense, 0, 0, s));
+        if (!dense) {
+            L->last_stream = s; L->last_batch = batch; L->last_mfma = true; L->last_fused = true; L->last_bt = 0; L->last_strip = false;
+            L->last_scratch = L->own_scratch();
+        }
+        return RSPARSE_OK;
+    }
     // two launches by default: the one-launch form (launches = 1) measured no faster on these weights --
     // its tail waits for up to `splits` same-address atomics that the two-launch form never waits for
     // (its arrival counters cover up to kSyncMaxZ batch tiles of 4 tokens)
@@ -906,10 +936,10 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         for (int i = 0; i < n_layers; ++i) bits[i] = layers[i]->chan_bits;
         const rsparse_tuning &t = layers[0]->tuning;
         if (fused) {
-            RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 3, false, t.mfma_rows, t.debug_wait_polls, t.debug_skip_stage1, s));
+            RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 3, false, t.debug_wait_polls, t.debug_skip_stage1, s));
         } else {
-            if (stages != 2) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 1, false, t.mfma_rows, 0, 0, s));
-            if (stages != 1) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, false, t.mfma_rows, 0, 0, s));
+            if (stages != 2) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 1, false, 0, 0, s));
+            if (stages != 1) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, false, 0, 0, s));
         }
     } else if (fused) {
         RS_HIP(launch_fused(v, lc, n_layers, X_dev, batch, Y_devs, s));
@@ -1051,7 +1081,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
         mfma = mfma && mfma_path_supported(mv[i], batch);
     }
     if (mfma) {
-        RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, nullptr, layers[0]->cus, 3, true, layers[0]->tuning.mfma_rows, 0, 0, s));
+        RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, nullptr, layers[0]->cus, 3, true, 0, 0, s));
         return RSPARSE_OK;
     }
     int kernel = layers[0]->tuning.dense_kernel;

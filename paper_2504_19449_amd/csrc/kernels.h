@@ -79,10 +79,12 @@ hipError_t launch_topk_rules(const void *X, int dtype, int batch, int d_in, int 
 // 16 rows][step of 32 columns][64 lanes][16 bytes], lane l of a tile = columns 8 (l / 16) .. + 7 of row l % 16; rows and
 // columns past the matrix are zero.
 struct MatrixView {
-    const uint16_t *W, *SVt, *U;   // W [d_out][d_in], S_r V_r^T [rank rounded up to 32][d_in], U_r [d_out][rank]
-    void *t;                       // t as two 16-bit halves, mfma_t_bytes(rank)
+    const uint16_t *W, *SVt, *U;   // (W null: its part comes from an earlier launch, in yc)  W [d_out][d_in], S_r V_r^T [rank rounded up to 32][d_in], U_r [d_out][rank]
+    void *t;                       // t in 16-bit parts, mfma_t_bytes(rank)
     float *t_acc;                  // fp32 sums of t, [32 tokens][rank rounded up to 32]; zero between calls
     int *t_flags;                  // [t_flag_words(rank)]; zero between calls
+    float *yc;                     // [token tile][yc_rows][16 tokens] fp32 sums of the W part; zero between calls
+    int yc_rows;
     int16_t keep_min;              // LayerView::tau_ge as the smallest kept 16-bit pattern of |x| (keep_signed: of x, as a two's complement number)
 };
 
@@ -181,7 +183,13 @@ hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, si
 // dst [cols][rows] = transpose of src [rows][cols], 16-bit, both multiples of 8 (device).
 hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream);
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
-                       int phases, bool dense, int rows_per_wg_hint, int wait_polls, int skip_stage1, hipStream_t stream);
+                       int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream);
+// 4-bit weights on the matrix cores (kernels_mfma_q4.hip), up to 32 tokens: adds the W part of the layer (dense: the whole
+// product) to yc, [token tile][qtiles * 1024][16 tokens]; launch_mfma with MatrixView::W null completes the layer.
+// with_t: t as well, in the parts that launch_mfma's phase 2 expects of such layers.
+int mfma_t_slices(int t_blocks, int d_in, int nw, int cus);
+hipError_t launch_mfma_q4(const LayerView &L, const MatrixView &M, bool with_t, const void *X, int batch, bool dense, int cus, hipStream_t stream);
+size_t mfma_q4_words(int qtiles, int max_batch);
 // The whole layer over strip-major weights (LayerView::Ms), up to 8 tokens per batch tile: one workgroup per strip
 // of strip_w output columns streams all kept rows of the strip and stores its slice of Y (cfg[i].splits == 1), or
 // `splits` workgroups per strip meet in yacc.  fused: stage 1 runs in the same launch and hands t over through

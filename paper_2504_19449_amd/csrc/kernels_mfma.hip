@@ -27,128 +27,13 @@
 // Measured (us per call, before: a first launch with sums over K slices in fp32 atomics, a split launch and a finish
 // launch): 8192 x 8192 r 1024 60.3 -> 41.7 at 32 tokens, 53.1 -> 34.7 at 8; 4096 x 4096 r 256 23.1 -> 14.6 at 8; dense
 // 4096 -> 14336 (two) and back 93.1 -> 71.1 at 16.
-#include "kernels.h"
-#include "device_common.h"
-#include "device_stage1.h"
+#include "device_mfma.h"
 
 #include <algorithm>
 
 namespace rsparse {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kMfmaK = 32;        // contraction depth of one MFMA
-// MFMA steps of one batch of loads, for units of NB blocks.  Measured on plain streams of this shape (512 workgroups of
-// 8 waves, 134 MB): two batches of 4 KiB per wave in flight 6.3 TB/s, of 8 KiB 5.6, of 16 KiB 4.5 -- more requests than
-// the memory system takes only push each other out.
-template <int NB> struct StepsOf { static constexpr int value = NB == 1 ? 4 : 2; };
-
-template <int DT>
-__device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x4 c)
-{
-    if (DT == BF16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-template <int DT>
-__device__ __forceinline__ uint16_t narrow(float f) { return DT == F16 ? to_f16(f) : to_bf16(f); }
-
-// The lo half of t is stored scaled by a power of two (exact): in fp16 the remainder t - hi would otherwise fall into
-// the subnormals for |t| below ~0.1 and lose the bits it is there to keep.
-template <int DT> struct LoScale { static constexpr float value = DT == F16 ? 2048.0f : 1.0f; };
-
-// ---------------------------------------------------------------------------------------------
-// The sparsification function on packed 16-bit patterns.  Magnitudes order like their patterns, so |x| >= t is
-// pattern(|x|) >= pattern_min (host-computed, exact), signed thresholds compare the sign-magnitude pattern as a two's
-// complement number, and NaN patterns lie above infinity's.
-// ---------------------------------------------------------------------------------------------
-struct KeepPattern {
-    uint32_t min2, inf2;       // smallest kept pattern and infinity's, each twice
-};
-
-// 0xffff in every half of x that the token DROPS.
-template <bool SIGNED>
-__device__ __forceinline__ uint32_t dropped2(uint32_t x, const KeepPattern &kp)
-{
-    const s16x2 mag = __builtin_bit_cast(s16x2, x & 0x7fff7fffu);
-    s16x2 key = mag;
-    if (SIGNED) {
-        const s16x2 sgn = __builtin_bit_cast(s16x2, x) >> 15;
-        key = (mag ^ sgn) - sgn;
-    }
-    const s16x2 below = __builtin_elementwise_sub_sat(key, __builtin_bit_cast(s16x2, kp.min2));
-    const s16x2 nan = __builtin_bit_cast(s16x2, kp.inf2) - mag;
-    return __builtin_bit_cast(uint32_t, (s16x2)((below | nan) >> 15));
-}
-
-__device__ __forceinline__ uint32_t and_over_16_lanes(uint32_t v)
-{
-    constexpr int kRowRor = 0x120;
-    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 8, 0xf, 0xf, false);
-    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 4, 0xf, 0xf, false);
-    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 2, 0xf, 0xf, false);
-    v &= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowRor + 1, 0xf, 0xf, false);
-    return v;
-}
-
-// All of this wave's earlier atomics and stores have been performed.
-__device__ __forceinline__ void wait_own_writes()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0);
-}
-
-constexpr int kMaskNone = 0, kMaskOwn = 1, kMaskUnion = 2;   // MfmaJob::mask_mode
-constexpr int kMaskSigned = 4;                               // ... + the rule applies to x itself
-
-// The part of the tokens a unit works on: kept values (want = 0) or dropped ones (want = ~0), the others zeroed.
-// Frags of one step: NF token tiles of 16; with the union mask a channel counts as kept if any token keeps it (lanes
-// past the batch hold a copy of its last token).
-template <int NF, int MODE>
-__device__ __forceinline__ void mask_step(u32x4 (&b)[NF], const KeepPattern &kp, uint32_t want)
-{
-    if (MODE == kMaskNone) return;
-    uint32_t d[NF][4];
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) d[f][i] = dropped2<(MODE & kMaskSigned) != 0>(b[f][i], kp);
-    if (MODE & kMaskUnion) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t all = d[0][i];
-#pragma unroll
-            for (int f = 1; f < NF; ++f) all &= d[f][i];
-            all = and_over_16_lanes(all);
-#pragma unroll
-            for (int f = 0; f < NF; ++f) d[f][i] = all;
-        }
-    }
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[f][i] &= ~(d[f][i] ^ want);
-}
-
-struct MfmaJob {
-    const uint16_t *W, *SVt, *U; // operand layout (MatrixView)
-    unsigned char *t;            // t in operand layout: [step of 32 rank indices][token tile][hi, lo][64 lanes][16 bytes]
-    float *t_acc;                // [block of 16 rank indices][token tile][4][64] fp32 sums of t's K slices, zero between calls
-    int *t_flags;                // a flag per block of t, zero between calls; then an arrival counter per block
-    void *Y;
-    const float *bias;
-    uint32_t *chan_bits;         // [d_in] bit b = token b keeps the channel (read-back), or nullptr
-    int *sync;
-    int d_out, rank;
-    int out_dtype, mask_mode;
-    KeepPattern kp;
-    int t_blocks, w_units;       // blocks of S_r V_r^T (0: no low-rank part), units of W
-};
 struct MfmaArgs {
     MfmaJob job[kMaxGroupLayers];
     int t_end[kMaxGroupLayers];  // t tasks (block, K slice) of jobs 0..i
@@ -159,97 +44,9 @@ struct MfmaArgs {
     int wait_polls, skip_stage1;
 };
 
-// One batch of a wave: S steps of NB weight tiles (1 KiB each) and the same 32 * S channels of all tokens, 4 * S lanes to
-// a token.
-template <int NB, int NF>
-struct Batch {
-    static constexpr int S = StepsOf<NB>::value, K = kMfmaK * S, kLanes = 4 * S, kX = NF * S;
-    static constexpr int kPitch = K * 2 + 16;   // bytes of a token in LDS: the 16 tokens of a read hit 16 bank groups
-    u32x4 a[S][NB], x[kX];
-};
-
-// Weights are read once: non-temporal (8192 x 8192 at 32 tokens 51.7 against 54.7 us with ordinary loads).
-__device__ __forceinline__ u32x4 ld16(const unsigned char *p)
-{
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-}
-
-// Batch `bi` of the contraction (past its end: its last values again).
-template <int NB, int NF>
-__device__ __forceinline__ void load_batch(const unsigned char *__restrict__ mat, const size_t (&aoff)[NB], const unsigned char *__restrict__ x,
-                                           const uint32_t (&xoff)[Batch<NB, NF>::kX], int lane, int d_in, int steps, int bi,
-                                           Batch<NB, NF> &v)
-{
-    using B = Batch<NB, NF>;
-    const uint32_t k = (uint32_t)min(bi * B::K + lane % B::kLanes * 8, d_in - 8) * 2u;
-#pragma unroll
-    for (int j = 0; j < B::kX; ++j) v.x[j] = *reinterpret_cast<const u32x4 *>(x + (size_t)(xoff[j] + k));
-#pragma unroll
-    for (int u = 0; u < B::S; ++u) {
-        const int s = min(bi * B::S + u, steps - 1);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) v.a[u][i] = ld16(mat + aoff[i] + (size_t)s * 1024 + lane * 16);
-    }
-    __builtin_amdgcn_sched_barrier(0);      // all of them are issued here, ahead of the batch that is used next
-}
-
-template <int DT, int NB, int NF, int MODE>
-__device__ __forceinline__ void use_batch(Batch<NB, NF> &v, unsigned char *sx, const KeepPattern &kp, uint32_t want, int lane,
-                                          int k_end, int bi, f32x4 (&acc)[NB][NF])
-{
-    using B = Batch<NB, NF>;
-    // the tokens change from kLanes lanes a token to the operand layout through this wave's own LDS
-    const bool in = bi * B::K + lane % B::kLanes * 8 < k_end;
-#pragma unroll
-    for (int j = 0; j < B::kX; ++j)
-        *reinterpret_cast<u32x4 *>(sx + (j * (64 / B::kLanes) + lane / B::kLanes) * B::kPitch + lane % B::kLanes * 16) =
-            in ? v.x[j] : u32x4{0, 0, 0, 0};
-    __builtin_amdgcn_wave_barrier();
-    f32x4 sum[NB][NF];
-#pragma unroll
-    for (int u = 0; u < B::S; ++u) {
-        u32x4 b[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-            b[f] = *reinterpret_cast<const u32x4 *>(sx + (f * 16 + (lane & 15)) * B::kPitch + u * 64 + (lane >> 4) * 16);
-        mask_step<NF, MODE>(b, kp, want);
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int f = 0; f < NF; ++f) sum[i][f] = mfma16<DT>(v.a[u][i], b[f], u ? sum[i][f] : f32x4{0.f, 0.f, 0.f, 0.f});
-    }
-    // a batch's sums are added to the task's with the vector ALU: the matrix cores' own long chains of sums lose bits
-    // (28672 channels: 3.8e-7 from the 64-bit result in one chain)
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int f = 0; f < NF; ++f) acc[i][f] += sum[i][f];
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// A wave's batches bi, bi + nw, ... below `end`, two in flight: every load is unconditional (past the end it re-reads the
-// last values, against tokens of zeros), so that the compiler counts the outstanding ones exactly and waits for the
-// current batch alone.  The first batch is in va already.
-template <int DT, int NB, int NF, int MODE>
-__device__ __forceinline__ void stream_rows(const unsigned char *__restrict__ mat, const size_t (&aoff)[NB],
-                                            const unsigned char *__restrict__ x, const uint32_t (&xoff)[Batch<NB, NF>::kX], unsigned char *sx,
-                                            const KeepPattern &kp, uint32_t want, int lane, int d_in, int bi, int end, int nw,
-                                            Batch<NB, NF> &va, f32x4 (&acc)[NB][NF])
-{
-    const int steps = (d_in + kMfmaK - 1) / kMfmaK;
-    Batch<NB, NF> vb;
-    const int k_end = min(end * Batch<NB, NF>::K, d_in);
-    for (; bi < end; bi += 2 * nw) {
-        load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, bi + nw, vb);
-        use_batch<DT, NB, NF, MODE>(va, sx, kp, want, lane, k_end, bi, acc);
-        load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, bi + 2 * nw, va);
-        use_batch<DT, NB, NF, MODE>(vb, sx, kp, want, lane, k_end, bi + nw, acc);
-    }
-}
-
-template <int DT, int NB, int NF>
-__global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaArgs ga)
+// HP: 16-bit parts of t.
+template <int DT, int NB, int NF, int HP>
+__global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaArgs ga)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = uniform(tid >> 6), nw = uniform(nthr >> 6);
@@ -258,15 +55,6 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
     const int steps = (d_in + kMfmaK - 1) / kMfmaK, n_batches = (steps + B::S - 1) / B::S;
     const size_t block_bytes = (size_t)steps * 1024;
     const unsigned char *x = reinterpret_cast<const unsigned char *>(ga.X);
-    // tokens past the batch repeat its last one; their results are not used
-    uint32_t xoff[B::kX];
-#pragma unroll
-    for (int j = 0; j < B::kX; ++j) xoff[j] = (uint32_t)min(j * (64 / B::kLanes) + lane / B::kLanes, batch - 1) * (uint32_t)d_in * 2u;
-    constexpr int kTiles = NB * NF;
-    // a wave's LDS: its tokens' staging, and its D tiles when the waves meet
-    constexpr int kWaveLds = NF * 16 * B::kPitch > kTiles * 1024 ? NF * 16 * B::kPitch : kTiles * 1024;
-    unsigned char *sx = smem + (size_t)w * kWaveLds;
-
     // the first t_wgs workgroups take a (block, K slice) of t each and wait for nothing; the others a unit of W each
     const int t_wgs = ga.t_end[kMaxGroupLayers - 1] * (ga.phases & 1);
     const bool is_t = (int)blockIdx.x < t_wgs;
@@ -278,22 +66,33 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
         if (first >= e) { job = j + 1; begin = e; }
     }
     const MfmaJob &jb = ga.job[job];
+    if (is_t) {
+        t_unit<DT, NF, HP>(jb, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, ga.phases == 3,
+                           ga.skip_stage1, smem);
+        return;
+    }
     const KeepPattern kp = jb.kp;
-    const int t_slices = ga.t_slices, slice = is_t ? (first - begin) % t_slices : 0;
-    const int unit = is_t ? (first - begin) / t_slices : first - begin;
-    const int lo = is_t ? (int)((unsigned)(n_batches * slice) / (unsigned)t_slices) : 0;
-    const int hi = is_t ? (int)((unsigned)(n_batches * (slice + 1)) / (unsigned)t_slices) : n_batches;
-    const int block0 = is_t ? unit : unit * NB, n_blocks = (jb.d_out + 15) / 16;
-    const unsigned char *mat = reinterpret_cast<const unsigned char *>(is_t ? jb.SVt : jb.W) + (size_t)block0 * block_bytes;
+    const int unit = first - begin, block0 = unit * NB, n_blocks = (jb.d_out + 15) / 16;
+    // tokens past the batch repeat its last one; their results are not used
+    uint32_t xoff[B::kX];
+#pragma unroll
+    for (int j = 0; j < B::kX; ++j) xoff[j] = (uint32_t)min(j * (64 / B::kLanes) + lane / B::kLanes, batch - 1) * (uint32_t)d_in * 2u;
+    constexpr int kTiles = NB * NF;
+    // a wave's LDS: its tokens' staging, and its D tiles when the waves meet
+    constexpr int kWaveLds = NF * 16 * B::kPitch > kTiles * 1024 ? NF * 16 * B::kPitch : kTiles * 1024;
+    unsigned char *sx = smem + (size_t)w * kWaveLds;
+
+    const unsigned char *mat = reinterpret_cast<const unsigned char *>(jb.W) + (size_t)block0 * block_bytes;
     size_t aoff[NB];                                            // (blocks past the matrix: the last one again)
 #pragma unroll
-    for (int k = 0; k < NB; ++k) aoff[k] = is_t ? 0 : (size_t)min(k, n_blocks - 1 - block0) * block_bytes;
+    for (int k = 0; k < NB; ++k) aoff[k] = (size_t)min(k, n_blocks - 1 - block0) * block_bytes;
 
     Batch<NB, NF> va;
-    load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, lo + w, va);
+    const bool streams = !jb.yc;
+    if (streams) load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, w, va);
 
     // ---- which tokens keep a channel, for read-back: the last wave, 16 channels at a time (a lane = a token)
-    if (!is_t && w == nw - 1) {
+    if (w == nw - 1) {
         for (int j = 0; j < ga.n; ++j) {
             const MfmaJob &pj = ga.job[j];
             if (!pj.chan_bits) continue;
@@ -327,9 +126,8 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint32_t want = is_t ? 0xffffffffu : 0u;
-#define RS_STREAM(MODE) stream_rows<DT, NB, NF, MODE>(mat, aoff, x, xoff, sx, kp, want, lane, d_in, lo + w, hi, nw, va, acc)
-    switch (jb.mask_mode) {
+#define RS_STREAM(MODE) stream_rows<DT, NB, NF, MODE>(mat, aoff, x, xoff, sx, kp, 0u, lane, d_in, w, n_batches, nw, va, acc)
+    if (streams) switch (jb.mask_mode) {
     case kMaskNone: RS_STREAM(kMaskNone); break;
     case kMaskOwn: RS_STREAM(kMaskOwn); break;
     case kMaskUnion: RS_STREAM(kMaskUnion); break;
@@ -337,7 +135,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
     default: RS_STREAM(kMaskUnion | kMaskSigned); break;
     }
 #undef RS_STREAM
-    const bool lowrank = !is_t && jb.t_blocks > 0, hand_off = lowrank && ga.phases == 3;
+    const bool lowrank = jb.t_blocks > 0, hand_off = lowrank && ga.phases == 3;
 
     // the waves meet in LDS; sum_up adds up item (tile, lane)
     auto meet = [&]() {
@@ -353,77 +151,19 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
         return s;
     };
 
-    if (is_t) {
-        // ---- t: one wave sums the waves up; with several slices it adds to t_acc, and the last slice to arrive takes the
-        //      sums out again (which leaves zeros); they are split and published
-        meet();
-        if (w == 0) {
-            f32x4 s[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) s[f] = sum_up(f * 64 + lane);
-            bool mine = true;
-            if (ga.t_slices > 1) {
-                float *ta = jb.t_acc + (size_t)unit * NF * 256 + lane;
-#pragma unroll
-                for (int f = 0; f < NF; ++f)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        __hip_atomic_fetch_add(ta + f * 256 + j * 64, s[f][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                wait_own_writes();
-                int *ctr = jb.t_flags + t_flag_pitch(jb.rank) + unit;
-                int arrived = 0;
-                if (lane == 0) arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                mine = uniform(arrived) == ga.t_slices - 1;
-                if (mine) {
-                    if (lane == 0) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                    for (int f = 0; f < NF; ++f)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            s[f][j] = __hip_atomic_exchange(ta + f * 256 + j * 64, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-            if (mine) {
-                const int row = unit * 16 + 4 * (lane >> 4);
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    // rank indices row..row+3 of a token, in operand layout; entries past the rank are zero
-                    uint32_t hi[2] = {0, 0}, lw[2] = {0, 0};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float v = row < jb.rank ? s[f][e] : 0.f;
-                        const uint16_t hb = narrow<DT>(v);
-                        hi[e >> 1] |= (uint32_t)hb << (16 * (e & 1));
-                        lw[e >> 1] |= (uint32_t)narrow<DT>((v - widen16<DT>(hb)) * LoScale<DT>::value) << (16 * (e & 1));
-                    }
-                    const int r = row % kMfmaK;
-                    unsigned char *p = jb.t + (size_t)(row / kMfmaK * NF + f) * 2048 + (size_t)((r / 8) * 16 + (lane & 15)) * 16 + (r % 8) * 2;
-                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)hi[0] | ((unsigned long long)hi[1] << 32),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p + 1024), (unsigned long long)lw[0] | ((unsigned long long)lw[1] << 32),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                if (ga.phases == 3) {
-                    wait_own_writes();                           // performed: now the block counts as ready
-                    if (lane == 0 && !ga.skip_stage1)
-                        __hip_atomic_store(jb.t_flags + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-        }
-        return;
-    }
-
     // ---- U_r t: the rank's steps of 32, one per wave in turn; the rows of U_r are requested before t is waited for
     if (lowrank) {
-        f32x4 ah[NB][NF], al[NB][NF];                          // the products with t's hi and lo halves
+        f32x4 ah[HP][NB][NF];                                  // the products with t's parts
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+        for (int h = 0; h < HP; ++h)
 #pragma unroll
-            for (int f = 0; f < NF; ++f) ah[i][f] = al[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) ah[h][i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
         const int usteps = (jb.rank + kMfmaK - 1) / kMfmaK;
         const size_t ublock = (size_t)usteps * 1024;
         const unsigned char *um = reinterpret_cast<const unsigned char *>(jb.U) + (size_t)block0 * ublock + lane * 16;
-        constexpr int US = NB * NF == 1 ? 4 : 2;
+        constexpr int US = NB * NF == 1 && HP == 2 ? 4 : 2;
         u32x4 ua[US][NB];
         auto request_u = [&](int s0) {
 #pragma unroll
@@ -458,15 +198,15 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
             __atomic_signal_fence(__ATOMIC_ACQUIRE);           // no load of t moves up here
         }
         for (int s0 = w; s0 < usteps; s0 += nw * US) {
-            u32x4 th[US][NF], tl[US][NF];
+            u32x4 th[US][NF][HP];
 #pragma unroll
             for (int u = 0; u < US; ++u) {
                 const int s = min(s0 + u * nw, usteps - 1);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    const unsigned char *p = jb.t + (size_t)(s * NF + f) * 2048 + lane * 16;
-                    th[u][f] = *reinterpret_cast<const u32x4 *>(p);
-                    tl[u][f] = *reinterpret_cast<const u32x4 *>(p + 1024);
+                    const unsigned char *p = jb.t + (size_t)(s * NF + f) * (HP * 1024) + lane * 16;
+#pragma unroll
+                    for (int h = 0; h < HP; ++h) th[u][f][h] = *reinterpret_cast<const u32x4 *>(p + h * 1024);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -476,10 +216,9 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
 #pragma unroll
                     for (int i = 0; i < NB; ++i)
 #pragma unroll
-                        for (int f = 0; f < NF; ++f) {
-                            ah[i][f] = mfma16<DT>(ua[u][i], th[u][f], ah[i][f]);
-                            al[i][f] = mfma16<DT>(ua[u][i], tl[u][f], al[i][f]);
-                        }
+                        for (int f = 0; f < NF; ++f)
+#pragma unroll
+                            for (int h = 0; h < HP; ++h) ah[h][i][f] = mfma16<DT>(ua[u][i], th[u][f][h], ah[h][i][f]);
                 }
             }
             if (s0 + nw * US < usteps) request_u(s0 + nw * US);
@@ -489,7 +228,11 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
 #pragma unroll
             for (int f = 0; f < NF; ++f)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][f][j] += ah[i][f][j] + al[i][f][j] * (1.0f / LoScale<DT>::value);
+                for (int j = 0; j < 4; ++j) {
+                    float rest = ah[1][i][f][j] * (1.0f / LoScale<DT>::value);
+                    if constexpr (HP > 2) rest += ah[2][i][f][j];
+                    acc[i][f][j] += ah[0][i][f][j] + rest;
+                }
     }
 
     meet();
@@ -502,10 +245,18 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 2) void k_mfma_rows(const MfmaAr
     if (counted) arrived = __hip_atomic_fetch_add(t_read + sub * 32, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int item = tid; item < kTiles * 64; item += nthr) {
         const int l = item & 63, tile = item >> 6, i = tile / NF, f = tile % NF;
-        const f32x4 s = sum_up(item);
+        f32x4 s = sum_up(item);
         const int tok = f * 16 + (l & 15);
         const int row = (block0 + i) * 16 + 4 * (l >> 4);       // four consecutive rows (d_out is a multiple of 8)
         if (tok < batch && row < jb.d_out) {
+            if (jb.yc) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float *y = jb.yc + ((size_t)f * jb.yc_rows + row + j) * 16 + (l & 15);
+                    s[j] += *y;
+                    *y = 0.f;
+                }
+            }
             float o[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = jb.bias ? s[j] + jb.bias[row + j] : s[j];
@@ -557,7 +308,7 @@ hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, si
     return hipGetLastError();
 }
 
-size_t mfma_t_bytes(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 2048; }
+size_t mfma_t_bytes(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 3 * 1024; }
 
 // 64 x 64 tiles through LDS, 16 bytes per access on both sides.
 __global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst)
@@ -591,8 +342,16 @@ hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uin
     return hipGetLastError();
 }
 
+// K slices of t: enough workgroups for the chip, a batch of loads for every wave of nw, and at most four, whose sums meet in
+// atomics (8192 x 8192, rank 1024, 8 tokens: 43.5 us with one slice, 39.0 with two, 34.5 with four; 4096 x 4096, rank 256:
+// 16.1 with one, 14.6 with four, 15.4 with sixteen)
+int mfma_t_slices(int t_blocks, int d_in, int nw, int cus)
+{
+    return t_blocks > 0 ? std::max(1, std::min({4, cus / t_blocks, (d_in + kMfmaK * 4 - 1) / (kMfmaK * 4) / nw})) : 1;
+}
+
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
-                       int phases, bool dense, int rows_per_wg_hint, int wait_polls, int skip_stage1, hipStream_t stream)
+                       int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream)
 {
     if (n < 1 || n > kMaxGroupLayers || batch < 1 || batch > 32 || phases < 1 || phases > 3) return hipErrorInvalidValue;
     const int nf = batch > 16 ? 2 : 1;
@@ -602,22 +361,21 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     a.skip_stage1 = skip_stage1;
     // Units of one block for up to 16 tokens, of two for more (a unit reads all tokens, from L2, beside its rows: at 32
     // tokens and one block twice the bytes of the rows; measured at 8192 x 8192, 32 tokens: dense 33.7 us with one block,
-    // 27.0 with two; at 8 tokens 23.2 and 22.9, at 4096 -> 14336 with 16 tokens 70.9 and 78.1) -- unless that leaves
-    // compute units without a unit.  Four waves a unit: with eight the same bytes are in flight in half the workgroups
-    // (8192 x 8192, 8 tokens: 24.7 against 25.8 us).
-    int nb = 1, nw = 4;
-    if (nf == 2) {
-        int blocks = 0;
-        for (int i = 0; i < n; ++i) blocks += (L[i].d_out + 15) / 16;
-        if (blocks >= 2 * cus || rows_per_wg_hint > 0) nb = 2;
-    }
+    // 27.0 with two; at 8 tokens 23.2 and 22.9, at 4096 -> 14336 with 16 tokens 70.9 and 78.1).  Four waves a unit: with eight
+    // the same bytes are in flight in half the workgroups (8192 x 8192, 8 tokens: 24.7 against 25.8 us).
+    const int nb = nf, nw = 4;
+    // fp32 t in two parts (fp16: 22 bits; bf16: 16), in three of bf16 where the W part was summed by an earlier launch: those
+    // layers' vector kernels keep t in 32 bits
+    bool parts3 = false;
     int w_total = 0, t_blocks = 0;
     for (int i = 0; i < n; ++i) {
         MfmaJob &jb = a.job[i];
         const LayerView &v = L[i];
         const MatrixView &m = M[i];
-        if (v.d_in != a.d_in || v.dtype != L[0].dtype || !mfma_path_supported(m, batch) || !Y[i]) return hipErrorInvalidValue;
+        if (v.d_in != a.d_in || v.dtype != L[0].dtype || (!m.W && !m.yc) || !Y[i]) return hipErrorInvalidValue;
         jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.Y = Y[i]; jb.bias = v.bias;
+        jb.yc = m.W ? nullptr : m.yc; jb.yc_rows = m.yc_rows;
+        if (jb.yc) parts3 = v.dtype == BF16;
         jb.t_acc = m.t_acc; jb.t_flags = m.t_flags;
         jb.chan_bits = dense ? nullptr : chan_bits[i];
         jb.sync = v.sync; jb.d_out = v.d_out; jb.rank = dense ? 0 : v.rank; jb.out_dtype = v.out_dtype;
@@ -630,11 +388,8 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
         t_blocks += jb.t_blocks;
         a.w_end[i] = w_total;
     }
-    const int batch_k = kMfmaK * (nb == 1 ? 4 : 2), n_batches = (a.d_in + batch_k - 1) / batch_k;
-    // K slices of t: enough workgroups for the chip, a batch of loads for every wave, and at most four, whose sums meet in
-    // atomics (8192 x 8192, rank 1024, 8 tokens: 43.5 us with one slice, 39.0 with two, 34.5 with four; 4096 x 4096, rank
-    // 256: 16.1 with one, 14.6 with four, 15.4 with sixteen)
-    a.t_slices = t_blocks > 0 ? std::max(1, std::min({4, cus / t_blocks, n_batches / nw})) : 1;
+    const int batch_k = kMfmaK * (nf == 1 ? 4 : 2);
+    a.t_slices = mfma_t_slices(t_blocks, a.d_in, nw, cus);
     int t_total = 0;
     for (int i = 0; i < kMaxGroupLayers; ++i) {
         if (i < n) t_total += a.job[i].t_blocks * a.t_slices;
@@ -645,15 +400,11 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     const size_t lds = (size_t)nw * std::max(nf * 16 * (batch_k * 2 + 16), nb * nf * 1024);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((phases & 1 ? t_total : 0) + (phases & 2 ? w_total : 0)), block(64 * nw);
-#define RS_M(DT, NBV, NFV) hipLaunchKernelGGL((k_mfma_rows<DT, NBV, NFV>), grid, block, lds, stream, a)
-#define RS_MD(DT)                                                                               \
-    do {                                                                                        \
-        if (nf == 1) RS_M(DT, 1, 1);                                                            \
-        else if (nb == 1) RS_M(DT, 1, 2);                                                       \
-        else RS_M(DT, 2, 2);                                                                    \
-    } while (0)
-    if (L[0].dtype == F16) RS_MD(F16); else RS_MD(BF16);
-#undef RS_MD
+#define RS_M(DT, NBV, NFV, HPV) hipLaunchKernelGGL((k_mfma_rows<DT, NBV, NFV, HPV>), grid, block, lds, stream, a)
+    const int parts = parts3 ? 3 : 2;
+    if (L[0].dtype == F16) { if (nf == 1) RS_M(F16, 1, 1, 2); else RS_M(F16, 2, 2, 2); }
+    else if (parts == 2) { if (nf == 1) RS_M(BF16, 1, 1, 2); else RS_M(BF16, 2, 2, 2); }
+    else { if (nf == 1) RS_M(BF16, 1, 1, 3); else RS_M(BF16, 2, 2, 3); }
 #undef RS_M
     return hipGetLastError();
 }

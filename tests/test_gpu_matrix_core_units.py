@@ -106,3 +106,30 @@ def test_bounded_wait_for_t_runs_out_and_the_handle_recovers():
     rs.rsparse_set_tuning(layer)
     for _ in range(2):
         _parity(layer, L, X16, tau)
+
+
+@pytest.mark.parametrize("d_in,d_out,rank,group", [(32, 8, 0, 32), (96, 136, 8, 32), (1024, 264, 40, 1024), (1152, 1160, 72, 128), (4160, 520, 24, 64)])
+@pytest.mark.parametrize("dt", [synth.F16, synth.BF16])
+def test_q4_units(d_in, d_out, rank, group, dt):
+    """4-bit weights: outputs that leave part of a 256-output unit or of its second half, contractions shorter than the waves
+    of a workgroup, groups cut by wave shares, both token tiles, own and union masks, batches in any order on one handle, and
+    the same results as the vector kernels."""
+    L = synth.random_layer(d_in, d_out, rank, dt, seed=11 + d_in + d_out)
+    Q, S16, Z = synth.quantize_q4(synth.decode16(L.W16, dt), dt, group)
+    X16, src = gu.tokens_for(L, 32, linear=5)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    U16, SV16 = (L.U16, L.SV16) if rank else (None, None)
+    for mode in (0, 1):
+        cfg = rs.make_config(d_in, d_out, rank, tau, dt, max_batch=32, out_dtype=rs.F32, batch_mask_mode=mode)
+        layer = rs.rsparse_prepare_q4(cfg, Q, S16, Z, group, U16, SV16)
+        for B in (16, 5, 32, 2, 17):
+            want = oracle.rsparse_linear_q4(Q, S16, Z, U16, SV16, X16[:B], dt, tau, group=group, batch_mask_mode=mode)
+            got = gu.run_linear(layer, X16[:B])
+            gu.check_lists(got, want)
+            gu.check_outputs(got["Y"], want["Y"], rs.F32)
+            rs.rsparse_set_tuning(layer, mfma_min_batch=33)
+            vec = gu.run_linear(layer, X16[:B])
+            rs.rsparse_set_tuning(layer)
+            gu.check_lists(got, vec)
+            gu.check_outputs(got["Y"], vec["Y"], rs.F32)
+        layer.destroy()
