@@ -75,9 +75,11 @@ typedef struct {
                                 strictly more accurate at the same bytes) */
     int32_t dense_rowmajor;  /* 1: also keep W row by row on the device, in the matrix cores' operand layout (doubles the
                                 weight footprint; layers under 2^22 weights keep a plain row-major copy besides).  Needed by
-                                the matrix-core path that rsparse_linear takes from 5 tokens on and rsparse_dense_ref at
-                                any batch (see mfma_min_batch), and by the row-dot kernel; without it batches from 5 tokens on
-                                run in tiles of up to 8 tokens on the vector ALU */
+                                the one-launch matrix-core path that rsparse_linear takes from 5 tokens on and
+                                rsparse_dense_ref at any batch (see mfma_min_batch), and by the row-dot kernel; without it
+                                batches from 5 tokens on take the matrix cores over column-major W (two launches; the
+                                factors are kept a second time, in operand layout, where max_batch >= 5); fixed-count
+                                activation and strips run in tiles of up to 8 tokens on the vector ALU */
     int32_t strip_cols;      /* layout of W on the device for the vector path (up to 8 tokens per batch tile).  0: column-major
                                 (Sec. 3.4), run by the column-tile kernel: tiles of 512 outputs x channel splits whose partial
                                 sums meet in fp32 atomics.  32, 64, 128, 256 or 512: the columns are cut into strips of that
@@ -117,8 +119,8 @@ typedef struct {
                                 only -- for timing one kernel in isolation; results are only valid with 0 */
     int32_t tile_map;        /* workgroup -> (column tile, split) mapping: 0 default, 1 tile-fastest (plain),
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
-    int32_t mfma_min_batch;  /* smallest batch that takes the matrix-core path (16-bit weights: needs dense_rowmajor = 1; 4-bit
-                                weights: needs max_batch >= 2): 0 = default (5 for rsparse_linear, 2 on 4-bit weights; for
+    int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
+                                dense_rowmajor = 1; 4-bit weights: max_batch >= 2): 0 = default (5 for rsparse_linear, 2 on 4-bit weights; for
                                 rsparse_dense_ref 1, 2 on layers under 2^22 weights, and with dense_kernel set 2, 4 on layers
                                 of 2^25 weights or more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on
                                 4-bit weights, on the vector ALU) */

@@ -235,6 +235,11 @@ constexpr size_t kRowdotWeights = (size_t)1 << 22;
 // (measured, us for gate, up and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 60 -> 65 at one token, 106 -> 66
 // at two, 226 -> 66 at four, 717 -> 68 at sixteen, 1342 -> 96 at 32).
 constexpr int kMfmaMinBatchQ4 = 2;
+// Smallest batch that column-major layers without the operand-layout copy run on the matrix cores (measured, us for gate, up
+// and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 76 at five,
+// 234 -> 79 at sixteen, 389 -> 93 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
+// gain does not make up for the launch that the gate / up pair then needs, nor for the factors' second copy.
+constexpr int kMfmaMinBatchCols = 5;
 
 int batch_tile_of(int batch) { return batch <= 1 ? 1 : batch <= 2 ? 2 : batch <= 4 ? 4 : 8; }
 
@@ -564,9 +569,11 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         }
         // 4-bit layers take the matrix cores from their own threshold on
         const bool q4_mm = q4 && cfg->max_batch >= kMfmaMinBatchQ4;
-        if (q4_mm) {
-            const size_t words = mfma_q4_words(L->qtiles, cfg->max_batch);
-            L->yc_rows = L->qtiles * kQ4Tile;
+        // ... and column-major layers without the operand-layout copy from theirs
+        const bool cols_mm = L->M && !cfg->dense_rowmajor && cfg->max_batch >= kMfmaMinBatchCols;
+        if (q4_mm || cols_mm) {
+            L->yc_rows = q4 ? L->qtiles * kQ4Tile : (int)d_out;
+            const size_t words = (size_t)((cfg->max_batch + 15) / 16) * L->yc_rows * 16;
             RS_HIP(hipMalloc((void **)&L->yc, words * 4));
             RS_HIP(hipMemset(L->yc, 0, words * 4));
             rsparse_status ts = RSPARSE_OK;
@@ -574,7 +581,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
             if (ts == RSPARSE_OK && r) ts = make_operand(L->U, d_out, r, 16, &L->Utile);
             if (ts != RSPARSE_OK) return ts;
         }
-        if (((cfg->dense_rowmajor && !q4) || q4_mm) && r) {
+        if (((cfg->dense_rowmajor && !q4) || q4_mm || cols_mm) && r) {
             RS_HIP(hipMalloc(&L->t16, mfma_t_bytes((int)r)));
             RS_HIP(hipMemset(L->t16, 0, mfma_t_bytes((int)r)));
             RS_HIP(hipMalloc((void **)&L->t_acc, (r + 31) / 32 * 32 * 32 * 4));
@@ -887,6 +894,10 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     for (int i = 0; i < n_layers; ++i) mv[i] = layers[i]->matrix(v[i]);
     bool mfma = !ov && batch >= (layers[0]->tuning.mfma_min_batch > 0 ? layers[0]->tuning.mfma_min_batch : kMfmaDefaultMinBatch);
     for (int i = 0; i < n_layers; ++i) mfma = mfma && mfma_path_supported(mv[i], batch) && layers[i]->cfg.topk == 0;
+    // column-major layers: the matrix cores over W as it is
+    const rsparse_tuning &tn = layers[0]->tuning;
+    bool cols = !mfma && !ov && tn.launches != 1 && batch >= (tn.mfma_min_batch > 0 ? tn.mfma_min_batch : kMfmaMinBatchCols);
+    for (int i = 0; i < n_layers; ++i) cols = cols && mv[i].yc && v[i].M && layers[i]->cfg.topk == 0;
     // a gated input is written out once first (one small launch), then the layer runs on it
     if (G_dev) {
         RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
@@ -899,7 +910,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
                                      const_cast<KeepRule *>(v[i].rules), s));
     // layers packed in strips go through the strip kernel; a group must share one layout (and one strip width),
     // otherwise its layers run one at a time
-    if (!mfma && n_layers > 1) {
+    if (!mfma && !cols && n_layers > 1) {
         bool same = true;
         for (int i = 1; i < n_layers; ++i) same = same && layers[i]->strip_w == layers[0]->strip_w;
         if (!same) {
@@ -910,7 +921,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
             return RSPARSE_OK;
         }
     }
-    const bool strip = !mfma && layers[0]->Ms != nullptr;
+    const bool strip = !mfma && !cols && layers[0]->Ms != nullptr;
     if (strip) {
         Launch sc[RSPARSE_MAX_GROUP];
         for (int i = 0; i < n_layers; ++i) sc[i] = resolve_strip(layers[i], batch, false, n_layers, fused);
@@ -941,6 +952,11 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
             if (stages != 2) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 1, false, 0, 0, s));
             if (stages != 1) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, false, 0, 0, s));
         }
+    } else if (cols) {
+        uint32_t *bits[RSPARSE_MAX_GROUP];
+        for (int i = 0; i < n_layers; ++i) bits[i] = layers[i]->chan_bits;
+        if (stages != 2) RS_HIP(launch_mfma_cols(v, mv, n_layers, X_dev, batch, false, layers[0]->cus, s));
+        if (stages != 1) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, false, 0, 0, s));
     } else if (fused) {
         RS_HIP(launch_fused(v, lc, n_layers, X_dev, batch, Y_devs, s));
     } else {
@@ -950,7 +966,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     for (int i = 0; i < n_layers; ++i) {
         layers[i]->last_stream = s;
         layers[i]->last_batch = batch;
-        layers[i]->last_mfma = mfma;
+        layers[i]->last_mfma = mfma || cols;
         layers[i]->last_fused = fused;
         layers[i]->last_bt = 0;
         layers[i]->last_strip = false;
@@ -983,7 +999,9 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
     for (int i = 0; i < 2; ++i) mfma = mfma && mfma_path_supported(pair[i]->matrix(v[i]), batch) && pair[i]->cfg.topk == 0;
     const int bt = batch_tile_of(batch);
     const bool one_tile = (batch + bt - 1) / bt == 1;
-    if (fused && !mfma && one_tile && lc[0].tile_map != 2 && lc[1].tile_map != 2 && gate->M && up->M) {
+    bool cols = gate->tuning.launches != 1 && batch >= (gate->tuning.mfma_min_batch > 0 ? gate->tuning.mfma_min_batch : kMfmaMinBatchCols);
+    for (int i = 0; i < 2; ++i) cols = cols && pair[i]->yc && pair[i]->M && pair[i]->cfg.topk == 0;
+    if (fused && !mfma && !cols && one_tile && lc[0].tile_map != 2 && lc[1].tile_map != 2 && gate->M && up->M) {
         // both projections and the activation in one launch: the last workgroup of a column tile
         // rounds g and u, applies silu(g) * u and stores H
         for (int i = 0; i < 2; ++i)
@@ -1082,6 +1100,14 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     }
     if (mfma) {
         RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, nullptr, layers[0]->cus, 3, true, 0, 0, s));
+        return RSPARSE_OK;
+    }
+    // column-major layers: the matrix cores over W as it is
+    bool cols = asked == 0 && batch >= (layers[0]->tuning.mfma_min_batch > 0 ? layers[0]->tuning.mfma_min_batch : kMfmaMinBatchCols);
+    for (int i = 0; i < n_layers; ++i) cols = cols && mv[i].yc && v[i].M;
+    if (cols) {
+        RS_HIP(launch_mfma_cols(v, mv, n_layers, X_dev, batch, true, layers[0]->cus, s));
+        RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, nullptr, layers[0]->cus, 2, true, 0, 0, s));
         return RSPARSE_OK;
     }
     int kernel = layers[0]->tuning.dense_kernel;

@@ -189,7 +189,9 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
 // with_t: t as well, in the parts that launch_mfma's phase 2 expects of such layers.
 int mfma_t_slices(int t_blocks, int d_in, int nw, int cus);
 hipError_t launch_mfma_q4(const LayerView &L, const MatrixView &M, bool with_t, const void *X, int batch, bool dense, int cus, hipStream_t stream);
-size_t mfma_q4_words(int qtiles, int max_batch);
+// The same over column-major W (kernels_mfma_cols.hip; layers without the operand-layout copy), n layers that read the same
+// input: yc [token tile][yc_rows >= d_out][16 tokens].
+hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, bool dense, int cus, hipStream_t stream);
 // The whole layer over strip-major weights (LayerView::Ms), up to 8 tokens per batch tile: one workgroup per strip
 // of strip_w output columns streams all kept rows of the strip and stores its slice of Y (cfg[i].splits == 1), or
 // `splits` workgroups per strip meet in yacc.  fused: stage 1 runs in the same launch and hands t over through

@@ -259,6 +259,4 @@ hipError_t launch_mfma_q4(const LayerView &L, const MatrixView &M, bool with_t, 
     return hipGetLastError();
 }
 
-size_t mfma_q4_words(int qtiles, int max_batch) { return (size_t)((max_batch + 15) / 16) * qtiles * kQ4Tile * 16; }
-
 }  // namespace rsparse

@@ -133,3 +133,44 @@ def test_q4_units(d_in, d_out, rank, group, dt):
             gu.check_lists(got, vec)
             gu.check_outputs(got["Y"], vec["Y"], rs.F32)
         layer.destroy()
+
+
+@pytest.mark.parametrize("d_in,d_out,rank", [(8, 8, 8), (40, 136, 0), (136, 120, 24), (1032, 264, 136), (4104, 1032, 72)])
+@pytest.mark.parametrize("dt", [synth.F16, synth.BF16])
+def test_column_major_units(d_in, d_out, rank, dt):
+    """Column-major W on the matrix cores: outputs that leave part of a 128-output unit, a last step partly past d_in, both
+    token tiles, both mask modes, batches in any order on one handle, the dense product, and the vector kernels' results."""
+    L = synth.random_layer(d_in, d_out, rank, dt, seed=17 + d_in + d_out)
+    X16, src = gu.tokens_for(L, 32, linear=6)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    for mode in (0, 1):
+        layer = gu.prepare(L, tau, max_batch=32, out_dtype=rs.F32, batch_mask_mode=mode)
+        for B in (16, 5, 32, 3, 17):
+            _parity(layer, L, X16[:B], tau, batch_mask_mode=mode)
+            got = gu.run_linear(layer, X16[:B])
+            rs.rsparse_set_tuning(layer, mfma_min_batch=33)
+            vec = gu.run_linear(layer, X16[:B])
+            rs.rsparse_set_tuning(layer)
+            gu.check_lists(got, vec)
+            gu.check_outputs(got["Y"], vec["Y"], rs.F32)
+            gu.check_outputs(gu.run_dense(layer, X16[:B]), oracle.dense_linear(L.W16, X16[:B], L.dtype, L.dtype, nthreads=8), rs.F32)
+        layer.destroy()
+
+
+def test_column_major_group_and_gate_up_pair():
+    """A group of layers and the gate / up pair share the two launches at 9 tokens; signed threshold with a bias on one."""
+    Ls = [synth.random_layer(520, o, r, synth.BF16, seed=60 + o) for o, r in ((264, 40), (264, 8), (72, 0))]
+    X16, src = gu.tokens_for(Ls[0], 9, linear=2)
+    tau = gu.calibrated_tau(Ls[0], src, 0.5)
+    layers = [gu.prepare(L, tau, max_batch=9) for L in Ls]
+    Xd = gu.to_dev16(X16)
+    for _ in range(2):
+        Ys = [gu._alloc_out(l, 9) for l in layers]
+        rs.rsparse_linear_group(layers, Xd.data_ptr(), 9, [y.data_ptr() for y in Ys], gu.stream_ptr())
+        outs = [gu._read_out(l, y) for l, y in zip(layers, Ys)]
+        for l, L, y in zip(layers, Ls, outs):
+            gu.check_outputs(y, gu.oracle_linear(L, X16, tau)["Y"], rs.BF16)
+    H = gu._alloc_out(layers[0], 9)
+    rs.rsparse_mlp_gate_up(layers[0], layers[1], Xd.data_ptr(), 9, H.data_ptr(), gu.stream_ptr())
+    want = oracle.gated_input(synth.encode16(outs[0], synth.BF16), synth.encode16(outs[1], synth.BF16), synth.BF16)
+    gu.check_outputs(gu._read_out(layers[0], H), synth.decode16(want, synth.BF16), rs.BF16)
