@@ -231,10 +231,12 @@ namespace {
 // Layers below this many weights keep W row-major beside the operand layout (dense_rowmajor = 1): the row-dot kernel is
 // the faster dense kernel there at one token (rsparse_dense_ref_group).
 constexpr size_t kRowdotWeights = (size_t)1 << 22;
-// Smallest batch that 4-bit layers run on the matrix cores
-// (measured, us for gate, up and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 60 -> 65 at one token, 106 -> 66
-// at two, 226 -> 66 at four, 717 -> 68 at sixteen, 1342 -> 96 at 32).
-constexpr int kMfmaMinBatchQ4 = 2;
+// 4-bit layers run on the matrix cores from two tokens on, and at one token up to 2^25 weights (measured, us, vector ALU ->
+// matrix cores, at one token: 4096 x 4096 15.4 -> 14.0, q/k/v grouped and o 57 -> 37, gate and up 4096 -> 8192 grouped and
+// down 48 -> 38, but gate and up 4096 -> 11008 and down, rank 512, 61.4 -> 62.1: half the codes are skipped there and the
+// stream is long enough to show it; at two tokens the last one 105 -> 63, at sixteen 717 -> 66, at 32 1340 -> 86).
+constexpr size_t kMfmaQ4OneToken = (size_t)1 << 25;
+int q4_min_batch(const rsparse_config &c) { return (size_t)c.d_in * c.d_out <= kMfmaQ4OneToken ? 1 : 2; }
 // Smallest batch that column-major layers without the operand-layout copy run on the matrix cores (measured, us for gate, up
 // and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 76 at five,
 // 234 -> 79 at sixteen, 389 -> 93 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
@@ -568,7 +570,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
             }
         }
         // 4-bit layers take the matrix cores from their own threshold on
-        const bool q4_mm = q4 && cfg->max_batch >= kMfmaMinBatchQ4;
+        const bool q4_mm = q4 && cfg->max_batch >= q4_min_batch(*cfg);
         // ... and column-major layers without the operand-layout copy from theirs
         const bool cols_mm = L->M && !cfg->dense_rowmajor && cfg->max_batch >= kMfmaMinBatchCols;
         if (q4_mm || cols_mm) {
@@ -603,7 +605,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->rules, (size_t)cfg->max_batch * sizeof(KeepRule)));
         RS_HIP(hipMemset(L->rules, 0, (size_t)cfg->max_batch * sizeof(KeepRule)));
         const size_t flags_at = (sync_words(std::max(L->tiles, L->strips)) + 31) / 32 * 32;
-        L->sync_n = flags_at + (r ? t_flag_words((int)r) : 0);     // (matrix-core path)
+        L->sync_n = flags_at + (L->t16 ? t_flag_words((int)r) : 0);   // (matrix-core path)
         RS_HIP(hipMalloc((void **)&L->sync, L->sync_n * 4));
         RS_HIP(hipMemset(L->sync, 0, L->sync_n * 4));
         L->t_flags = L->sync + flags_at;
@@ -770,23 +772,44 @@ Launch resolve_launch_q4(const rsparse_layer *L, int batch, bool dense, bool fus
     return c;
 }
 
-// One layer with 4-bit weights: first launch (codes dequantised in registers), then the common finish.
+// Whether 4-bit layers that read the same input run on the matrix cores, all in the same two launches.
+bool q4_matrix_cores(rsparse_layer *const *layers, int n, int batch)
+{
+    const rsparse_tuning &t = layers[0]->tuning;
+    bool ok = t.launches != 1;
+    for (int i = 0; i < n; ++i)
+        ok = ok && layers[i]->q4() && layers[i]->yc && batch >= (t.mfma_min_batch > 0 ? t.mfma_min_batch : q4_min_batch(layers[i]->cfg));
+    return ok;
+}
+
+rsparse_status linear_q4_matrix_cores(rsparse_layer *const *layers, int n, const void *X_dev, int32_t batch, void *const *Y_devs, bool dense,
+                                      hipStream_t s)
+{
+    LayerView v[RSPARSE_MAX_GROUP];
+    MatrixView mv[RSPARSE_MAX_GROUP];
+    uint32_t *bits[RSPARSE_MAX_GROUP];
+    for (int i = 0; i < n; ++i) {
+        v[i] = layers[i]->view(nullptr, batch, dense);
+        mv[i] = layers[i]->matrix(v[i]);
+        bits[i] = layers[i]->chan_bits;
+    }
+    const int stages = layers[0]->tuning.stages;
+    if (stages != 2) RS_HIP(launch_mfma_q4(v, mv, n, X_dev, batch, dense, layers[0]->cus, s));
+    if (stages != 1) RS_HIP(launch_mfma(v, mv, n, X_dev, batch, Y_devs, bits, layers[0]->cus, 2, dense, 0, 0, s));
+    if (!dense)
+        for (int i = 0; i < n; ++i) {
+            rsparse_layer *L = layers[i];
+            L->last_stream = s; L->last_batch = batch; L->last_mfma = true; L->last_fused = true; L->last_bt = 0; L->last_strip = false;
+            L->last_scratch = L->own_scratch();
+        }
+    return RSPARSE_OK;
+}
+
+// One layer with 4-bit weights on the vector ALU: first launch (codes dequantised in registers), then the common finish.
 rsparse_status linear_q4(rsparse_layer *L, const void *X_dev, int32_t batch, void *Y_dev, bool dense, hipStream_t s)
 {
     const LayerView v = L->view(nullptr, batch, dense);
     const int stages = L->tuning.stages;
-    const int mm_min = L->tuning.mfma_min_batch > 0 ? L->tuning.mfma_min_batch : kMfmaMinBatchQ4;
-    if (L->yc && batch >= mm_min && L->tuning.launches != 1) {
-        const MatrixView mv = L->matrix(v);
-        uint32_t *bits = L->chan_bits;
-        if (stages != 2) RS_HIP(launch_mfma_q4(v, mv, true, X_dev, batch, dense, L->cus, s));
-        if (stages != 1) RS_HIP(launch_mfma(&v, &mv, 1, X_dev, batch, &Y_dev, &bits, L->cus, 2, dense, 0, 0, s));
-        if (!dense) {
-            L->last_stream = s; L->last_batch = batch; L->last_mfma = true; L->last_fused = true; L->last_bt = 0; L->last_strip = false;
-            L->last_scratch = L->own_scratch();
-        }
-        return RSPARSE_OK;
-    }
     // two launches by default: the one-launch form (launches = 1) measured no faster on these weights --
     // its tail waits for up to `splits` same-address atomics that the two-launch form never waits for
     // (its arrival counters cover up to kSyncMaxZ batch tiles of 4 tokens)
@@ -866,13 +889,16 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     bool any_q4 = false;
     for (int i = 0; i < n_layers; ++i) any_q4 = any_q4 || layers[i]->q4();
     if (any_q4) {
-        // layers with 4-bit weights run one at a time, each in its own pair of launches
+        // layers with 4-bit weights: together on the matrix cores, or one at a time, each in its own pair of launches
         if (G_dev) {
             RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
             X_dev = layers[0]->xg;
         }
+        if (q4_matrix_cores(layers, n_layers, batch)) return linear_q4_matrix_cores(layers, n_layers, X_dev, batch, Y_devs, false, s);
         for (int i = 0; i < n_layers; ++i) {
-            rsparse_status qs = layers[i]->q4() ? linear_q4(layers[i], X_dev, batch, Y_devs[i], false, s)
+            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch)
+                                                       ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], false, s)
+                                                       : linear_q4(layers[i], X_dev, batch, Y_devs[i], false, s))
                                                 : linear_group_impl(&layers[i], 1, X_dev, nullptr, batch, &Y_devs[i], stream);
             if (qs != RSPARSE_OK) return qs;
         }
@@ -1065,7 +1091,9 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
             }
             if (Lq->q4() && Lq->tuning.dense_kernel == 2)
                 return fail(RSPARSE_EINVAL, "row-dot dense kernel on 4-bit weights needs dense_rowmajor=1, groups >= 32 and batch_tile*d_in*2.125 <= 64 KiB");
-            rsparse_status qs = layers[i]->q4() ? linear_q4(layers[i], X_dev, batch, Y_devs[i], true, s)
+            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch)
+                                                       ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], true, s)
+                                                       : linear_q4(layers[i], X_dev, batch, Y_devs[i], true, s))
                                                 : rsparse_dense_ref_group(&layers[i], 1, X_dev, batch, &Y_devs[i], stream);
             if (qs != RSPARSE_OK) return qs;
         }

@@ -184,11 +184,11 @@ hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, si
 hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream);
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
                        int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream);
-// 4-bit weights on the matrix cores (kernels_mfma_q4.hip), up to 32 tokens: adds the W part of the layer (dense: the whole
-// product) to yc, [token tile][qtiles * 1024][16 tokens]; launch_mfma with MatrixView::W null completes the layer.
-// with_t: t as well, in the parts that launch_mfma's phase 2 expects of such layers.
+// 4-bit weights on the matrix cores (kernels_mfma_q4.hip), up to 32 tokens, n layers that read the same input: adds the W
+// part of each layer (dense: the whole product) to its yc, [token tile][qtiles * 1024][16 tokens], and stores t in the parts
+// that launch_mfma's phase 2 expects of such layers (MatrixView::W null), which completes them.
 int mfma_t_slices(int t_blocks, int d_in, int nw, int cus);
-hipError_t launch_mfma_q4(const LayerView &L, const MatrixView &M, bool with_t, const void *X, int batch, bool dense, int cus, hipStream_t stream);
+hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, bool dense, int cus, hipStream_t stream);
 // The same over column-major W (kernels_mfma_cols.hip; layers without the operand-layout copy), n layers that read the same
 // input: yc [token tile][yc_rows >= d_out][16 tokens].
 hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, bool dense, int cus, hipStream_t stream);

@@ -26,15 +26,18 @@ namespace {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-struct MfmaQ4Args {
+struct MfmaQ4Job {
+    MfmaJob t;                   // its t part, mask, yc [token tile][yc_rows][16] fp32, added to with atomics
     const uint8_t *Mq, *qz;
-    const uint16_t *qs, *X;
-    float *yc;                   // [token tile][d_out rounded up to 256][16] fp32, added to with atomics
-    MfmaJob t;                   // (its t part only)
-    int t_slices, t_wgs;         // workgroups of t, at the front of the grid
-    int d_in, batch, qtiles, qshift, splits, units, rows_pad;
-    int mask_mode;
-    KeepPattern kp;
+    const uint16_t *qs;
+    int qtiles, qshift, splits, units;
+};
+struct MfmaQ4Args {
+    MfmaQ4Job job[kMaxGroupLayers];
+    int t_end[kMaxGroupLayers];  // workgroups of t of jobs 0..i, at the front of the grid
+    int w_end[kMaxGroupLayers];  // workgroups of the codes of jobs 0..i
+    const uint16_t *X;
+    int d_in, batch, t_slices;
 };
 
 // Kept values of one token tile under the union mask of a batch of two tiles.
@@ -90,22 +93,34 @@ __device__ __forceinline__ void operands(const u32x2 (&c)[8], int h, u32x4 (&a)[
 
 // NF: token tiles of 16 of the call (for t; a workgroup of the codes takes one tile).
 template <int DT, int NF>
-__global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args a)
+__global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args ga)
 {
     // per wave: scales (16-bit) and zero points (bytes) of its 256 outputs; later half the waves' sums [out][token]
     constexpr int kLds = kQ4Waves * kQ4Outs * 16 * 4 / 2, kLdsT = kQ4Waves * t_unit_lds<NF>;
     __shared__ __align__(16) unsigned char smem[kLds > kLdsT ? kLds : kLdsT];
-    if ((int)blockIdx.x < a.t_wgs) {
-        t_unit<DT, NF, DT == BF16 ? 3 : 2>(a.t, a.X, a.batch, a.d_in, (int)blockIdx.x / a.t_slices, (int)blockIdx.x % a.t_slices, a.t_slices, false, 0, smem);
+    const int t_wgs = ga.t_end[kMaxGroupLayers - 1];
+    const bool is_t = (int)blockIdx.x < t_wgs;
+    const int first = is_t ? (int)blockIdx.x : (int)blockIdx.x - t_wgs;
+    int job = 0, begin = 0;
+#pragma unroll
+    for (int j = 0; j < kMaxGroupLayers - 1; ++j) {
+        const int e = is_t ? ga.t_end[j] : ga.w_end[j];
+        if (first >= e) { job = j + 1; begin = e; }
+    }
+    const MfmaQ4Job &a = ga.job[job];
+    const int d_in = ga.d_in, batch = ga.batch;
+    if (is_t) {
+        t_unit<DT, NF, DT == BF16 ? 3 : 2>(a.t, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, false, 0, smem);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
-    const int id = (int)blockIdx.x - a.t_wgs, split = id % a.splits, unit = id / a.splits % a.units, ttile = id / a.splits / a.units, tok0 = ttile * 16;
-    const int d_in = a.d_in, i16 = lane & 15, g4 = lane >> 4;
+    const int id = first - begin, split = id % a.splits, unit = id / a.splits % a.units, ttile = id / a.splits / a.units, tok0 = ttile * 16;
+    const int i16 = lane & 15, g4 = lane >> 4, mode = a.t.mask_mode;
+    const KeepPattern kp = a.t.kp;
     const int tile = unit >> 2, lb = (unit & 3) * 16;           // 1024-output tile, first of its 16 lane slots
     const size_t ldq = (size_t)a.qtiles * (kQ4Tile / 2), lds = (size_t)a.qtiles * kQ4Tile;
     const uint8_t *codes = a.Mq + (size_t)tile * (kQ4Tile / 2) + (lb + i16) * 8;
-    const uint16_t *xrow = a.X + (size_t)min(tok0 + i16, a.batch - 1) * d_in;
+    const uint16_t *xrow = ga.X + (size_t)min(tok0 + i16, batch - 1) * d_in;
     // the unit's outputs: tile * 1024 + h * 512 + lb * 8 + 0..127 for h = 0, 1
     const int col0 = tile * kQ4Tile + lb * 8;
     const int steps = d_in / kMfmaK, gsteps = 1 << (a.qshift - 5);     // groups hold 32 channels or more
@@ -135,16 +150,16 @@ __global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args a
     };
     auto use_step = [&](const Q4Step &v, int s) {
         u32x4 b[1] = {v.x};
-        switch (a.mask_mode) {
+        switch (mode) {
         case kMaskNone: break;
-        case kMaskOwn: mask_step<1, kMaskOwn>(b, a.kp, 0u); break;
-        case kMaskOwn | kMaskSigned: mask_step<1, kMaskOwn | kMaskSigned>(b, a.kp, 0u); break;
-        case kMaskUnion: if (a.batch <= 16) mask_step<1, kMaskUnion>(b, a.kp, 0u); break;
-        default: if (a.batch <= 16) mask_step<1, kMaskUnion | kMaskSigned>(b, a.kp, 0u); break;
+        case kMaskOwn: mask_step<1, kMaskOwn>(b, kp, 0u); break;
+        case kMaskOwn | kMaskSigned: mask_step<1, kMaskOwn | kMaskSigned>(b, kp, 0u); break;
+        case kMaskUnion: if (batch <= 16) mask_step<1, kMaskUnion>(b, kp, 0u); break;
+        default: if (batch <= 16) mask_step<1, kMaskUnion | kMaskSigned>(b, kp, 0u); break;
         }
-        if ((a.mask_mode & kMaskUnion) && a.batch > 16) {       // the other tile's tokens count too
-            const u32x4 o = *reinterpret_cast<const u32x4 *>(a.X + (size_t)min((tok0 ^ 16) + i16, a.batch - 1) * d_in + s * kMfmaK + g4 * 8);
-            mask_union_two(b[0], o, a.kp, (a.mask_mode & kMaskSigned) != 0);
+        if ((mode & kMaskUnion) && batch > 16) {       // the other tile's tokens count too
+            const u32x4 o = *reinterpret_cast<const u32x4 *>(ga.X + (size_t)min((tok0 ^ 16) + i16, batch - 1) * d_in + s * kMfmaK + g4 * 8);
+            mask_union_two(b[0], o, kp, (mode & kMaskSigned) != 0);
         }
         sx = mfma16<DT>(ones, b[0], sx);
 #pragma unroll
@@ -204,7 +219,7 @@ __global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args a
 
     // ---- the waves meet in LDS, one half of the outputs at a time: [wave][128 outputs][16 tokens]
     float *red = reinterpret_cast<float *>(smem);
-    float *out = a.yc + (size_t)ttile * a.rows_pad * 16;
+    float *out = a.t.yc + (size_t)ttile * a.t.yc_rows * 16;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         __syncthreads();
@@ -217,7 +232,7 @@ __global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args a
             float s = red[i];
 #pragma unroll
             for (int ww = 1; ww < kQ4Waves; ++ww) s += red[ww * 2048 + i];
-            if (tok0 + (i & 15) < a.batch)                       // (the next launch clears what it reads, real tokens only)
+            if (tok0 + (i & 15) < batch)                       // (the next launch clears what it reads, real tokens only)
                 __hip_atomic_fetch_add(out + (size_t)(col0 + h * 512) * 16 + i, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -225,31 +240,45 @@ __global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args a
 
 }  // namespace
 
-hipError_t launch_mfma_q4(const LayerView &L, const MatrixView &M, bool with_t, const void *X, int batch, bool dense, int cus, hipStream_t stream)
+hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, bool dense, int cus, hipStream_t stream)
 {
-    if (!L.Mq || !L.qs || !L.qz || !M.yc || batch < 1 || batch > 32 || L.qshift < 5 || L.d_in % kMfmaK) return hipErrorInvalidValue;
+    if (n < 1 || n > kMaxGroupLayers || batch < 1 || batch > 32) return hipErrorInvalidValue;
     MfmaQ4Args a{};
-    a.Mq = L.Mq; a.qz = L.qz; a.qs = L.qs; a.X = (const uint16_t *)X; a.yc = M.yc;
-    a.d_in = L.d_in; a.batch = batch; a.qtiles = L.qtiles; a.qshift = L.qshift;
-    a.mask_mode = dense ? kMaskNone : (L.batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (L.keep_signed ? kMaskSigned : 0);
-    a.kp = KeepPattern{(uint32_t)(uint16_t)M.keep_min * 0x10001u, (L.dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
-    a.t_slices = 1;
-    if (with_t && !dense && L.rank > 0) {
-        if (!M.SVt || !M.t || !M.t_acc || !M.t_flags) return hipErrorInvalidValue;
-        MfmaJob &j = a.t;
-        j.SVt = M.SVt; j.t = (unsigned char *)M.t; j.t_acc = M.t_acc; j.t_flags = M.t_flags; j.rank = L.rank; j.mask_mode = a.mask_mode; j.kp = a.kp;
-        j.t_blocks = (L.rank + 31) / 32 * 2;
-        a.t_slices = mfma_t_slices(j.t_blocks, L.d_in, kQ4Waves, cus);
-        a.t_wgs = j.t_blocks * a.t_slices;
-    }
+    a.X = (const uint16_t *)X; a.d_in = L[0].d_in; a.batch = batch;
     const int tiles = (batch + 15) / 16;
-    a.units = (L.qtiles - 1) * 4 + std::min(4, (L.d_out - (L.qtiles - 1) * kQ4Tile + 127) / 128);
-    a.rows_pad = L.qtiles * kQ4Tile;
-    // One workgroup per compute unit, a step for every wave: each split adds to every output (gate, up and down at 4096 /
-    // 11008, 16 tokens: 84 us at half as many, 68 at this number, 74 at twice as many).
-    a.splits = std::max(1, std::min(cus / (a.units * tiles), L.d_in / kMfmaK / kQ4Waves));
-    dim3 grid(a.t_wgs + a.units * a.splits * tiles), block(64 * kQ4Waves);
-    if (L.dtype == F16) {
+    int t_blocks = 0, units = 0;
+    for (int i = 0; i < n; ++i) {
+        const LayerView &v = L[i];
+        const MatrixView &m = M[i];
+        if (!v.Mq || !v.qs || !v.qz || !m.yc || v.qshift < 5 || v.d_in % kMfmaK || v.d_in != a.d_in || v.dtype != L[0].dtype) return hipErrorInvalidValue;
+        MfmaQ4Job &c = a.job[i];
+        MfmaJob &j = c.t;
+        c.Mq = v.Mq; c.qz = v.qz; c.qs = v.qs; c.qtiles = v.qtiles; c.qshift = v.qshift;
+        c.units = (v.qtiles - 1) * 4 + std::min(4, (v.d_out - (v.qtiles - 1) * kQ4Tile + 127) / 128);
+        units += c.units;
+        j.yc = m.yc; j.yc_rows = m.yc_rows; j.rank = dense ? 0 : v.rank;
+        j.mask_mode = dense ? kMaskNone : (v.batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (v.keep_signed ? kMaskSigned : 0);
+        j.kp = KeepPattern{(uint32_t)(uint16_t)m.keep_min * 0x10001u, (v.dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
+        j.SVt = m.SVt; j.t = (unsigned char *)m.t; j.t_acc = m.t_acc; j.t_flags = m.t_flags;
+        if (j.rank > 0 && (!j.SVt || !j.t || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
+        j.t_blocks = (j.rank + 31) / 32 * 2;
+        t_blocks += j.t_blocks;
+    }
+    a.t_slices = mfma_t_slices(t_blocks, a.d_in, kQ4Waves, cus);
+    int t_total = 0, w_total = 0;
+    for (int i = 0; i < kMaxGroupLayers; ++i) {
+        if (i < n) {
+            // One workgroup per compute unit over the launch, a step for every wave: each split adds to every output (gate,
+            // up and down at 4096 / 11008, 16 tokens: 84 us at half as many, 68 at this number, 74 at twice as many).
+            a.job[i].splits = std::max(1, std::min((cus + units * tiles / 2) / (units * tiles), a.d_in / kMfmaK / kQ4Waves));
+            t_total += a.job[i].t.t_blocks * a.t_slices;
+            w_total += a.job[i].units * a.job[i].splits * tiles;
+        }
+        a.t_end[i] = t_total;
+        a.w_end[i] = w_total;
+    }
+    dim3 grid(t_total + w_total), block(64 * kQ4Waves);
+    if (L[0].dtype == F16) {
         if (tiles == 1) hipLaunchKernelGGL((k_mfma_q4<F16, 1>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((k_mfma_q4<F16, 2>), grid, block, 0, stream, a);
     } else {
