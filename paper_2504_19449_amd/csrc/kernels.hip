@@ -47,23 +47,23 @@ namespace {
 
 // ---------------------------------------------------------------------------------------------
 // Streaming primitive: acc[b][0:8] += sum_j coef[j][b] * M[idx[j], col:col+8] over the n staged rows.
-// Wave w of nw takes kUnroll consecutive rows per batch; a batch's loads are all issued before its
+// Wave w of nw takes R consecutive rows per batch; a batch's loads are all issued before its
 // first FMA, and the next batch is issued before the current one is consumed (two batches of
 // 16-byte loads in flight per lane).  idx / coef live in LDS and are wave-uniform (scalar registers).
 // ---------------------------------------------------------------------------------------------
-template <bool NT>
+template <bool NT, int R>
 __device__ __forceinline__ void load_batch(const uint16_t *__restrict__ M, size_t ld, int col, bool colok,
-                                           const int *s_idx, int n, int j0, u32x4 (&v)[kUnroll])
+                                           const int *s_idx, int n, int j0, u32x4 (&v)[R])
 {
-    if (j0 + kUnroll <= n) {
+    if (j0 + R <= n) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < R; ++u) {
             const int idx = uniform(s_idx[j0 + u]);
             v[u] = colok ? ldg16<NT>(M + (size_t)idx * ld + col) : u32x4{0, 0, 0, 0};
         }
     } else {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < R; ++u) {
             v[u] = u32x4{0, 0, 0, 0};
             if (j0 + u < n) {
                 const int idx = uniform(s_idx[j0 + u]);
@@ -73,12 +73,12 @@ __device__ __forceinline__ void load_batch(const uint16_t *__restrict__ M, size_
     }
 }
 
-template <int DT, int BT>
-__device__ __forceinline__ void fma_batch(const u32x4 (&v)[kUnroll], const float *s_coef, int n, int j0,
+template <int DT, int BT, int R>
+__device__ __forceinline__ void fma_batch(const u32x4 (&v)[R], const float *s_coef, int n, int j0,
                                           float (&acc)[BT][8])
 {
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
+    for (int u = 0; u < R; ++u) {
         if (j0 + u < n) {
             float f[8];
             unpack8<DT>(v[u], f);
@@ -95,21 +95,21 @@ __device__ __forceinline__ void fma_batch(const u32x4 (&v)[kUnroll], const float
 // Consume the already-issued batch `va` (rows j0..) and stream the rest of the wave's rows.
 // before_fma(j0) runs ahead of the FMAs of the batch that starts at row j0 (its loads, and those of
 // the following batch, are already in flight).
-template <int DT, int BT, bool NT, typename Hook>
+template <int DT, int BT, bool NT, int R, typename Hook>
 __device__ __forceinline__ void stream_rest(const uint16_t *__restrict__ M, size_t ld, int col, bool colok,
                                             const int *s_idx, const float *s_coef, int n, int j0, int step,
-                                            u32x4 (&va)[kUnroll], float (&acc)[BT][8], Hook &&before_fma)
+                                            u32x4 (&va)[R], float (&acc)[BT][8], Hook &&before_fma)
 {
-    u32x4 vb[kUnroll];
+    u32x4 vb[R];
     while (j0 < n) {
-        load_batch<NT>(M, ld, col, colok, s_idx, n, j0 + step, vb);
+        load_batch<NT, R>(M, ld, col, colok, s_idx, n, j0 + step, vb);
         before_fma(j0);
-        fma_batch<DT, BT>(va, s_coef, n, j0, acc);
+        fma_batch<DT, BT, R>(va, s_coef, n, j0, acc);
         j0 += step;
         if (j0 >= n) break;
-        load_batch<NT>(M, ld, col, colok, s_idx, n, j0 + step, va);
+        load_batch<NT, R>(M, ld, col, colok, s_idx, n, j0 + step, va);
         before_fma(j0);
-        fma_batch<DT, BT>(vb, s_coef, n, j0, acc);
+        fma_batch<DT, BT, R>(vb, s_coef, n, j0, acc);
         j0 += step;
     }
 }
@@ -289,8 +289,8 @@ __device__ __forceinline__ void lowrank_gather(const GatherArgs &a, unsigned cha
     if (g < ng) {
         u32x4 va[kUnroll];
         const int j_first = g * kUnroll, step = ng * kUnroll;
-        load_batch<NT>(L.SVc, (size_t)r, col, colok, s_idx, n, j_first, va);
-        stream_rest<DT, BT, NT>(L.SVc, (size_t)r, col, colok, s_idx, s_coef, n, j_first, step, va, acc, [](int) {});
+        load_batch<NT, kUnroll>(L.SVc, (size_t)r, col, colok, s_idx, n, j_first, va);
+        stream_rest<DT, BT, NT, kUnroll>(L.SVc, (size_t)r, col, colok, s_idx, s_coef, n, j_first, step, va, acc, [](int) {});
     }
     // b must stay a compile-time index (a run-time subscript would push acc[][] into scratch memory)
     float *const t_sum = L.t_sum + (size_t)z * BT * r;
@@ -522,7 +522,7 @@ __device__ __forceinline__ void q4_consume(Q4State<BT> &st, const LayerView &L, 
 // The two groups are independent, so they share one launch.
 // grid.x = lr_wgs + tiles * splits, grid.z = batch tiles of BT tokens, block = 64 * waves.
 // ---------------------------------------------------------------------------------------------
-template <int DT, int BT, bool NT, bool FUSED, bool Q4 = false, bool EXT = true>
+template <int DT, int BT, bool NT, bool FUSED, bool Q4 = false, bool EXT = true, int R = kUnroll>
 __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *smem)
 {
     const int z = blockIdx.z;
@@ -647,8 +647,8 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
     for (int b = 0; b < BT; ++b)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[b][e] = 0.f;
-    u32x4 va[kUnroll];
-    const int j_first = w * kUnroll, step = nw * kUnroll;
+    u32x4 va[R];
+    const int j_first = w * R, step = nw * R;
     // 4-bit weights: this wave's contiguous run [jq_lo, jq_hi) of the list, 8 bytes per lane and row
     // (wave index and row count go through readfirstlane: the compiler cannot know they are wave-uniform, and
     //  would otherwise run the row loop and the group tests under execution masks)
@@ -670,7 +670,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
             q4_open<BT>(st, L, uniform(s.idx[jq_lo]) >> L.qshift, colq);
         }
     } else {
-        load_batch<NT>(L.M, (size_t)d_out, col, colok, s.idx, n_all, j_first, va);
+        load_batch<NT, R>(L.M, (size_t)d_out, col, colok, s.idx, n_all, j_first, va);
     }
 
     // ---- ... and fetch the coefficients x[b, c] * m[b, c] of my rows while those loads fly
@@ -707,7 +707,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
     auto request_t = [&](int jb) {
         const int j = jb + lane / BT, b = lane % BT;
         tq = 0u;
-        tq_valid = jb < n_all && jb + kUnroll > n && lane < kUnroll * BT && j >= n && j < n_all && b < nb;
+        tq_valid = jb < n_all && jb + R > n && lane < R * BT && j >= n && j < n_all && b < nb;
         if (tq_valid) {
             tq_at = b * L.rank + (s.idx[j] - d_in);
             tq = __hip_atomic_load(t_pub + tq_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -726,10 +726,10 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         if (!ok && lane == 0) __hip_atomic_store(L.sync + kSyncError, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     auto need_t = [&](int j0) {
-        if (j0 + kUnroll > n) {                      // this batch holds rows of U_r^T
+        if (j0 + R > n) {                            // this batch holds rows of U_r^T
             settle_t();
             const int j = j0 + lane / BT;
-            if (lane < kUnroll * BT && j >= n && j < n_all) s.coef[j * BT + lane % BT] = tq_valid ? as_f(tq) : 0.f;
+            if (lane < R * BT && j >= n && j < n_all) s.coef[j * BT + lane % BT] = tq_valid ? as_f(tq) : 0.f;
             __builtin_amdgcn_wave_barrier();          // read back by this wave only
         }
         request_t(j0 + step);
@@ -763,10 +763,10 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
             const int ju = n + j_first;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                u32x4 ua[kUnroll];
-                load_batch<NT>(Uv, ldu, colq + h * 512, true, s.idx, n_all, ju, ua);
+                u32x4 ua[R];
+                load_batch<NT, R>(Uv, ldu, colq + h * 512, true, s.idx, n_all, ju, ua);
                 request_t(ju);
-                stream_rest<DT, BT, NT>(Uv, ldu, colq + h * 512, true, s.idx, s.coef, n_all, ju, step, ua, st.acc[h], need_t);
+                stream_rest<DT, BT, NT, R>(Uv, ldu, colq + h * 512, true, s.idx, s.coef, n_all, ju, step, ua, st.acc[h], need_t);
             }
         }
         // the two 512-column halves of the tile go through the 16-bit path's reduction one after the other
@@ -775,12 +775,12 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         reduce_to_yacc<BT>(st.acc[1], s.red, L.yacc, b0, nb, d_out, tile * 2 + 1);
         if constexpr (!FUSED) return;
     } else if (!FUSED) {
-        stream_rest<DT, BT, NT>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n, j_first, step, va, acc, [](int) {});
+        stream_rest<DT, BT, NT, R>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n, j_first, step, va, acc, [](int) {});
         reduce_to_yacc<BT>(acc, s.red, L.yacc, b0, nb, d_out, tile);
         return;
     } else {
         request_t(j_first);
-        stream_rest<DT, BT, NT>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n_all, j_first, step, va, acc, need_t);
+        stream_rest<DT, BT, NT, R>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n_all, j_first, step, va, acc, need_t);
         reduce_to_yacc<BT>(acc, s.red, L.yacc, b0, nb, d_out, tile);
     }
 
@@ -888,11 +888,12 @@ __global__ __launch_bounds__(BT >= 8 ? 256 : 512) void k_sparse_and_t(const Grou
 // EXT = false: no layer of the launch has a fixed-count rule, a signed threshold or a bias (the host checks), and the
 // code for those is left out -- this kernel's once-per-launch code runs from a cold instruction cache, and the
 // general keep-predicate in its token scan measured +0.3 us per launch.
-template <int DT, int BT, bool NT, bool EXT>
+// R: rows per batch of loads of a wave (launch_fused chooses).
+template <int DT, int BT, bool NT, bool EXT, int R>
 __global__ __launch_bounds__(BT >= 8 ? 256 : 512, BT >= 8 ? 3 : 4) void k_rsparse_fused(const GroupArgs ga)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    sparse_body<DT, BT, NT, true, false, EXT>(ga, smem);
+    sparse_body<DT, BT, NT, true, false, EXT, R>(ga, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -940,8 +941,8 @@ __global__ __launch_bounds__(BT >= 8 ? 256 : 512) void k_dense_axpy(const GroupA
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[b][e] = 0.f;
     u32x4 va[kUnroll];
-    load_batch<NT>(L.M, (size_t)d_out, col, colok, s.idx, n, w * kUnroll, va);
-    stream_rest<DT, BT, NT>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n, w * kUnroll, nw * kUnroll, va, acc,
+    load_batch<NT, kUnroll>(L.M, (size_t)d_out, col, colok, s.idx, n, w * kUnroll, va);
+    stream_rest<DT, BT, NT, kUnroll>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n, w * kUnroll, nw * kUnroll, va, acc,
                             [](int) {});
     reduce_to_yacc<BT>(acc, s.red, L.yacc, b0, nb, d_out, tile);
 }
@@ -1361,12 +1362,25 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
     const bool nt = cfg[0].nontemporal != 0;
     bool ext = false;
     for (int i = 0; i < n; ++i) ext = ext || L[i].rules || L[i].bias || L[i].keep_signed;
+    // Rows per batch: eight, four where a wave of the longest share has no more than two batches of eight (the last one
+    // nearly empty: 4096 x 4096 at one token, 9 rows a wave, 13.6 -> 12.8 us; with 35 rows and more a wave eight are as
+    // fast or faster: gate / up and down at 4096 / 11008 175.3 against 176.5 us, an 8192 / 28672 block 207.9 against 211.8),
+    // and four always at four tokens (fewer registers: gate / up and down at 4096 / 14336 167.9 -> 164.1 us).
+    bool few = true;
+    for (int i = 0; i < n; ++i) {
+        const int rows = (L[i].d_in / 2 + L[i].rank + cfg[i].splits - 1) / cfg[i].splits;     // expected
+        few = few && rows <= 16 * cfg[0].waves;
+    }
+    const bool four = nt && few && bt == 1;
 #define RS_U(DT)                                                                                        \
-    RS_DISPATCH_BT(bt, {                                                                                \
-        if (nt && !ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, false>), grid, block, lds, stream, ga);      \
-        else if (nt) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, true>), grid, block, lds, stream, ga);          \
-        else if (!ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, false, false>), grid, block, lds, stream, ga);      \
-        else hipLaunchKernelGGL((k_rsparse_fused<DT, BT, false, true>), grid, block, lds, stream, ga);                 \
+    if (four && !ext) hipLaunchKernelGGL((k_rsparse_fused<DT, 1, true, false, 4>), grid, block, lds, stream, ga);       \
+    else if (four) hipLaunchKernelGGL((k_rsparse_fused<DT, 1, true, true, 4>), grid, block, lds, stream, ga);           \
+    else RS_DISPATCH_BT(bt, {                                                                           \
+        constexpr int RR = BT == 4 ? 4 : kUnroll;                                                       \
+        if (nt && !ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, false, RR>), grid, block, lds, stream, ga);      \
+        else if (nt) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, true, RR>), grid, block, lds, stream, ga);          \
+        else if (!ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, false, false, RR>), grid, block, lds, stream, ga);      \
+        else hipLaunchKernelGGL((k_rsparse_fused<DT, BT, false, true, RR>), grid, block, lds, stream, ga);                 \
     })
     if (L[0].dtype == F16) { RS_U(F16) } else { RS_U(BF16) }
 #undef RS_U
