@@ -879,6 +879,19 @@ rsparse_status rsparse_linear_gated(rsparse_layer *L, const void *G_dev, const v
 }
 
 namespace {
+// The rules of the layers with a fixed-count activation, in one launch (none: nothing is launched).
+hipError_t topk_rules_of(rsparse_layer *const *layers, const LayerView *v, int n, const void *X_dev, int batch, hipStream_t s)
+{
+    int k[RSPARSE_MAX_GROUP], m = 0;
+    KeepRule *rules[RSPARSE_MAX_GROUP];
+    for (int i = 0; i < n; ++i)
+        if (layers[i]->cfg.topk > 0 && v[i].rules) {
+            k[m] = layers[i]->cfg.topk;
+            rules[m++] = const_cast<KeepRule *>(v[i].rules);
+        }
+    return m > 0 ? launch_topk_rules(X_dev, layers[0]->cfg.dtype, batch, layers[0]->cfg.d_in, k, rules, m, s) : hipSuccess;
+}
+
 // ov: per-call scratch to use instead of the handles' own (rsparse_linear_static; one layer, vector path only)
 rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers, const void *X_dev, const void *G_dev,
                                  int32_t batch, void *const *Y_devs, void *stream, const ScratchView *ov)
@@ -929,11 +942,8 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
         X_dev = layers[0]->xg;
     }
-    // fixed-count activation: each token's rule (its k-th magnitude and tie cut) first, one small launch per layer
-    for (int i = 0; i < n_layers; ++i)
-        if (layers[i]->cfg.topk > 0 && v[i].rules)
-            RS_HIP(launch_topk_rules(X_dev, layers[i]->cfg.dtype, batch, layers[i]->cfg.d_in, layers[i]->cfg.topk,
-                                     const_cast<KeepRule *>(v[i].rules), s));
+    // fixed-count activation: each token's rule (its k-th magnitude and tie cut) first, one small launch for the group
+    RS_HIP(topk_rules_of(layers, v, n_layers, X_dev, batch, s));
     // layers packed in strips go through the strip kernel; a group must share one layout (and one strip width),
     // otherwise its layers run one at a time
     if (!mfma && !cols && n_layers > 1) {
@@ -1030,10 +1040,7 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
     if (fused && !mfma && !cols && one_tile && lc[0].tile_map != 2 && lc[1].tile_map != 2 && gate->M && up->M) {
         // both projections and the activation in one launch: the last workgroup of a column tile
         // rounds g and u, applies silu(g) * u and stores H
-        for (int i = 0; i < 2; ++i)
-            if (pair[i]->cfg.topk > 0)
-                RS_HIP(launch_topk_rules(X_dev, pair[i]->cfg.dtype, batch, pair[i]->cfg.d_in, pair[i]->cfg.topk,
-                                         const_cast<KeepRule *>(v[i].rules), s));
+        RS_HIP(topk_rules_of(pair, v, 2, X_dev, batch, s));
         RS_HIP(launch_fused(v, lc, 2, X_dev, batch, outs, s, true));
         for (int i = 0; i < 2; ++i) {
             pair[i]->last_stream = s; pair[i]->last_batch = batch; pair[i]->last_mfma = false; pair[i]->last_fused = true; pair[i]->last_bt = 0; pair[i]->last_strip = false;

@@ -72,8 +72,8 @@ hipError_t launch_q4_dense_rowdot(const uint8_t *Qrow, const uint16_t *Srow, con
                                   int d_in, int d_out, const void *X, int batch, void *Y, hipStream_t stream);
 
 // Fixed-count activation: per token of X [batch][d_in] the KeepRule that keeps exactly min(k, non-NaN channels)
-// channels of largest magnitude (ties: lower channel first).  One workgroup per token.
-hipError_t launch_topk_rules(const void *X, int dtype, int batch, int d_in, int k, KeepRule *rules, hipStream_t stream);
+// channels of largest magnitude (ties: lower channel first), for n layers that read X in one launch.
+hipError_t launch_topk_rules(const void *X, int dtype, int batch, int d_in, const int *k, KeepRule *const *rules, int n, hipStream_t stream);
 
 // What the matrix-core path holds of a layer beside LayerView (all null without it).  Operand layout of a matrix: [block of
 // 16 rows][step of 32 columns][64 lanes][16 bytes], lane l of a tile = columns 8 (l / 16) .. + 7 of row l % 16; rows and

@@ -262,3 +262,27 @@ def test_topk_with_bias_in_a_replayed_graph(strip_cols):
         for b in range(B):
             assert np.array_equal(rs.rsparse_last_active(layer, b), want["act"][b])
     layer.destroy()
+
+
+@pytest.mark.parametrize("d_in", [8, 8192, 8200, 16384, 16392, 65536])
+def test_topk_rules_of_a_group_at_the_edges_of_a_threads_share(d_in):
+    """1024 threads with one, two or up to eight chunks of 8 channels each; three layers' rules come from one launch.  Kept
+    lists bit-exact with ties across threads, at the first channels and at the last."""
+    dt = synth.F16
+    Ls = [synth.random_layer(d_in, 16, 8, dt, seed=90 + i) for i in range(3)]
+    X16, _ = gu.tokens_for(Ls[0], 2)
+    X16[0, ::3] = X16[0, 7]                                  # ties over all threads
+    X16[1, -8:] = X16[1, 0] ^ 0x8000                         # ties in the first and the last chunk
+    ks = (1, max(1, d_in // 3), d_in - 1)
+    layers = [gu.prepare(L, 0.0, max_batch=2, topk=k) for L, k in zip(Ls, ks)]
+    torch = gu.torch_mod()
+    Xd = gu.to_dev16(X16)
+    Ys = [torch.zeros((2, 16), dtype=torch.int16, device="cuda") for _ in Ls]
+    rs.rsparse_linear_group(layers, Xd.data_ptr(), 2, [Y.data_ptr() for Y in Ys], gu.stream_ptr())
+    torch.cuda.synchronize()
+    for layer, L, Y, k in zip(layers, Ls, Ys, ks):
+        want = gu.oracle_linear(L, X16, 0.0, topk=k)
+        gu.check_outputs(synth.decode16(Y.cpu().numpy().view(np.uint16), dt), want["Y"], dt)
+        for t in range(2):
+            assert np.array_equal(rs.rsparse_last_active(layer, t), want["act"][t])
+        layer.destroy()
