@@ -23,6 +23,17 @@ __device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, const f32x
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
+// acc += A B for 8 consecutive k per lane (a: 16-bit, b: fp32), each product and sum in fp32: what a 16-bit operand cannot hold of b.
+template <int DT>
+__device__ __forceinline__ f32x4 mfma_f32(const u32x4 a, const f32x4 (&b)[2], f32x4 acc)
+{
+    float f[8];
+    unpack8<DT>(a, f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], b[e >> 2][e & 3], acc, 0, 0, 0);
+    return acc;
+}
+
 template <int DT>
 __device__ __forceinline__ uint16_t narrow(float f) { return DT == F16 ? to_f16(f) : to_bf16(f); }
 
@@ -108,9 +119,14 @@ __device__ __forceinline__ void mask_step(u32x4 (&b)[NF], const KeepPattern &kp,
 // the memory system takes only push each other out.
 template <int NB, int NF> struct StepsOf { static constexpr int value = NB * NF == 1 ? 4 : 2; };
 
+// Bytes of the 16-bit parts of t in its buffer; t in fp32 follows and takes as many.
+inline size_t t32_offset(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 2 * 1024; }
+inline float *t32_of(const MatrixView &m, int rank) { return m.t ? reinterpret_cast<float *>((unsigned char *)m.t + t32_offset(rank)) : nullptr; }
+
 struct MfmaJob {
     const uint16_t *W, *SVt, *U; // operand layout (MatrixView)
-    unsigned char *t;            // t in operand layout: [step of 32 rank indices][token tile][part][64 lanes][16 bytes]
+    unsigned char *t;            // t in two 16-bit parts: [step of 32 rank indices][token tile][part][64 lanes][16 bytes]
+    float *t32;                  // t as it is: [step of 32 rank indices][token tile][64 lanes][8]
     float *t_acc;                // [block of 16 rank indices][token tile][4][64] fp32 sums of t's K slices, zero between calls
     int *t_flags;                // a flag per block of t, zero between calls; then an arrival counter per block
     void *Y;
@@ -215,12 +231,13 @@ __device__ __forceinline__ void stream_rows(const unsigned char *__restrict__ ma
 
 // A unit of t: block `unit` of 16 rank indices over K slice `slice` of t_slices, by all waves of a workgroup (nw *
 // t_unit_lds<NF> bytes of LDS).  One wave sums the waves up; with several slices it adds to t_acc, and the last slice to
-// arrive takes the sums out again (which leaves zeros).  They are split into HP 16-bit parts and stored; flags: the block's
-// flag is set when the stores have been performed, for readers in the same launch.
+// arrive takes the sums out again (which leaves zeros).  They are stored as they are (PARTS = false), or in two 16-bit parts
+// -- in fp16, whose range t can leave, as they are besides.  flags: the block's flag is set when the stores have been
+// performed, for readers in the same launch.
 template <int NF>
 constexpr int t_unit_lds = NF * 16 * Batch<1, NF>::kPitch;
 
-template <int DT, int NF, int HP>
+template <int DT, int NF, bool PARTS>
 __device__ __forceinline__ void t_unit(const MfmaJob &jb, const uint16_t *X, int batch, int d_in, int unit, int slice, int t_slices, bool flags,
                                        int skip_flag, unsigned char *smem)
 {
@@ -288,23 +305,32 @@ __device__ __forceinline__ void t_unit(const MfmaJob &jb, const uint16_t *X, int
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 // rank indices row..row+3 of a token, in operand layout; entries past the rank are zero
-                unsigned long long part[HP] = {};
+                const int r = row % kMfmaK, at = r / 8 * 16 + (lane & 15);
+                const f32x4 v4 = row < jb.rank ? s[f] : f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (!PARTS || DT == F16) {
+                    unsigned long long *p = reinterpret_cast<unsigned long long *>(jb.t32 + ((size_t)(row / kMfmaK * NF + f) * 64 + at) * 8 + r % 8);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float v = row < jb.rank ? s[f][e] : 0.f;
-#pragma unroll
-                    for (int h = 0; h < HP; ++h) {          // each part rounds what the parts before it left over (exact)
-                        const float scale = h == 1 ? LoScale<DT>::value : 1.0f;
-                        const uint16_t b16 = narrow<DT>(v * scale);
-                        part[h] |= (unsigned long long)b16 << (16 * e);
-                        v -= widen16<DT>(b16) * (1.0f / scale);
-                    }
+                    for (int h = 0; h < 2; ++h)
+                        __hip_atomic_store(p + h, (unsigned long long)as_u(v4[2 * h]) | ((unsigned long long)as_u(v4[2 * h + 1]) << 32), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
                 }
-                const int r = row % kMfmaK;
-                unsigned char *p = jb.t + (size_t)(row / kMfmaK * NF + f) * (HP * 1024) + (size_t)((r / 8) * 16 + (lane & 15)) * 16 + (r % 8) * 2;
+                if constexpr (PARTS) {
+                    constexpr uint32_t kInf = DT == F16 ? 0x7c00u : 0x7f80u;
+                    unsigned long long part[2] = {};
 #pragma unroll
-                for (int h = 0; h < HP; ++h)
-                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p + h * 1024), part[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int e = 0; e < 4; ++e) {
+                        const float v = v4[e];
+                        const uint16_t hi = narrow<DT>(v);
+                        // the second part rounds what the first left over (exact); nothing is left over of an infinity
+                        const float rest = (hi & kInf) == kInf ? 0.f : (v - widen16<DT>(hi)) * LoScale<DT>::value;
+                        part[0] |= (unsigned long long)hi << (16 * e);
+                        part[1] |= (unsigned long long)narrow<DT>(rest) << (16 * e);
+                    }
+                    unsigned char *p = jb.t + (size_t)(row / kMfmaK * NF + f) * 2048 + (size_t)at * 16 + (r % 8) * 2;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        __hip_atomic_store(reinterpret_cast<unsigned long long *>(p + h * 1024), part[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
             if (flags) {
                 wait_own_writes();                           // performed: now the block counts as ready

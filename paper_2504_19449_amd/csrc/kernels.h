@@ -80,7 +80,7 @@ hipError_t launch_topk_rules(const void *X, int dtype, int batch, int d_in, cons
 // columns past the matrix are zero.
 struct MatrixView {
     const uint16_t *W, *SVt, *U;   // (W null: its part comes from an earlier launch, in yc)  W [d_out][d_in], S_r V_r^T [rank rounded up to 32][d_in], U_r [d_out][rank]
-    void *t;                       // t in 16-bit parts, mfma_t_bytes(rank)
+    void *t;                       // t: its 16-bit parts, then as it is; mfma_t_bytes(rank)
     float *t_acc;                  // fp32 sums of t, [32 tokens][rank rounded up to 32]; zero between calls
     int *t_flags;                  // [t_flag_words(rank)]; zero between calls
     float *yc;                     // [token tile][yc_rows][16 tokens] fp32 sums of the W part; zero between calls
@@ -185,8 +185,8 @@ hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uin
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
                        int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream);
 // 4-bit weights on the matrix cores (kernels_mfma_q4.hip), up to 32 tokens, n layers that read the same input: adds the W
-// part of each layer (dense: the whole product) to its yc, [token tile][qtiles * 1024][16 tokens], and stores t in the parts
-// that launch_mfma's phase 2 expects of such layers (MatrixView::W null), which completes them.
+// part of each layer (dense: the whole product) to its yc, [token tile][qtiles * 1024][16 tokens], and stores t in fp32, as
+// launch_mfma's phase 2 expects it of such layers (MatrixView::W null), which completes them.
 int mfma_t_slices(int t_blocks, int d_in, int nw, int cus);
 hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, bool dense, int cus, hipStream_t stream);
 // The same over column-major W (kernels_mfma_cols.hip; layers without the operand-layout copy), n layers that read the same

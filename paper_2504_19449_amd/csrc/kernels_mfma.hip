@@ -20,9 +20,10 @@
 // launch.  Bound by HBM: the tokens come from L2, change to the operand layout through the wave's own LDS and are masked
 // there in their 16-bit patterns (five packed integer operations per two values); the waves' D tiles meet in LDS once.
 // The first workgroups of the grid take t, a (block of 16 rank indices, K slice) each, and wait for nothing; the last
-// slice of a block splits the sums into two 16-bit halves (hi + lo, ~16 mantissa bits of the fp32 t) and stores them in
-// operand layout with write-through stores, waits for these to be acknowledged and sets the block's flag.  A unit of W
-// waits for the flags (bounded) when its rows are done and adds U_r t.  The t buffer is read with ordinary loads: its
+// slice of a block splits the sums into two 16-bit halves (hi + lo, ~16 mantissa bits of the fp32 t, 22 in fp16) and stores
+// them in operand layout with write-through stores, waits for these to be acknowledged and sets the block's flag.  A unit of
+// W waits for the flags (bounded) when its rows are done and adds U_r t.  fp16 halves cannot hold |t| >= 65520: fp16 layers
+// store t in fp32 beside them, and a step that meets an infinite half is multiplied from there with the fp32 MFMA.  The t buffer is read with ordinary loads: its
 // lines are first touched in a launch by readers that have seen the flags, so no older copy of them is in a cache.
 // Measured (us per call, before: a first launch with sums over K slices in fp32 atomics, a split launch and a finish
 // launch): 8192 x 8192 r 1024 60.3 -> 41.7 at 32 tokens, 53.1 -> 34.7 at 8; 4096 x 4096 r 256 23.1 -> 14.6 at 8; dense
@@ -44,8 +45,8 @@ struct MfmaArgs {
     int wait_polls, skip_stage1;
 };
 
-// HP: 16-bit parts of t.
-template <int DT, int NB, int NF, int HP>
+// SUMS: the W part was summed by an earlier launch (yc), and t is read in fp32: what is left is U_r t, the sum and the rounding.
+template <int DT, int NB, int NF, bool SUMS>
 __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaArgs ga)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -56,8 +57,8 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
     const size_t block_bytes = (size_t)steps * 1024;
     const unsigned char *x = reinterpret_cast<const unsigned char *>(ga.X);
     // the first t_wgs workgroups take a (block, K slice) of t each and wait for nothing; the others a unit of W each
-    const int t_wgs = ga.t_end[kMaxGroupLayers - 1] * (ga.phases & 1);
-    const bool is_t = (int)blockIdx.x < t_wgs;
+    const int t_wgs = SUMS ? 0 : ga.t_end[kMaxGroupLayers - 1] * (ga.phases & 1);
+    const bool is_t = !SUMS && (int)blockIdx.x < t_wgs;
     const int first = is_t ? (int)blockIdx.x : (int)blockIdx.x - t_wgs;
     int job = 0, begin = 0;
 #pragma unroll
@@ -66,10 +67,12 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
         if (first >= e) { job = j + 1; begin = e; }
     }
     const MfmaJob &jb = ga.job[job];
-    if (is_t) {
-        t_unit<DT, NF, HP>(jb, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, ga.phases == 3,
-                           ga.skip_stage1, smem);
-        return;
+    if constexpr (!SUMS) {
+        if (is_t) {
+            t_unit<DT, NF, true>(jb, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, ga.phases == 3,
+                                 ga.skip_stage1, smem);
+            return;
+        }
     }
     const KeepPattern kp = jb.kp;
     const int unit = first - begin, block0 = unit * NB, n_blocks = (jb.d_out + 15) / 16;
@@ -88,8 +91,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
     for (int k = 0; k < NB; ++k) aoff[k] = (size_t)min(k, n_blocks - 1 - block0) * block_bytes;
 
     Batch<NB, NF> va;
-    const bool streams = !jb.yc;
-    if (streams) load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, w, va);
+    if constexpr (!SUMS) load_batch<NB, NF>(mat, aoff, x, xoff, lane, d_in, steps, w, va);
 
     // ---- which tokens keep a channel, for read-back: the last wave, 16 channels at a time (a lane = a token)
     if (w == nw - 1) {
@@ -127,15 +129,17 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
 #define RS_STREAM(MODE) stream_rows<DT, NB, NF, MODE>(mat, aoff, x, xoff, sx, kp, 0u, lane, d_in, w, n_batches, nw, va, acc)
-    if (streams) switch (jb.mask_mode) {
-    case kMaskNone: RS_STREAM(kMaskNone); break;
-    case kMaskOwn: RS_STREAM(kMaskOwn); break;
-    case kMaskUnion: RS_STREAM(kMaskUnion); break;
-    case kMaskOwn | kMaskSigned: RS_STREAM(kMaskOwn | kMaskSigned); break;
-    default: RS_STREAM(kMaskUnion | kMaskSigned); break;
+    if constexpr (!SUMS) {
+        switch (jb.mask_mode) {
+        case kMaskNone: RS_STREAM(kMaskNone); break;
+        case kMaskOwn: RS_STREAM(kMaskOwn); break;
+        case kMaskUnion: RS_STREAM(kMaskUnion); break;
+        case kMaskOwn | kMaskSigned: RS_STREAM(kMaskOwn | kMaskSigned); break;
+        default: RS_STREAM(kMaskUnion | kMaskSigned); break;
+        }
     }
 #undef RS_STREAM
-    const bool lowrank = jb.t_blocks > 0, hand_off = lowrank && ga.phases == 3;
+    const bool lowrank = jb.t_blocks > 0, hand_off = lowrank && !SUMS && ga.phases == 3;
 
     // the waves meet in LDS; sum_up adds up item (tile, lane)
     auto meet = [&]() {
@@ -153,9 +157,9 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
 
     // ---- U_r t: the rank's steps of 32, one per wave in turn; the rows of U_r are requested before t is waited for
     if (lowrank) {
-        f32x4 ah[HP][NB][NF];                                  // the products with t's parts
+        f32x4 ah[2][NB][NF];                                   // the products with t's parts (SUMS: with t, the first alone)
 #pragma unroll
-        for (int h = 0; h < HP; ++h)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
         const int usteps = (jb.rank + kMfmaK - 1) / kMfmaK;
         const size_t ublock = (size_t)usteps * 1024;
         const unsigned char *um = reinterpret_cast<const unsigned char *>(jb.U) + (size_t)block0 * ublock + lane * 16;
-        constexpr int US = NB * NF == 1 && HP == 2 ? 4 : 2;
+        constexpr int US = NB * NF == 1 && !SUMS ? 4 : 2;
         u32x4 ua[US][NB];
         auto request_u = [&](int s0) {
 #pragma unroll
@@ -197,28 +201,77 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
             __syncthreads();
             __atomic_signal_fence(__ATOMIC_ACQUIRE);           // no load of t moves up here
         }
+        auto t_as_it_is = [&](int s, int f, f32x4 (&tf)[2]) {
+            const float *p = jb.t32 + ((size_t)(s * NF + f) * 64 + lane) * 8;
+            tf[0] = *reinterpret_cast<const f32x4 *>(p);
+            tf[1] = *reinterpret_cast<const f32x4 *>(p + 4);
+        };
         for (int s0 = w; s0 < usteps; s0 += nw * US) {
-            u32x4 th[US][NF][HP];
+            if constexpr (SUMS) {
+                f32x4 tf[US][NF][2];
 #pragma unroll
-            for (int u = 0; u < US; ++u) {
-                const int s = min(s0 + u * nw, usteps - 1);
+                for (int u = 0; u < US; ++u)
 #pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    const unsigned char *p = jb.t + (size_t)(s * NF + f) * (HP * 1024) + lane * 16;
+                    for (int f = 0; f < NF; ++f) t_as_it_is(min(s0 + u * nw, usteps - 1), f, tf[u][f]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int h = 0; h < HP; ++h) th[u][f][h] = *reinterpret_cast<const u32x4 *>(p + h * 1024);
+                for (int u = 0; u < US; ++u) {
+                    if (s0 + u * nw < usteps) {
+#pragma unroll
+                        for (int i = 0; i < NB; ++i)
+#pragma unroll
+                            for (int f = 0; f < NF; ++f) ah[0][i][f] = mfma_f32<DT>(ua[u][i], tf[u][f], ah[0][i][f]);
+                    }
                 }
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            } else {
+                u32x4 th[US][NF][2];
+                uint32_t beyond = 0u;                          // fp16: sign bits where a first part is infinite or NaN
 #pragma unroll
-            for (int u = 0; u < US; ++u) {
-                if (s0 + u * nw < usteps) {
+                for (int u = 0; u < US; ++u) {
+                    const int s = min(s0 + u * nw, usteps - 1);
 #pragma unroll
-                    for (int i = 0; i < NB; ++i)
+                    for (int f = 0; f < NF; ++f) {
+                        const unsigned char *p = jb.t + (size_t)(s * NF + f) * 2048 + lane * 16;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) th[u][f][h] = *reinterpret_cast<const u32x4 *>(p + h * 1024);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (DT == F16) {
+#pragma unroll
+                    for (int u = 0; u < US; ++u)
 #pragma unroll
                         for (int f = 0; f < NF; ++f)
 #pragma unroll
-                            for (int h = 0; h < HP; ++h) ah[h][i][f] = mfma16<DT>(ua[u][i], th[u][f][h], ah[h][i][f]);
+                            for (int e = 0; e < 4; ++e) beyond |= (th[u][f][0][e] & 0x7c007c00u) + 0x04000400u;
+                }
+                if (DT == F16 && __any((beyond & 0x80008000u) != 0u)) {
+                    // some t is beyond fp16's range: these steps in fp32
+                    for (int u = 0; u < US && s0 + u * nw < usteps; ++u) {
+                        u32x4 au[NB];
+#pragma unroll
+                        for (int i = 0; i < NB; ++i)
+                            au[i] = ld16(um + min(i, n_blocks - 1 - block0) * ublock + (size_t)(s0 + u * nw) * 1024);
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) {
+                            f32x4 tf[2];
+                            t_as_it_is(s0 + u * nw, f, tf);
+#pragma unroll
+                            for (int i = 0; i < NB; ++i) ah[0][i][f] = mfma_f32<DT>(au[i], tf, ah[0][i][f]);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < US; ++u) {
+                        if (s0 + u * nw < usteps) {
+#pragma unroll
+                            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                                    for (int h = 0; h < 2; ++h) ah[h][i][f] = mfma16<DT>(ua[u][i], th[u][f][h], ah[h][i][f]);
+                        }
+                    }
                 }
             }
             if (s0 + nw * US < usteps) request_u(s0 + nw * US);
@@ -228,11 +281,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
 #pragma unroll
             for (int f = 0; f < NF; ++f)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float rest = ah[1][i][f][j] * (1.0f / LoScale<DT>::value);
-                    if constexpr (HP > 2) rest += ah[2][i][f][j];
-                    acc[i][f][j] += ah[0][i][f][j] + rest;
-                }
+                for (int j = 0; j < 4; ++j) acc[i][f][j] += SUMS ? ah[0][i][f][j] : ah[0][i][f][j] + ah[1][i][f][j] * (1.0f / LoScale<DT>::value);
     }
 
     meet();
@@ -249,7 +298,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
         const int tok = f * 16 + (l & 15);
         const int row = (block0 + i) * 16 + 4 * (l >> 4);       // four consecutive rows (d_out is a multiple of 8)
         if (tok < batch && row < jb.d_out) {
-            if (jb.yc) {
+            if constexpr (SUMS) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     float *y = jb.yc + ((size_t)f * jb.yc_rows + row + j) * 16 + (l & 15);
@@ -308,7 +357,7 @@ hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, si
     return hipGetLastError();
 }
 
-size_t mfma_t_bytes(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 3 * 1024; }
+size_t mfma_t_bytes(int rank) { return t32_offset(rank) * 2; }
 
 // 64 x 64 tiles through LDS, 16 bytes per access on both sides.
 __global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst)
@@ -353,7 +402,7 @@ int mfma_t_slices(int t_blocks, int d_in, int nw, int cus)
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
                        int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream)
 {
-    if (n < 1 || n > kMaxGroupLayers || batch < 1 || batch > 32 || phases < 1 || phases > 3) return hipErrorInvalidValue;
+    if (n < 1 || n > kMaxGroupLayers || batch < 1 || batch > 32 || phases < 1 || phases > 3 || (!M[0].W && phases != 2)) return hipErrorInvalidValue;
     const int nf = batch > 16 ? 2 : 1;
     MfmaArgs a{};
     a.n = n; a.X = (const uint16_t *)X; a.batch = batch; a.d_in = L[0].d_in; a.phases = phases;
@@ -364,18 +413,17 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     // 27.0 with two; at 8 tokens 23.2 and 22.9, at 4096 -> 14336 with 16 tokens 70.9 and 78.1).  Four waves a unit: with eight
     // the same bytes are in flight in half the workgroups (8192 x 8192, 8 tokens: 24.7 against 25.8 us).
     const int nb = nf, nw = 4;
-    // fp32 t in two parts (fp16: 22 bits; bf16: 16), in three of bf16 where the W part was summed by an earlier launch: those
-    // layers' vector kernels keep t in 32 bits
-    bool parts3 = false;
+    // Where the W part was summed by an earlier launch t stays in 32 bits, as those layers' vector kernels keep it; beside a W part
+    // it is multiplied in two 16-bit parts (fp16: 22 bits, in fp32 beyond its range; bf16: 16)
+    const bool sums = M[0].W == nullptr;
     int w_total = 0, t_blocks = 0;
     for (int i = 0; i < n; ++i) {
         MfmaJob &jb = a.job[i];
         const LayerView &v = L[i];
         const MatrixView &m = M[i];
-        if (v.d_in != a.d_in || v.dtype != L[0].dtype || (!m.W && !m.yc) || !Y[i]) return hipErrorInvalidValue;
-        jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.Y = Y[i]; jb.bias = v.bias;
-        jb.yc = m.W ? nullptr : m.yc; jb.yc_rows = m.yc_rows;
-        if (jb.yc) parts3 = v.dtype == BF16;
+        if (v.d_in != a.d_in || v.dtype != L[0].dtype || (sums ? m.W || !m.yc : !m.W) || !Y[i]) return hipErrorInvalidValue;
+        jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.t32 = t32_of(m, v.rank); jb.Y = Y[i]; jb.bias = v.bias;
+        jb.yc = m.yc; jb.yc_rows = m.yc_rows;
         jb.t_acc = m.t_acc; jb.t_flags = m.t_flags;
         jb.chan_bits = dense ? nullptr : chan_bits[i];
         jb.sync = v.sync; jb.d_out = v.d_out; jb.rank = dense ? 0 : v.rank; jb.out_dtype = v.out_dtype;
@@ -400,11 +448,11 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     const size_t lds = (size_t)nw * std::max(nf * 16 * (batch_k * 2 + 16), nb * nf * 1024);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((phases & 1 ? t_total : 0) + (phases & 2 ? w_total : 0)), block(64 * nw);
-#define RS_M(DT, NBV, NFV, HPV) hipLaunchKernelGGL((k_mfma_rows<DT, NBV, NFV, HPV>), grid, block, lds, stream, a)
-    const int parts = parts3 ? 3 : 2;
-    if (L[0].dtype == F16) { if (nf == 1) RS_M(F16, 1, 1, 2); else RS_M(F16, 2, 2, 2); }
-    else if (parts == 2) { if (nf == 1) RS_M(BF16, 1, 1, 2); else RS_M(BF16, 2, 2, 2); }
-    else { if (nf == 1) RS_M(BF16, 1, 1, 3); else RS_M(BF16, 2, 2, 3); }
+#define RS_M(DT, NV, SV) hipLaunchKernelGGL((k_mfma_rows<DT, NV, NV, SV>), grid, block, lds, stream, a)
+#define RS_MS(DT) do { if (nf == 1) { if (sums) RS_M(DT, 1, true); else RS_M(DT, 1, false); }    \
+                       else { if (sums) RS_M(DT, 2, true); else RS_M(DT, 2, false); } } while (0)
+    if (L[0].dtype == F16) RS_MS(F16); else RS_MS(BF16);
+#undef RS_MS
 #undef RS_M
     return hipGetLastError();
 }

@@ -36,7 +36,7 @@ struct ColsStep {
     u32x4 c[8], x[NF];           // channel 8 g + c of the step: 8 outputs; the lane's 8 channels of token lane % 16
 };
 
-template <int DT, int NF, int HP>
+template <int DT, int NF>
 __global__ __launch_bounds__(64 * kColWaves, 2) void k_mfma_cols(const ColsArgs ga)
 {
     // t's staging, or the waves' sums of half the unit's outputs [wave][64][16 * NF]
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_mfma_cols(const ColsArgs 
     const ColsJob &cj = ga.job[job];
     const int d_in = ga.d_in, batch = ga.batch;
     if (is_t) {
-        t_unit<DT, NF, HP>(cj.t, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, false, 0, smem);
+        t_unit<DT, NF, false>(cj.t, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, false, 0, smem);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), i16 = lane & 15, g4 = lane >> 4;
@@ -179,8 +179,8 @@ hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, cons
         j.yc = M[i].yc; j.yc_rows = M[i].yc_rows; j.d_out = L[i].d_out; j.rank = dense ? 0 : L[i].rank;
         j.mask_mode = dense ? kMaskNone : (L[i].batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (L[i].keep_signed ? kMaskSigned : 0);
         j.kp = KeepPattern{(uint32_t)(uint16_t)M[i].keep_min * 0x10001u, (L[i].dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
-        j.SVt = M[i].SVt; j.t = (unsigned char *)M[i].t; j.t_acc = M[i].t_acc; j.t_flags = M[i].t_flags;
-        if (j.rank > 0 && (!j.SVt || !j.t || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
+        j.SVt = M[i].SVt; j.t32 = t32_of(M[i], L[i].rank); j.t_acc = M[i].t_acc; j.t_flags = M[i].t_flags;
+        if (j.rank > 0 && (!j.SVt || !j.t32 || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
         j.t_blocks = (j.rank + 31) / 32 * 2;
         t_blocks += j.t_blocks;
     }
@@ -200,11 +200,11 @@ hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, cons
     }
     dim3 grid(t_total + w_total), block(64 * kColWaves);
     if (L[0].dtype == F16) {
-        if (batch <= 16) hipLaunchKernelGGL((k_mfma_cols<F16, 1, 2>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((k_mfma_cols<F16, 2, 2>), grid, block, 0, stream, a);
+        if (batch <= 16) hipLaunchKernelGGL((k_mfma_cols<F16, 1>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((k_mfma_cols<F16, 2>), grid, block, 0, stream, a);
     } else {
-        if (batch <= 16) hipLaunchKernelGGL((k_mfma_cols<BF16, 1, 3>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((k_mfma_cols<BF16, 2, 3>), grid, block, 0, stream, a);
+        if (batch <= 16) hipLaunchKernelGGL((k_mfma_cols<BF16, 1>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((k_mfma_cols<BF16, 2>), grid, block, 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * kQ4Waves, 2) void k_mfma_q4(const MfmaQ4Args g
     const MfmaQ4Job &a = ga.job[job];
     const int d_in = ga.d_in, batch = ga.batch;
     if (is_t) {
-        t_unit<DT, NF, DT == BF16 ? 3 : 2>(a.t, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, false, 0, smem);
+        t_unit<DT, NF, false>(a.t, ga.X, batch, d_in, (first - begin) / ga.t_slices, (first - begin) % ga.t_slices, ga.t_slices, false, 0, smem);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
@@ -259,8 +259,8 @@ hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const 
         j.yc = m.yc; j.yc_rows = m.yc_rows; j.rank = dense ? 0 : v.rank;
         j.mask_mode = dense ? kMaskNone : (v.batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (v.keep_signed ? kMaskSigned : 0);
         j.kp = KeepPattern{(uint32_t)(uint16_t)m.keep_min * 0x10001u, (v.dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
-        j.SVt = m.SVt; j.t = (unsigned char *)m.t; j.t_acc = m.t_acc; j.t_flags = m.t_flags;
-        if (j.rank > 0 && (!j.SVt || !j.t || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
+        j.SVt = m.SVt; j.t32 = t32_of(m, v.rank); j.t_acc = m.t_acc; j.t_flags = m.t_flags;
+        if (j.rank > 0 && (!j.SVt || !j.t32 || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
         j.t_blocks = (j.rank + 31) / 32 * 2;
         t_blocks += j.t_blocks;
     }
