@@ -74,10 +74,9 @@ typedef struct {
                                 channels anyway, its columns are loaded either way, and using them for every token is
                                 strictly more accurate at the same bytes) */
     int32_t dense_rowmajor;  /* 1: also keep W row by row on the device, in the matrix cores' operand layout (doubles the
-                                weight footprint; layers under 2^22 weights keep a plain row-major copy besides).  Needed by
-                                the one-launch matrix-core path that rsparse_linear takes from 5 tokens on and
-                                rsparse_dense_ref at any batch (see mfma_min_batch), and by the row-dot kernel; without it
-                                batches from 5 tokens on take the matrix cores over column-major W (two launches; the
+                                weight footprint).  Needed by the one-launch matrix-core path that rsparse_linear takes from 5
+                                tokens on and rsparse_dense_ref from 2 (see mfma_min_batch), and by the row-dot kernel; without
+                                it batches from 5 tokens on take the matrix cores over column-major W (two launches; the
                                 factors are kept a second time, in operand layout, where max_batch >= 5); fixed-count
                                 activation and strips run in tiles of up to 8 tokens on the vector ALU */
     int32_t strip_cols;      /* layout of W on the device for the vector path (up to 8 tokens per batch tile).  0: column-major
@@ -111,8 +110,8 @@ typedef struct {
     int32_t splits;          /* channel splits per column tile of the gather / dense-axpy kernels */
     int32_t waves;           /* waves (of 64 lanes) per workgroup in those kernels: 1, 2, 4 or 8 */
     int32_t lowrank_rows;    /* rows of S_r V_r^T per stage-1 workgroup */
-    int32_t dense_kernel;    /* rsparse_dense_ref: 0 auto, 1 axpy over column-major W, 2 row-dot (matrix cores on layers of
-                                2^22 weights or more) */
+    int32_t dense_kernel;    /* rsparse_dense_ref: 0 auto, 1 axpy over column-major W, 2 row-dot over the copy that
+                                dense_rowmajor = 1 keeps; both up to the batches from which the matrix cores run (mfma_min_batch) */
     int32_t nontemporal;     /* weight loads of the vector-path kernels: 0 default (non-temporal), 1 non-temporal,
                                 2 ordinary (temporal) loads */
     int32_t stages;          /* rsparse_linear, two-launch form: 0 the whole layer, 1 first launch only, 2 second
@@ -121,9 +120,10 @@ typedef struct {
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
                                 dense_rowmajor = 1; 4-bit weights above 2^25: max_batch >= 2): 0 = default (5 for
-                                rsparse_linear; 2 on 4-bit weights, 1 up to 2^25 of them; for rsparse_dense_ref 1, 2 on layers under 2^22 weights, and with dense_kernel set 2, 4 on layers
-                                of 2^25 weights or more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on
-                                4-bit weights, on the vector ALU) */
+                                rsparse_linear; 2 on 4-bit weights, 1 up to 2^25 of them; for rsparse_dense_ref 2, 1 above
+                                8192 channels or from 2^27 weights in a call, and with dense_kernel set 2, 4 on layers of 2^25
+                                weights or more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on 4-bit
+                                weights, on the vector ALU) */
     int32_t mfma_rows;       /* 0, 64, 128 or 256; without effect (rows per workgroup of earlier matrix-core kernels: now 16, and
                                 32 above 16 tokens) */
     int32_t launches;        /* rsparse_linear: 0 default

@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -144,7 +145,7 @@ struct rsparse_layer {
     rsparse_tuning tuning{};
     int device = 0;
     int cus = 256;
-    uint16_t *M = nullptr, *SVt = nullptr, *U = nullptr, *Wrow = nullptr;
+    uint16_t *M = nullptr, *SVt = nullptr, *U = nullptr;
     uint16_t *Wtile = nullptr, *SVtile = nullptr, *Utile = nullptr;   // matrix-core operands (dense_rowmajor = 1)
     uint16_t *Ms = nullptr;                // strip-major W + U_r^T: [strips][d_in + rank][strip_w]
     int strip_w = 0, strips = 0;
@@ -173,7 +174,7 @@ struct rsparse_layer {
     uint16_t *xg = nullptr;                // [max_batch][d_in] gated input x = round16(silu(g) * u), written out per call
     size_t n_t = 0, n_y = 0, sync_n = 0;
     bool last_fused = false;
-    // 4-bit weights (rsparse_prepare_q4): codes, group scales, group zero points; M and Wrow stay null
+    // 4-bit weights (rsparse_prepare_q4): codes, group scales, group zero points; M stays null
     uint8_t *Mq = nullptr, *qz = nullptr;
     uint8_t *Qrow = nullptr, *Zrow = nullptr;   // row-major codes and zero points (dense_rowmajor = 1): the row-dot dense baseline
     uint16_t *Srow = nullptr;
@@ -207,7 +208,7 @@ struct rsparse_layer {
     {
         const ScratchView sp = ov ? *ov : own_scratch();
         LayerView v{};
-        v.M = M; v.SVt = SVt; v.U = U; v.Wrow = Wrow; v.t = sp.t; v.yacc = sp.yacc; v.SVc = SVc; v.t_sum = ov ? nullptr : t_sum;
+        v.M = M; v.SVt = SVt; v.U = U; v.t = sp.t; v.yacc = sp.yacc; v.SVc = SVc; v.t_sum = ov ? nullptr : t_sum;
         v.act_list = sp.act_list; v.act_bits = sp.act_bits; v.act_count = sp.act_count; v.sync = sp.sync; v.t_pub = sp.t_pub;
         v.d_in = cfg.d_in; v.d_out = cfg.d_out; v.rank = cfg.rank;
         v.dtype = cfg.dtype; v.out_dtype = cfg.out_dtype; v.cmp_mode = cfg.cmp_mode;
@@ -228,9 +229,6 @@ struct rsparse_layer {
 
 namespace {
 
-// Layers below this many weights keep W row-major beside the operand layout (dense_rowmajor = 1): the row-dot kernel is
-// the faster dense kernel there at one token (rsparse_dense_ref_group).
-constexpr size_t kRowdotWeights = (size_t)1 << 22;
 // 4-bit layers run on the matrix cores from two tokens on, and at one token up to 2^25 weights (measured, us, vector ALU ->
 // matrix cores, at one token: 4096 x 4096 15.4 -> 14.0, q/k/v grouped and o 57 -> 37, gate and up 4096 -> 8192 grouped and
 // down 48 -> 38, but gate and up 4096 -> 11008 and down, rank 512, 61.4 -> 62.1: half the codes are skipped there and the
@@ -402,7 +400,7 @@ rsparse_status check_call(rsparse_layer *L, const void *X, int32_t batch, void *
 void free_layer(rsparse_layer *L)
 {
     if (!L) return;
-    (void)hipFree(L->M); (void)hipFree(L->SVt); (void)hipFree(L->U); (void)hipFree(L->Wrow); (void)hipFree(L->t);
+    (void)hipFree(L->M); (void)hipFree(L->SVt); (void)hipFree(L->U); (void)hipFree(L->t);
     (void)hipFree(L->yacc); (void)hipFree(L->act_bits); (void)hipFree(L->chan_bits);
     (void)hipFree(L->act_list); (void)hipFree(L->act_count); (void)hipFree(L->sync); (void)hipFree(L->t_pub); (void)hipFree(L->xg); (void)hipFree(L->hy);
     (void)hipFree(L->Wtile); (void)hipFree(L->SVtile); (void)hipFree(L->Utile);
@@ -553,21 +551,20 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
             RS_HIP(hipMemset(L->t_sum, 0, n_sum * 4));
         }
         if (cfg->dense_rowmajor && !q4) {
-            RS_HIP(hipMalloc((void **)&L->Wrow, d_in * d_out * 2));
-            RS_HIP(hipMemcpy(L->Wrow, W, d_in * d_out * 2, hipMemcpyHostToDevice));
-            rsparse_status ts = make_operand(L->Wrow, d_out, d_in, 16, &L->Wtile);
+            // row-major W is on the device only while the other layouts are made from it
+            uint16_t *rows = nullptr;
+            RS_HIP(hipMalloc((void **)&rows, d_in * d_out * 2));
+            const std::unique_ptr<uint16_t, void (*)(uint16_t *)> rows_owner(rows, [](uint16_t *p) { (void)hipFree(p); });
+            RS_HIP(hipMemcpy(rows, W, d_in * d_out * 2, hipMemcpyHostToDevice));
+            rsparse_status ts = make_operand(rows, d_out, d_in, 16, &L->Wtile);
             if (ts == RSPARSE_OK && r) ts = make_operand(L->SVt, r, d_in, 32, &L->SVtile);
             if (ts == RSPARSE_OK && r) ts = make_operand(L->U, d_out, r, 16, &L->Utile);
             if (ts != RSPARSE_OK) return ts;
             if (on_device) {
-                RS_HIP(launch_transpose16(L->Wrow, d_out, d_in, L->M, nullptr));
+                RS_HIP(launch_transpose16(rows, d_out, d_in, L->M, nullptr));
                 if (r) RS_HIP(launch_transpose16(L->U, d_out, r, L->M + d_in * d_out, nullptr));
             }
-            if (d_in * d_out >= kRowdotWeights) {
-                RS_HIP(hipDeviceSynchronize());
-                RS_HIP(hipFree(L->Wrow));
-                L->Wrow = nullptr;
-            }
+            RS_HIP(hipDeviceSynchronize());
         }
         // 4-bit layers take the matrix cores from their own threshold on
         const bool q4_mm = q4 && cfg->max_batch >= q4_min_batch(*cfg);
@@ -1114,20 +1111,22 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
         lc[i] = resolve_launch(layers[i], batch, true, n_layers, i ? lc[0].waves : 0);
         can_rowdot = can_rowdot && layers[i]->Wtile != nullptr && rowdot_supported(layers[i]->cfg.d_in, batch);
     }
-    // The dense product runs on the matrix cores at every batch (measured, us, vector ALU -> matrix cores: 4096 x 4096 9.2
-    // -> 8.7 at one token and 15.0 -> 8.7 at two, 8192 x 8192 25.8 -> 24.1 and 32.9 -> 24.2, 28672 -> 8192 86 -> 75 and 90
-    // -> 76; errors against 64 bits alike), except one token on layers that keep the row-major copy for the row-dot
-    // kernel (1024 x 1024 3.5 against 4.3, 2048 x 2048 both 5.2).  A kernel asked for by name gets the batches it had.
+    // The dense product runs on the matrix cores (measured, us, vector ALU -> matrix cores: 4096 x 4096 15.0 -> 8.7 at two
+    // tokens, 8192 x 8192 32.9 -> 24.2, 28672 -> 8192 86 -> 75 at one and 90 -> 76 at two; errors against 64 bits alike), but
+    // for one token, up to 8192 channels and 2^27 weights, where the row-dot kernel is as fast or faster (us over 512 MB of
+    // layers, matrix cores against row dots: 1024 x 1024 3.3 - 2.8, 2048 x 2048 5.0 - 3.8, 4096 x 4096 7.9 - 7.8, 6144 x 6144
+    // 15.3 - 13.4, 8192 -> 1024 9.5 - 6.7, q/k/v of 4096 / 1024 12.2 - 10.7, 4096 -> 11008 17.1 - 17.4, 8192 -> 4096 12.9 -
+    // 13.1, bf16 13.0 - 13.7, 8192 x 8192 21.5 - 22.0; above, 11008 -> 4096 16.9 - 16.8, bf16 17.0 - 18.2, 28672 -> 8192 76 -
+    // 80, gate and up of 8192 / 28672 and down 200 - 204).  A kernel asked for by name gets the batches it had.
     const bool large = (size_t)layers[0]->cfg.d_in * layers[0]->cfg.d_out >= ((size_t)1 << 25);
-    bool all_rowdot = can_rowdot;
-    for (int i = 0; i < n_layers; ++i) all_rowdot = all_rowdot && layers[i]->Wrow != nullptr;
     const int asked = layers[0]->tuning.dense_kernel;
+    size_t weights = 0;
+    for (int i = 0; i < n_layers; ++i) weights += (size_t)layers[i]->cfg.d_in * layers[i]->cfg.d_out;
+    const bool rowdot1 = can_rowdot && layers[0]->cfg.d_in <= 8192 && weights < ((size_t)1 << 27);
     bool mfma = batch >= (layers[0]->tuning.mfma_min_batch > 0 ? layers[0]->tuning.mfma_min_batch
                           : asked != 0                         ? (large ? 4 : kMfmaDefaultMinBatchDense)
-                          : all_rowdot                         ? 2
+                          : rowdot1                            ? 2
                                                                : 1);
-    // (the row-dot kernel reads rows: on layers without the row-major copy the matrix cores stand in for it)
-    if (asked == 2 && can_rowdot && !all_rowdot) mfma = true;
     MatrixView mv[RSPARSE_MAX_GROUP];
     for (int i = 0; i < n_layers; ++i) {
         mv[i] = layers[i]->matrix(v[i]);
@@ -1148,8 +1147,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     int kernel = layers[0]->tuning.dense_kernel;
     if (kernel == 2 && !can_rowdot)
         return fail(RSPARSE_EINVAL, "row-dot dense kernel needs dense_rowmajor=1 and batch_tile*d_in*2 <= 64 KiB");
-    // row dots win for short rows; for long rows (and for more than one token) the axpy form streams better
-    if (kernel == 0) kernel = (all_rowdot && layers[0]->cfg.d_in <= 8192 && batch == 1) ? 2 : 1;
+    if (kernel == 0) kernel = rowdot1 && batch == 1 ? 2 : 1;
     bool strip = true, colmajor = true;
     for (int i = 0; i < n_layers; ++i) {
         strip = strip && layers[i]->Ms != nullptr && layers[i]->strip_w == layers[0]->strip_w;
@@ -1164,7 +1162,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
         return RSPARSE_OK;
     }
     if (kernel == 2) {
-        RS_HIP(launch_dense_rowdot(v, lc, n_layers, X_dev, batch, Y_devs, s));
+        RS_HIP(launch_dense_rowdot(v, mv, lc, n_layers, X_dev, batch, Y_devs, s));
     } else if (strip) {
         // the strip kernel with every channel kept and no low-rank part
         Launch sc[RSPARSE_MAX_GROUP];

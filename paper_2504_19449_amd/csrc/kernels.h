@@ -31,7 +31,6 @@ struct LayerView {
     const uint16_t *U;      // [d_out][rank] = U_r, row-major
     const uint16_t *SVc;    // [d_in][rank] channel-major copy of S_r V_r^T (row c = its column c), or nullptr
     float *t_sum;           // [nz][BT][rank] fp32 sums of the stage 1 that reads SVc; zero between calls (or nullptr)
-    const uint16_t *Wrow;   // [d_out][d_in] row-major copy of W, or nullptr
     float *t;               // [nz][BT][rank] stage-1 result, fp32
     float *yacc;            // [max_batch][d_out] fp32 accumulators; zero between calls
     int32_t *act_list;      // [nz][d_in] ascending kept channels of batch tile z (union over its tokens)
@@ -48,7 +47,7 @@ struct LayerView {
     int strip_w;
     long long strip_stride; // 16-bit elements from one strip to the next: (d_in + rank + padding rows) * strip_w
     int32_t *act_seg;       // [nz][d_in / 8] strip kernel: kept channels found in each channel range of batch tile z
-    // 4-bit weights (Mq != nullptr; then M and Wrow are null).  A column tile is kQ4Tile = 1024 outputs: lane l
+    // 4-bit weights (Mq != nullptr; then M is null).  A column tile is kQ4Tile = 1024 outputs: lane l
     // of a wave owns the 8 bytes T * 512 + l * 8 .. of a row, two words h = 0, 1; byte k of word h holds the
     // code of column T * 1024 + h * 512 + l * 8 + k in its low nibble and of column ... + 4 + k in its high one.
     const uint8_t *Mq;      // [d_in][qtiles * 512] bytes, row c = the codes of W[:, c]
@@ -169,7 +168,8 @@ hipError_t launch_finish(const LayerView *L, int n, int batch, void *const *Y, b
 // Dense baselines.
 hipError_t launch_dense_axpy(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
                              hipStream_t stream);
-hipError_t launch_dense_rowdot(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
+// Row dots over the operand-layout copy of W (MatrixView::W), a batch of up to 8 tokens per tile within 64 KiB of LDS.
+hipError_t launch_dense_rowdot(const LayerView *L, const MatrixView *M, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
                                hipStream_t stream);
 // Matrix-core path for up to 32 tokens over the row-major copy of W: n layers that read the same input in one launch.
 // chan_bits[i] [d_in] receives, per channel, the bit mask of the tokens that keep it.  phases: 3 = the whole call (t is

@@ -1086,74 +1086,6 @@ __global__ __launch_bounds__(256) void k_finish(const FinishGroupArgs ga)
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Dense baseline, row-dot form over row-major W [d_out][d_in]: one wave per output row, x staged
-// in LDS, no cross-workgroup reduction at all.  grid.x workgroups of 4 waves; grid.z batch tiles.
-// ---------------------------------------------------------------------------------------------
-struct RowdotArgs {
-    LayerView L;
-    const uint16_t *X;
-    void *Y;
-    int batch;
-};
-
-struct RowdotGroupArgs {
-    RowdotArgs job[kMaxGroup];
-    int wg_end[kMaxGroup];
-    int n;
-};
-
-template <int DT, int BT, bool NT>
-__global__ __launch_bounds__(256) void k_dense_rowdot(const RowdotGroupArgs ga)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int z = blockIdx.z;
-    int wg, wg_count;
-    {
-        const int li = find_job(ga.wg_end, ga.n, blockIdx.x, wg);
-        wg_count = ga.wg_end[li] - (li ? ga.wg_end[li - 1] : 0);
-    }
-    const RowdotArgs &a = ga.job[find_job(ga.wg_end, ga.n, blockIdx.x, wg)];
-    const LayerView &L = a.L;
-    const int d_in = L.d_in, d_out = L.d_out;
-    const int b0 = z * BT;
-    const int nb = min(BT, a.batch - b0);
-    uint16_t *s_x = reinterpret_cast<uint16_t *>(smem);   // [BT][d_in]
-    const int nq = d_in / 8;
-    for (int q = tid; q < nq; q += 256)
-#pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            u32x4 v = u32x4{0, 0, 0, 0};
-            if (b < nb) v = *reinterpret_cast<const u32x4 *>(a.X + (size_t)(b0 + b) * d_in + q * 8);
-            *reinterpret_cast<u32x4 *>(s_x + (size_t)b * d_in + q * 8) = v;
-        }
-    __syncthreads();
-    for (int o = wg * 4 + w; o < d_out; o += wg_count * 4) {
-        const uint16_t *row = L.Wrow + (size_t)o * d_in;
-        float acc[BT];
-#pragma unroll
-        for (int b = 0; b < BT; ++b) acc[b] = 0.f;
-#pragma unroll 8
-        for (int q = lane; q < nq; q += 64) {
-            float f[8];
-            unpack8<DT>(ldg16<NT>(row + q * 8), f);
-#pragma unroll
-            for (int b = 0; b < BT; ++b) {
-                float xf[8];
-                unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_x + (size_t)b * d_in + q * 8), xf);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[b] = __builtin_fmaf(f[e], xf[e], acc[b]);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            float v = wave_sum(acc[b]);
-            if (lane == 0 && b < nb) store_out(a.Y, (size_t)(b0 + b) * d_out + o, v, L.out_dtype);
-        }
-    }
-}
-
 int batch_tile(int batch)
 {
     if (batch <= 1) return 1;
@@ -1185,11 +1117,6 @@ size_t gather_lds_bytes(int d_in, int splits, int waves, int bt, int fused_rank)
 size_t lowrank_lds_bytes(int d_in, int bt)
 {
     return (size_t)bt * lowrank_chunk(d_in, bt) * 2 + 16;
-}
-
-bool rowdot_supported(int d_in, int batch)
-{
-    return (size_t)batch_tile(batch) * d_in * 2 <= 65536;
 }
 
 #define RS_DISPATCH_BT(BTV, ...)                      \
@@ -1457,36 +1384,6 @@ hipError_t launch_dense_axpy(const LayerView *L, const Launch *cfg, int n, const
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_finish(L, n, batch, Y, false, stream);
-}
-
-hipError_t launch_dense_rowdot(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
-                               hipStream_t stream)
-{
-    if (!same_shape_class(L, n)) return hipErrorInvalidValue;
-    const int bt = batch_tile(batch);
-    const int nz = (batch + bt - 1) / bt;
-    RowdotGroupArgs ga{};
-    ga.n = n;
-    int total = 0;
-    for (int i = 0; i < n; ++i) {
-        ga.job[i] = RowdotArgs{L[i], (const uint16_t *)X, Y[i], batch};
-        int wgs = (L[i].d_out + 3) / 4;
-        if (wgs > 2048) wgs = 2048;
-        total += wgs;
-        ga.wg_end[i] = total;
-    }
-    for (int i = n; i < kMaxGroup; ++i) ga.wg_end[i] = total;
-    const size_t lds = (size_t)bt * L[0].d_in * 2;
-    dim3 grid(total, 1, nz), block(256);
-    const bool nt = cfg[0].nontemporal != 0;
-#define RS_R(DT)                                                                                      \
-    RS_DISPATCH_BT(bt, {                                                                              \
-        if (nt) hipLaunchKernelGGL((k_dense_rowdot<DT, BT, true>), grid, block, lds, stream, ga);     \
-        else hipLaunchKernelGGL((k_dense_rowdot<DT, BT, false>), grid, block, lds, stream, ga);       \
-    })
-    if (L[0].dtype == F16) { RS_R(F16) } else { RS_R(BF16) }
-#undef RS_R
-    return hipGetLastError();
 }
 
 // x = round16(silu(g) * u) written out (Sec. 3.1).  Forming it inside the gather kernel's own token loads was

@@ -1,5 +1,5 @@
 // gfx950 matrix-core path of the R-Sparse linear layer (R-Sparse, Sec. 3.4) for 5 to 32 tokens, and of the dense product
-// for 1 to 32, over a copy of W in operand layout (dense_rowmajor = 1).
+// from 2 (1 on the largest), over a copy of W in operand layout (dense_rowmajor = 1).
 //
 // At 5 tokens and more the union of kept channels is nearly all of them and 2*B flops per weight byte is more than the
 // vector ALU sustains at HBM speed, so all three products are skinny GEMMs on MFMA, still one pass over the weights:
