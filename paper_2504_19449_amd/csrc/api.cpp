@@ -769,13 +769,16 @@ Launch resolve_launch_q4(const rsparse_layer *L, int batch, bool dense, bool fus
     return c;
 }
 
-// Whether 4-bit layers that read the same input run on the matrix cores, all in the same two launches.
-bool q4_matrix_cores(rsparse_layer *const *layers, int n, int batch)
+// Whether 4-bit layers that read the same input run on the matrix cores, all in the same two launches: every layer's own
+// tuning has to allow it (the dense product asks dense_kernel, R-Sparse launches), and they have to share `stages`.
+bool q4_matrix_cores(rsparse_layer *const *layers, int n, int batch, bool dense)
 {
-    const rsparse_tuning &t = layers[0]->tuning;
-    bool ok = t.launches != 1;
-    for (int i = 0; i < n; ++i)
-        ok = ok && layers[i]->q4() && layers[i]->yc && batch >= (t.mfma_min_batch > 0 ? t.mfma_min_batch : q4_min_batch(layers[i]->cfg));
+    bool ok = true;
+    for (int i = 0; i < n; ++i) {
+        const rsparse_tuning &t = layers[i]->tuning;
+        ok = ok && layers[i]->q4() && layers[i]->yc && (dense ? t.dense_kernel == 0 : t.launches != 1) && t.stages == layers[0]->tuning.stages &&
+             batch >= (t.mfma_min_batch > 0 ? t.mfma_min_batch : q4_min_batch(layers[i]->cfg));
+    }
     return ok;
 }
 
@@ -904,9 +907,9 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
             RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
             X_dev = layers[0]->xg;
         }
-        if (q4_matrix_cores(layers, n_layers, batch)) return linear_q4_matrix_cores(layers, n_layers, X_dev, batch, Y_devs, false, s);
+        if (q4_matrix_cores(layers, n_layers, batch, false)) return linear_q4_matrix_cores(layers, n_layers, X_dev, batch, Y_devs, false, s);
         for (int i = 0; i < n_layers; ++i) {
-            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch)
+            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch, false)
                                                        ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], false, s)
                                                        : linear_q4(layers[i], X_dev, batch, Y_devs[i], false, s))
                                                 : linear_group_impl(&layers[i], 1, X_dev, nullptr, batch, &Y_devs[i], stream);
@@ -1095,7 +1098,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
             }
             if (Lq->q4() && Lq->tuning.dense_kernel == 2)
                 return fail(RSPARSE_EINVAL, "row-dot dense kernel on 4-bit weights needs dense_rowmajor=1, groups >= 32 and batch_tile*d_in*2.125 <= 64 KiB");
-            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch)
+            rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch, true)
                                                        ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], true, s)
                                                        : linear_q4(layers[i], X_dev, batch, Y_devs[i], true, s))
                                                 : rsparse_dense_ref_group(&layers[i], 1, X_dev, batch, &Y_devs[i], stream);

@@ -391,3 +391,49 @@ def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, launches):
         assert not np.any(np.isfinite(want["Y"][b]))                  # the definition: +-Inf, or NaN where W~[o][c] = 0
         assert np.all(~np.isfinite(got["Y"][b]))
     layer.destroy()
+
+
+def _one_wave_dense(layer, X16, **tuning):
+    """The dense product in its smallest launch shape: one wave per column tile, so that every output is one sum in one order
+    and a result identifies the kernel that gave it."""
+    rs.rsparse_set_tuning(layer, splits=1, waves=1, **tuning)
+    return gu.run_dense(layer, X16)
+
+
+@pytest.mark.parametrize("B", [1, 3])
+def test_q4_dense_kernel_asked_for_is_the_one_that_runs(B):
+    """dense_kernel = 1 is the channel-major vector kernel, bit for bit, whatever the batch; launches, which is about
+    rsparse_linear, does not change the dense product."""
+    dt = synth.BF16
+    q = Q4Layer(synth.random_layer(128, 1024, 0, dt, seed=5), 32)
+    X16, _ = gu.tokens_for(q.L, B, linear=B)
+    layer = q.prepare(0.5, max_batch=4, out_dtype=rs.F32)
+    vector = _one_wave_dense(layer, X16, mfma_min_batch=33)
+    auto = _one_wave_dense(layer, X16)
+    assert not np.array_equal(vector, auto)                          # (the matrix cores sum in another order)
+    assert np.array_equal(_one_wave_dense(layer, X16, dense_kernel=1), vector)
+    assert np.array_equal(_one_wave_dense(layer, X16, launches=1), auto)
+    for got in (vector, auto):
+        gu.check_outputs(got, q.dense(X16), rs.F32)
+    layer.destroy()
+
+
+def test_q4_every_layer_of_a_group_runs_by_its_own_tuning():
+    """One layer of a group is kept off the matrix cores: it gives the vector kernel's bits, the other one its usual result."""
+    dt = synth.BF16
+    qs = [Q4Layer(synth.random_layer(128, 1024, 0, dt, seed=8 + i), 32) for i in range(2)]
+    X16, src = gu.tokens_for(qs[0].L, 2)
+    tau = gu.calibrated_tau(qs[0].L, src, 0.5)
+    layers = [q.prepare(tau, max_batch=2, out_dtype=rs.F32) for q in qs]
+    vector = dict(splits=1, waves=1, mfma_min_batch=33)
+    auto = gu.run_linear(layers[1], X16)["Y"]
+    rs.rsparse_set_tuning(layers[1], **vector)
+    want = gu.run_linear(layers[1], X16)["Y"]
+    assert not np.array_equal(want, auto)
+    Xd = gu.to_dev16(X16)
+    Ys = [gu._alloc_out(l, 2) for l in layers]
+    rs.rsparse_linear_group(layers, Xd.data_ptr(), 2, [y.data_ptr() for y in Ys], gu.stream_ptr())
+    assert np.array_equal(gu._read_out(layers[1], Ys[1]), want)
+    gu.check_outputs(gu._read_out(layers[0], Ys[0]), qs[0].oracle(X16, tau)["Y"], rs.F32)
+    for l in layers:
+        l.destroy()
