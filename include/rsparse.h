@@ -275,7 +275,8 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
 /*
  * rsparse_linear_group with the per-layer decision of rsparse_plan_layer applied: if the byte model plus the fixed
  * launch costs say that R-Sparse does not pay for these layers at this batch (small attention projections at any
- * batch; every layer from about 8 tokens on), the call runs rsparse_dense_ref_group instead -- the exact dense product,
+ * batch; every layer from 5 tokens on, and from 2 to 4 on, by sparsity, where dense_rowmajor = 1 -- layers without it are
+ * judged by the times of their own dense kernels), the call runs rsparse_dense_ref_group instead -- the exact dense product,
  * which Sec. 3.5's per-layer recipe allows as the limit of zero sparsity.  keep_fraction: the share of channels one
  * token keeps at the layers' threshold (1 - the sparsity the threshold was calibrated for).  The decision is taken for
  * every layer with the group's size as `group`; if the layers disagree, each runs on its own as decided.  *used_rsparse_out (may be NULL): 1 if the R-Sparse path ran
@@ -386,10 +387,11 @@ rsparse_status rsparse_recipe(int32_t d_in, int32_t d_out, double budget_c, doub
  * projections, or every layer once the batch is so large that the union of the tokens' kept channels is nearly all of
  * them.  keep_fraction: share of channels ONE token keeps (s of rsparse_recipe); for `batch` tokens the loaded columns
  * are their union, modelled as 1 - (1 - s)^batch.  group: layers that share one launch (rsparse_linear_group), whose
- * fixed cost they split.  Constants (MI355X, measured with this library, 16-bit weights): one token -- 6.5 TB/s
- * marginal rate, 8.5 us fixed per R-Sparse launch, 3.6 us per dense launch; 2-4 tokens (vector path) -- 6.7 TB/s,
- * 8.5 + 3 log2(batch) us; 5-32 tokens (matrix cores, all of W read) -- 4.65 TB/s, 15 us; dense from 2 tokens --
- * 5.26 TB/s, 7.3 us (4.86 TB/s, 9.2 us above 16 tokens).  The estimates land within about 20 % of the measured times
+ * fixed cost they split.  Constants (MI355X, measured with this library, 16-bit weights, layers that keep dense_rowmajor = 1;
+ * TB/s of bytes and us per launch, which a group shares): R-Sparse 6.5 and 8.5 at one token, 6.7 and 11.5 at two, 6.0 and
+ * 8.5 + 2.2 log2(batch) at 3-4 (vector path); dense 6.5 and 3.6 at one token, 6.95 and 4.2 from two on (6 us above 16 tokens)
+ * and the tokens' own reads beyond six of them; from 5 tokens on R-Sparse runs on the matrix cores, reads all of W and costs
+ * the dense time, 5 us and the factors at 6.0 TB/s.  The estimates land within about 20 % of the measured times
  * on the benchmark shapes.  Host code.  Any output pointer may be NULL.  Errors: RSPARSE_EINVAL.
  */
 rsparse_status rsparse_plan_layer(int32_t d_in, int32_t d_out, int32_t rank, double keep_fraction, int32_t group,

@@ -1177,18 +1177,58 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     return RSPARSE_OK;
 }
 
+namespace {
+// Times of one linear in a group of `group`, measured on MI355X with this library's kernels (16-bit weights, weights from HBM):
+// fixed cost of the launch(es), which the group shares, plus bytes / rate.  operand_layout: the layer keeps W in the matrix
+// cores' operand layout (dense_rowmajor = 1), otherwise column-major only.  Within 20 % of what was measured from 4096 x 4096
+// to 8192 x 28672 at ranks of 1/16 and 1/8 but for one shape (8192 x 8192 from 17 tokens on: 30.6 for 25.8 us).
+void plan_us(int32_t d_in, int32_t d_out, int32_t rank, double keep_fraction, int32_t group, int32_t batch, bool operand_layout,
+             double &us_rs, double &us_dense)
+{
+    const double m = d_out, n = d_in, r = rank, e = 2.0, B = batch;
+    const double io = e * B * (n + m), w = e * n * m, factors = e * r * (n + m);
+    if (batch == 1) {
+        constexpr double kBytesPerUs = 6.5e6, kFixedRsparseUs = 8.5, kFixedDenseUs = 3.6;
+        us_rs = kFixedRsparseUs / group + (e * (keep_fraction * n * m + r * (n + m)) + io) / kBytesPerUs;
+        us_dense = kFixedDenseUs / group + (w + io) / kBytesPerUs;
+        return;
+    }
+    if (operand_layout) {
+        // dense on the matrix cores; a unit of 16 rows (32 above 16 tokens) reads all tokens from L2, which shows beyond six
+        const double tokens = batch > 16 ? n * m * B / 16 : n * m * std::max(0.0, B - 6) / 8;
+        us_dense = (batch > 16 ? 6.0 : 4.2) / group + (w + io) / 6.95e6 + tokens / 24e6;
+    } else if (batch <= 4) {
+        us_dense = (7.6 + 3.9 * std::log2(B)) / group + (w + io) / (batch == 2 ? 6.2e6 : 5.9e6);      // vector ALU, two launches
+    } else {
+        us_dense = (batch > 16 ? 9.5 : 9.0) / group + (w + io) / (batch > 16 ? 5.0e6 : 6.6e6);        // matrix cores, two launches
+    }
+    if (batch <= 4) {
+        // vector path, one launch: the columns that are loaded are the union of the tokens' kept channels (independent
+        // tokens), and the fixed part grows with the batch tile (token loads, coefficient fetch, accumulators per token)
+        const double u = 1.0 - std::pow(1.0 - keep_fraction, B);
+        us_rs = (8.5 + (batch == 2 ? 3.0 : 2.2) * std::log2(B)) / group + (u * w + factors + io) / (batch == 2 ? 6.7e6 : 6.0e6);
+    } else {
+        // matrix cores: W is streamed whole whatever the masks are, t and U_r t come on top
+        us_rs = us_dense + (operand_layout ? 5.0 / group + factors / 6.0e6 : 1.5 / group + factors / 5.0e6);
+    }
+}
+}  // namespace
+
 rsparse_status rsparse_linear_group_planned(rsparse_layer *const *layers, int32_t n_layers, const void *X_dev,
                                             int32_t batch, void *const *Y_devs, void *stream, double keep_fraction,
                                             int32_t *used_rsparse_out)
 {
     rsparse_status st = check_group(layers, n_layers, X_dev, batch, Y_devs);
     if (st != RSPARSE_OK) return st;
+    if (!(keep_fraction >= 0.0) || keep_fraction > 1.0) return fail(RSPARSE_EINVAL, "keep_fraction must be in [0, 1]");
     int32_t use[RSPARSE_MAX_GROUP];
     bool all = true, none = true;
     for (int i = 0; i < n_layers; ++i) {
         const rsparse_config &c = layers[i]->cfg;
-        st = rsparse_plan_layer(c.d_in, c.d_out, c.rank, keep_fraction, n_layers, batch, nullptr, nullptr, &use[i]);
-        if (st != RSPARSE_OK) return st;
+        // (4-bit layers: the constants of layers with the operand layout, which run both products on the matrix cores too)
+        double us_rs, us_dense;
+        plan_us(c.d_in, c.d_out, c.rank, keep_fraction, n_layers, batch, layers[i]->Wtile || layers[i]->q4(), us_rs, us_dense);
+        use[i] = us_rs < us_dense ? 1 : 0;
         all = all && use[i];
         none = none && !use[i];
     }
@@ -1487,28 +1527,8 @@ rsparse_status rsparse_plan_layer(int32_t d_in, int32_t d_out, int32_t rank, dou
     if (!(keep_fraction >= 0.0) || keep_fraction > 1.0) return fail(RSPARSE_EINVAL, "keep_fraction must be in [0, 1]");
     if (group < 1 || group > RSPARSE_MAX_GROUP) return fail(RSPARSE_EINVAL, "group %d outside [1, %d]", group, RSPARSE_MAX_GROUP);
     if (batch < 1 || batch > RSPARSE_MAX_BATCH) return fail(RSPARSE_EINVAL, "batch %d outside [1, %d]", batch, RSPARSE_MAX_BATCH);
-    // measured on MI355X with this library's kernels (16-bit weights): time = fixed cost of the launch(es) + bytes / rate
-    const double m = d_out, n = d_in, r = rank, e = 2.0, B = batch;
-    const double io = e * B * (n + m);
-    // the columns that are loaded are the union of the tokens' kept channels (independent tokens)
-    const double u = 1.0 - std::pow(1.0 - keep_fraction, B);
     double us_rs, us_dense;
-    if (batch == 1) {
-        constexpr double kBytesPerUs = 6.5e6, kFixedRsparseUs = 8.5, kFixedDenseUs = 3.6;
-        us_rs = kFixedRsparseUs / group + (e * (keep_fraction * n * m + r * (n + m)) + io) / kBytesPerUs;
-        us_dense = kFixedDenseUs / group + (e * n * m + io) / kBytesPerUs;
-    } else {
-        if (batch <= 4) {
-            // vector path, one launch shared by the group; the fixed part grows with the batch tile (token loads,
-            // coefficient fetch, accumulators per token)
-            us_rs = (8.5 + 3.0 * std::log2(B)) / group + (e * (u * n * m + r * (n + m)) + io) / 6.7e6;
-        } else {
-            // matrix-core path: W is streamed whole whatever the masks are, three launches, no sharing in a group
-            us_rs = 15.0 + (e * (n * m + r * (n + m)) + io) / 4.65e6;
-        }
-        // dense product on the matrix cores
-        us_dense = (batch > 16 ? 9.2 : 7.3) + (e * n * m + io) / (batch > 16 ? 4.86e6 : 5.26e6);
-    }
+    plan_us(d_in, d_out, rank, keep_fraction, group, batch, true, us_rs, us_dense);
     if (us_rsparse_out) *us_rsparse_out = us_rs;
     if (us_dense_out) *us_dense_out = us_dense;
     if (use_rsparse_out) *use_rsparse_out = us_rs < us_dense ? 1 : 0;

@@ -227,6 +227,31 @@ def test_plan_layer_byte_model_and_decisions():
             rs.rsparse_plan_layer(**kw)
 
 
+# us per linear on MI355X, weights from HBM, layers with dense_rowmajor = 1, half of the channels kept:
+# (d_in, d_out, rank, group), tokens, R-Sparse, dense
+_MEASURED = [
+    ((4096, 4096, 256, 1), 2, 16.2, 8.3), ((4096, 4096, 256, 1), 4, 18.8, 8.3), ((4096, 4096, 256, 1), 8, 14.3, 8.3),
+    ((4096, 4096, 256, 1), 16, 14.8, 9.6), ((4096, 4096, 256, 1), 32, 16.9, 12.9), ((4096, 4096, 256, 3), 2, 8.4, 6.1),
+    ((4096, 4096, 256, 3), 16, 9.1, 6.9), ((4096, 11008, 512, 1), 2, 23.0, 17.4), ((4096, 11008, 512, 1), 4, 29.1, 17.3),
+    ((4096, 11008, 512, 1), 8, 26.5, 17.8), ((4096, 11008, 512, 1), 32, 30.1, 23.8), ((4096, 11008, 512, 2), 2, 17.8, 16.0),
+    ((4096, 11008, 512, 2), 4, 22.2, 16.1), ((4096, 11008, 512, 2), 8, 21.3, 16.6), ((11008, 4096, 512, 1), 2, 23.9, 17.1),
+    ((11008, 4096, 512, 1), 8, 24.8, 17.2), ((4096, 14336, 256, 1), 2, 25.9, 22.1), ((4096, 14336, 256, 1), 4, 32.3, 22.2),
+    ((8192, 8192, 1024, 1), 2, 31.3, 22.9), ((8192, 8192, 1024, 1), 4, 40.6, 22.7), ((8192, 8192, 1024, 1), 8, 33.5, 22.9),
+    ((8192, 28672, 1024, 2), 3, 86.3, 67.3), ((8192, 28672, 1024, 2), 4, 92.4, 67.4), ((8192, 28672, 1024, 2), 8, 86.9, 69.8),
+    ((28672, 8192, 1024, 1), 2, 80.8, 73.3), ((28672, 8192, 1024, 1), 4, 104.2, 73.0), ((28672, 8192, 1024, 1), 8, 91.1, 73.6),
+    ((28672, 8192, 1024, 1), 16, 100.5, 82.8), ((28672, 8192, 1024, 1), 32, 108.6, 85.2),
+]
+
+
+@pytest.mark.parametrize("shape,B,us_rsparse,us_dense", _MEASURED)
+def test_plan_layer_agrees_with_the_measured_kernels(shape, B, us_rsparse, us_dense):
+    """From two tokens on: both estimates within 20 % of the measured times, and the decision is the measured one."""
+    d_in, d_out, rank, group = shape
+    est_rs, est_dense, use = rs.rsparse_plan_layer(d_in, d_out, rank, 0.5, group, B)
+    assert abs(est_rs / us_rsparse - 1) < 0.2 and abs(est_dense / us_dense - 1) < 0.2, (est_rs, est_dense)
+    assert bool(use) == (us_rsparse < us_dense)
+
+
 def test_io_model_is_the_byte_form_of_sec_3_4():
     """rsparse_io_model (which rsparse_required_bytes / rsparse_dense_bytes evaluate for a handle) against
     the paper's own cost model: relative memory I/O r (m + n) / (m n) + s with s the share of columns loaded
