@@ -74,7 +74,7 @@ typedef struct {
                                 channels anyway, its columns are loaded either way, and using them for every token is
                                 strictly more accurate at the same bytes) */
     int32_t dense_rowmajor;  /* 1: also keep W row by row on the device, in the matrix cores' operand layout (doubles the
-                                weight footprint).  Needed by the one-launch matrix-core path that rsparse_linear takes from 5
+                                weight footprint; W goes up in slices of 64 MiB, so preparing needs no more).  Needed by the one-launch matrix-core path that rsparse_linear takes from 5
                                 tokens on and rsparse_dense_ref from 2 (see mfma_min_batch), and by the row-dot kernel; without
                                 it batches from 5 tokens on take the matrix cores over column-major W (two launches; the
                                 factors are kept a second time, in operand layout, where max_batch >= 5); fixed-count
@@ -178,7 +178,8 @@ rsparse_status rsparse_prepare_factors(const rsparse_config *cfg, const void *W_
  * contiguous run of d_out / 2 bytes) and dequantises in registers: per quantisation group it accumulates
  * sum x_c q_c and sum x_c and applies scale and zero point once.  From 2 tokens on (1 on layers of up to 2^25
  * weights) the products run on the matrix cores, codes converted exactly; rsparse_linear and friends run this path as two
- * launches, which layers of a group share (tuning launches = 1 selects a one-launch form of the vector kernel, which takes
+ * launches, which layers of a group share, and read both factors in an operand layout of their own (kept beside the plain
+ * ones: 4 rank (d_in + d_out) bytes in all; above 2^25 weights only where max_batch >= 2) (tuning launches = 1 selects a one-launch form of the vector kernel, which takes
  * batches above 4 tokens as tiles of 4, the codes streamed once per tile); otherwise grouped
  * calls and rsparse_mlp_gate_up take such layers one at a time.  rsparse_dense_ref gives the dense product with W~:
  * with dense_rowmajor = 1 (a second, row-major copy of the codes, scales and zero points: + d_in * d_out / 2 bytes)

@@ -551,19 +551,24 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
             RS_HIP(hipMemset(L->t_sum, 0, n_sum * 4));
         }
         if (cfg->dense_rowmajor && !q4) {
-            // row-major W is on the device only while the other layouts are made from it
+            // W goes up in slices of whole 64-row tiles (64 MiB or less), and the other layouts are made from each on the
+            // device: beside what the layer keeps, one slice is resident at a time
+            const size_t slice = std::min(d_out, std::max<size_t>(1, ((size_t)64 << 20) / (d_in * 2 * 64)) * 64);
             uint16_t *rows = nullptr;
-            RS_HIP(hipMalloc((void **)&rows, d_in * d_out * 2));
+            RS_HIP(hipMalloc((void **)&L->Wtile, mfma_operand_bytes(d_out, d_in, 16)));
+            RS_HIP(hipMalloc((void **)&rows, slice * d_in * 2));
             const std::unique_ptr<uint16_t, void (*)(uint16_t *)> rows_owner(rows, [](uint16_t *p) { (void)hipFree(p); });
-            RS_HIP(hipMemcpy(rows, W, d_in * d_out * 2, hipMemcpyHostToDevice));
-            rsparse_status ts = make_operand(rows, d_out, d_in, 16, &L->Wtile);
-            if (ts == RSPARSE_OK && r) ts = make_operand(L->SVt, r, d_in, 32, &L->SVtile);
+            for (size_t r0 = 0; r0 < d_out; r0 += slice) {
+                const size_t n = std::min(slice, d_out - r0);
+                RS_HIP(hipMemcpy(rows, W + r0 * d_in, n * d_in * 2, hipMemcpyHostToDevice));
+                RS_HIP(launch_pack_operand(rows, n, d_in, 16, L->Wtile + mfma_operand_bytes(r0, d_in, 16) / 2, nullptr));
+                if (on_device) RS_HIP(launch_transpose16(rows, n, d_in, L->M + r0, d_out, nullptr));
+            }
+            rsparse_status ts = RSPARSE_OK;
+            if (r) ts = make_operand(L->SVt, r, d_in, 32, &L->SVtile);
             if (ts == RSPARSE_OK && r) ts = make_operand(L->U, d_out, r, 16, &L->Utile);
             if (ts != RSPARSE_OK) return ts;
-            if (on_device) {
-                RS_HIP(launch_transpose16(rows, d_out, d_in, L->M, nullptr));
-                if (r) RS_HIP(launch_transpose16(L->U, d_out, r, L->M + d_in * d_out, nullptr));
-            }
+            if (on_device && r) RS_HIP(launch_transpose16(L->U, d_out, r, L->M + d_in * d_out, d_out, nullptr));
             RS_HIP(hipDeviceSynchronize());
         }
         // 4-bit layers take the matrix cores from their own threshold on

@@ -180,8 +180,8 @@ size_t mfma_t_bytes(int rank);
 // A row-major matrix [rows][cols] (device; cols a multiple of 8) in operand layout, rows padded to row_pad (16 or 32).
 size_t mfma_operand_bytes(size_t rows, size_t cols, size_t row_pad);
 hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, size_t row_pad, uint16_t *dst, hipStream_t stream);
-// dst [cols][rows] = transpose of src [rows][cols], 16-bit, both multiples of 8 (device).
-hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream);
+// dst [cols][ld >= rows] = transpose of src [rows][cols], 16-bit, all multiples of 8 (device).
+hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, size_t ld, hipStream_t stream);
 hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const void *X, int batch, void *const *Y, uint32_t *const *chan_bits, int cus,
                        int phases, bool dense, int wait_polls, int skip_stage1, hipStream_t stream);
 // 4-bit weights on the matrix cores (kernels_mfma_q4.hip), up to 32 tokens, n layers that read the same input: adds the W

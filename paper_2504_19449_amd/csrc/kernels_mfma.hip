@@ -360,7 +360,7 @@ hipError_t launch_pack_operand(const uint16_t *src, size_t rows, size_t cols, si
 size_t mfma_t_bytes(int rank) { return t32_offset(rank) * 2; }
 
 // 64 x 64 tiles through LDS, 16 bytes per access on both sides.
-__global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst)
+__global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, size_t ld)
 {
     __shared__ uint16_t tile[64][66];
     const size_t c0 = (size_t)blockIdx.x * 64, r0 = (size_t)blockIdx.y * 64;
@@ -379,15 +379,15 @@ __global__ __launch_bounds__(256) void k_transpose16(const uint16_t *src, size_t
             u32x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (uint32_t)tile[i % 8 * 8 + 2 * e][i / 8] | ((uint32_t)tile[i % 8 * 8 + 2 * e + 1][i / 8] << 16);
-            *reinterpret_cast<u32x4 *>(dst + c * rows + r) = v;
+            *reinterpret_cast<u32x4 *>(dst + c * ld + r) = v;
         }
     }
 }
 
-hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, hipStream_t stream)
+hipError_t launch_transpose16(const uint16_t *src, size_t rows, size_t cols, uint16_t *dst, size_t ld, hipStream_t stream)
 {
     if (rows == 0 || cols == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_transpose16, dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)), dim3(256), 0, stream, src, rows, cols, dst);
+    hipLaunchKernelGGL(k_transpose16, dim3((unsigned)((cols + 63) / 64), (unsigned)((rows + 63) / 64)), dim3(256), 0, stream, src, rows, cols, dst, ld);
     return hipGetLastError();
 }
 

@@ -174,3 +174,39 @@ def test_column_major_group_and_gate_up_pair():
     rs.rsparse_mlp_gate_up(layers[0], layers[1], Xd.data_ptr(), 9, H.data_ptr(), gu.stream_ptr())
     want = oracle.gated_input(synth.encode16(outs[0], synth.BF16), synth.encode16(outs[1], synth.BF16), synth.BF16)
     gu.check_outputs(gu._read_out(layers[0], H), synth.decode16(want, synth.BF16), rs.BF16)
+
+
+def test_preparing_keeps_two_copies_of_w_at_a_time():
+    """dense_rowmajor = 1 doubles the weight footprint, also while the layer is prepared (W goes up in slices): a second thread
+    watches the free device memory.  Several slices give the layouts of one upload: the dense product by two kernels that read
+    one layout each, and R-Sparse, on rows of the first, a middle and the last slice."""
+    import threading
+
+    torch = gu.torch_mod()
+    dt, d_in, d_out = synth.F16, 8192, 16392
+    L = synth.random_layer(d_in, d_out, 8, dt, seed=2)
+    w = d_in * d_out * 2
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    least, stop = [free0], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            least[0] = min(least[0], torch.cuda.mem_get_info()[0])
+
+    th = threading.Thread(target=watch)
+    th.start()
+    layer = gu.prepare(L, 0.5, max_batch=8, out_dtype=rs.F32, dense_rowmajor=1)
+    stop.set()
+    th.join()
+    assert free0 - least[0] < 2 * w + (128 << 20), (free0 - least[0]) / w
+    X16, src = gu.tokens_for(L, 5)
+    rows = np.r_[0:64, 4000:4200, 8000:8300, d_out - 40:d_out]
+    want = synth.decode16(X16, dt) @ synth.decode16(L.W16[rows], dt).T
+    for tuning, B in ((dict(dense_kernel=1), 1), (dict(dense_kernel=2), 1), (dict(), 5)):
+        rs.rsparse_set_tuning(layer, **tuning)
+        gu.check_outputs(gu.run_dense(layer, X16[:B])[:, rows], want[:B], rs.F32)
+    rs.rsparse_set_tau(layer, float("-inf"))                         # every channel kept: R-Sparse is the dense product too
+    for B in (1, 5):
+        gu.check_outputs(gu.run_linear(layer, X16[:B], lists=False)["Y"][:, rows], want[:B], rs.F32)
+    layer.destroy()
