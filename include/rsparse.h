@@ -120,9 +120,10 @@ typedef struct {
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
                                 dense_rowmajor = 1; 4-bit weights above 2^25: max_batch >= 2): 0 = default (5 for
-                                rsparse_linear; 2 on 4-bit weights, 1 up to 2^25 of them; for rsparse_dense_ref 2, 1 above
-                                8192 channels or from 2^27 weights in a call, and with dense_kernel set 2, 4 on layers of 2^25
-                                weights or more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on 4-bit
+                                rsparse_linear; 2 on 4-bit weights, 1 up to 2^24 of them, and up to 2^25 each in a call of
+                                several layers; for rsparse_dense_ref 2, 1 above 8192 channels or from 2^27 weights in a call
+                                (4-bit: 2, 1 up to 2^25 weights), and with dense_kernel set 2, 4 on layers of 2^25 weights or
+                                more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on 4-bit
                                 weights, on the vector ALU) */
     int32_t mfma_rows;       /* 0, 64, 128 or 256; without effect (rows per workgroup of earlier matrix-core kernels: now 16, and
                                 32 above 16 tokens) */
@@ -176,8 +177,8 @@ rsparse_status rsparse_prepare_factors(const rsparse_config *cfg, const void *W_
  * U16_host / SV16_host stay 16-bit and are the caller's (of the unquantised W, or of W~).  group_size: a power
  * of two in [32, 1024] that divides d_in.  The library packs the codes channel-major (one kept channel = one
  * contiguous run of d_out / 2 bytes) and dequantises in registers: per quantisation group it accumulates
- * sum x_c q_c and sum x_c and applies scale and zero point once.  From 2 tokens on (1 on layers of up to 2^25
- * weights) the products run on the matrix cores, codes converted exactly; rsparse_linear and friends run this path as two
+ * sum x_c q_c and sum x_c and applies scale and zero point once.  From 2 tokens on (1 on layers of up to 2^24
+ * weights, and up to 2^25 each in a call of several) the products run on the matrix cores, codes converted exactly; rsparse_linear and friends run this path as two
  * launches, which layers of a group share, and read both factors in an operand layout of their own (kept beside the plain
  * ones: 4 rank (d_in + d_out) bytes in all; above 2^25 weights only where max_batch >= 2) (tuning launches = 1 selects a one-launch form of the vector kernel, which takes
  * batches above 4 tokens as tiles of 4, the codes streamed once per tile); otherwise grouped

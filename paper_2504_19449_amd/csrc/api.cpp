@@ -229,12 +229,18 @@ struct rsparse_layer {
 
 namespace {
 
-// 4-bit layers run on the matrix cores from two tokens on, and at one token up to 2^25 weights (measured, us, vector ALU ->
-// matrix cores, at one token: 4096 x 4096 15.4 -> 14.0, q/k/v grouped and o 57 -> 37, gate and up 4096 -> 8192 grouped and
-// down 48 -> 38, but gate and up 4096 -> 11008 and down, rank 512, 61.4 -> 62.1: half the codes are skipped there and the
-// stream is long enough to show it; at two tokens the last one 105 -> 63, at sixteen 717 -> 66, at 32 1340 -> 86).
-constexpr size_t kMfmaQ4OneToken = (size_t)1 << 25;
-int q4_min_batch(const rsparse_config &c) { return (size_t)c.d_in * c.d_out <= kMfmaQ4OneToken ? 1 : 2; }
+// 4-bit layers run on the matrix cores from two tokens on (measured, us, vector ALU -> matrix cores, gate and up 4096 -> 11008
+// and down, rank 512: 105 -> 63 at two, 717 -> 66 at sixteen, 1340 -> 86 at 32; 2048 / 5632 at 50 to 90 % sparsity 51 to 58 -> 31
+// at two).  At one token the vector kernel skips the dropped channels' codes but takes two launches per layer, the matrix cores
+// stream every code in two launches per call: calls of several layers up to 2^25 weights each run on the matrix cores (vector
+// -> matrix, at 50 and at 90 % sparsity, fp16: two of 4096 -> 8192 31 -> 22 and 29 -> 22, q/k/v of 4096 42 -> 21 and 41 -> 22,
+// three of 5632 x 5632 54 -> 33 and 48 -> 34; two of 4096 -> 11008 in bf16 37 -> 34 and 32 -> 34), calls of one layer up to 2^24
+// (4096 x 4096 14.3 -> 13.3 and 14.0 -> 13.3, 2048 -> 8192 13.4 -> 13.0 and 12.9 -> 13.1; above, 4096 -> 5120 14.8 -> 15.6 and
+// 14.0 -> 15.6, 5760 x 5760 in bf16 16.7 -> 18.3 and 14.4 -> 18.5).  The dense product skips nothing: 2^25 there.
+int q4_min_batch(const rsparse_config &c, bool one_layer)
+{
+    return (size_t)c.d_in * c.d_out <= ((size_t)1 << (one_layer ? 24 : 25)) ? 1 : 2;
+}
 // Smallest batch that column-major layers without the operand-layout copy run on the matrix cores (measured, us for gate, up
 // and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 76 at five,
 // 234 -> 79 at sixteen, 389 -> 93 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
@@ -572,7 +578,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
             RS_HIP(hipDeviceSynchronize());
         }
         // 4-bit layers take the matrix cores from their own threshold on
-        const bool q4_mm = q4 && cfg->max_batch >= q4_min_batch(*cfg);
+        const bool q4_mm = q4 && cfg->max_batch >= q4_min_batch(*cfg, false);
         // ... and column-major layers without the operand-layout copy from theirs
         const bool cols_mm = L->M && !cfg->dense_rowmajor && cfg->max_batch >= kMfmaMinBatchCols;
         if (q4_mm || cols_mm) {
@@ -782,7 +788,7 @@ bool q4_matrix_cores(rsparse_layer *const *layers, int n, int batch, bool dense)
     for (int i = 0; i < n; ++i) {
         const rsparse_tuning &t = layers[i]->tuning;
         ok = ok && layers[i]->q4() && layers[i]->yc && (dense ? t.dense_kernel == 0 : t.launches != 1) && t.stages == layers[0]->tuning.stages &&
-             batch >= (t.mfma_min_batch > 0 ? t.mfma_min_batch : q4_min_batch(layers[i]->cfg));
+             batch >= (t.mfma_min_batch > 0 ? t.mfma_min_batch : q4_min_batch(layers[i]->cfg, n == 1 && !dense));
     }
     return ok;
 }

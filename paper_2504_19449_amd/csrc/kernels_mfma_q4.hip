@@ -1,4 +1,4 @@
-// Matrix-core kernel for 4-bit weights (R-Sparse, Sec. 4.4) at 2 tokens and more: yc += X' (q - z) s over the
+// Matrix-core kernel for 4-bit weights (R-Sparse, Sec. 4.4) from 2 tokens on, on smaller layers from 1: yc += X' (q - z) s over the
 // channel-major codes (layout: LayerView::Mq), X' the kept part of the tokens (all of them for the dense product).
 //
 // The union of kept channels is most of them (nearly all from 4 tokens on), so every channel is streamed, once for 16
