@@ -210,3 +210,40 @@ def test_preparing_keeps_two_copies_of_w_at_a_time():
     for B in (1, 5):
         gu.check_outputs(gu.run_linear(layer, X16[:B], lists=False)["Y"][:, rows], want[:B], rs.F32)
     layer.destroy()
+
+
+@pytest.mark.parametrize("form,B", [("columns", 5), ("columns", 20), ("q4", 1), ("q4", 20)])
+def test_replayed_graphs_of_the_two_launch_forms(form, B):
+    """Column-major and 4-bit layers on the matrix cores inside a captured graph: every replay, with new tokens in the same
+    buffer and an eager call at another batch size between replays, equals the oracle (the sums of the first
+    launch are taken out by the second)."""
+    torch = gu.torch_mod()
+    dt = synth.BF16
+    L = synth.random_layer(1056, 520, 40, dt, seed=77)
+    X16, src = gu.tokens_for(L, 4 * B, linear=B)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    if form == "q4":
+        Q, S16, Z = synth.quantize_q4(synth.decode16(L.W16, dt), dt, 32)
+        cfg = rs.make_config(L.d_in, L.d_out, L.rank, tau, dt, max_batch=32, out_dtype=rs.F32)
+        layer = rs.rsparse_prepare_q4(cfg, Q, S16, Z, 32, L.U16, L.SV16)
+        oracle_of = lambda X: oracle.rsparse_linear_q4(Q, S16, Z, L.U16, L.SV16, X, dt, tau, group=32)["Y"]
+    else:
+        layer = gu.prepare(L, tau, max_batch=32, out_dtype=rs.F32)
+        oracle_of = lambda X: gu.oracle_linear(L, X, tau)["Y"]
+    Xd = gu.to_dev16(X16[:B])
+    Y = gu._alloc_out(layer, B)
+    rs.rsparse_linear(layer, Xd.data_ptr(), B, Y.data_ptr(), gu.stream_ptr())
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        rs.rsparse_linear(layer, Xd.data_ptr(), B, Y.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    for rep in range(4):
+        xb = X16[rep * B:(rep + 1) * B]
+        Xd.copy_(torch.from_numpy(np.ascontiguousarray(xb).view(np.int16)))
+        Y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        gu.check_outputs(Y.cpu().numpy().astype(np.float64), oracle_of(xb), rs.F32)
+        other = np.concatenate([xb, xb, xb, xb, xb])[:17 if B <= 16 else 5]
+        gu.check_outputs(gu.run_linear(layer, other)["Y"], oracle_of(other), rs.F32)
+    layer.destroy()

@@ -26,13 +26,14 @@ def config0():
 def _parity(L, X16, tau, out_dtype=None, max_batch=None, tuning=None, **cfg_kw):
     X16 = np.atleast_2d(X16)
     layer = gu.prepare(L, tau, max_batch=max_batch or X16.shape[0], out_dtype=out_dtype, **cfg_kw)
-    if tuning:
-        rs.rsparse_set_tuning(layer, **tuning)
-    got = gu.run_linear(layer, X16)
     want = gu.oracle_linear(L, X16, tau, cmp_mode=cfg_kw.get("cmp_mode", 0),
                             batch_mask_mode=cfg_kw.get("batch_mask_mode", 0))
-    gu.check_lists(got, want)
-    gu.check_outputs(got["Y"], want["Y"], layer.cfg.out_dtype)
+    # from 5 tokens on the matrix cores run; the vector kernels (tiles of 8 tokens) take the same call where they are asked for
+    for form in ({}, dict(mfma_min_batch=33))[:2 if X16.shape[0] >= 5 else 1]:
+        rs.rsparse_set_tuning(layer, **dict(tuning or {}, **form))
+        got = gu.run_linear(layer, X16)
+        gu.check_lists(got, want)
+        gu.check_outputs(got["Y"], want["Y"], layer.cfg.out_dtype)
     layer.destroy()
     return got, want
 
@@ -312,8 +313,8 @@ def test_gated_matches_ungated_on_the_materialised_input(ragged):
 @pytest.mark.parametrize("B", [1, 3, 8, 12])
 def test_mlp_gate_up_with_fused_activation(dt, B):
     """rsparse_mlp_gate_up: H = round(silu(round g) * round u) (Sec. 3.1) from the two R-Sparse
-    projections.  One launch on the vector path (1-8 tokens without the row-major copy), the
-    two-layers-then-elementwise fallback elsewhere; kept-channel lists of both layers must equal the
+    projections.  One launch on the vector path (1-4 tokens, up to 8 with launches = 1), the
+    two-layers-then-elementwise form elsewhere; kept-channel lists of both layers must equal the
     oracle's, H within the 16-bit output bounds.  Different rank and threshold per layer."""
     import oracle
     torch = gu.torch_mod()
@@ -323,7 +324,7 @@ def test_mlp_gate_up_with_fused_activation(dt, B):
     tg, tu = gu.calibrated_tau(Lg, src, 0.5), gu.calibrated_tau(Lg, src, 0.6)
     wg, wu = gu.oracle_linear(Lg, X16, tg), gu.oracle_linear(Lu, X16, tu)
     h_want = synth.decode16(oracle.gated_input(synth.encode16(wg["Y"], dt), synth.encode16(wu["Y"], dt), dt), dt)
-    for rowmajor, launches in ((0, 1), (0, 2), (1, 1)):
+    for rowmajor, launches in ((0, 0), (0, 1), (0, 2), (1, 1)):
         gate = gu.prepare(Lg, tg, max_batch=B, dense_rowmajor=rowmajor)
         up = gu.prepare(Lu, tu, max_batch=B, dense_rowmajor=rowmajor)
         rs.rsparse_set_tuning(gate, launches=launches)
@@ -719,7 +720,7 @@ def test_nothing_is_written_past_the_end_of_the_outputs(ragged):
     X16, src = gu.tokens_for(L, 9, linear=12)
     tau = gu.calibrated_tau(L, src, 0.5)
     pad = 4096                                                   # 16-bit words of canary on each side
-    for kw, tuning, B in ((dict(), dict(), 1), (dict(), dict(launches=2), 3), (dict(), dict(), 8),
+    for kw, tuning, B in ((dict(), dict(), 1), (dict(), dict(launches=2), 3), (dict(), dict(), 8), (dict(), dict(mfma_min_batch=33), 8),
                           (dict(dense_rowmajor=1), dict(), 9), (dict(strip_cols=32), dict(), 1),
                           (dict(strip_cols=64), dict(splits=3), 9), (dict(out_dtype=rs.F32), dict(), 2)):
         layer = gu.prepare(L, tau, max_batch=B, **kw)

@@ -47,12 +47,14 @@ def ragged_q4():
 def _parity(q, X16, tau, out_dtype=None, tuning=None, **kw):
     X16 = np.atleast_2d(X16)
     layer = q.prepare(tau, max_batch=X16.shape[0], out_dtype=out_dtype, **kw)
-    if tuning:
-        rs.rsparse_set_tuning(layer, **tuning)
-    got = gu.run_linear(layer, X16)
     want = q.oracle(X16, tau, cmp_mode=kw.get("cmp_mode", 0), batch_mask_mode=kw.get("batch_mask_mode", 0))
-    gu.check_lists(got, want)
-    gu.check_outputs(got["Y"], want["Y"], layer.cfg.out_dtype)
+    # the matrix cores, which most sizes here take by themselves, and the vector kernel in two launches, which takes the
+    # launch shape that `tuning` asks for (launches = 1 is the vector kernel already)
+    for form in ({"mfma_min_batch": 33}, {}) if (tuning or {}).get("launches") != 1 else ({},):
+        rs.rsparse_set_tuning(layer, **dict(tuning or {}, **form))
+        got = gu.run_linear(layer, X16)
+        gu.check_lists(got, want)
+        gu.check_outputs(got["Y"], want["Y"], layer.cfg.out_dtype)
     layer.destroy()
     return got, want
 
@@ -71,8 +73,9 @@ def test_q4_ragged_batch1(ragged_q4, dt, out):
 @pytest.mark.parametrize("B", [2, 3, 4, 5, 8, 9, 16, 17, 32])
 @pytest.mark.parametrize("mask_mode", [0, 1])
 def test_q4_batches(ragged_q4, B, mask_mode):
-    """Up to 4 tokens share one pass over the codes; larger batches run as batch tiles of 4.  Both launch
-    forms (the one-launch form covers up to 16 tokens and falls back to two launches beyond)."""
+    """The matrix cores up to 32 tokens; on the vector kernel up to 4 tokens share one pass over the codes and larger batches
+    run as batch tiles of 4, in both launch forms (the one-launch form covers up to 16 tokens and falls back to two launches
+    beyond)."""
     q = ragged_q4[synth.BF16]
     X16, src = gu.tokens_for(q.L, B, linear=B)
     tau = gu.calibrated_tau(q.L, src, 0.5)
@@ -100,7 +103,7 @@ def test_q4_launch_shapes(ragged_q4, tuning):
     q = ragged_q4[synth.BF16]
     X16, src = gu.tokens_for(q.L, 3, linear=7)
     tau = gu.calibrated_tau(q.L, src, 0.5)
-    _parity(q, X16, tau, out_dtype=rs.F32, tuning=tuning)                       # two launches (the default)
+    _parity(q, X16, tau, out_dtype=rs.F32, tuning=tuning)                       # two launches (and the matrix cores)
     _parity(q, X16, tau, out_dtype=rs.F32, tuning=dict(tuning, launches=1))     # the whole layer in one launch
 
 
@@ -133,16 +136,17 @@ def test_q4_extreme_codes_and_zero_points():
     _parity(q, X16, gu.calibrated_tau(L, src, 0.5), out_dtype=rs.F32)
 
 
-@pytest.mark.parametrize("launches", [1, 2])
+@pytest.mark.parametrize("launches", [1, 2, "vector"])
 @pytest.mark.parametrize("B", [1, 4])
 def test_q4_both_launch_forms_on_a_reused_handle(ragged_q4, launches, B):
-    """Back-to-back calls with different kept sets on one handle, in either form: the one-launch form's arrival
-    counters, published intermediates and accumulators must be back in their idle state after every call."""
+    """Back-to-back calls with different kept sets on one handle, in either form of the vector kernel and on the matrix cores
+    (launches = 2): the one-launch form's arrival counters, published intermediates and accumulators must be back in their
+    idle state after every call."""
     q = ragged_q4[synth.F16]
     X16, src = gu.tokens_for(q.L, B, linear=60 + B)
     tau = gu.calibrated_tau(q.L, src, 0.5)
     layer = q.prepare(tau, max_batch=B, out_dtype=rs.F32)
-    rs.rsparse_set_tuning(layer, launches=launches)
+    rs.rsparse_set_tuning(layer, **(dict(mfma_min_batch=33) if launches == "vector" else dict(launches=launches)))
     for t in (tau, -INF, gu.calibrated_tau(q.L, src, 0.8), INF, tau):
         rs.rsparse_set_tau(layer, t)
         got = gu.run_linear(layer, X16)
@@ -188,6 +192,9 @@ def test_q4_dense_baseline_and_reuse(ragged_q4):
         gu.check_lists(got, want)
         gu.check_outputs(got["Y"], want["Y"], rs.F32)
         gu.check_outputs(gu.run_dense(layer, X16[:B]), q.dense(X16[:B]), rs.F32)
+        rs.rsparse_set_tuning(layer, dense_kernel=1)               # the channel-major vector kernel with every channel kept
+        gu.check_outputs(gu.run_dense(layer, X16[:B]), q.dense(X16[:B]), rs.F32)
+        rs.rsparse_set_tuning(layer)
     rs.rsparse_set_tau(layer, 0.0)
     gu.check_outputs(gu.run_linear(layer, X16[:2], lists=False)["Y"], q.oracle(X16[:2], 0.0)["Y"], rs.F32)
     assert rs.rsparse_required_bytes(layer, 1, q.L.d_in) > rs.rsparse_dense_bytes(layer, 1)
@@ -268,8 +275,8 @@ def test_q4_config1_shapes_as_benchmarked():
         want = q.oracle(X16, tau)
         Xd = gu.to_dev16(X16)
         Y = gu._alloc_out(layer, 1)
-        for launches in (1, 2):
-            rs.rsparse_set_tuning(layer, launches=launches)
+        for form in (dict(launches=1), dict(launches=2), dict(mfma_min_batch=33)):
+            rs.rsparse_set_tuning(layer, **form)
             got = gu.run_linear(layer, X16)
             gu.check_lists(got, want)
             gu.check_outputs(got["Y"], want["Y"], dt)
@@ -364,7 +371,7 @@ def test_q4_dense_rowdot_extreme_codes_group_sizes_and_benchmark_shape():
     layer.destroy()
 
 
-@pytest.mark.parametrize("launches", [1, 2])
+@pytest.mark.parametrize("launches", [1, 2, "vector"])
 def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, launches):
     """NaN is never kept and reaches every output through the low-rank part; -0 is 0; a kept +-Inf channel makes that
     token's outputs non-finite (NaN here, where the definition W~ x gives +-Inf or NaN output by output -- the
@@ -381,7 +388,7 @@ def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, launches):
     x[3, 11] = -np.inf
     X16 = synth.encode16(x, dt)
     layer = q.prepare(tau, max_batch=4, out_dtype=rs.F32)
-    rs.rsparse_set_tuning(layer, launches=launches)
+    rs.rsparse_set_tuning(layer, **(dict(mfma_min_batch=33) if launches == "vector" else dict(launches=launches)))
     got = gu.run_linear(layer, X16)
     want = q.oracle(X16, tau)
     gu.check_lists(got, want)
