@@ -440,10 +440,10 @@ def measure_workload(label, cfg_no, args, mods, timers, want_cpu):
     lay = min(res, key=lambda k: res[k]["ms_per_step"])
     ms_step = res[lay]["ms_per_step"]
     us_linear = ms_step * 1000.0 / n_lin
-    # ---- dense GEMV baselines: every dense kernel of the library, same grouping; the best is the baseline
+    # ---- dense GEMV baselines: every dense kernel of the library, same grouping, and its own choice; the best is the baseline
     dense_us = {}
-    for key, ring, kw in (("rowdot", col, dict(dense_kernel=2)), ("axpy", col, dict(dense_kernel=1)),
-                          ("strip", strip, dict(dense_kernel=1))):
+    for key, ring, kw in (("rowdot", col, dict(dense_kernel=2)), ("matrix_cores", col, dict(mfma_min_batch=1)),
+                          ("axpy", col, dict(dense_kernel=1)), ("strip", strip, dict(dense_kernel=1)), ("auto", col, dict())):
         ring.set_all(**kw)
         dense_us[key] = best(ring.pass_fn(dense=True), blocks)[0] * 1000.0 / n_lin
         ring.set_all()
