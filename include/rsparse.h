@@ -127,9 +127,10 @@ typedef struct {
                                 weights, on the vector ALU) */
     int32_t mfma_rows;       /* 0, 64, 128 or 256; without effect (rows per workgroup of earlier matrix-core kernels: now 16, and
                                 32 above 16 tokens) */
-    int32_t launches;        /* rsparse_linear: 0 default
-                                (one launch; two on 4-bit weights), 1 one launch, 2 two launches (stage 2 and the
-                                rounding in a second kernel).  stages != 0 implies two launches */
+    int32_t launches;        /* rsparse_linear: 0 default (one launch; two on 4-bit weights, and from 5 tokens on on column-major
+                                layers without dense_rowmajor), 1 one launch: keeps 4-bit and such column-major layers off the
+                                matrix cores, which need two (vector kernels, at 5 tokens 125 against 76 us for an MLP of 4096 /
+                                11008), 2 two launches (stage 2 and the rounding in a second kernel).  stages != 0 implies two */
     int32_t lowrank_wgs;     /* stage-1 workgroups of the channel-major form (cfg.lowrank_channel_major): 0 default (64, or 128
                                 from 16 MB of rows to read, within the resident slots the layer's other workgroups leave free;
                                 128 on skinny layers; the copy is used only where it was measured to pay), > 0: that many,
@@ -242,8 +243,8 @@ rsparse_status rsparse_linear_gated(rsparse_layer *layer, const void *G_dev, con
  * layers' outputs, each rounded once to the 16-bit type first -- i.e. what rsparse_linear on `gate` and on
  * `up` followed by rsparse_gated_input would store, without storing g and u.  gate, up: distinct
  * handles with equal d_in, d_out and dtype, out_dtype == dtype; X_dev, H_dev as in rsparse_linear.
- * Up to 8 tokens on the vector path this is ONE launch (the last workgroup of each column tile applies
- * the activation); other cases run the two layers into the handles' scratch and then one elementwise
+ * On the vector path (up to 4 tokens, up to 8 with tuning launches = 1 or mfma_min_batch = 33) this is ONE launch (the last
+ * workgroup of each column tile applies the activation); other cases run the two layers into the handles' scratch and then one elementwise
  * launch.  rsparse_last_active works on either handle afterwards.
  */
 rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const void *X_dev,

@@ -244,7 +244,10 @@ int q4_min_batch(const rsparse_config &c, bool one_layer)
 // Smallest batch that column-major layers without the operand-layout copy run on the matrix cores (measured, us for gate, up
 // and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 76 at five,
 // 234 -> 79 at sixteen, 389 -> 93 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
-// gain does not make up for the launch that the gate / up pair then needs, nor for the factors' second copy.
+// gain does not make up for the launch that the gate / up pair then needs, nor for the factors' second copy.  Small layers gain
+// more (512 x 512 at five 16.4 -> 7.4); with few channels kept the vector kernels skip more (90 % sparsity, at five: 1024 x
+// 1024 16.4 -> 8.6, gate / up pair and down at 4096 / 11008 77 -> 73, at 8192 / 28672 320 -> 281, but 8192 x 8192 35.7 -> 38.0, at
+// six 37.1 -> 38.0, at eight 42.8 -> 38.1); the share of kept channels is not known on the host.
 constexpr int kMfmaMinBatchCols = 5;
 
 int batch_tile_of(int batch) { return batch <= 1 ? 1 : batch <= 2 ? 2 : batch <= 4 ? 4 : 8; }

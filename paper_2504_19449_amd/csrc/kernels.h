@@ -9,8 +9,9 @@ namespace rsparse {
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kTile = 512;       // output columns per wave: 64 lanes x one 16-byte load (8 x 16-bit)
 constexpr int kMaxBT = 8;        // tokens held in registers per workgroup (batch tile)
-// Smallest batch that takes the matrix-core path by default (measured cross-over on MI355X: the
-// vector path wins up to 4 tokens for R-Sparse; the dense baseline is faster on MFMA from 2 tokens).
+// Smallest batch that R-Sparse on layers with the operand-layout copy takes to the matrix cores by default (measured: the
+// vector path wins up to 4 tokens: 4096 x 4096 18.8 us at four, 14.1 on the matrix cores at five, but 16.2 at two), and the
+// smallest at which a dense kernel asked for by name gives way to them (the automatic choice: rsparse_dense_ref_group).
 constexpr int kMfmaDefaultMinBatch = 5;
 constexpr int kMfmaDefaultMinBatchDense = 2;
 

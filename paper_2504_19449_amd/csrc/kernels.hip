@@ -1289,10 +1289,12 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
     const bool nt = cfg[0].nontemporal != 0;
     bool ext = false;
     for (int i = 0; i < n; ++i) ext = ext || L[i].rules || L[i].bias || L[i].keep_signed;
-    // Rows per batch: eight, four where a wave of the longest share has no more than two batches of eight (the last one
-    // nearly empty: 4096 x 4096 at one token, 9 rows a wave, 13.6 -> 12.8 us; with 35 rows and more a wave eight are as
-    // fast or faster: gate / up and down at 4096 / 11008 175.3 against 176.5 us, an 8192 / 28672 block 207.9 against 211.8),
-    // and four always at four tokens (fewer registers: gate / up and down at 4096 / 14336 167.9 -> 164.1 us).
+    // Rows per batch: eight, four where a wave of the longest share has no more than two batches of eight at half of the
+    // channels kept (the last one nearly empty: 4096 x 4096 at one token, 9 rows a wave, 13.6 -> 12.8 us, and 1.00 to 1.07 times
+    // as fast on 512 to 4096 wide layers at 30, 50 and 90 % sparsity; with 35 rows and more a wave eight are as fast or faster:
+    // gate / up and down at 4096 / 11008 175.3 against 176.5 us, an 8192 / 28672 block 207.9 against 211.8), and four always at
+    // four tokens (fewer registers: 0.99 to 1.05 times as fast on 512 to 8192 wide layers at 30, 50 and 90 % sparsity, own and
+    // union masks, gate / up and down at 4096 / 14336 167.9 -> 164.1 us; only 8192 x 8192 at 90 % is 2 % slower, 24.1 -> 24.5).
     bool few = true;
     for (int i = 0; i < n; ++i) {
         const int rows = (L[i].d_in / 2 + L[i].rank + cfg[i].splits - 1) / cfg[i].splits;     // expected
