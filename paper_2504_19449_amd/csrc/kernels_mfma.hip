@@ -167,7 +167,8 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
         const int usteps = (jb.rank + kMfmaK - 1) / kMfmaK;
         const size_t ublock = (size_t)usteps * 1024;
         const unsigned char *um = reinterpret_cast<const unsigned char *>(jb.U) + (size_t)block0 * ublock + lane * 16;
-        constexpr int US = NB * NF == 1 && !SUMS ? 4 : 2;
+        // (steps whose loads are requested together; t comes from L2 and nothing else hides its latency)
+        constexpr int US = SUMS || NB * NF == 1 ? 4 : 2;
         u32x4 ua[US][NB];
         auto request_u = [&](int s0) {
 #pragma unroll
@@ -408,14 +409,19 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     a.n = n; a.X = (const uint16_t *)X; a.batch = batch; a.d_in = L[0].d_in; a.phases = phases;
     a.wait_polls = wait_polls > 0 ? wait_polls : kWaitLimitPolls;
     a.skip_stage1 = skip_stage1;
+    // Where the W part was summed by an earlier launch t stays in 32 bits, as those layers' vector kernels keep it; beside a W part
+    // it is multiplied in two 16-bit parts (fp16: 22 bits, in fp32 beyond its range; bf16: 16).  The fp32 MFMA has a sixteenth of
+    // the rate: against parts in 16 bits 3 to 5 % of a call at 17 to 32 tokens (gate, up and down at 4096 / 11008, rank 512, fp16,
+    // column-major 90.6 -> 94.8 us, 4-bit 72.0 -> 75.5) and at rank 1024 (8192 x 8192 at five tokens 35.6 -> 36.4), nothing else;
+    // three exact 16-bit parts measured 94.4 to 98.4 and 75.7.
+    const bool sums = M[0].W == nullptr;
     // Units of one block for up to 16 tokens, of two for more (a unit reads all tokens, from L2, beside its rows: at 32
     // tokens and one block twice the bytes of the rows; measured at 8192 x 8192, 32 tokens: dense 33.7 us with one block,
     // 27.0 with two; at 8 tokens 23.2 and 22.9, at 4096 -> 14336 with 16 tokens 70.9 and 78.1).  Four waves a unit: with eight
-    // the same bytes are in flight in half the workgroups (8192 x 8192, 8 tokens: 24.7 against 25.8 us).
-    const int nb = nf, nw = 4;
-    // Where the W part was summed by an earlier launch t stays in 32 bits, as those layers' vector kernels keep it; beside a W part
-    // it is multiplied in two 16-bit parts (fp16: 22 bits, in fp32 beyond its range; bf16: 16)
-    const bool sums = M[0].W == nullptr;
+    // the same bytes are in flight in half the workgroups (8192 x 8192, 8 tokens: 24.7 against 25.8 us).  Without rows of W a unit
+    // is one block at any batch (column-major 2048 x 2048, rank 256, 32 tokens: 15.5 us with two, 14.5 with one; gate, up and
+    // down at 2048 / 5632, 24 tokens 47.4 and 45.4; alike at 4096 and 8192 channels).
+    const int nb = sums ? 1 : nf, nw = 4;
     int w_total = 0, t_blocks = 0;
     for (int i = 0; i < n; ++i) {
         MfmaJob &jb = a.job[i];
@@ -448,9 +454,9 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
     const size_t lds = (size_t)nw * std::max(nf * 16 * (batch_k * 2 + 16), nb * nf * 1024);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((phases & 1 ? t_total : 0) + (phases & 2 ? w_total : 0)), block(64 * nw);
-#define RS_M(DT, NV, SV) hipLaunchKernelGGL((k_mfma_rows<DT, NV, NV, SV>), grid, block, lds, stream, a)
-#define RS_MS(DT) do { if (nf == 1) { if (sums) RS_M(DT, 1, true); else RS_M(DT, 1, false); }    \
-                       else { if (sums) RS_M(DT, 2, true); else RS_M(DT, 2, false); } } while (0)
+#define RS_M(DT, NB, NF, SV) hipLaunchKernelGGL((k_mfma_rows<DT, NB, NF, SV>), grid, block, lds, stream, a)
+#define RS_MS(DT) do { if (nf == 1) { if (sums) RS_M(DT, 1, 1, true); else RS_M(DT, 1, 1, false); }    \
+                       else { if (sums) RS_M(DT, 1, 2, true); else RS_M(DT, 2, 2, false); } } while (0)
     if (L[0].dtype == F16) RS_MS(F16); else RS_MS(BF16);
 #undef RS_MS
 #undef RS_M
