@@ -120,13 +120,12 @@ __device__ __forceinline__ void mask_step(u32x4 (&b)[NF], const KeepPattern &kp,
 template <int NB, int NF> struct StepsOf { static constexpr int value = NB * NF == 1 ? 4 : 2; };
 
 // Bytes of the 16-bit parts of t in its buffer; t in fp32 follows and takes as many.
-inline size_t t32_offset(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 2 * 1024; }
-inline float *t32_of(const MatrixView &m, int rank) { return m.t ? reinterpret_cast<float *>((unsigned char *)m.t + t32_offset(rank)) : nullptr; }
+__host__ __device__ inline size_t t32_offset(int rank) { return (size_t)((rank + kMfmaK - 1) / kMfmaK) * 2 * 2 * 1024; }
 
 struct MfmaJob {
     const uint16_t *W, *SVt, *U; // operand layout (MatrixView)
-    unsigned char *t;            // t in two 16-bit parts: [step of 32 rank indices][token tile][part][64 lanes][16 bytes]
-    float *t32;                  // t as it is: [step of 32 rank indices][token tile][64 lanes][8]
+    unsigned char *t;            // t in two 16-bit parts: [step of 32 rank indices][token tile][part][64 lanes][16 bytes], and
+                                 // from t32_offset(rank) on as it is: [step of 32 rank indices][token tile][64 lanes][8] floats
     float *t_acc;                // [block of 16 rank indices][token tile][4][64] fp32 sums of t's K slices, zero between calls
     int *t_flags;                // a flag per block of t, zero between calls; then an arrival counter per block
     void *Y;
@@ -139,6 +138,7 @@ struct MfmaJob {
     int out_dtype, mask_mode;
     KeepPattern kp;
     int t_blocks, w_units;       // blocks of S_r V_r^T (0: no low-rank part), units of W
+    __device__ float *t32() const { return reinterpret_cast<float *>(t + t32_offset(rank)); }
 };
 // One batch of a wave: S steps of NB weight tiles (1 KiB each) and the same 32 * S channels of all tokens, 4 * S lanes to
 // a token.
@@ -308,7 +308,7 @@ __device__ __forceinline__ void t_unit(const MfmaJob &jb, const uint16_t *X, int
                 const int r = row % kMfmaK, at = r / 8 * 16 + (lane & 15);
                 const f32x4 v4 = row < jb.rank ? s[f] : f32x4{0.f, 0.f, 0.f, 0.f};
                 if constexpr (!PARTS || DT == F16) {
-                    unsigned long long *p = reinterpret_cast<unsigned long long *>(jb.t32 + ((size_t)(row / kMfmaK * NF + f) * 64 + at) * 8 + r % 8);
+                    unsigned long long *p = reinterpret_cast<unsigned long long *>(jb.t32() + ((size_t)(row / kMfmaK * NF + f) * 64 + at) * 8 + r % 8);
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
                         __hip_atomic_store(p + h, (unsigned long long)as_u(v4[2 * h]) | ((unsigned long long)as_u(v4[2 * h + 1]) << 32), __ATOMIC_RELAXED,

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
             __atomic_signal_fence(__ATOMIC_ACQUIRE);           // no load of t moves up here
         }
         auto t_as_it_is = [&](int s, int f, f32x4 (&tf)[2]) {
-            const float *p = jb.t32 + ((size_t)(s * NF + f) * 64 + lane) * 8;
+            const float *p = jb.t32() + ((size_t)(s * NF + f) * 64 + lane) * 8;
             tf[0] = *reinterpret_cast<const f32x4 *>(p);
             tf[1] = *reinterpret_cast<const f32x4 *>(p + 4);
         };
@@ -428,7 +428,7 @@ hipError_t launch_mfma(const LayerView *L, const MatrixView *M, int n, const voi
         const LayerView &v = L[i];
         const MatrixView &m = M[i];
         if (v.d_in != a.d_in || v.dtype != L[0].dtype || (sums ? m.W || !m.yc : !m.W) || !Y[i]) return hipErrorInvalidValue;
-        jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.t32 = t32_of(m, v.rank); jb.Y = Y[i]; jb.bias = v.bias;
+        jb.W = m.W; jb.SVt = m.SVt; jb.U = m.U; jb.t = (unsigned char *)m.t; jb.Y = Y[i]; jb.bias = v.bias;
         jb.yc = m.yc; jb.yc_rows = m.yc_rows;
         jb.t_acc = m.t_acc; jb.t_flags = m.t_flags;
         jb.chan_bits = dense ? nullptr : chan_bits[i];

@@ -179,8 +179,8 @@ hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, cons
         j.yc = M[i].yc; j.yc_rows = M[i].yc_rows; j.d_out = L[i].d_out; j.rank = dense ? 0 : L[i].rank;
         j.mask_mode = dense ? kMaskNone : (L[i].batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (L[i].keep_signed ? kMaskSigned : 0);
         j.kp = KeepPattern{(uint32_t)(uint16_t)M[i].keep_min * 0x10001u, (L[i].dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
-        j.SVt = M[i].SVt; j.t32 = t32_of(M[i], L[i].rank); j.t_acc = M[i].t_acc; j.t_flags = M[i].t_flags;
-        if (j.rank > 0 && (!j.SVt || !j.t32 || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
+        j.SVt = M[i].SVt; j.t = (unsigned char *)M[i].t; j.t_acc = M[i].t_acc; j.t_flags = M[i].t_flags;
+        if (j.rank > 0 && (!j.SVt || !j.t || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
         j.t_blocks = (j.rank + 31) / 32 * 2;
         t_blocks += j.t_blocks;
     }

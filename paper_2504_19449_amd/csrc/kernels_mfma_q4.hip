@@ -259,8 +259,8 @@ hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const 
         j.yc = m.yc; j.yc_rows = m.yc_rows; j.rank = dense ? 0 : v.rank;
         j.mask_mode = dense ? kMaskNone : (v.batch_mask_mode == 1 ? kMaskUnion : kMaskOwn) | (v.keep_signed ? kMaskSigned : 0);
         j.kp = KeepPattern{(uint32_t)(uint16_t)m.keep_min * 0x10001u, (v.dtype == F16 ? 0x7c00u : 0x7f80u) * 0x10001u};
-        j.SVt = m.SVt; j.t32 = t32_of(m, v.rank); j.t_acc = m.t_acc; j.t_flags = m.t_flags;
-        if (j.rank > 0 && (!j.SVt || !j.t32 || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
+        j.SVt = m.SVt; j.t = (unsigned char *)m.t; j.t_acc = m.t_acc; j.t_flags = m.t_flags;
+        if (j.rank > 0 && (!j.SVt || !j.t || !j.t_acc || !j.t_flags)) return hipErrorInvalidValue;
         j.t_blocks = (j.rank + 31) / 32 * 2;
         t_blocks += j.t_blocks;
     }
