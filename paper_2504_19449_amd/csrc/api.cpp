@@ -230,7 +230,7 @@ struct rsparse_layer {
 namespace {
 
 // 4-bit layers run on the matrix cores from two tokens on (measured, us, vector ALU -> matrix cores, gate and up 4096 -> 11008
-// and down, rank 512: 105 -> 63 at two, 717 -> 66 at sixteen, 1340 -> 86 at 32; 2048 / 5632 at 50 to 90 % sparsity 51 to 58 -> 31
+// and down, rank 512: 105 -> 56 at two, 717 -> 59 at sixteen, 1340 -> 82 at 32; 2048 / 5632 at 50 to 90 % sparsity 51 to 58 -> 31
 // at two).  At one token the vector kernel skips the dropped channels' codes but takes two launches per layer, the matrix cores
 // stream every code in two launches per call: calls of several layers up to 2^25 weights each run on the matrix cores (vector
 // -> matrix, at 50 and at 90 % sparsity, fp16: two of 4096 -> 8192 31 -> 22 and 29 -> 22, q/k/v of 4096 42 -> 21 and 41 -> 22,
@@ -242,8 +242,8 @@ int q4_min_batch(const rsparse_config &c, bool one_layer)
     return (size_t)c.d_in * c.d_out <= ((size_t)1 << (one_layer ? 24 : 25)) ? 1 : 2;
 }
 // Smallest batch that column-major layers without the operand-layout copy run on the matrix cores (measured, us for gate, up
-// and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 76 at five,
-// 234 -> 79 at sixteen, 389 -> 93 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
+// and down at 4096 / 11008, rank 512, vector ALU -> matrix cores: 63 -> 77 at two tokens, 80 -> 76 at four, 125 -> 72 at five,
+// 234 -> 75 at sixteen, 389 -> 95 at 32; 8192 x 8192 33 -> 39 at two, 42 -> 40 at four, 61 -> 40 at five).  At four the
 // gain does not make up for the launch that the gate / up pair then needs, nor for the factors' second copy.  Small layers gain
 // more (512 x 512 at five 16.4 -> 7.4); with few channels kept the vector kernels skip more (90 % sparsity, at five: 1024 x
 // 1024 16.4 -> 8.6, gate / up pair and down at 4096 / 11008 77 -> 73, at 8192 / 28672 320 -> 281, but 8192 x 8192 35.7 -> 38.0, at

@@ -8,8 +8,8 @@
 // wave's tile is 128 outputs x 32 channels a step, 8 MFMAs per 16 tokens.  A workgroup of four waves takes a K slice of a
 // unit of 128 outputs; slices meet in fp32 atomics on yc.  The workgroups of t stand at the front of the grid; U_r t, the
 // sum and the rounding are the next launch's (k_mfma_rows without a W part).  Bound by HBM.
-// Measured (gate, up and down at 4096 / 11008, rank 512, f16, us, vector kernels in tiles of 8 tokens -> this): 125 -> 76 at
-// 5 tokens, 234 -> 79 at 16, 389 -> 93 at 32; of the 79, 66 are the two launches of this kernel (270 MB at 7 TB/s: 39).
+// Measured (gate, up and down at 4096 / 11008, rank 512, f16, us, vector kernels in tiles of 8 tokens -> this): 125 -> 72 at
+// 5 tokens, 234 -> 75 at 16, 389 -> 95 at 32; of the 75, 59 are the two launches of this kernel (270 MB at 7 TB/s: 39).
 #include "device_mfma.h"
 
 #include <algorithm>

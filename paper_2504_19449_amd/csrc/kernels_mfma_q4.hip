@@ -15,8 +15,8 @@
 // (k_mfma_rows without a W part).
 // At full streams it would be bound by the vector ALU (about 2.5 instructions per code in bf16) and HBM in equal parts; at
 // decode sizes a wave has 3 to 10 steps and latency counts: 9 us at 4096 x 4096, 14 at 4096 x 11008 (4 us of HBM time).
-// Measured (gate, up and down at 4096 / 11008, rank 512, bf16, us, vector kernels -> this): 106 -> 66 at two tokens,
-// 717 -> 68 at sixteen, 1342 -> 96 at 32.
+// Measured (gate, up and down at 4096 / 11008, rank 512, bf16, us, vector kernels -> this): 106 -> 56 at two tokens,
+// 717 -> 59 at sixteen, 1342 -> 82 at 32.
 #include "device_mfma.h"
 
 #include <algorithm>
