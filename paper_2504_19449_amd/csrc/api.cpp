@@ -615,7 +615,7 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->chan_bits, d_in * 4));
         RS_HIP(hipMalloc((void **)&L->rules, (size_t)cfg->max_batch * sizeof(KeepRule)));
         RS_HIP(hipMemset(L->rules, 0, (size_t)cfg->max_batch * sizeof(KeepRule)));
-        const size_t flags_at = (sync_words(std::max(L->tiles, L->strips)) + 31) / 32 * 32;
+        const size_t flags_at = sync_words(std::max(L->tiles, L->strips), L->nz_max);
         L->sync_n = flags_at + (L->t16 ? t_flag_words((int)r) : 0);   // (matrix-core path)
         RS_HIP(hipMalloc((void **)&L->sync, L->sync_n * 4));
         RS_HIP(hipMemset(L->sync, 0, L->sync_n * 4));

@@ -287,7 +287,7 @@ __device__ __forceinline__ void t_unit(const MfmaJob &jb, const uint16_t *X, int
                 for (int j = 0; j < 4; ++j)
                     __hip_atomic_fetch_add(ta + f * 256 + j * 64, s[f][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wait_own_writes();
-            int *ctr = jb.t_flags + t_flag_pitch(jb.rank) + unit;
+            int *ctr = jb.t_flags + t_arrival(jb.rank, unit);
             int arrived = 0;
             if (lane == 0) arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             mine = uniform(arrived) == t_slices - 1;

@@ -314,7 +314,7 @@ __device__ __forceinline__ void lowrank_gather(const GatherArgs &a, unsigned cha
     wait_own_writes();
     __syncthreads();
     if (tid == 0) {
-        int *ctr = L.sync + kSyncStage1 + z;
+        int *ctr = L.sync + kSyncStage1 + z * kSyncLine;
         const int arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_wtot[nw] = arrived == a.lr_wgs - 1;
         if (arrived == a.lr_wgs - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -793,7 +793,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
     int *const sync = pair ? ga.job[0].L.sync : L.sync;    // owner of the counters: the gate layer
     float *const yacc_g = pair ? ga.job[0].L.yacc : L.yacc;
     const int arrivals = pair ? ga.job[0].splits + ga.job[1].splits : a.splits;
-    int *tile_ctr = sync + kSyncTile + z * a.tiles + tile;
+    int *tile_ctr = sync + sync_tile(a.tiles, z, tile);
     if (tid == 0) {
         const int arrived = __hip_atomic_fetch_add(tile_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int last_of_layer = 0;

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(512, NF == 1 ? 4 : 3) void k_mfma_rows(const MfmaAr
     // together, do not queue up on one address (the answer is looked at after the stores)
     const bool counted = hand_off && tid == 0;
     const int sub = unit % kTReadSubs;
-    int *const t_read = jb.t_flags + 2 * t_flag_pitch(jb.rank);
+    int *const t_read = jb.t_flags + t_read_at(jb.rank);
     int arrived = -1;
     if (counted) arrived = __hip_atomic_fetch_add(t_read + sub * 32, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int item = tid; item < kTiles * 64; item += nthr) {

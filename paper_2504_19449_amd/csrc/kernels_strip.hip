@@ -557,7 +557,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);               // my own adds have been performed
     __syncthreads();
-    int *tile_ctr = L.sync + kSyncTile + z * tiles + tile;
+    int *tile_ctr = L.sync + sync_tile(tiles, z, tile);
     if (tid == 0) {
         const int arrived = __hip_atomic_fetch_add(tile_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (arrived == n_splits - 1) __hip_atomic_store(tile_ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

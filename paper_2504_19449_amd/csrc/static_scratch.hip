@@ -24,7 +24,9 @@ constexpr size_t kOffSeg = kOffBits + up((size_t)kStaticMaxDim * 4);
 constexpr size_t kOffCount = kOffSeg + up((size_t)kStaticMaxDim / 8 * 4);
 constexpr size_t kOffRules = kOffCount + up(16);
 constexpr size_t kOffSync = kOffRules + up((size_t)kStaticMaxBatch * sizeof(KeepRule));
-constexpr size_t kSyncWords = kSyncTile + (size_t)kSyncMaxZ * (kStaticMaxDim / 32);     // strips of 32 columns at most
+// one batch tile, strips of 32 columns at most
+constexpr size_t kSyncWords = kSyncTile + (size_t)(kStaticMaxDim / 32) * kSyncLine;
+static_assert(kStaticMaxBatch <= kMaxBT, "one batch tile");
 constexpr size_t kStaticBytes = 2u << 20;
 static_assert(kOffSync + up(kSyncWords * 4) <= kStaticBytes, "the carve-up must fit the array");
 
@@ -92,7 +94,7 @@ hipError_t static_scratch_for_call(int device, int d_out, int rank, int batch, h
     sp.t_slots = kStaticMaxBatch;
     sp.n_t = (size_t)kStaticMaxBatch * (size_t)(rank > 0 ? rank : 1);
     sp.n_y = (size_t)batch * d_out;
-    sp.sync_n = kSyncWords;
+    sp.sync_n = sync_words((d_out + 31) / 32, 1);
     const size_t most = sp.n_y > sp.sync_n ? sp.n_y : sp.sync_n;
     unsigned blocks = (unsigned)((most + 255) / 256);
     if (blocks > 1024) blocks = 1024;
