@@ -153,6 +153,7 @@ struct rsparse_layer {
     unsigned long long *t_tag = nullptr;   // [t_slots][rank] {generation, t} of the strip kernel
     int t_slots = 0;
     int32_t *act_seg = nullptr;            // [nz_max][d_in / 8] kept channels per channel range (strip kernel)
+    bool last_direct = false;              // the last call went through the one-launch column kernel (16-bit weights)
     bool last_strip = false;               // the last call went through the strip kernel ...
     int last_ranges = 0;                   // ... with this many channel ranges (splits x waves)
     float *t = nullptr, *yacc = nullptr;
@@ -277,18 +278,58 @@ rsparse_status check_config(const rsparse_config *c)
     return RSPARSE_OK;
 }
 
-// Launch shape: column tiles x channel splits ~ a few workgroups per compute unit, each with
-// enough rows to amortise its scan, and the staged share small enough for 64 KiB of LDS.
-// Stage-1 workgroups get about as many bytes of S_r V_r^T as a gather workgroup gets of W.
-Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, int group, int waves_of_group = 0,
-                      bool fused = false, size_t launch_weights = 0)
+// Expected rows of W that a call streams.
+int expected_rows(const rsparse_layer *L) { return std::max(8, L->cfg.d_in / 2); }
+
+// The layers of one launch together.
+struct LaunchTotals {
+    size_t weights = 0;
+    int tiles = 0, strips = 0, n = 1;
+    bool svc = false;                          // stage 1 reads the channel-major copies of S_r V_r^T by default
+    int svc_wgs = 0;                           // ... with this many workgroups
+};
+
+// Stage-1 workgroups over the channel-major copy (each on fixed channels): one per 256 KiB of rows it is expected to read, 16 to
+// 64; 64 on skinny layers (d_out of the order of the rank: the k / v projections of grouped-query attention), where stage 1 is
+// half or more of what the gather workgroups read.
+int svc_workgroups(const rsparse_layer *L)
+{
+    const double rows = expected_rows(L), s1_bytes = 2.0 * L->cfg.rank * (L->cfg.d_in - rows), gather_bytes = 2.0 * (rows + L->cfg.rank) * L->cfg.d_out;
+    return 2.0 * s1_bytes >= gather_bytes ? 64 : std::max(16, std::min(64, (int)(s1_bytes / (256 * 1024))));
+}
+
+LaunchTotals totals_of(rsparse_layer *const *layers, int n, int batch)
+{
+    LaunchTotals t;
+    t.n = n;
+    bool unions = true, copies = true;
+    for (int i = 0; i < n; ++i) {
+        const rsparse_config &c = layers[i]->cfg;
+        t.weights += (size_t)c.d_in * c.d_out;
+        t.tiles += layers[i]->tiles;
+        t.strips += layers[i]->strips;
+        unions = unions && (c.batch_mask_mode == 1 || (c.batch_mask_mode == 2 && batch >= 4));
+        copies = copies && (layers[i]->SVc || c.rank == 0);
+        if (layers[i]->SVc) t.svc_wgs += svc_workgroups(layers[i]);
+    }
+    // Where reading only the dropped channels' rows pays: launches of several layers of 2^26 weights or more and of one of 2^27
+    // (t is published three dependent round trips later than by the row dots, which a shorter launch does not hide: 8192 x 8192,
+    // rank 1024 24.3 us with it, 22.2 with the row dots), and at four tokens under the union mask (hardly any channel is
+    // dropped then, so stage 1 reads almost nothing).
+    const int bt = batch_tile_of(batch);
+    t.svc = copies && t.svc_wgs > 0 && (t.weights >= ((size_t)1 << (n > 1 ? 26 : 27)) || (bt == 4 && unions));
+    return t;
+}
+
+// Launch shape: column tiles x channel splits, the same number of splits for every layer of the launch (they share d_in, so that
+// a workgroup of each has as many rows), each with enough rows to amortise its start, and the staged share small enough
+// for 64 KiB of LDS.  fused: the one-launch kernel.
+Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const LaunchTotals &all, int waves_of_group = 0, bool fused = false)
 {
     Launch c{};
     const rsparse_tuning &t = L->tuning;
     const int bt = batch_tile_of(batch);
-    // 8 waves per workgroup and ~1.5 workgroups per compute unit measured best on MI355X: enough
-    // loads in flight, while each output column only receives `splits` atomic adds (same-address
-    // device-scope atomics serialise at ~0.1 us each, which sets the kernel's tail).
+    // 8 waves per workgroup: enough loads in flight, while each output column only receives `splits` atomic adds
     c.waves = (t.waves == 1 || t.waves == 2 || t.waves == 4 || t.waves == 8) ? t.waves : (bt >= 8 ? 4 : 8);
     if (waves_of_group > 0) c.waves = waves_of_group;   // one block size per launch: the first layer's
     if (bt >= 8 && c.waves > 4) c.waves = 4;      // the 8-token kernels are built for at most 256 lanes
@@ -296,70 +337,62 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, int group, 
     c.wait_polls = t.debug_wait_polls;
     c.skip_stage1 = t.debug_skip_stage1 ? 1 : 0;
     c.tile_map = t.tile_map == 0 ? 1 : t.tile_map;
-    const int rows = dense ? L->cfg.d_in : std::max(8, L->cfg.d_in / 2);     // expected rows to stream
+    const int rows = dense ? L->cfg.d_in : expected_rows(L);
+    const int tiles = all.tiles > 0 ? all.tiles : L->tiles, slots = 2 * L->cus;       // two 8-wave workgroups per compute unit
+    const bool svc = fused && !dense && bt <= 4 && L->SVc && L->cfg.rank > 0 && (t.lowrank_wgs > 0 || (t.lowrank_wgs == 0 && all.svc));
     int splits = t.splits;
     if (splits <= 0) {
-        // one resident round of workgroups for the whole launch (a group of layers shares it):
-        // ~1.5 per compute unit, for the 8-wave kernels and for the 4-wave 8-token kernels alike
-        // (those hold two workgroups per compute unit at their register count)
-        const int target_wgs = std::max(L->tiles, (3 * L->cus) / 2 / std::max(1, group));
-        splits = (target_wgs + L->tiles - 1) / L->tiles;
-        const int max_by_rows = std::max(1, rows / (c.waves * 4));          // >= 4 rows per wave
-        splits = std::max(1, std::min(splits, max_by_rows));
+        // one resident round of workgroups for the whole launch: ~1.5 per compute unit, for the 8-wave kernels and for the 4-wave
+        // 8-token kernels alike (those hold two workgroups per compute unit at their register count)
+        splits = (std::max(tiles, 3 * L->cus / 2) + tiles - 1) / tiles;
         // every output receives `splits` same-address atomic adds, which serialise at the end of the
         // kernel: beyond 32 they cost more than the extra workgroups bring, as long as one workgroup
         // per compute unit remains (measured on 11008 -> 4096: 32 splits beat 48)
-        if (fused) splits = std::min(splits, std::max(32, (L->cus + L->tiles - 1) / L->tiles));
+        if (fused) splits = std::min(splits, std::max(32, (L->cus + tiles - 1) / tiles));
+        if (svc && all.svc) {
+            // How the workgroups spread over the compute units decides more than their number: one whose share of the launch is
+            // stage-1 workgroups idles once t is there.  Few of those and as many gather workgroups as there are slots
+            // left (us per pass, gather workgroups of 512: gate / up of 4096 / 11008 at one token 440: 170, 484: 166,
+            // 528: 178; at four tokens of 4096 / 14336 392: 164, 448: 153, 504: 157; 28672 -> 8192 384: 216, 448: 210, 512: 238;
+            // q/k/v of 8192 / 1024 with 42 + 128 + 128 stage-1 workgroups and as many gather workgroups for each 218, with
+            // 64 each and 16 splits 215).
+            splits = std::max(1, std::min((slots + L->cus / 32 - all.svc_wgs) / tiles, std::max(32, (L->cus + tiles - 1) / tiles)));
+        } else if (fused && bt <= 4) {
+            // Where a wave has few rows (16) anyway, one workgroup per compute unit, stage 1 included, shares the chip evenly
+            // (4096 x 4096, rank 256: 9.5 us with 24 splits and 64 stage-1 workgroups, 9.8 with 32, 9.9 with 16).
+            const int one = (L->cus - all.n * ((L->cfg.rank + 3) / 4)) / tiles;
+            if (one >= 1 && (rows + L->cfg.rank + one - 1) / one <= 16 * c.waves) splits = std::min(splits, one);
+        }
+        const int max_by_rows = std::max(1, rows / (c.waves * 4));          // >= 4 rows per wave
+        splits = std::max(1, std::min(splits, max_by_rows));
     }
     splits = std::min(splits, 4096);
-    while (gather_lds_bytes(L->cfg.d_in, splits, c.waves, bt, fused ? L->cfg.rank : 0) > 60 * 1024 && splits < 65536) splits *= 2;
+    while ((fused ? direct_lds_bytes(L->cfg.d_in, splits, c.waves, bt) : gather_lds_bytes(L->cfg.d_in, splits, c.waves, bt)) > 60 * 1024 && splits < 65536) splits *= 2;
     c.splits = splits;
     int lr = t.lowrank_rows;
     if (lr <= 0) {
-        const double wg_bytes = (double)rows / splits * kTile * 2.0;          // W bytes of one gather workgroup
+        // two launches: stage-1 workgroups get about as many bytes of S_r V_r^T as a gather workgroup gets of W
+        const double wg_bytes = (double)rows / splits * kTile * 2.0;
         lr = (int)(wg_bytes / (2.0 * L->cfg.d_in) + 0.5);
     }
     c.lowrank_rows = std::max(1, std::min(lr, 4 * c.waves));                  // at most 4 rows per wave
     // one launch: the gather workgroups end with rows that need t, so stage 1 is cut as fine as the
-    // launch allows: its workgroups get the resident slots (two per compute unit, shared by the
-    // layers of a group) that the gather workgroups leave free, with one row per wave on at least
-    // half of the waves.  A launch that needs a second round of workgroups loses more than finer
-    // stage-1 workgroups gain (measured on 4096 -> 11008 and 28672 -> 8192).
+    // launch allows: its workgroups get the resident slots (shared by the
+    // layers of a group) that the gather workgroups leave free, with four rows or more.  A launch that needs a
+    // second round of workgroups loses more than finer stage-1 workgroups gain (measured on 4096 -> 11008 and 28672 -> 8192).
     if (fused && t.lowrank_rows <= 0) {
-        const int free_slots = 2 * L->cus / std::max(1, group) - L->tiles * splits;
+        const int free_slots = (slots - tiles * splits) / all.n;
         const int need = free_slots > 0 ? (L->cfg.rank + free_slots - 1) / free_slots : 4 * c.waves;
         c.lowrank_rows = std::max(std::max(1, c.waves / 2), std::min(4 * c.waves, need));
     }
-    // one token over a channel-major copy of S_r V_r^T: stage 1 reads the dropped channels' rows only, each of its
-    // workgroups on a fixed channel range.  64 workgroups, 128 from 16 MB of expected rows (measured on 4096 x 4096
-    // up to 28672 -> 8192: fewer publish t too late for the gather workgroups' rows of U_r^T, more only add atomics) ...
-    // By default only where it was measured to pay: in launches that read 2^26 weights or more (t is published one
-    // dependent phase later than by the row dots, which a shorter launch does not hide), and at four tokens under the
-    // union mask (hardly any channel is dropped then, so stage 1 reads almost nothing).  lowrank_wgs > 0 forces it.
-    const size_t lw = launch_weights ? launch_weights : (size_t)L->cfg.d_in * L->cfg.d_out;
-    const bool union_now = L->cfg.batch_mask_mode == 1 || (L->cfg.batch_mask_mode == 2 && batch >= 4);
-    const bool pays = lw >= ((size_t)1 << 26) || (bt == 4 && union_now);
-    if (fused && !dense && bt <= 4 && L->SVc && L->cfg.rank > 0 && (t.lowrank_wgs > 0 || (t.lowrank_wgs == 0 && pays))) {
-        const double s1_bytes = 2.0 * L->cfg.rank * (L->cfg.d_in - rows);
-        // ... as many as the resident slots (two per compute unit, shared by the layers of a group) that this layer's
-        // gather workgroups leave free, between 16 and that number (measured: gate/up grouped 32 each, q/k/v grouped
-        // 42 + 64 + 64, o 64, down 128 -- a launch that needs a second round of workgroups loses more)
-        const int base = s1_bytes >= 16.0 * 1024 * 1024 ? 128 : 64;
-        const int free_slots = 2 * L->cus / std::max(1, group) - L->tiles * splits;
-        c.lowrank_wgs = t.lowrank_wgs > 0 ? t.lowrank_wgs : std::max(16, std::min(base, free_slots));
-        // skinny layers (d_out of the order of the rank: the k / v projections of grouped-query attention), where stage 1
-        // is half or more of what the gather workgroups read: 128 whatever the slots (measured in the q/k/v group of
-        // 8192 -> 8192 / 1024 / 1024, r = 1024: 30.2 us against 32.0 us)
-        const double gather_bytes = 2.0 * ((double)rows + L->cfg.rank) * L->cfg.d_out;
-        if (t.lowrank_wgs == 0 && 2.0 * s1_bytes >= gather_bytes) c.lowrank_wgs = 128;
-    }
+    if (svc) c.lowrank_wgs = t.lowrank_wgs > 0 ? t.lowrank_wgs : svc_workgroups(L);
     return c;
 }
 
-// Launch shape of the strip kernel: one workgroup per strip when the launch then still has a workgroup for at
-// least half of the compute units; layers with fewer strips split the channels over several workgroups per strip.
-Launch resolve_strip(const rsparse_layer *L, int batch, bool dense, int group, bool fused)
+// Launch shape of the strip kernel: layers with few strips split the channels over several workgroups per strip.
+Launch resolve_strip(const rsparse_layer *L, int batch, bool dense, const LaunchTotals &all, bool fused)
 {
+    const int group = all.n;
     Launch c{};
     const rsparse_tuning &t = L->tuning;
     const int bt = batch_tile_of(batch);
@@ -371,22 +404,27 @@ Launch resolve_strip(const rsparse_layer *L, int batch, bool dense, int group, b
     const int rank = dense ? 0 : L->cfg.rank;
     int splits = t.splits;
     if (splits <= 0) {
-        // measured: small layers (under 2^26 weights) run best at about one workgroup per two compute units, large
-        // ones at one per compute unit, the linears of a grouped call sharing that number
-        const bool large = (size_t)L->cfg.d_in * L->cfg.d_out >= ((size_t)1 << 26);
-        const int target = std::max(1, (large ? L->cus : L->cus / 2) / std::max(1, group));
-        splits = std::max(1, (target + L->strips / 2) / L->strips);
+        if (dense) {
+            // measured: small layers (under 2^26 weights) run best at about one workgroup per two compute units, large
+            // ones at one per compute unit, the linears of a grouped call sharing that number
+            const bool large = (size_t)L->cfg.d_in * L->cfg.d_out >= ((size_t)1 << 26);
+            const int target = std::max(1, (large ? L->cus : L->cus / 2) / std::max(1, group));
+            splits = std::max(1, (target + L->strips / 2) / L->strips);
+        } else {
+            // One number of splits for the layers of a launch, for about 160 workgroups below 2^26 weights, 320 in larger groups and
+            // one per compute unit in larger single layers (us per pass at 1 - 2 - 3 - 4 - 5 splits: q/k/v of 4096, strips of 128
+            // 136 - 116 - 126 - 120; of 256 176 - 134 - 122 - 127 - 133; of 64 124 - 126 - 145; q/k/v of 8192 82 - 67 - 66 - 68 - 65,
+            // of 8192 / 1024 118 - 115 - 99 - 95; 2048 93 - 85 - 83 - 91; 8192 x 8192 alone 40 at 4, 45 at 5).
+            const int target = all.weights < ((size_t)1 << 26) ? 5 * L->cus / 8 : group > 1 ? 5 * L->cus / 4 : L->cus;
+            splits = std::max(1, (target + all.strips / 2) / std::max(1, all.strips));
+        }
     }
     splits = std::max(1, std::min(splits, 4096));
     while (strip_list_cap(L->cfg.d_in, rank, splits, c.waves, bt, L->strip_w) <= 0 && splits < 4096) ++splits;
     c.splits = splits;
-    // stage 1: a row of S_r V_r^T is shared by enough waves that a wave's part is one batch of loads (8 KiB), as long
-    // as that leaves at most about one stage-1 workgroup per compute unit
-    const int chunk = std::min(L->cfg.d_in, (24576 / bt) & ~7);
-    int ws = 1;
-    while (ws < c.waves && chunk * 2 / ws > 8192) ws *= 2;
-    int rpw = c.waves / ws;
-    while (rpw < c.waves && (L->cfg.rank + rpw - 1) / rpw > L->cus / std::max(1, group)) rpw *= 2;
+    // stage 1: four rows of S_r V_r^T per workgroup while that is one workgroup for every second compute unit or less, else eight
+    // (8192 x 8192, rank 512: 40.5 against 45.7 us; q/k/v of 4096, rank 256: 134 against 116)
+    int rpw = all.n * ((L->cfg.rank + 3) / 4) <= L->cus / 2 ? 4 : 8;
     if (t.lowrank_rows > 0) {
         rpw = 1;
         while (rpw * 2 <= std::min(t.lowrank_rows, c.waves)) rpw *= 2;
@@ -620,10 +658,6 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->sync, L->sync_n * 4));
         RS_HIP(hipMemset(L->sync, 0, L->sync_n * 4));
         L->t_flags = L->sync + flags_at;
-        {
-            const int one = 1;                        // generation 1: no entry of t_tag (all zero) carries it
-            RS_HIP(hipMemcpy(L->sync + kSyncGen, &one, 4, hipMemcpyHostToDevice));
-        }
         L->t_slots = (int)bpad;
         RS_HIP(hipMalloc((void **)&L->t_tag, n_t * 8));
         RS_HIP(hipMemset(L->t_tag, 0, n_t * 8));
@@ -813,7 +847,7 @@ rsparse_status linear_q4_matrix_cores(rsparse_layer *const *layers, int n, const
     if (!dense)
         for (int i = 0; i < n; ++i) {
             rsparse_layer *L = layers[i];
-            L->last_stream = s; L->last_batch = batch; L->last_mfma = true; L->last_fused = true; L->last_bt = 0; L->last_strip = false;
+            L->last_stream = s; L->last_batch = batch; L->last_mfma = true; L->last_fused = true; L->last_bt = 0; L->last_strip = L->last_direct = false;
             L->last_scratch = L->own_scratch();
         }
     return RSPARSE_OK;
@@ -839,7 +873,7 @@ rsparse_status linear_q4(rsparse_layer *L, const void *X_dev, int32_t batch, voi
         L->last_stream = s; L->last_batch = batch; L->last_mfma = false; L->last_fused = fused;
         L->last_scratch = L->own_scratch();
         L->last_bt = std::min(4, batch_tile_of(batch));
-        L->last_strip = false;
+        L->last_strip = L->last_direct = false;
     }
     return RSPARSE_OK;
 }
@@ -935,12 +969,13 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     Launch lc[RSPARSE_MAX_GROUP];
     const int stages = layers[0]->tuning.stages;
     // one launch unless asked otherwise (timing a stage alone needs the two-launch form)
-    const bool fused = layers[0]->tuning.launches != 2 && stages == 0;
-    size_t launch_weights = 0;
-    for (int i = 0; i < n_layers; ++i) launch_weights += (size_t)layers[i]->cfg.d_in * layers[i]->cfg.d_out;
+    bool fused = layers[0]->tuning.launches != 2 && stages == 0;
+    // (the column kernel reaches M through a 32-bit buffer descriptor; larger layers take two launches)
+    for (int i = 0; i < n_layers; ++i) fused = fused && (!layers[i]->M || direct_supported(layers[i]->cfg.d_in, layers[i]->cfg.d_out, layers[i]->cfg.rank));
+    const LaunchTotals all = totals_of(layers, n_layers, batch);
     for (int i = 0; i < n_layers; ++i) {
         v[i] = layers[i]->view(ov, batch);
-        lc[i] = resolve_launch(layers[i], batch, false, n_layers, i ? lc[0].waves : 0, fused, launch_weights);
+        lc[i] = resolve_launch(layers[i], batch, false, all, i ? lc[0].waves : 0, fused);
         layers[i]->last_scratch = ov ? *ov : layers[i]->own_scratch();
     }
     MatrixView mv[RSPARSE_MAX_GROUP];
@@ -974,7 +1009,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     const bool strip = !mfma && !cols && layers[0]->Ms != nullptr;
     if (strip) {
         Launch sc[RSPARSE_MAX_GROUP];
-        for (int i = 0; i < n_layers; ++i) sc[i] = resolve_strip(layers[i], batch, false, n_layers, fused);
+        for (int i = 0; i < n_layers; ++i) sc[i] = resolve_strip(layers[i], batch, false, all, fused);
         if (fused) {
             RS_HIP(launch_strip(v, sc, n_layers, X_dev, batch, Y_devs, true, false, layers[0]->cus, s));
         } else {
@@ -988,6 +1023,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
             layers[i]->last_fused = true;           // rsparse_synchronize looks at the device-side error word
             layers[i]->last_bt = 0;
             layers[i]->last_strip = true;
+            layers[i]->last_direct = false;
             layers[i]->last_ranges = sc[i].splits * sc[i].waves;
         }
         return RSPARSE_OK;
@@ -1020,6 +1056,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         layers[i]->last_fused = fused;
         layers[i]->last_bt = 0;
         layers[i]->last_strip = false;
+        layers[i]->last_direct = fused && !mfma && !cols;
     }
     return RSPARSE_OK;
 }
@@ -1037,13 +1074,14 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
         return fail(RSPARSE_EINVAL, "rsparse_mlp_gate_up needs out_dtype == dtype on both layers");
     hipStream_t s = (hipStream_t)stream;
     const int stages = gate->tuning.stages;
-    const bool fused = gate->tuning.launches != 2 && stages == 0;
+    const bool fused = gate->tuning.launches != 2 && stages == 0 && direct_supported(gate->cfg.d_in, gate->cfg.d_out, gate->cfg.rank) &&
+                       direct_supported(up->cfg.d_in, up->cfg.d_out, up->cfg.rank);
     LayerView v[2];
     Launch lc[2];
+    const LaunchTotals all = totals_of(pair, 2, batch);
     for (int i = 0; i < 2; ++i) {
         v[i] = pair[i]->view(nullptr, batch);
-        lc[i] = resolve_launch(pair[i], batch, false, 2, i ? lc[0].waves : 0, fused,
-                               (size_t)pair[0]->cfg.d_in * pair[0]->cfg.d_out + (size_t)pair[1]->cfg.d_in * pair[1]->cfg.d_out);
+        lc[i] = resolve_launch(pair[i], batch, false, all, i ? lc[0].waves : 0, fused);
     }
     bool mfma = batch >= (gate->tuning.mfma_min_batch > 0 ? gate->tuning.mfma_min_batch : kMfmaDefaultMinBatch);
     for (int i = 0; i < 2; ++i) mfma = mfma && mfma_path_supported(pair[i]->matrix(v[i]), batch) && pair[i]->cfg.topk == 0;
@@ -1057,7 +1095,7 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
         RS_HIP(topk_rules_of(pair, v, 2, X_dev, batch, s));
         RS_HIP(launch_fused(v, lc, 2, X_dev, batch, outs, s, true));
         for (int i = 0; i < 2; ++i) {
-            pair[i]->last_stream = s; pair[i]->last_batch = batch; pair[i]->last_mfma = false; pair[i]->last_fused = true; pair[i]->last_bt = 0; pair[i]->last_strip = false;
+            pair[i]->last_stream = s; pair[i]->last_batch = batch; pair[i]->last_mfma = false; pair[i]->last_fused = true; pair[i]->last_bt = 0; pair[i]->last_strip = false; pair[i]->last_direct = true;
             pair[i]->last_scratch = pair[i]->own_scratch();
         }
         return RSPARSE_OK;
@@ -1123,9 +1161,10 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     LayerView v[RSPARSE_MAX_GROUP];
     Launch lc[RSPARSE_MAX_GROUP];
     bool can_rowdot = true;
+    const LaunchTotals all = totals_of(layers, n_layers, batch);
     for (int i = 0; i < n_layers; ++i) {
         v[i] = layers[i]->view(nullptr, batch, true);
-        lc[i] = resolve_launch(layers[i], batch, true, n_layers, i ? lc[0].waves : 0);
+        lc[i] = resolve_launch(layers[i], batch, true, all, i ? lc[0].waves : 0);
         can_rowdot = can_rowdot && layers[i]->Wtile != nullptr && rowdot_supported(layers[i]->cfg.d_in, batch);
     }
     // The dense product runs on the matrix cores (measured, us, vector ALU -> matrix cores: 4096 x 4096 15.0 -> 8.7 at two
@@ -1183,7 +1222,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     } else if (strip) {
         // the strip kernel with every channel kept and no low-rank part
         Launch sc[RSPARSE_MAX_GROUP];
-        for (int i = 0; i < n_layers; ++i) sc[i] = resolve_strip(layers[i], batch, true, n_layers, false);
+        for (int i = 0; i < n_layers; ++i) sc[i] = resolve_strip(layers[i], batch, true, all, false);
         RS_HIP(launch_strip(v, sc, n_layers, X_dev, batch, Y_devs, false, true, layers[0]->cus, s));
     } else {
         RS_HIP(launch_dense_axpy(v, lc, n_layers, X_dev, batch, Y_devs, s));
@@ -1272,11 +1311,9 @@ rsparse_status rsparse_synchronize(rsparse_layer *L)
         int flag = 0;
         RS_HIP(hipMemcpy(&flag, sp.sync + kSyncError, 4, hipMemcpyDeviceToHost));
         if (flag != 0) {
-            // leave the counters usable for the next call
-            int gen = 0;                              // the generation of the strip kernel's hand-off survives the reset
-            RS_HIP(hipMemcpy(&gen, sp.sync + kSyncGen, 4, hipMemcpyDeviceToHost));
+            // leave the counters and generations usable for the next call
             RS_HIP(hipMemset(sp.sync, 0, sp.sync_n * 4));
-            RS_HIP(hipMemcpy(sp.sync + kSyncGen, &gen, 4, hipMemcpyHostToDevice));
+            RS_HIP(hipMemset(sp.t_tag, 0, sp.n_t * 8));
             RS_HIP(hipMemset(sp.t_pub, 0xff, sp.n_t * 4));
             RS_HIP(hipMemset(sp.yacc, 0, sp.n_y * 4));
             return fail(RSPARSE_EHIP, "a cross-workgroup wait of the one-launch kernel ran out; the last result is invalid");
@@ -1312,6 +1349,15 @@ rsparse_status rsparse_last_active(rsparse_layer *L, int32_t token, int32_t *idx
     std::vector<int32_t> seg, seg_list;
     std::vector<uint32_t> seg_bits;
     auto fetch = [&](int z) -> rsparse_status {
+        if (L->last_direct) {
+            // the one-launch column kernel leaves, per channel, which tokens of the batch tile keep it
+            seg_bits.resize(d_in);
+            RS_HIP(hipMemcpy(seg_bits.data(), sp.act_bits + z * d_in, d_in * 4, hipMemcpyDeviceToHost));
+            list.clear(); bits.clear();
+            for (size_t c = 0; c < d_in; ++c)
+                if (seg_bits[c]) { list.push_back((int32_t)c); bits.push_back(seg_bits[c]); }
+            return RSPARSE_OK;
+        }
         if (L->last_strip) {
             // the strip kernel leaves one ascending list per channel range, at the range's first channel; the
             // ranges in order are the ascending list of the batch tile

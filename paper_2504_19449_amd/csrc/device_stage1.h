@@ -4,16 +4,24 @@
 #include "device_common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace rsparse {
 
 // Phase time stamps, only in builds with -DRSPARSE_STAMPS=1 (python -m paper_2504_19449_amd.build --stamps): every wave of
-// the strip kernel's launches writes one record of kStampWords 64-bit words -- {kind | workgroup << 8 | wave << 40,
+// the one-launch kernels writes one record of kStampWords 64-bit words -- {kind | workgroup << 8 | wave << 40,
 // stamps of the 100 MHz wall clock at its phase boundaries (words 1..14), rows streamed (word 15)} -- into a caller's buffer
 // (rsparse_debug_stamps).  Product builds compile none of it.
 constexpr int kStampWords = 16;
 #if RSPARSE_STAMPS
-extern __device__ unsigned long long *g_stamp_buf;
-extern __device__ int g_stamp_cap;
+static __device__ unsigned long long *g_stamp_buf = nullptr;      // one of each per kernel file
+static __device__ int g_stamp_cap = 0;
+static inline hipError_t set_stamps_of_this_file(void *buf, int capacity_waves)
+{
+    hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(g_stamp_buf), &buf, sizeof buf);
+    if (e != hipSuccess) return e;
+    return hipMemcpyToSymbol(HIP_SYMBOL(g_stamp_cap), &capacity_waves, sizeof capacity_waves);
+}
 #define RS_STAMP_DECL unsigned long long rs_tt[kStampWords] = {}
 #define RS_STAMP(i) rs_tt[i] = (unsigned long long)wall_clock64()
 #define RS_STAMP_SET(i, v) rs_tt[i] = (unsigned long long)(v)
@@ -178,6 +186,14 @@ __device__ __forceinline__ const T *pin(const T *p)
     return (const T *)reinterpret_cast<global_ptr>(u);
 }
 
+// A pointer the compiler has lost track of (out of inline asm) as one into global memory: global, not generic accesses.
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p)
+{
+    typedef T __attribute__((address_space(1))) *global_ptr;
+    return (T *)reinterpret_cast<global_ptr>(reinterpret_cast<uintptr_t>(p));
+}
+
 // Balanced share [lo, hi) of n items for part p of `parts`: the first n % parts shares hold one item more.
 // 32-bit arithmetic on wave-uniform values -- a 64-bit division is some 200 emulated instructions here,
 // and it sat on every workgroup's path to its first weight load.
@@ -189,47 +205,209 @@ __device__ __forceinline__ void balanced_share(int n, int parts, int p, int &lo,
     hi = lo + (int)base + (pp < rem ? 1 : 0);
 }
 
-// Tagged hand-off of t (strip kernel).  Entries are {generation, fp32 bits}; a launch's generation G is the value of
-// sync[kSyncGen] while the launch runs.  Every wave that reads G reports so with one store-and-forget atomic, after
-// its read has returned; the poller waits until all `readers` waves of the launch have reported (they all start:
-// they wait for nothing but stage 1, which waits for nothing), clears the counts and bumps the generation.  The next
-// launch therefore sees G + 1 in every wave, and entries tagged G or older never match it.  No wave can read the
-// generation after the bump, since the bump waits for its report.
-__device__ __forceinline__ void generation_was_read(int *sync, uint32_t gen, int wave_id)
+// Tagged hand-off of t inside one launch.  Entries are {tag, fp32 bits}; a launch's tag is one more than its generation, a
+// number that is kept per column tile (strip) for those who read t and per batch tile for those who write it, each in the line
+// of the arrival counter that ends its use: whoever arrives last puts the counter back and bumps the generation.  All of them
+// move once per launch and start at zero together, so they agree.  Nobody can read a generation after its bump (everybody
+// who reads it arrives afterwards), entries of earlier launches never match, and nothing has to be reset at the end of a
+// launch: a reset needs to know that every tile has read t, which is one more counter between the sums and the stores (0.6 us).
+__device__ __forceinline__ uint32_t generation(const int *line)
 {
-    // the read has returned once its value can be consumed: the empty asm consumes it, and nothing after it is
-    // issued before
-    __asm__ volatile("s_waitcnt vmcnt(0)" : "+v"(gen) : : "memory");
-    if ((threadIdx.x & 63) == 0)
-        __hip_atomic_fetch_add(sync + kSyncStarted + (wave_id & (kSyncStartedN - 1)), 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+    return (uint32_t)__hip_atomic_load(line + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void end_of_line(int *line)
+{
+    __hip_atomic_store(line, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(line + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_t(unsigned long long *entry, uint32_t gen, float v)
+{
+    __hip_atomic_store(entry, ((unsigned long long)(gen + 1u) << 32) | as_u(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Token slots that a call does not use keep the tags of earlier launches.  Every 2^30 launches they are written too, so that
+// none is ever old enough to match again: slots bt .. of batch tile 0 (the others are always full) of rank index `row`.
+__device__ __forceinline__ void refresh_unused(unsigned long long *t_tag, int rank, int t_slots, int bt, int z, uint32_t gen, int row)
+{
+    if (z == 0 && (gen & 0x3fffffffu) == 0u)
+        for (int sl = bt; sl < min(kMaxBT, t_slots); ++sl) publish_t(t_tag + (size_t)sl * rank + row, gen, 0.f);
 }
 
-__device__ __forceinline__ void close_generation(int *sync, int readers)
+// Sum over the 64 lanes, in lane 63: rotations inside the rows of 16 lanes, then the row totals broadcast down.
+__device__ __forceinline__ float wave_sum63(float v)
 {
-    const int lane = threadIdx.x & 63;
-    const long long t0 = wall_clock64();
-    bool ok = false;
-    while (!ok) {
-        int v = 0;
+    constexpr int kRowRor = 0x120, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+    auto dpp = [](float x, auto ctrl, auto rows) { return as_f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)as_u(x), decltype(ctrl)::value, decltype(rows)::value, 0xf, false)); };
+    v += dpp(v, std::integral_constant<int, kRowRor + 8>{}, std::integral_constant<int, 0xf>{});
+    v += dpp(v, std::integral_constant<int, kRowRor + 4>{}, std::integral_constant<int, 0xf>{});
+    v += dpp(v, std::integral_constant<int, kRowRor + 2>{}, std::integral_constant<int, 0xf>{});
+    v += dpp(v, std::integral_constant<int, kRowRor + 1>{}, std::integral_constant<int, 0xf>{});
+    v += dpp(v, std::integral_constant<int, kRowBcast15>{}, std::integral_constant<int, 0xa>{});
+    v += dpp(v, std::integral_constant<int, kRowBcast31>{}, std::integral_constant<int, 0xc>{});
+    return v;
+}
+
+// Raw buffer descriptors: an access past the end reads zero without touching memory, so that loads can be unconditional.
+constexpr int kBufferFlags = 0x00020000;               // raw buffer, 32-bit elements
+constexpr uint32_t kOutside = 0x80000000u;             // past any descriptor used here
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const uint16_t *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p), 0, (int)bytes, kBufferFlags);
+}
+template <bool NT>
+__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t off)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, NT ? 2 : 0));
+}
+
+// ---------------------------------------------------------------------------------------------
+// Stage 1 of the low-rank part inside a one-launch kernel: t_i = sum_c (S_r V_r^T)[i, c] (x - sigma_t(x))_c.
+// Everything else in the launch ends with rows that need t, so this is a chain of latencies first: a workgroup takes `rows`
+// rows of S_r V_r^T, its waves share the channels (wave w every nw-th run of 512), and a lane requests its 8 channels of the
+// token(s) and of kS1Rows rows at once -- the rows do not depend on the token --, masks the token in registers (once for all
+// rows) and multiplies; the waves meet in LDS and one lane per row and token publishes.  No staging of the token and no barrier
+// before the last product.  (A wave per row over a token staged in LDS published t 1.5 us later at 4096 channels.)
+// ---------------------------------------------------------------------------------------------
+struct Stage1Args {
+    const uint16_t *X, *SVt;
+    int *sync;
+    unsigned long long *t_tag;
+    int d_in, rank, batch, rows;       // rows: of S_r V_r^T per workgroup
+    int wgs, t_slots, union_all, skip; // workgroups; token slots of t_tag; test hook: publish nothing
+    float tau_ge;
+    int waves;
+};
+template <int BT> struct S1Shape {
+    static constexpr int kRows = BT >= 8 ? 1 : BT >= 4 ? 2 : 4;      // rows that share a token in registers
+};
+
+template <int DT, int BT, bool EXT>
+__device__ __forceinline__ void stage1_rows(const Stage1Args &args, const LayerView &L, unsigned char *smem, int wg, int z)
+{
+    constexpr int RW = S1Shape<BT>::kRows;
+    Stage1Args s = args;
+    __asm__ volatile("" : "+s"(s.X), "+s"(s.SVt), "+s"(s.sync), "+s"(s.t_tag), "+s"(s.d_in), "+s"(s.rank), "+s"(s.batch), "+s"(s.rows), "+s"(s.wgs),
+                     "+s"(s.union_all), "+s"(s.tau_ge), "+s"(s.waves));
+    const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), nw = s.waves;
+    const int d_in = s.d_in, r = s.rank, b0 = z * BT, nb = min(BT, s.batch - b0);
+    int *const line = as_global(s.sync) + kSyncStage1 + z * kSyncLine;
+    float *const s_part = reinterpret_cast<float *>(smem);                  // [2][RW * BT][nw]
+    const __amdgpu_buffer_rsrc_t tokens = buffer_of(s.X, (uint32_t)s.batch * d_in * 2u);
+    RS_STAMP_DECL;
+    RS_STAMP(1);
+    uint32_t gen = 0;
+    TileRules<BT> rules;
+    load_rules<BT, EXT>(L, b0, nb, rules);
+    if (!EXT) {
 #pragma unroll
-        for (int k = 0; k < kSyncStartedN / 64; ++k)
-            v += __hip_atomic_load(sync + kSyncStarted + k * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int b = 0; b < BT; ++b) rules.r[b].ge = s.tau_ge;
+    }
+    const int row_end = min(r, (wg + 1) * s.rows);
+    // (rows, run of 512 channels) in the order in which they are taken: two are in flight, also from one set of rows to the next
+    struct Pos { int row0, c0; };
+    auto advance = [&](Pos &p) {
+        p.c0 += nw * 512;
+        if (p.c0 - w * 512 >= d_in) { p.c0 = w * 512; p.row0 += RW; }
+    };
+    float part[RW][BT];
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-        ok = v == readers;
-        if (!ok) {
-            if (wall_clock64() - t0 > kWaitLimitTicks) break;
-            __builtin_amdgcn_s_sleep(16);
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int b = 0; b < BT; ++b) part[i][b] = 0.f;
+    struct Run { u32x4 x[BT], v[RW]; };
+    auto request = [&](const Pos &p, Run &q) {
+        const int c = p.c0 + lane * 8, n_rows = max(0, min(RW, row_end - p.row0));     // (past the workgroup's rows: outside)
+        const __amdgpu_buffer_rsrc_t rows = buffer_of(s.SVt + (size_t)min(p.row0, r - 1) * d_in, (uint32_t)n_rows * d_in * 2u);
+#pragma unroll
+        for (int b = 0; b < BT; ++b) q.x[b] = buffer_load16<false>(tokens, c < d_in && b < nb ? (uint32_t)((b0 + b) * d_in + c) * 2u : kOutside);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) q.v[i] = buffer_load16<true>(rows, c < d_in ? (uint32_t)(i * d_in + c) * 2u : kOutside);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto use = [&](const Pos &p, const Run &q) {
+        const int c = p.c0 + lane * 8;
+        float xf[BT][8];
+#pragma unroll
+        for (int b = 0; b < BT; ++b) unpack8<DT>(q.x[b], xf[b]);
+        uint32_t other_kept = 0u;
+        if (BT > 1 && s.union_all) {
+            // every token uses the union over the WHOLE batch (also the tokens of other batch tiles)
+            for (int bb = 0; bb < s.batch; ++bb) {
+                if (bb >= b0 && bb < b0 + nb) continue;
+                float of[8];
+                unpack8<DT>(buffer_load16<false>(tokens, c < d_in ? (uint32_t)(bb * d_in + c) * 2u : kOutside), of);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) other_kept |= (uint32_t)keep(of[e], c + e, EXT ? rule_of(L, bb) : rules.r[0], rules.sgn) << e;
+            }
         }
-    }
 #pragma unroll
-    for (int k = 0; k < kSyncStartedN / 64; ++k)
-        __hip_atomic_store(sync + kSyncStarted + k * 64 + lane, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lane == 0) {
-        if (!ok) __hip_atomic_fetch_or(sync + kSyncError, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(sync + kSyncGen, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int e = 0; e < 8; ++e) {
+            bool kept[BT], any = ((other_kept >> e) & 1u) != 0u;
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                kept[b] = EXT ? keep(xf[b][e], c + e, rules.r[b], rules.sgn) : keep_threshold(xf[b][e], rules.r[b]);
+                any = any || (kept[b] && b < nb);
+            }
+#pragma unroll
+            for (int b = 0; b < BT; ++b) xf[b][e] = (BT > 1 && s.union_all ? any : kept[b]) ? 0.f : xf[b][e];
+        }
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            float f[8];
+            unpack8<DT>(q.v[i], f);
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part[i][b] = __builtin_fmaf(f[e], xf[b][e], part[i][b]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the last run of a set of rows: the waves meet in LDS (two buffers in turn: a wave is never two sets ahead of another)
+    int buffer = 0;
+    auto finish = [&](const Pos &p) {
+        float *const sum = s_part + buffer * (RW * BT * nw);
+        buffer ^= 1;
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const float v = wave_sum63(part[i][b]);
+                if (lane == 63) sum[(i * BT + b) * nw + w] = v;
+                part[i][b] = 0.f;
+            }
+        __syncthreads();
+        const int i = tid / BT, b = tid % BT;
+        if (tid < RW * BT && p.row0 + i < row_end && !s.skip) {
+            float v = 0.f;
+            for (int k = 0; k < nw; ++k) v += sum[tid * nw + k];
+            publish_t(as_global(s.t_tag) + ((size_t)z * BT + b) * r + p.row0 + i, gen, v);
+            if (b == 0) refresh_unused(as_global(s.t_tag), r, s.t_slots, BT, z, gen, p.row0 + i);
+        }
+    };
+    auto last_run = [&](const Pos &p) { return p.row0 < row_end && p.c0 - w * 512 + nw * 512 >= d_in; };
+    Run qa, qb;
+    Pos ahead{wg * s.rows, w * 512}, at = ahead;
+    request(ahead, qa);
+    advance(ahead);
+    gen = generation(line);
+    while (at.row0 < row_end) {
+        request(ahead, qb);
+        advance(ahead);
+        use(at, qa);
+        RS_STAMP(2);
+        if (last_run(at)) finish(at);
+        advance(at);
+        request(ahead, qa);
+        advance(ahead);
+        use(at, qb);
+        if (last_run(at)) finish(at);
+        advance(at);
     }
+    RS_STAMP(3);
+    RS_STAMP(4);
+    static_assert(RW * BT <= 64, "the lanes that use the generation are wave 0's");
+    if (tid == 0 && __hip_atomic_fetch_add(line, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == s.wgs - 1) end_of_line(line);
+    RS_STAMP(5);
+    RS_STAMP_FLUSH(1, wg, w);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -129,12 +129,10 @@ struct Launch {
 constexpr int kSyncLine = 32;
 constexpr int kSyncTilesDone = 0;              // column tiles (over all batch tiles) whose outputs have been stored
 constexpr int kSyncError = 1 * kSyncLine;      // set when a bounded wait ran out (results of that call are invalid)
-constexpr int kSyncGen = 2 * kSyncLine;        // strip kernel: generation number of the next launch (bumped once per launch)
 constexpr int kSyncMaxZ = 4;                   // batch tiles per launch
-constexpr int kSyncStage1 = 3 * kSyncLine;     // [kSyncMaxZ] one-launch kernel, per batch tile, a line apart: stage-1 workgroups (channel-major form) that have added their partial t
-constexpr int kSyncStarted = kSyncStage1 + kSyncMaxZ * kSyncLine;   // strip kernel: [kSyncStartedN] how many waves of the launch have read the generation
-constexpr int kSyncStartedN = 256;
-constexpr int kSyncTile = kSyncStarted + kSyncStartedN;   // [nz][tiles], a line apart: channel splits of the tile that have added their sums
+// {counter, generation} (the hand-off of t, device_stage1.h), a line each:
+constexpr int kSyncStage1 = 2 * kSyncLine;     // [kSyncMaxZ] per batch tile: stage-1 workgroups that have published their t, or (channel-major form) added their part of it
+constexpr int kSyncTile = kSyncStage1 + kSyncMaxZ * kSyncLine;   // [nz][tiles]: channel splits of the column tile (strip) that have added their sums
 __host__ __device__ inline int sync_tile(int tiles, int z, int tile) { return kSyncTile + (z * tiles + tile) * kSyncLine; }
 inline size_t sync_words(int tiles, int nz) { return (size_t)kSyncTile + (size_t)(nz < kSyncMaxZ ? nz : kSyncMaxZ) * tiles * kSyncLine; }
 // Matrix-core path, MatrixView::t_flags (32-bit words; every part starts a 128-byte line of its own): a flag per block of 16
@@ -157,7 +155,7 @@ hipError_t launch_sparse_and_t(const LayerView *L, const Launch *cfg, int n, con
 // The whole layer in ONE launch: the stage-1 workgroups publish t, every gather workgroup also streams
 // its share of the rows of U_r^T (as channels d_in.. with coefficients t), and the last workgroup to
 // arrive at a column tile rounds and stores that tile of Y.  cfg[i].splits must satisfy
-// gather_lds_bytes(d_in, splits, waves, bt, rank) <= 64 KiB.
+// direct_lds_bytes(d_in, splits, waves, bt) <= 64 KiB.
 // gate_up: L[0], L[1] are the gate and up projections of an MLP (same d_out, out_dtype == dtype); the kernel
 // stores H = round(silu(round(g)) * round(u)) to Y[0] instead of the two outputs (Y[1] is not written).
 hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
@@ -207,9 +205,10 @@ hipError_t launch_mfma_cols(const LayerView *L, const MatrixView *M, int n, cons
 // (every channel kept, no low-rank part).  Layers of a group share d_in, dtype and strip_w.
 hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, void *const *Y,
                         bool fused, bool dense, int cus, hipStream_t stream);
-// Stamps builds only (see device_stage1.h): where the strip kernel's waves write their phase time stamps;
+// Stamps builds only (see device_stage1.h): where the waves of the one-launch kernels write their phase time stamps;
 // hipErrorNotSupported in product builds.
 hipError_t set_stamp_buffer(void *buf_dev, int capacity_waves);
+hipError_t set_stamp_buffer_columns(void *buf_dev, int capacity_waves);      // (of kernels.hip, for set_stamp_buffer)
 int strip_waves(int batch);                       // waves per workgroup the strip kernel runs with
 // list entries per wave that fit in LDS for this launch shape; 0 = the shape does not fit (more splits needed)
 int strip_list_cap(int d_in, int rank, int splits, int waves, int bt, int strip_w);
@@ -217,6 +216,8 @@ bool strip_width_ok(int w);
 // out[0:n) = round16(silu(G) * Up), n a multiple of 8, all 16-byte aligned.
 hipError_t launch_gated_input(const void *G, const void *Up, void *out, size_t n, int dtype, hipStream_t stream);
 size_t gather_lds_bytes(int d_in, int splits, int waves, int bt, int fused_rank = 0);
+size_t direct_lds_bytes(int d_in, int splits, int waves, int bt);   // launch_fused's gather workgroups
+bool direct_supported(int d_in, int d_out, int rank);               // launch_fused: M within its buffer descriptor (2 GiB less 16 MiB)
 size_t lowrank_lds_bytes(int d_in, int bt);
 bool rowdot_supported(int d_in, int batch);
 

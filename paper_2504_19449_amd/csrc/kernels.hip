@@ -25,17 +25,13 @@
 //
 // or ONE launch (k_rsparse_fused), which removes the second kernel's launch and start-up latency:
 // M carries r more rows, U_r^T, so that stage 2 of the low-rank part is r more "channels" whose
-// coefficients are t.  Every gather workgroup appends its share of those rows to its list; only the
-// FMAs of those rows need t, which the stage-1 workgroups (at the front of the grid, so dispatched
-// first) publish into t_pub.  An entry of t_pub holds an all-ones bit pattern until it is written, so
-// a consumer needs no separate flag: it requests its entries one batch ahead and re-reads (bounded)
-// while it still sees that pattern.  All cross-workgroup data (t_pub, yacc, arrival counters) moves
-// through agent-scope relaxed atomics, which are performed at the device's coherence point, so no
-// cache write-back or invalidate is needed; a workgroup waits for its own atomics to be acknowledged
-// (s_waitcnt) before it bumps a counter.  The last workgroup to arrive at a column tile swaps the
-// tile's sums out of yacc (which re-zeroes them), rounds once and stores Y; the last tile of the
-// layer puts t_pub and the counters back.  For the gate / up pair of an MLP (Sec. 3.1) the two layers
-// share one set of counters and the finisher stores H = round(silu(g) * u) instead of g and u.
+// coefficients are t.  Every gather wave ends with its share of those rows; only the FMAs of those rows need t,
+// which the stage-1 workgroups (at the front of the grid, so dispatched first) publish as {tag, fp32 bits} (device_stage1.h).
+// All cross-workgroup data (t, yacc, arrival counters) moves through agent-scope relaxed atomics, which are performed at the
+// device's coherence point, so no cache write-back or invalidate is needed; a workgroup waits for its own atomics to be
+// acknowledged (s_waitcnt) before it bumps a counter.  The last workgroup to arrive at a column tile swaps the
+// tile's sums out of yacc (which re-zeroes them), rounds once and stores Y.  For the gate / up pair of an MLP (Sec. 3.1) the two
+// layers share one set of counters and the finisher stores H = round(silu(g) * u) instead of g and u.
 #include "kernels.h"
 #include "device_common.h"
 #include "device_stage1.h"
@@ -43,6 +39,9 @@
 #include <algorithm>
 
 namespace rsparse {
+#if RSPARSE_STAMPS
+hipError_t set_stamp_buffer_columns(void *buf, int capacity_waves) { return set_stamps_of_this_file(buf, capacity_waves); }
+#endif
 namespace {
 
 // ---------------------------------------------------------------------------------------------
@@ -158,15 +157,32 @@ struct GatherArgs {
     const uint16_t *X;
     int batch, splits, tiles, cap;
     int lr_wgs, lr_rows, lr_chunk;     // stage-1 workgroups at the front of the grid, rows each, LDS chunk
-    int lr_gather, lr_cap;             // one-launch kernel, one token: stage 1 over the channel-major copy of S_r V_r^T
-                                       // (lowrank_gather); lr_cap = list slots of a stage-1 workgroup
     int tile_map;
     void *Y;                           // one-launch path only: the output, [batch][d_out]
     int nz;                            // one-launch path only: batch tiles in the grid
     int wait_polls;                    // one-launch path only: bound on re-reads of a t entry that is not ready
     int skip_stage1;                   // test hook: the stage-1 workgroups publish nothing (exercises the bound)
     int dense;                         // 4-bit kernel only: keep every channel (the dense baseline)
-    int gen_readers;                   // (strip kernel only; here for the shared stage-1 code)
+};
+
+// What a gather workgroup of the one-launch kernel needs, side by side: it is fetched in a few wide scalar loads, and all of it
+// before anything else (left alone, the compiler fetches an argument where it is used, a round trip each).
+struct DirectArgs {
+    const uint16_t *X, *M;
+    const uint16_t *SVc;               // stage 1 over the channel-major copy of S_r V_r^T (stage1_gather), or null
+    int *sync;
+    unsigned long long *t_tag;
+    float *yacc;
+    uint32_t *act_bits;
+    int d_in, d_out, rank, batch;
+    int tiles, splits, cap, lr_wgs;
+    uint32_t tiles_inv;                // 2^32 / tiles + 1 (0: one tile): g / tiles = umulhi(g, tiles_inv)
+    int tile_map, union_all;
+    float tau_ge;
+    int q_base, q_rem, u_base, u_rem;  // balanced shares of d_in / 8 and of the rank over the splits * waves waves of a tile
+    int waves;                         // per workgroup
+    int cap_s1;                        // list slots of a wave of stage1_gather
+    Stage1Args s1;
 };
 
 // All of this wave's earlier atomics and stores have been acknowledged by the memory system.
@@ -198,102 +214,266 @@ __device__ __forceinline__ bool map_tile(const GatherArgs &a, int g, int &tile, 
     return map_tile(a.tile_map, a.tiles, a.splits, g, tile, split);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Stage 1 of the low-rank part over the channel-major copy SVc [d_in][rank] (row c = (S_r V_r^T)[:, c]), one
-// token (or a batch tile of up to 4, every token with its own coefficients): t = sum over the DROPPED channels c of x_c SVc[c, :] (Sec. 3.4: the low-rank part acts on x - sigma_t(x),
-// whose kept channels are zero), so only the rows of dropped channels are read -- rank * (d_in - k) elements
-// instead of rank * d_in.  Stage-1 workgroup wg of lr_wgs owns a fixed range of channels: it thresholds that range
-// only, compacts the dropped channels with wave scans, streams their rows (a wave covers 512 columns of a row per
-// load, the waves of a 512-column part share the list in batches of kUnroll rows), sums its waves in LDS and adds
-// the range's partial t to t_sum with fp32 atomics.  The last workgroup to arrive swaps the sums out (which
-// re-zeroes them) and publishes t.  No workgroup waits for another here.
-// ---------------------------------------------------------------------------------------------
-template <int DT, int BT, bool NT, bool EXT>
-__device__ __forceinline__ void lowrank_gather(const GatherArgs &a, unsigned char *smem, int wg, int z)
+// Several layers that read the same input share one launch: job i owns workgroups
+// [wg_end[i-1], wg_end[i]) of the grid.
+constexpr int kMaxGroup = 4;
+struct GroupArgs {
+    DirectArgs direct[kMaxGroup];   // (one-launch kernel of 16-bit weights)
+    GatherArgs job[kMaxGroup];
+    int wg_end[kMaxGroup];
+    int n;
+    int gate_up;       // one-launch kernel: jobs 0 and 1 are the gate and up projections of an MLP (same d_out);
+                       // the column tiles are finished jointly and H = round(silu(g) * u) is stored to job[0].Y
+};
+__device__ __forceinline__ int find_job(const int (&wg_end)[kMaxGroup], int n, int wg, int &local)
 {
-    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = uniform(tid >> 6), nw = nthr >> 6;
-    const LayerView &L = a.L;
-    const int d_in = L.d_in, r = L.rank, cap = a.lr_cap;
-    const int b0 = z * BT;
-    const int nb = min(BT, a.batch - b0);
-    const bool union_all = L.batch_mask_mode == 1;
+    int li = 0, begin = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxGroup - 1; ++i)
+        if (i + 1 < n && wg >= wg_end[i]) { li = i + 1; begin = wg_end[i]; }
+    local = wg - begin;
+    return li;
+}
+
+// ---------------------------------------------------------------------------------------------
+// The one-launch kernel (16-bit weights).  What bounds a call of a decoder's size is not the stream but the chain of dependent
+// round trips to memory (0.9 us each) around it: token -> rows -> sums -> arrival -> swap, and the same for t before its last
+// rows.  So a wave owns fixed chunks of 8 channels (chunk rho, rho + R, ... of the R = splits * waves waves of the column
+// tile: neighbouring channels go to different waves, whatever part of the token is large), reads only those channels of
+// the token(s), thresholds them (Sec. 3.4, sigma_t) and compacts the kept ones with ballots into its own list in LDS: no scan of the
+// whole token and one barrier in front of the first weight load, and little code, which runs once per launch from a
+// cold instruction cache.  After the barrier the waves of a workgroup stream equal shares of their lists (with each on its
+// own list the longest of eight held the others up: 15 rows against 9 at 4096 x 4096).
+// Rows are read through a buffer descriptor: a lane past the last column or a list entry past the list's end lies outside of it
+// and reads zero without touching memory, so that every load is unconditional and the compiler counts the outstanding ones
+// exactly.  Measured, a scan of the whole token and one balanced list of all splits per workgroup -> this (us per pass, one token):
+// 4096 x 4096 10.8 -> 9.3, gate / up and down at 4096 / 11008 (four) 172.7 -> 171.0, an 8192 / 28672 block 206.9 -> 202.1, with a fixed count
+// 5128 / 13832 (two) 146.7 -> 138.4; four tokens at 4096 / 14336 (two) 162.9 -> 154.3.
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kMaxBufferBytes = 0x7f000000u;      // rows that a descriptor covers; offsets from here on are outside
+constexpr uint32_t kRowOutside = 0x7f000000u;          // (plus any lane's offset, kOutside among them: still outside)
+
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+
+// What a wave compacts: chunk j of its n_ch chunks holds channels ((j * step + first) * 8 ..) + 7.
+template <int BT>
+struct Channels {
+    const uint16_t *X;
+    int d_in, batch, b0, nb, n_ch, step, first;
+    bool union_all;
     TileRules<BT> rules;
-    load_rules<BT, EXT>(L, b0, nb, rules);
-    float *s_red = reinterpret_cast<float *>(smem);                 // [nw][kTile]
-    float *s_coef = s_red + (size_t)nw * kTile;                     // [cap][BT]
-    int *s_idx = reinterpret_cast<int *>(s_coef + (size_t)cap * BT);// [cap]
-    int *s_wtot = s_idx + cap;                                      // [nw], then the arrival flag
-    int q_lo, q_hi;
-    balanced_share(d_in / 8, a.lr_wgs, wg, q_lo, q_hi);             // my chunks of 8 channels
-    // every list slot starts as a valid row with zero coefficients
-    for (int i = tid; i < cap; i += nthr) s_idx[i] = 0;
-    for (int i = tid; i < cap * BT; i += nthr) s_coef[i] = 0.f;
+};
+template <int BT> constexpr int kTokenPieces = BT == 1 ? 3 : BT == 2 ? 2 : 1;     // runs of 64 channels requested together
+
+template <int BT>
+__device__ __forceinline__ void request_channels(const Channels<BT> &ch, int p0, uint32_t (&xr)[kTokenPieces<BT>][BT])
+{
+    const int lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t tokens = buffer_of(ch.X, (uint32_t)ch.batch * ch.d_in * 2u);
+#pragma unroll
+    for (int j = 0; j < kTokenPieces<BT>; ++j) {
+        const int jc = (p0 + j) * 8 + (lane >> 3), c = (jc * ch.step + ch.first) * 8 + (lane & 7);
+        // (past my channels or the batch: outside, zero)
+#pragma unroll
+        for (int b = 0; b < BT; ++b)
+            xr[j][b] = __builtin_amdgcn_raw_buffer_load_b16(tokens, (int)(jc < ch.n_ch && b < ch.nb ? (uint32_t)((ch.b0 + b) * ch.d_in + c) * 2u : kOutside), 0, 0);
+    }
+}
+
+// The list of the channels that some token keeps (DROP: drops): offsets c * pitch of their rows in s_off, the coefficients of
+// the tile's tokens in s_cf [entry][BT]; returns its length.  One lane per channel: the channels of a ballot, their places in the
+// list a count of the lower lanes' bits.  The first channels have been requested.  act_bits (or null): which tokens keep each
+// channel, for read-back.
+template <int DT, int BT, bool EXT, bool DROP>
+__device__ __forceinline__ int compact_channels(const Channels<BT> &ch, const LayerView &L, uint32_t pitch, uint32_t (&xr)[kTokenPieces<BT>][BT],
+                                                uint32_t *s_off, uint32_t *s_cf, uint32_t *act_bits)
+{
+    constexpr int PX = kTokenPieces<BT>;
+    const int lane = threadIdx.x & 63, np = (ch.n_ch + 7) >> 3;
     int n = 0;
-    for (int qb = q_lo; qb < q_hi; qb += nthr) {
-        const int q = qb + tid;
-        u32x4 raw[BT];
-        uint32_t dm[BT];                                            // per token: the channels of the chunk it drops
-        uint32_t drop = 0u;                                         // dropped by at least one token of the tile
+    for (int p0 = 0; p0 < np; p0 += PX) {
+        if (p0 > 0) request_channels<BT>(ch, p0, xr);
 #pragma unroll
-        for (int b = 0; b < BT; ++b) { raw[b] = u32x4{0, 0, 0, 0}; dm[b] = 0u; }
-        if (q < q_hi) {
-            load_raw8<BT>(a.X, b0, nb, d_in, q * 8, raw);
-            uint32_t m[BT];
-            masks_of8<DT, BT>(L, a.X, a.batch, b0, nb, d_in, q * 8, rules, union_all, raw, m);
+        for (int j = 0; j < PX; ++j) {
+            if (p0 + j < np) {
+                const int jc = (p0 + j) * 8 + (lane >> 3), c = (jc * ch.step + ch.first) * 8 + (lane & 7);
+                const bool valid = jc < ch.n_ch;
+                float xf[BT];
+                bool kb[BT], any = false;
 #pragma unroll
-            for (int b = 0; b < BT; ++b) {
-                dm[b] = b < nb ? (~m[b] & 0xffu) : 0u;
-                drop |= dm[b];
+                for (int b = 0; b < BT; ++b) {
+                    xf[b] = widen16<DT>((uint16_t)xr[j][b]);
+                    kb[b] = valid && b < ch.nb && (EXT ? keep(xf[b], c, ch.rules.r[b], ch.rules.sgn) : keep_threshold(xf[b], ch.rules.r[b]));
+                    any = any || kb[b];
+                }
+                if (BT > 1 && ch.union_all) {
+                    // every token uses the union over the WHOLE batch (also the tokens of other batch tiles)
+                    for (int bb = 0; bb < ch.batch; ++bb) {
+                        if (bb >= ch.b0 && bb < ch.b0 + ch.nb) continue;
+                        const float xo = valid ? widen16<DT>(as_global(ch.X)[(size_t)bb * ch.d_in + c]) : 0.f;
+                        any = any || (valid && keep(xo, c, EXT ? rule_of(L, bb) : ch.rules.r[0], ch.rules.sgn));
+                    }
+#pragma unroll
+                    for (int b = 0; b < BT; ++b) kb[b] = any && b < ch.nb;
+                }
+                if (!DROP && act_bits && valid) {
+                    uint32_t bits = 0;
+#pragma unroll
+                    for (int b = 0; b < BT; ++b) bits |= (uint32_t)kb[b] << b;
+                    act_bits[c] = bits;
+                }
+                if (DROP) {
+                    any = false;
+#pragma unroll
+                    for (int b = 0; b < BT; ++b) {
+                        kb[b] = valid && b < ch.nb && !kb[b];
+                        any = any || kb[b];
+                    }
+                }
+                const unsigned long long mask = __ballot(any);
+                const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (any) {
+                    s_off[at] = (uint32_t)c * pitch;
+#pragma unroll
+                    for (int b = 0; b < BT; ++b) s_cf[at * BT + b] = kb[b] ? as_u(xf[b]) : 0u;
+                }
+                n += __popcll(mask);
             }
         }
-        const int c = __popc(drop);
-        const int inc = wave_inclusive_scan(c);
-        if (lane == 63) s_wtot[w] = inc;
-        __syncthreads();
-        int woff = 0, tot = 0;
-        for (int i = 0; i < nw; ++i) {
-            const int v = s_wtot[i];
-            woff += i < w ? v : 0;
-            tot += v;
-        }
-        if (drop != 0u) {
-            float f[BT][8];
-#pragma unroll
-            for (int b = 0; b < BT; ++b) unpack8<DT>(raw[b], f[b]);
-            int p = n + woff + inc - c;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (((drop >> e) & 1u) && p < cap) {
-                    s_idx[p] = q * 8 + e;
-#pragma unroll
-                    for (int b = 0; b < BT; ++b) s_coef[p * BT + b] = ((dm[b] >> e) & 1u) ? f[b][e] : 0.f;
-                    ++p;
-                }
-        }
-        n += tot;
-        __syncthreads();
     }
-    n = min(uniform(n), cap);
+    return n;
+}
 
-    // ---- stream the dropped channels' rows: wave w -> 512-column part w % parts, row group w / parts
-    const int parts = (r + kTile - 1) / kTile;                      // host: parts <= nw
-    const int ng = nw / parts;
-    const int part = w % parts, g = w / parts;
+// The lists of a workgroup's waves as one: entry p lies at p + at[j] of the lists' array, j the last wave whose list starts at or
+// before p.
+struct SharedList {
+    int n, start[8], at[8];
+    const uint32_t *off, *cf;            // [nw][cap], [nw][cap][BT]
+    __device__ __forceinline__ int slot(int p) const
+    {
+        int a = p;
+#pragma unroll
+        for (int j = 1; j < 8; ++j) a = p >= start[j] ? p + at[j] : a;
+        return a;
+    }
+};
+// (a barrier) n: this wave's entries; s_cnt [8].
+__device__ __forceinline__ void share_lists(SharedList &sl, int n, int cap, int nw, int *s_cnt)
+{
+    const int tid = threadIdx.x, w = uniform(tid >> 6);
+    if ((tid & 63) == 0) s_cnt[w] = n;
+    __syncthreads();
+    const int4 lo = *reinterpret_cast<const int4 *>(s_cnt), hi = *reinterpret_cast<const int4 *>(s_cnt + 4);
+    const int cnt[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    int sum = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        sl.start[j] = j < nw ? sum : 0x7fffffff;
+        sl.at[j] = j * cap - sum;
+        if (j < nw) sum += uniform(cnt[j]);
+    }
+    sl.n = sum;
+}
+
+// acc[b][0:8] += sum_i cf_i[b] row_i[lane_off ..] over the entries [lo, lo + n) of the list and then n_extra rows at extra_off,
+// + pitch, ... with coefficient zero, R rows per batch, two batches in flight.  64 entries at a time lie in registers, an
+// entry per lane, and become wave-uniform with one readlane each.  before(i0, cv): ahead of the products of the batch at
+// entry i0; cv = the coefficients of the group of 64 that holds it.
+template <int DT, int BT, bool NT, int R, typename Hook>
+__device__ __forceinline__ void stream_list(__amdgpu_buffer_rsrc_t rows, uint32_t lane_off, const SharedList &sl, int lo, int n, int n_extra, uint32_t extra_off,
+                                            uint32_t pitch, float (&acc)[BT][8], Hook &&before)
+{
+    static_assert(64 % R == 0, "a group of 64 list entries is whole batches");
+    const int lane = threadIdx.x & 63, n_all = n + n_extra;
+    uint32_t ov = 0u, cv[BT];
+    auto issue = [&](int i0, u32x4 (&v)[R]) {
+        if ((i0 & 63) == 0) {
+            const int i = i0 + lane;
+            ov = i < n_all ? extra_off + (uint32_t)(i - n) * pitch : kRowOutside;
+            if (i < n) ov = sl.off[sl.slot(lo + i)];
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) v[u] = buffer_load16<NT>(rows, lane_off + lane_value(ov, (i0 & 63) + u));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto consume = [&](int i0, const u32x4 (&v)[R]) {
+        if ((i0 & 63) == 0) {
+            const int i = i0 + lane, at = sl.slot(lo + (i < n ? i : 0));
+#pragma unroll
+            for (int b = 0; b < BT; ++b) cv[b] = i < n ? sl.cf[at * BT + b] : 0u;
+        }
+        before(i0, cv);
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            float f[8];
+            unpack8<DT>(v[u], f);
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const float cf = as_f(lane_value(cv[b], (i0 & 63) + u));
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[b][e] = __builtin_fmaf(cf, f[e], acc[b][e]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    u32x4 va[R], vb[R];
+    issue(0, va);
+    for (int i = 0; i < n_all; i += 2 * R) {
+        issue(i + R, vb);
+        consume(i, va);
+        issue(i + 2 * R, va);
+        consume(i + R, vb);
+    }
+}
+
+// Stage 1 of the low-rank part over the channel-major copy SVc [d_in][rank] (row c = (S_r V_r^T)[:, c]), up to four tokens:
+// t = sum over the DROPPED channels c of x_c SVc[c, :] (Sec. 3.4: the low-rank part acts on x - sigma_t(x), whose kept
+// channels are zero), so only the rows of dropped channels are read -- rank * (d_in - k) elements instead of rank * d_in.  A wave
+// takes 512 columns (part w % parts) of the rows of its own channels, the waves of a part meet in LDS, and the workgroup's
+// partial t goes to t_sum with fp32 atomics.  The last workgroup to arrive swaps the sums out (which re-zeroes them) and
+// publishes t.  No workgroup waits for another here.
+template <int DT, int BT, bool NT, bool EXT, int R>
+__device__ __forceinline__ void stage1_gather(const DirectArgs &h, const LayerView &L, unsigned char *smem, int wg, int z)
+{
+    RS_STAMP_DECL;
+    RS_STAMP(1);
+    const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), nw = h.waves, nthr = nw * 64;
+    const int d_in = h.d_in, r = h.rank, cap = h.cap_s1;
+    const int b0 = z * BT, nb = min(BT, h.batch - b0);
+    const int parts = (r + kTile - 1) / kTile, ng = nw / parts;     // host: parts <= nw
+    const int part = w % parts, g = w / parts, nq = d_in / 8;
+    Channels<BT> ch{h.X, d_in, h.batch, b0, nb, 0, h.s1.wgs * nw, wg * nw + w, h.union_all != 0, {}};
+    ch.n_ch = max(0, (nq - ch.first + ch.step - 1) / ch.step);
+    uint32_t xr[kTokenPieces<BT>][BT];
+    request_channels<BT>(ch, 0, xr);
+    load_rules<BT, EXT>(L, b0, nb, ch.rules);
+    if (!EXT) {
+#pragma unroll
+        for (int b = 0; b < BT; ++b) ch.rules.r[b].ge = h.tau_ge;
+    }
+    uint32_t *const s_off = reinterpret_cast<uint32_t *>(smem), *const s_cf = s_off + nw * cap;  // [nw][cap], [nw][cap][BT]
+    float *const s_red = reinterpret_cast<float *>(s_cf + nw * cap * BT);                        // [nw][kTile]
+    int *const s_misc = reinterpret_cast<int *>(s_red + (size_t)nw * kTile);
+    const uint32_t pitch = (uint32_t)r * 2u;
+    SharedList sl;
+    sl.off = s_off;
+    sl.cf = s_cf;
+    share_lists(sl, compact_channels<DT, BT, EXT, true>(ch, L, pitch, xr, s_off + w * cap, s_cf + w * cap * BT, nullptr), cap, nw, s_misc);
+    RS_STAMP(2);
+    int lo = 0, hi = 0;                       // (waves past the last whole set of parts have none)
+    if (g < ng) balanced_share(sl.n, ng, g, lo, hi);
     const int col = part * kTile + lane * 8;
-    const bool colok = col < r;
     float acc[BT][8];
 #pragma unroll
     for (int b = 0; b < BT; ++b)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[b][e] = 0.f;
-    if (g < ng) {
-        u32x4 va[kUnroll];
-        const int j_first = g * kUnroll, step = ng * kUnroll;
-        load_batch<NT, kUnroll>(L.SVc, (size_t)r, col, colok, s_idx, n, j_first, va);
-        stream_rest<DT, BT, NT, kUnroll>(L.SVc, (size_t)r, col, colok, s_idx, s_coef, n, j_first, step, va, acc, [](int) {});
-    }
+    stream_list<DT, BT, NT, R>(buffer_of(h.SVc, (uint32_t)d_in * pitch), col < r ? (uint32_t)col * 2u : kOutside, sl, lo, hi - lo, 0, 0u, 0u, acc,
+                                [](int, uint32_t (&)[BT]) {});
+    RS_STAMP(3);
+    RS_STAMP_SET(15, hi - lo);
     // b must stay a compile-time index (a run-time subscript would push acc[][] into scratch memory)
-    float *const t_sum = L.t_sum + (size_t)z * BT * r;
+    float *const t_sum = as_global(L.t_sum) + (size_t)z * BT * r;
 #pragma unroll
     for (int b = 0; b < BT; ++b) {
         if (b >= nb) break;
@@ -311,42 +491,206 @@ __device__ __forceinline__ void lowrank_gather(const GatherArgs &a, unsigned cha
     }
 
     // ---- arrive; the last stage-1 workgroup of the batch tile publishes its t
+    int *const line = as_global(h.sync) + kSyncStage1 + z * kSyncLine;
+    const uint32_t gen = generation(line);
     wait_own_writes();
     __syncthreads();
-    if (tid == 0) {
-        int *ctr = L.sync + kSyncStage1 + z * kSyncLine;
-        const int arrived = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_wtot[nw] = arrived == a.lr_wgs - 1;
-        if (arrived == a.lr_wgs - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    RS_STAMP(4);
+    if (tid == 0) s_misc[0] = __hip_atomic_fetch_add(line, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (!s_wtot[nw]) return;
-    uint32_t *const t_pub = L.t_pub + (size_t)z * BT * r;
-    for (int i = tid; i < nb * r; i += nthr) {
-        uint32_t bits = as_u(__hip_atomic_exchange(t_sum + i, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (bits == kNotReady) bits = 0x7fc00000u;
-        if (!a.skip_stage1) __hip_atomic_store(t_pub + i, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    RS_STAMP(5);
+    if (s_misc[0] != h.s1.wgs - 1) {
+        RS_STAMP_FLUSH(1, wg, w);
+        return;
     }
+    unsigned long long *const t_tag = as_global(h.t_tag);
+    for (int i = tid; i < nb * r; i += nthr) {
+        const float v = __hip_atomic_exchange(t_sum + i, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!h.s1.skip) publish_t(t_tag + (size_t)z * BT * r + i, gen, v);
+    }
+    RS_STAMP(6);
+    RS_STAMP_FLUSH(3, wg, w);
+    for (int i = tid; i < r; i += nthr) refresh_unused(t_tag, r, h.s1.t_slots, nb, z, gen, i);
+    if (tid == 0) end_of_line(line);          // (every wave has used the generation: it came before the barriers)
 }
 
-// Several layers that read the same input share one launch: job i owns workgroups
-// [wg_end[i-1], wg_end[i]) of the grid.
-constexpr int kMaxGroup = 4;
-struct GroupArgs {
-    GatherArgs job[kMaxGroup];
-    int wg_end[kMaxGroup];
-    int n;
-    int gate_up;       // one-launch kernel: jobs 0 and 1 are the gate and up projections of an MLP (same d_out);
-                       // the column tiles are finished jointly and H = round(silu(g) * u) is stored to job[0].Y
-};
-__device__ __forceinline__ int find_job(const int (&wg_end)[kMaxGroup], int n, int wg, int &local)
+template <int DT, int BT, bool NT, bool EXT, int R>
+__device__ __forceinline__ void direct_body(const GroupArgs &ga, unsigned char *smem)
 {
-    int li = 0, begin = 0;
+    RS_STAMP_DECL;
+    RS_STAMP(1);
+    const int z = blockIdx.z;
+    int wg;
+    const int job = find_job(ga.wg_end, ga.n, blockIdx.x, wg);
+    const GatherArgs &a = ga.job[job];
+    const LayerView &L = a.L;
+    DirectArgs h = ga.direct[job];
+    __asm__ volatile("" : "+s"(h.X), "+s"(h.M), "+s"(h.sync), "+s"(h.t_tag), "+s"(h.yacc), "+s"(h.act_bits), "+s"(h.d_in), "+s"(h.d_out), "+s"(h.rank),
+                     "+s"(h.batch), "+s"(h.tiles), "+s"(h.splits), "+s"(h.cap), "+s"(h.lr_wgs), "+s"(h.tiles_inv), "+s"(h.tile_map), "+s"(h.union_all),
+                     "+s"(h.tau_ge), "+s"(h.q_base), "+s"(h.q_rem), "+s"(h.u_base), "+s"(h.u_rem), "+s"(h.waves), "+s"(h.SVc));
+    RS_STAMP(2);
+    const int lr_wgs = h.lr_wgs, n_tiles = h.tiles, n_splits = h.splits, d_in = h.d_in, d_out = h.d_out, cap = h.cap, rank = h.rank;
+    if (__builtin_expect(wg < lr_wgs, 0)) {
+        // every gather workgroup ends with rows that need t: the stage-1 waves issue ahead of the gather waves they
+        // share a compute unit with (measured: q/k/v grouped at 8192 wide 37.0 -> 35.6 us, the other launches unchanged)
+        __builtin_amdgcn_s_setprio(3);
+        if constexpr (BT <= 4) {
+            if (h.SVc) {
+                stage1_gather<DT, BT, NT, EXT, BT == 1 ? 8 : 4>(h, L, smem, wg, z);
+                return;
+            }
+        }
+        stage1_rows<DT, BT, EXT>(ga.direct[job].s1, L, smem, wg, z);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), nw = h.waves, nthr = nw * 64;
+    int tile, split;
+    if (h.tile_map != 2) {
+        split = h.tiles_inv ? (int)__umulhi((uint32_t)(wg - lr_wgs), h.tiles_inv) : wg - lr_wgs;
+        tile = wg - lr_wgs - split * n_tiles;
+    } else if (!map_tile(2, n_tiles, n_splits, wg - lr_wgs, tile, split)) {
+        return;
+    }
+    const int b0 = z * BT;
+    const int nb = min(BT, h.batch - b0);
+    const int rho = split * nw + w;
+    Channels<BT> ch{h.X, d_in, h.batch, b0, nb, h.q_base + (rho < h.q_rem ? 1 : 0), n_splits * nw, rho, h.union_all != 0, {}};
+    uint32_t xr[kTokenPieces<BT>][BT];
+    request_channels<BT>(ch, 0, xr);
+    int *const line = as_global(h.sync) + sync_tile(n_tiles, z, tile);
+    const uint32_t gen = generation(line);
+    load_rules<BT, EXT>(L, b0, nb, ch.rules);
+    if (!EXT) {
 #pragma unroll
-    for (int i = 0; i < kMaxGroup - 1; ++i)
-        if (i + 1 < n && wg >= wg_end[i]) { li = i + 1; begin = wg_end[i]; }
-    local = wg - begin;
-    return li;
+        for (int b = 0; b < BT; ++b) ch.rules.r[b].ge = h.tau_ge;
+    }
+    uint32_t *const s_off = reinterpret_cast<uint32_t *>(smem), *const s_cf = s_off + nw * cap;  // [nw][cap], [nw][cap][BT]
+    float *const s_red = reinterpret_cast<float *>(s_cf + nw * cap * BT);                        // [nw][kTile]
+    int *const s_misc = reinterpret_cast<int *>(s_red + (size_t)nw * kTile);
+
+    // ---- sigma_t on my channels; then an equal share of the workgroup's kept ones, and my rows of U_r^T as rows d_in + j of M
+    //      with coefficients t
+    const uint32_t pitch = (uint32_t)d_out * 2u;
+    SharedList sl;
+    sl.off = s_off;
+    sl.cf = s_cf;
+    share_lists(sl, compact_channels<DT, BT, EXT, false>(ch, L, pitch, xr, s_off + w * cap, s_cf + w * cap * BT,
+                                                         tile == 0 ? as_global(h.act_bits) + (size_t)z * d_in : nullptr), cap, nw, s_misc);
+    const int lo = (int)((unsigned)(sl.n * w) / (unsigned)nw), n = (int)((unsigned)(sl.n * (w + 1)) / (unsigned)nw) - lo;
+    const int u_lo = rho * h.u_base + min(rho, h.u_rem), nu = h.u_base + (rho < h.u_rem ? 1 : 0), n_all = n + nu;
+    RS_STAMP(3);
+
+    // t of the list entries from n on in the current group of 64: requested a batch before the first that holds one, re-read
+    // (bounded) where it is not there yet.  Stage 1 runs in workgroups dispatched before this one and waits for nothing, so
+    // the wait ends; the bound turns the impossible into an error flag.
+    unsigned long long tq[BT];
+#pragma unroll
+    for (int b = 0; b < BT; ++b) tq[b] = 0ull;
+    const unsigned long long *const t_tag = as_global(h.t_tag) + (size_t)z * BT * rank + u_lo - n;
+    auto has_t = [&](int e) { return e >= n && e < n_all; };
+    auto request_t = [&](int i0) {
+        const int e = (i0 & ~63) + lane;
+#pragma unroll
+        for (int b = 0; b < BT; ++b)
+            if (has_t(e) && b < nb) tq[b] = __hip_atomic_load(t_tag + (size_t)b * rank + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto need_t = [&](int i0, uint32_t (&cv)[BT]) {
+        const bool first_t = i0 + R > n && (i0 <= n || (i0 & 63) == 0) && i0 < n_all;
+        if (!first_t) {
+            if (i0 + 2 * R > n && i0 + R <= n && ((i0 + R) & 63) != 0) request_t(i0);
+            return;
+        }
+        if ((i0 & 63) == 0) request_t(i0);
+        const int e = (i0 & ~63) + lane;
+        auto missing = [&]() {
+            bool m = false;
+#pragma unroll
+            for (int b = 0; b < BT; ++b) m = m || (b < nb && (uint32_t)(tq[b] >> 32) != gen + 1u);
+            return m && has_t(e);
+        };
+        if (__any(missing())) {
+            const long long t0 = wall_clock64();
+            bool ok = false;
+            for (int polls = 0; polls < a.wait_polls && !ok; ++polls) {
+                __builtin_amdgcn_s_sleep(2);
+                request_t(i0);
+                ok = !__any(missing());
+                if (!ok && wall_clock64() - t0 > kWaitLimitTicks) break;
+            }
+            if (!ok && lane == 0) __hip_atomic_store(as_global(h.sync) + kSyncError, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const bool put = has_t(e) && !missing();
+#pragma unroll
+        for (int b = 0; b < BT; ++b) cv[b] = put && b < nb ? (uint32_t)tq[b] : cv[b];
+        RS_STAMP(5);
+    };
+    float acc[BT][8];
+#pragma unroll
+    for (int b = 0; b < BT; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[b][e] = 0.f;
+    const int col = tile * kTile + lane * 8;
+    stream_list<DT, BT, NT, R>(buffer_of(h.M, (uint32_t)(d_in + rank) * pitch), col < d_out ? (uint32_t)col * 2u : kOutside, sl, lo, n, nu,
+                               (uint32_t)(d_in + u_lo) * pitch, pitch, acc, need_t);
+    RS_STAMP(6);
+    RS_STAMP_SET(15, n_all);
+    RS_STAMP_SET(14, ((unsigned)__builtin_amdgcn_s_getreg(20 | (3 << 11)) << 16) | ((unsigned)__builtin_amdgcn_s_getreg(4 | (31 << 11)) & 0xffff));
+    reduce_to_yacc<BT>(acc, s_red, as_global(h.yacc), b0, nb, d_out, tile);
+    RS_STAMP(7);
+
+    // ---- arrive at the tile; the last of its `splits` workgroups owns the finish.  For a gate/up pair
+    //      the two layers share the gate layer's counters and the tile is finished once, by the last
+    //      of both layers' workgroups (Sec. 3.1: H = X W_up^T (.) silu(X W_gate^T)).
+    wait_own_writes();
+    __syncthreads();
+    RS_STAMP(8);
+    const bool pair = ga.gate_up != 0;
+    int *const arrive = pair ? ga.job[0].L.sync + sync_tile(n_tiles, z, tile) : line;
+    const int arrivals = pair ? ga.job[0].splits + ga.job[1].splits : n_splits;
+    if (tid == 0) s_misc[0] = __hip_atomic_fetch_add(arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    RS_STAMP(9);
+    if (s_misc[0] != arrivals - 1) {
+        RS_STAMP_FLUSH(0, wg, w);
+        return;
+    }
+
+    // ---- Y = round(Y_s + Y_r): swap the sums out (this re-zeroes yacc for the next call), round once
+    float *const yacc_g = pair ? ga.job[0].L.yacc : as_global(h.yacc);
+    for (int c = tid; c < kTile; c += nthr) {
+        const int o = tile * kTile + c;
+        if (o < d_out) {
+            float v[BT], vu[BT];
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                const size_t at = (size_t)(b0 + b) * d_out + o;
+                v[b] = b < nb ? __hip_atomic_exchange(yacc_g + at, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+                vu[b] = (pair && b < nb)
+                            ? __hip_atomic_exchange(ga.job[1].L.yacc + at, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                            : 0.f;
+            }
+#pragma unroll
+            for (int b = 0; b < BT; ++b) {
+                if (b >= nb) continue;
+                const size_t at = (size_t)(b0 + b) * d_out + o;
+                if (!pair) {
+                    store_out(a.Y, at, EXT ? v[b] + bias_at(L, o) : v[b], L.out_dtype);
+                } else {
+                    // g and u are rounded to the storage type first, as the two projections would store them
+                    const float gb = EXT ? v[b] + bias_at(ga.job[0].L, o) : v[b], ub = EXT ? vu[b] + bias_at(ga.job[1].L, o) : vu[b];
+                    const uint16_t g16 = DT == F16 ? to_f16(gb) : to_bf16(gb);
+                    const uint16_t u16 = DT == F16 ? to_f16(ub) : to_bf16(ub);
+                    ((uint16_t *)ga.job[0].Y)[at] = gated1<DT>(g16, u16);
+                }
+            }
+        }
+    }
+    RS_STAMP(10);
+    RS_STAMP_FLUSH(2, wg, w);
+    if (tid == 0) {
+        end_of_line(arrive);
+        if (pair) end_of_line(ga.job[1].L.sync + sync_tile(n_tiles, z, tile));
+    }
 }
 
 // LDS carve-up of the gather part.
@@ -538,12 +882,6 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         // every gather workgroup ends with rows that need t: the stage-1 waves issue ahead of the gather waves they
         // share a compute unit with (measured: q/k/v grouped at 8192 wide 37.0 -> 35.6 us, the other launches unchanged)
         if constexpr (FUSED) __builtin_amdgcn_s_setprio(3);
-        if constexpr (FUSED && BT <= 4 && !Q4) {
-            if (a.lr_gather) {
-                lowrank_gather<DT, BT, NT, EXT>(a, smem, wg, z);
-                return;
-            }
-        }
         lowrank_rows<DT, BT, FUSED ? kPubNotReady : kPubPlain, GatherArgs, EXT>(a, smem, wg, z);
         return;
     }
@@ -774,14 +1112,10 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         __syncthreads();
         reduce_to_yacc<BT>(st.acc[1], s.red, L.yacc, b0, nb, d_out, tile * 2 + 1);
         if constexpr (!FUSED) return;
-    } else if (!FUSED) {
+    } else {
         stream_rest<DT, BT, NT, R>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n, j_first, step, va, acc, [](int) {});
         reduce_to_yacc<BT>(acc, s.red, L.yacc, b0, nb, d_out, tile);
         return;
-    } else {
-        request_t(j_first);
-        stream_rest<DT, BT, NT, R>(L.M, (size_t)d_out, col, colok, s.idx, s.coef, n_all, j_first, step, va, acc, need_t);
-        reduce_to_yacc<BT>(acc, s.red, L.yacc, b0, nb, d_out, tile);
     }
 
     // ---- arrive at the tile; the last of its `splits` workgroups owns the finish.  For a gate/up pair
@@ -886,14 +1220,13 @@ __global__ __launch_bounds__(BT >= 8 ? 256 : 512) void k_sparse_and_t(const Grou
 
 // The whole layer in one launch (see the file header).  Same grid as k_sparse_and_t.
 // EXT = false: no layer of the launch has a fixed-count rule, a signed threshold or a bias (the host checks), and the
-// code for those is left out -- this kernel's once-per-launch code runs from a cold instruction cache, and the
-// general keep-predicate in its token scan measured +0.3 us per launch.
-// R: rows per batch of loads of a wave (launch_fused chooses).
+// code for those is left out -- this kernel's once-per-launch code runs from a cold instruction cache.
+// R: rows per batch of loads of a wave: four (two batches of 4 KiB in flight; with eight 0 to 3 % slower).
 template <int DT, int BT, bool NT, bool EXT, int R>
 __global__ __launch_bounds__(BT >= 8 ? 256 : 512, BT >= 8 ? 3 : 4) void k_rsparse_fused(const GroupArgs ga)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    sparse_body<DT, BT, NT, true, false, EXT, R>(ga, smem);
+    direct_body<DT, BT, NT, EXT, R>(ga, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1099,6 +1432,10 @@ int gather_cap(int d_in, int splits, int fused_rank = 0)
     return (d_in + splits - 1) / splits + 2 + (fused_rank > 0 ? (fused_rank + splits - 1) / splits + 1 : 0);
 }
 
+// List slots of a wave of the one-launch kernel: all channels of its chunks.
+int direct_cap(int d_in, int R) { return (d_in / 8 + R - 1) / R * 8; }
+size_t direct_lds(int cap, int waves, int bt) { return (size_t)waves * (cap * (1 + bt) + kTile) * 4 + 64; }
+
 int lowrank_chunk(int d_in, int bt)
 {
     int chunk = (24576 / bt) & ~7;
@@ -1113,6 +1450,10 @@ size_t gather_lds_bytes(int d_in, int splits, int waves, int bt, int fused_rank)
     return (waves > 1 ? (size_t)waves * kTile * 4 : 0) + cap * bt * 4 + cap * 4 + 16 * 4 + (size_t)d_in / 8 + 16 +
            (size_t)d_in / 2 + 4 + 2 * ((size_t)d_in / 512 + 2) * 4;   // ... + keep-bits of every 8 channels + their list positions
 }
+
+size_t direct_lds_bytes(int d_in, int splits, int waves, int bt) { return direct_lds(direct_cap(d_in, splits * waves), waves, bt); }
+
+bool direct_supported(int d_in, int d_out, int rank) { return (unsigned long long)(d_in + rank) * (unsigned)d_out * 2u <= kMaxBufferBytes; }
 
 size_t lowrank_lds_bytes(int d_in, int bt)
 {
@@ -1251,33 +1592,45 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
         GatherArgs &a = ga.job[i];
         const int tiles = (L[i].d_out + kTile - 1) / kTile;
         a.L = L[i]; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = tiles;
-        a.cap = gather_cap(L[i].d_in, cfg[i].splits, L[i].rank);
+        if (!L[i].M || cfg[i].splits < 1 || !direct_supported(L[i].d_in, L[i].d_out, L[i].rank) || (L[i].rank > 0 && (!L[i].t_tag || L[i].t_slots < nz * bt)))
+            return hipErrorInvalidValue;
+        const int R_all = cfg[i].splits * cfg[0].waves;
+        a.cap = direct_cap(L[i].d_in, R_all);
         a.lr_rows = cfg[i].lowrank_rows;
-        a.lr_wgs = L[i].rank > 0 ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        a.lr_chunk = lowrank_chunk(L[i].d_in, bt);
-        size_t lr_lds = a.lr_wgs > 0 ? lowrank_lds_bytes(L[i].d_in, bt) : 0;
-        // one token and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
-        if (bt <= 4 && cfg[i].lowrank_wgs > 0 && L[i].rank > 0 && L[i].SVc && L[i].t_sum &&
-            (L[i].rank + kTile - 1) / kTile <= cfg[0].waves) {
-            const int nq = L[i].d_in / 8;
-            const int entry = 4 + 4 * bt;                            // bytes of a list entry: index + a coefficient per token
-            a.lr_gather = 1;
-            a.lr_wgs = std::min(cfg[i].lowrank_wgs, nq);
-            // a workgroup's list of dropped channels (all of its range at worst) has to fit LDS next to the reduction
-            // buffer: at least as many workgroups as keep it under 32 KiB
-            a.lr_wgs = std::max(a.lr_wgs, (nq * 8 * entry + 32 * 1024 - 1) / (32 * 1024));
-            a.lr_cap = ((nq + a.lr_wgs - 1) / a.lr_wgs) * 8;
-            lr_lds = (size_t)cfg[0].waves * kTile * 4 + (size_t)a.lr_cap * entry + (size_t)(cfg[0].waves + 1) * 4;
+        a.lr_wgs = L[i].rank > 0 ? (L[i].rank + a.lr_rows - 1) / a.lr_rows : 0;
+        size_t lr_lds = (size_t)2 * 16 * 8 * 4;
+        DirectArgs &h = ga.direct[i];
+        h.SVc = nullptr;
+        // up to four tokens and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
+        const int parts = (L[i].rank + kTile - 1) / kTile;
+        if (bt <= 4 && cfg[i].lowrank_wgs > 0 && L[i].rank > 0 && L[i].SVc && L[i].t_sum && parts <= cfg[0].waves &&
+            (unsigned long long)L[i].d_in * L[i].rank * 2 <= kMaxBufferBytes) {
+            h.SVc = L[i].SVc;
+            a.lr_wgs = std::min(cfg[i].lowrank_wgs, L[i].d_in / 8);
+            // a wave's list (all of its channels at worst) has to fit: at least as many workgroups as keep the launch's LDS under 40 KiB
+            while (direct_lds(h.cap_s1 = direct_cap(L[i].d_in, a.lr_wgs * cfg[0].waves), cfg[0].waves, bt) > 40 * 1024 && a.lr_wgs < L[i].d_in / 8) a.lr_wgs *= 2;
+            lr_lds = direct_lds(h.cap_s1, cfg[0].waves, bt);
         }
+        h.s1 = Stage1Args{a.X, L[i].SVt, L[i].sync, L[i].t_tag, L[i].d_in, L[i].rank, batch, a.lr_rows, a.lr_wgs, L[i].t_slots,
+                          L[i].batch_mask_mode == 1, cfg[i].skip_stage1, L[i].tau_ge, cfg[0].waves};
         a.tile_map = cfg[i].tile_map;
         a.Y = Y[i];
         a.nz = nz;
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
         a.skip_stage1 = cfg[i].skip_stage1;
         const int gather_wgs = cfg[i].tile_map == 2 ? ((tiles + 7) / 8) * 8 * cfg[i].splits : tiles * cfg[i].splits;
+        if (cfg[i].tile_map != 2 && (unsigned long long)gather_wgs * tiles >= 1ull << 32) return hipErrorInvalidValue;   // (tiles_inv is exact below)
+        h.X = a.X; h.M = L[i].M; h.sync = L[i].sync; h.t_tag = L[i].t_tag; h.yacc = L[i].yacc; h.act_bits = L[i].act_bits;
+        h.waves = cfg[0].waves;
+        h.d_in = L[i].d_in; h.d_out = L[i].d_out; h.rank = L[i].rank; h.batch = batch;
+        h.tiles = tiles; h.splits = cfg[i].splits; h.cap = a.cap; h.lr_wgs = a.lr_wgs;
+        h.tiles_inv = tiles == 1 ? 0u : (uint32_t)((1ull << 32) / tiles + 1);
+        h.tile_map = a.tile_map; h.union_all = L[i].batch_mask_mode == 1; h.tau_ge = L[i].tau_ge;
+        h.q_base = L[i].d_in / 8 / R_all; h.q_rem = L[i].d_in / 8 % R_all;
+        h.u_base = L[i].rank / R_all; h.u_rem = L[i].rank % R_all;
         total += a.lr_wgs + gather_wgs;
         ga.wg_end[i] = total;
-        const size_t need = gather_lds_bytes(L[i].d_in, cfg[i].splits, cfg[0].waves, bt, L[i].rank);
+        const size_t need = direct_lds(a.cap, cfg[0].waves, bt);
         if (need > 64 * 1024) return hipErrorInvalidValue;
         lds = std::max(lds, need);
         if (lr_lds > 64 * 1024) return hipErrorInvalidValue;
@@ -1289,23 +1642,9 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
     const bool nt = cfg[0].nontemporal != 0;
     bool ext = false;
     for (int i = 0; i < n; ++i) ext = ext || L[i].rules || L[i].bias || L[i].keep_signed;
-    // Rows per batch: eight, four where a wave of the longest share has no more than two batches of eight at half of the
-    // channels kept (the last one nearly empty: 4096 x 4096 at one token, 9 rows a wave, 13.6 -> 12.8 us, and 1.00 to 1.07 times
-    // as fast on 512 to 4096 wide layers at 30, 50 and 90 % sparsity; with 35 rows and more a wave eight are as fast or faster:
-    // gate / up and down at 4096 / 11008 175.3 against 176.5 us, an 8192 / 28672 block 207.9 against 211.8), and four always at
-    // four tokens (fewer registers: 0.99 to 1.05 times as fast on 512 to 8192 wide layers at 30, 50 and 90 % sparsity, own and
-    // union masks, gate / up and down at 4096 / 14336 167.9 -> 164.1 us; only 8192 x 8192 at 90 % is 2 % slower, 24.1 -> 24.5).
-    bool few = true;
-    for (int i = 0; i < n; ++i) {
-        const int rows = (L[i].d_in / 2 + L[i].rank + cfg[i].splits - 1) / cfg[i].splits;     // expected
-        few = few && rows <= 16 * cfg[0].waves;
-    }
-    const bool four = nt && few && bt == 1;
 #define RS_U(DT)                                                                                        \
-    if (four && !ext) hipLaunchKernelGGL((k_rsparse_fused<DT, 1, true, false, 4>), grid, block, lds, stream, ga);       \
-    else if (four) hipLaunchKernelGGL((k_rsparse_fused<DT, 1, true, true, 4>), grid, block, lds, stream, ga);           \
-    else RS_DISPATCH_BT(bt, {                                                                           \
-        constexpr int RR = BT == 4 ? 4 : kUnroll;                                                       \
+    RS_DISPATCH_BT(bt, {                                                                                \
+        constexpr int RR = 4;                                                                           \
         if (nt && !ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, false, RR>), grid, block, lds, stream, ga);      \
         else if (nt) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, true, true, RR>), grid, block, lds, stream, ga);          \
         else if (!ext) hipLaunchKernelGGL((k_rsparse_fused<DT, BT, false, false, RR>), grid, block, lds, stream, ga);      \

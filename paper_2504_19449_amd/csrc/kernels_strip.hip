@@ -20,13 +20,8 @@
 // A wave-wide 16-byte load covers 64 / LPR rows of the strip at once (LPR = strip_w / 8 lanes per row); row index
 // and coefficient are per lane, read from the wave's list.
 //
-// Stage 1 of the low-rank part, t = S_r V_r^T (x - sigma_t(x)), runs in workgroups at the front of the same grid
-// (dispatched first).  They publish each t_j as one 64-bit word {generation, fp32 bits}.  The generation number
-// of a launch is a word in device memory that every wave reads at its start; a wave reports its read with a
-// store-and-forget atomic, and the first stage-1 workgroup, once all waves of the launch have reported, bumps the
-// number for the next launch.  A consumer accepts an entry only when it carries the launch's generation, so
-// entries left by earlier launches never match, nothing has to be reset at the end of a launch, and no workgroup
-// waits for anything at its end.
+// Stage 1 of the low-rank part, t = S_r V_r^T (x - sigma_t(x)), runs in workgroups of the same grid, which hand each t_j over
+// as one 64-bit word {tag, fp32 bits} (device_stage1.h).
 #include "kernels.h"
 #include "device_common.h"
 #include "device_stage1.h"
@@ -35,13 +30,10 @@
 
 namespace rsparse {
 #if RSPARSE_STAMPS
-__device__ unsigned long long *g_stamp_buf = nullptr;
-__device__ int g_stamp_cap = 0;
 hipError_t set_stamp_buffer(void *buf, int capacity_waves)
 {
-    hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(g_stamp_buf), &buf, sizeof buf);
-    if (e != hipSuccess) return e;
-    return hipMemcpyToSymbol(HIP_SYMBOL(g_stamp_cap), &capacity_waves, sizeof capacity_waves);
+    hipError_t e = set_stamp_buffer_columns(buf, capacity_waves);
+    return e != hipSuccess ? e : set_stamps_of_this_file(buf, capacity_waves);
 }
 #else
 hipError_t set_stamp_buffer(void *, int) { return hipErrorNotSupported; }
@@ -55,11 +47,11 @@ struct StripArgs {
     int batch;
     int tiles, splits;                 // strips of the layer; workgroups (channel splits) per strip
     int cap;                           // list entries per wave (LDS)
-    int lr_wgs, lr_rows, lr_chunk;     // stage-1 workgroups at the front of the job's range, rows each, LDS chunk
+    int lr_wgs;                        // stage-1 workgroups at the front of the job's range
+    Stage1Args s1;
     int lr_last;                       // stage-1 workgroups at the END of the job's range instead (see launch_strip)
-    int wait_polls, skip_stage1;
+    int wait_polls;
     int dense;                         // every channel kept and no low-rank part: the dense product Y = X W^T
-    int gen_readers;                   // waves of the layer's part of the launch (all batch tiles): each reads the generation
 };
 
 struct StripGroupArgs {
@@ -76,148 +68,6 @@ __device__ __forceinline__ int job_of(const int (&wg_end)[kMaxGroupLayers], int 
         if (i + 1 < n && wg >= wg_end[i]) { li = i + 1; begin = wg_end[i]; }
     local = wg - begin;
     return li;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Stage 1 of the low-rank part inside the strip kernel's launch: t_i = sum_c (S_r V_r^T)[i, c] (x - sigma_t(x))_c.
-// The rows of S_r V_r^T do not depend on the token, so a wave requests its part of its row FIRST and stages the
-// masked token afterwards: the requests are on their way before the strip workgroups (which need the token to
-// know their rows) start to load, and t is ready long before they need it.  A row is shared by `ws` waves of the
-// workgroup (so that a wave's part of a row is one batch of loads for the usual row lengths); the parts meet in
-// LDS.  a.lr_rows = rows per workgroup = waves / ws.
-// ---------------------------------------------------------------------------------------------
-constexpr int kS1Batches = 2;      // batches of row loads a stage-1 wave keeps in flight
-
-template <int DT, int BT, typename Args>
-__device__ __forceinline__ void stage1_tagged(const Args &a, unsigned char *smem, int wg, int z)
-{
-    constexpr int LU = 8;
-    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = uniform(tid >> 6), nw = nthr >> 6;
-    const LayerView &L = a.L;
-    const int d_in = L.d_in, r = L.rank;
-    const int b0 = z * BT;
-    const int nb = min(BT, a.batch - b0);
-    const bool union_all = L.batch_mask_mode == 1;
-    TileRules<BT> rules;
-    load_rules<BT>(L, b0, nb, rules);
-    const int rpw = a.lr_rows, ws = nw / rpw;              // rows per workgroup, waves per row
-    const int row = wg * rpw + w / ws, seg = w % ws;
-    const bool have = row < r;
-    uint16_t *s_xm = reinterpret_cast<uint16_t *>(smem);                                   // [BT][chunk]
-    float *s_part = reinterpret_cast<float *>(smem + (((size_t)BT * a.lr_chunk * 2 + 15) & ~(size_t)15));   // [nw][BT]
-    const uint32_t gen = __hip_atomic_load(L.sync + kSyncGen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    RS_STAMP_DECL;
-    RS_STAMP(1);
-
-    float part[BT];
-#pragma unroll
-    for (int b = 0; b < BT; ++b) part[b] = 0.f;
-
-    for (int c0 = 0; c0 < d_in; c0 += a.lr_chunk) {
-        const int len = min(a.lr_chunk, d_in - c0);
-        const int nq = len / 8;
-        int s_lo, s_hi;                                     // my part of the chunk, in 16-byte pieces
-        balanced_share(nq, ws, seg, s_lo, s_hi);
-        const uint16_t *rowp = L.SVt + (size_t)(have ? row : 0) * d_in + c0;
-        // up to kS1Batches batches of LU loads in flight per lane.  The loads are unconditional (positions past the
-        // wave's part re-read its last piece and are dropped when consumed) so that the compiler counts the
-        // outstanding ones exactly and a wave really keeps the later batches in flight while it consumes the first;
-        // with one batch at a time a wave of the 28672-channel down projection needed four dependent round trips
-        // through a memory system that the strip waves keep saturated, and the strips waited 9 us for t
-        u32x4 v[kS1Batches][LU];
-        const int q_last = max(nq - 1, 0);
-        auto request = [&](u32x4 (&dst)[LU], int q0) {
-#pragma unroll
-            for (int u = 0; u < LU; ++u) dst[u] = ldg16<true>(rowp + min(q0 + u * 64, q_last) * 8);
-        };
-        constexpr int kStep = 64 * LU;
-        int q0 = s_lo + lane;
-#pragma unroll
-        for (int i = 0; i < kS1Batches; ++i)
-            if (s_lo + i * kStep < s_hi) request(v[i], q0 + i * kStep);     // before the token: these loads need only the row
-        if (c0 > 0) __syncthreads();
-        constexpr int PB = TokenBatch<BT>::kGroups;
-        for (int p0 = tid; p0 < nq; p0 += nthr * PB) {
-            u32x4 raw[PB][BT];
-#pragma unroll
-            for (int p = 0; p < PB; ++p)
-                if (p0 + p * nthr < nq) load_raw8<BT>(a.X, b0, nb, d_in, c0 + (p0 + p * nthr) * 8, raw[p]);
-#pragma unroll
-            for (int p = 0; p < PB; ++p) {
-                const int q = p0 + p * nthr;
-                if (q < nq) {
-                    uint32_t m[BT];
-                    masks_of8<DT, BT>(L, a.X, a.batch, b0, nb, d_in, c0 + q * 8, rules, union_all, raw[p], m);
-#pragma unroll
-                    for (int b = 0; b < BT; ++b) {
-                        u32x4 o = raw[p][b];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            if ((m[b] >> e) & 1u) o[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;   // kept -> 0
-                        *reinterpret_cast<u32x4 *>(s_xm + (size_t)b * a.lr_chunk + q * 8) = o;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (c0 == 0) {
-            RS_STAMP(2);
-            generation_was_read(L.sync, gen, (int)blockIdx.x * nw + w);
-        }
-        bool more = s_lo < s_hi;                            // wave-uniform
-        while (more) {
-#pragma unroll
-            for (int i = 0; i < kS1Batches; ++i) {
-                if (more) {
-#pragma unroll
-                    for (int u = 0; u < LU; ++u) {
-                        const int q = q0 + u * 64;
-                        if (have && q < s_hi) {
-                            float f[8];
-                            unpack8<DT>(v[i][u], f);
-#pragma unroll
-                            for (int b = 0; b < BT; ++b) {
-                                float xf[8];
-                                unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_xm + (size_t)b * a.lr_chunk + q * 8), xf);
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) part[b] = __builtin_fmaf(f[e], xf[e], part[b]);
-                            }
-                        }
-                    }
-                    const int qn = q0 + kS1Batches * kStep;
-                    if (qn - lane < s_hi) request(v[i], qn);
-                    q0 += kStep;
-                    more = q0 - lane < s_hi;
-                }
-            }
-        }
-    }
-    RS_STAMP(3);
-    // the ws parts of a row meet in LDS; the first wave of the row publishes
-#pragma unroll
-    for (int b = 0; b < BT; ++b) {
-        const float v = wave_sum(part[b]);
-        if (lane == 0) s_part[w * BT + b] = v;
-    }
-    __syncthreads();
-    if (seg == 0 && have && lane < BT && !a.skip_stage1) {
-        float v = 0.f;
-        for (int i = 0; i < ws; ++i) v += s_part[(w + i) * BT + lane];
-        __hip_atomic_store(L.t_tag + ((size_t)z * BT + lane) * r + row, ((unsigned long long)gen << 32) | as_u(v),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // the token slots this call does not use get the generation too (value 0), so that no slot ever carries a tag
-    // older than the previous call's -- a slot left alone for 2^32 calls could otherwise match again
-    if (z == (int)gridDim.z - 1 && seg == 0 && have && !a.skip_stage1) {
-        for (int sl = (int)gridDim.z * BT + lane; sl < L.t_slots; sl += 64)
-            __hip_atomic_store(L.t_tag + (size_t)sl * r + row, (unsigned long long)gen << 32, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
-    RS_STAMP(4);
-    // the layer's first stage-1 workgroup doubles as the launch's poller (see device_stage1.h)
-    if (wg == 0 && z == 0 && w == 0) close_generation(L.sync, a.gen_readers);
-    RS_STAMP(5);
-    RS_STAMP_FLUSH(1, wg, w);
 }
 
 // The wave's list lives in LDS in blocks of kUnroll wave-wide loads (BLK = kUnroll * RPI entries, RPI = rows per
@@ -249,7 +99,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     if (FUSED && lr_wgs > 0) {
         const bool lr_last = pin(a.lr_last) != 0;
         if (lr_last ? wg >= n_strip_wgs : wg < lr_wgs) {
-            stage1_tagged<DT, BT>(a, smem, lr_last ? wg - n_strip_wgs : wg, z);
+            stage1_rows<DT, BT, true>(a.s1, L, smem, lr_last ? wg - n_strip_wgs : wg, z);
             return;
         }
         if (!lr_last) wg -= lr_wgs;
@@ -279,8 +129,8 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     // the generation of this launch, requested before anything else
     uint32_t gen = 0;
     const bool tagged = FUSED && rank > 0;
-    if (tagged) gen = __hip_atomic_load(L.sync + kSyncGen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    bool reported = !tagged;
+    int *const line = L.sync + sync_tile(tiles, z, tile);
+    if (tagged) gen = generation(line);
 
     unsigned char *const wbase = smem + (size_t)w * strip_wave_bytes(cap, BT);
     float *const s_cf = reinterpret_cast<float *>(wbase);                         // [cap][BT], blocked (see list_slot)
@@ -393,11 +243,6 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
         __builtin_amdgcn_wave_barrier();         // the list is read back by this wave only
         if (pub == 0) RS_STAMP(2);               // (first segment) my part of the token is here and compacted
         pub += n;
-        // the token has arrived, and with it the generation requested before it: say so (once)
-        if (!reported) {
-            generation_was_read(L.sync, gen, (int)blockIdx.x * nw + w);
-            reported = true;
-        }
 
         // ---- stream the segment, block by block: a block's eight loads are requested while the block before it is
         //      consumed (two blocks in flight)
@@ -466,7 +311,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
                             const int v = v0 + lane;
                             const bool mine = v < nus * BT;
                             unsigned long long val = v0 == 0 ? tq[0] : (v0 == 64 ? tq[1] : 0ull);
-                            auto ready = [&]() { return !mine || (uint32_t)(val >> 32) == gen; };
+                            auto ready = [&]() { return !mine || (uint32_t)(val >> 32) == gen + 1u; };
                             if (v0 >= 128 && mine)
                                 val = __hip_atomic_load(t_tag + slot_addr(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             if (__any(!ready())) {
@@ -548,6 +393,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     }
     RS_STAMP(8);
     if (!split_k) {
+        if (tagged && tid == 0) __hip_atomic_fetch_add(line + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (all waves have read it)
         RS_STAMP_FLUSH(0, wg, w);
         return;
     }
@@ -557,12 +403,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);               // my own adds have been performed
     __syncthreads();
-    int *tile_ctr = L.sync + sync_tile(tiles, z, tile);
-    if (tid == 0) {
-        const int arrived = __hip_atomic_fetch_add(tile_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (arrived == n_splits - 1) __hip_atomic_store(tile_ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_misc[0] = arrived;
-    }
+    if (tid == 0) s_misc[0] = __hip_atomic_fetch_add(line, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     RS_STAMP(9);
     if (s_misc[0] != n_splits - 1) {
@@ -576,6 +417,10 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
             const float v = __hip_atomic_exchange(L.yacc + at, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             store_out(a.Y, at, v + bias_at(L, o), L.out_dtype);
         }
+    }
+    if (tid == 0) {
+        if (tagged) end_of_line(line);
+        else __hip_atomic_store(line, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     RS_STAMP(10);
     RS_STAMP_FLUSH(2, wg, w);
@@ -653,7 +498,7 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
         if (L[i].d_in != L[0].d_in || L[i].dtype != L[0].dtype || L[i].strip_w != L[0].strip_w) return hipErrorInvalidValue;
         if (!L[i].Ms || !strip_width_ok(L[i].strip_w) || !Y[i] || cfg[i].splits < 1) return hipErrorInvalidValue;
         const int rank = dense ? 0 : L[i].rank;
-        if (fused && rank > 0 && (!L[i].t_tag || !L[i].sync || L[i].t_slots < nz * bt)) return hipErrorInvalidValue;
+        if (fused && rank > 0 && (!L[i].t_tag || !L[i].sync || L[i].t_slots < nz * bt || nz > kSyncMaxZ)) return hipErrorInvalidValue;
         if (cfg[i].splits > 1 && (!L[i].yacc || !L[i].sync || nz > kSyncMaxZ)) return hipErrorInvalidValue;
         StripArgs &a = ga.job[i];
         a.L = L[i]; a.X = (const uint16_t *)X; a.Y = Y[i]; a.batch = batch;
@@ -662,18 +507,15 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
         a.cap = strip_list_cap(L[i].d_in, rank, a.splits, waves, bt, L[i].strip_w);
         if (a.cap <= 0) return hipErrorInvalidValue;
         a.dense = dense ? 1 : 0;
-        // stage 1: lowrank_rows rows per workgroup, waves / lowrank_rows waves per row
-        a.lr_rows = cfg[i].lowrank_rows;
         a.lr_wgs = (fused && rank > 0) ? (rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        if (a.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || cfg[i].lowrank_rows > waves || waves % cfg[i].lowrank_rows)) return hipErrorInvalidValue;
-        a.lr_chunk = std::min(L[i].d_in, (24576 / bt) & ~7);
+        if (a.lr_wgs > 0 && cfg[i].lowrank_rows < 1) return hipErrorInvalidValue;
+        a.s1 = Stage1Args{a.X, L[i].SVt, L[i].sync, L[i].t_tag, L[i].d_in, rank, batch, cfg[i].lowrank_rows, a.lr_wgs, L[i].t_slots,
+                          L[i].batch_mask_mode == 1, cfg[i].skip_stage1, L[i].tau_ge, waves};
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
-        a.skip_stage1 = cfg[i].skip_stage1;
-        a.gen_readers = nz * (a.lr_wgs + a.tiles * a.splits) * waves;
         total += a.lr_wgs + a.tiles * a.splits;
         ga.wg_end[i] = total;
         lds = std::max(lds, strip_lds_bytes(waves, bt, L[i].strip_w, a.cap));
-        if (a.lr_wgs > 0) lds = std::max(lds, (size_t)bt * a.lr_chunk * 2 + 32 + (size_t)waves * bt * 4);
+        if (a.lr_wgs > 0) lds = std::max(lds, (size_t)2 * 16 * 8 * 4);
     }
     for (int i = n; i < kMaxGroupLayers; ++i) ga.wg_end[i] = total;
     if (lds > 64 * 1024) return hipErrorInvalidValue;

@@ -16,8 +16,7 @@ constexpr size_t up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
 // carve-up for the largest call (kStaticMax*): offsets in bytes
 constexpr size_t kOffYacc = 0;
 constexpr size_t kOffT = kOffYacc + up((size_t)kStaticMaxBatch * kStaticMaxDim * 4);
-constexpr size_t kOffTpub = kOffT + up((size_t)kStaticMaxBatch * kStaticMaxRank * 4);
-constexpr size_t kOffTtag = kOffTpub + up((size_t)kStaticMaxBatch * kStaticMaxRank * 4);
+constexpr size_t kOffTtag = kOffT + up((size_t)kStaticMaxBatch * kStaticMaxRank * 4);
 constexpr size_t kOffList = kOffTtag + up((size_t)kStaticMaxBatch * kStaticMaxRank * 8);
 constexpr size_t kOffBits = kOffList + up((size_t)kStaticMaxDim * 4);
 constexpr size_t kOffSeg = kOffBits + up((size_t)kStaticMaxDim * 4);
@@ -37,25 +36,14 @@ constexpr int kMaxDevices = 64;
 unsigned char *g_ptr[kMaxDevices] = {};
 std::mutex g_mu;
 
-// What must start at zero (or at "not written") for one call: the accumulators of its outputs, every counter
-// (the generation of the strip kernel's hand-off is kept, but never 0: fresh entries carry tag 0), the hand-off
-// entries of both kernels, the list count.
-__global__ void k_static_clear(float *yacc, size_t n_y, int *sync, size_t n_sync, uint32_t *t_pub, unsigned long long *t_tag,
-                               size_t n_t, int32_t *act_count)
+// What must start at zero for one call: the accumulators of its outputs, every counter and generation (whose first tag is 1),
+// the hand-off entries, the list count.
+__global__ void k_static_clear(float *yacc, size_t n_y, int *sync, size_t n_sync, unsigned long long *t_tag, size_t n_t, int32_t *act_count)
 {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = i0; i < n_y; i += stride) yacc[i] = 0.f;
-    for (size_t i = i0; i < n_sync; i += stride) {
-        if (i == (size_t)kSyncGen) {
-            if (sync[i] == 0) sync[i] = 1;
-        } else {
-            sync[i] = 0;
-        }
-    }
-    for (size_t i = i0; i < n_t; i += stride) {
-        t_pub[i] = 0xffffffffu;
-        t_tag[i] = 0ull;
-    }
+    for (size_t i = i0; i < n_sync; i += stride) sync[i] = 0;
+    for (size_t i = i0; i < n_t; i += stride) t_tag[i] = 0ull;
     if (i0 == 0) act_count[0] = 0;
 }
 
@@ -83,7 +71,6 @@ hipError_t static_scratch_for_call(int device, int d_out, int rank, int batch, h
     ScratchView sp{};
     sp.yacc = reinterpret_cast<float *>(ptr + kOffYacc);
     sp.t = reinterpret_cast<float *>(ptr + kOffT);
-    sp.t_pub = reinterpret_cast<uint32_t *>(ptr + kOffTpub);
     sp.t_tag = reinterpret_cast<unsigned long long *>(ptr + kOffTtag);
     sp.act_list = reinterpret_cast<int32_t *>(ptr + kOffList);
     sp.act_bits = reinterpret_cast<uint32_t *>(ptr + kOffBits);
@@ -98,8 +85,7 @@ hipError_t static_scratch_for_call(int device, int d_out, int rank, int batch, h
     const size_t most = sp.n_y > sp.sync_n ? sp.n_y : sp.sync_n;
     unsigned blocks = (unsigned)((most + 255) / 256);
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(k_static_clear, dim3(blocks), dim3(256), 0, stream, sp.yacc, sp.n_y, sp.sync, sp.sync_n, sp.t_pub,
-                       sp.t_tag, sp.n_t, sp.act_count);
+    hipLaunchKernelGGL(k_static_clear, dim3(blocks), dim3(256), 0, stream, sp.yacc, sp.n_y, sp.sync, sp.sync_n, sp.t_tag, sp.n_t, sp.act_count);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     *out = sp;
