@@ -779,20 +779,21 @@ namespace {
 
 // Launch shape of the 4-bit kernel: the weight stream is a quarter of the 16-bit one, so fewer, 4-wave
 // workgroups with longer contiguous runs (a wave folds scale and zero point once per quantisation group it meets).
-Launch resolve_launch_q4(const rsparse_layer *L, int batch, bool dense, bool fused)
+Launch resolve_launch_q4(const rsparse_layer *L, int batch, bool dense, bool fused, int tiles, int waves_of_group = 0)
 {
     Launch c{};
     const rsparse_tuning &t = L->tuning;
     const int bt = std::min(4, batch_tile_of(batch));
     c.waves = (t.waves == 1 || t.waves == 2 || t.waves == 4 || t.waves == 8) ? t.waves : 4;
     if (bt >= 4 && c.waves > 4) c.waves = 4;         // the 4-token kernel is built for at most 256 lanes
+    if (waves_of_group > 0) c.waves = waves_of_group;
     c.nontemporal = t.nontemporal == 2 ? 0 : 1;
     c.tile_map = 1;
     const int rows = dense ? L->cfg.d_in : std::max(8, L->cfg.d_in / 2);
     int splits = t.splits;
     if (splits <= 0) {
-        const int target_wgs = std::max(L->qtiles, 2 * L->cus);
-        splits = (target_wgs + L->qtiles - 1) / L->qtiles;
+        // two per compute unit over the layers of the launch, not one more (gate and up of 4096 / 11008: 24 splits 93.0 us a pass, 23 90.5)
+        splits = std::max(1, 2 * L->cus / tiles);
         splits = std::max(1, std::min(splits, std::max(1, rows / (c.waves * 8))));      // >= 8 rows per wave
     }
     splits = std::min(splits, 4096);
@@ -853,29 +854,52 @@ rsparse_status linear_q4_matrix_cores(rsparse_layer *const *layers, int n, const
     return RSPARSE_OK;
 }
 
-// One layer with 4-bit weights on the vector ALU: first launch (codes dequantised in registers), then the common finish.
-rsparse_status linear_q4(rsparse_layer *L, const void *X_dev, int32_t batch, void *Y_dev, bool dense, hipStream_t s)
+// Layers with 4-bit weights on the vector ALU: first launch (codes dequantised in registers), then the common finish, both
+// shared by layers that read the same input (gate, up and down of 4096 / 11008, rank 512, one token, two blocks: 120.6 us a pass with
+// two launches per layer, 90.3 so).
+rsparse_status linear_q4(rsparse_layer *const *layers, int n, const void *X_dev, int32_t batch, void *const *Y_devs, bool dense, hipStream_t s)
 {
-    const LayerView v = L->view(nullptr, batch, dense);
-    const int stages = L->tuning.stages;
+    const int stages = layers[0]->tuning.stages;
     // two launches by default: the one-launch form (launches = 1) measured no faster on these weights --
     // its tail waits for up to `splits` same-address atomics that the two-launch form never waits for
     // (its arrival counters cover up to kSyncMaxZ batch tiles of 4 tokens)
-    const bool fused = !dense && L->tuning.launches == 1 && stages == 0 && (batch + 3) / 4 <= kSyncMaxZ;
-    const Launch lc = resolve_launch_q4(L, batch, dense, fused);
+    const bool fused = n == 1 && !dense && layers[0]->tuning.launches == 1 && stages == 0 && (batch + 3) / 4 <= kSyncMaxZ;
+    LayerView v[RSPARSE_MAX_GROUP];
+    Launch lc[RSPARSE_MAX_GROUP];
+    int tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += layers[i]->qtiles;
+    for (int i = 0; i < n; ++i) {
+        v[i] = layers[i]->view(nullptr, batch, dense);
+        lc[i] = resolve_launch_q4(layers[i], batch, dense, fused, tiles, i ? lc[0].waves : 0);
+    }
     if (fused) {
-        RS_HIP(launch_q4(v, lc, X_dev, batch, true, false, Y_dev, s));
+        RS_HIP(launch_q4(v, lc, 1, X_dev, batch, true, false, Y_devs[0], s));
     } else {
-        if (stages != 2) RS_HIP(launch_q4(v, lc, X_dev, batch, true, dense, nullptr, s));
-        if (stages != 1) RS_HIP(launch_finish(&v, 1, batch, &Y_dev, !dense, s));
+        if (stages != 2) RS_HIP(launch_q4(v, lc, n, X_dev, batch, true, dense, nullptr, s));
+        if (stages != 1) RS_HIP(launch_finish(v, n, batch, Y_devs, !dense, s));
     }
-    if (!dense) {
-        L->last_stream = s; L->last_batch = batch; L->last_mfma = false; L->last_fused = fused;
-        L->last_scratch = L->own_scratch();
-        L->last_bt = std::min(4, batch_tile_of(batch));
-        L->last_strip = L->last_direct = false;
-    }
+    if (!dense)
+        for (int i = 0; i < n; ++i) {
+            rsparse_layer *L = layers[i];
+            L->last_stream = s; L->last_batch = batch; L->last_mfma = false; L->last_fused = fused;
+            L->last_scratch = L->own_scratch();
+            L->last_bt = std::min(4, batch_tile_of(batch));
+            L->last_strip = L->last_direct = false;
+        }
     return RSPARSE_OK;
+}
+
+// Whether 4-bit layers that read the same input share the vector kernels' two launches: all 4-bit, the same stages asked for and no
+// launch shape or form of their own.
+bool q4_share_launches(rsparse_layer *const *layers, int n)
+{
+    bool ok = true;
+    for (int i = 0; i < n; ++i) {
+        const rsparse_tuning &t = layers[i]->tuning;
+        ok = ok && layers[i]->q4() && t.launches != 1 && t.stages == layers[0]->tuning.stages && t.waves == layers[0]->tuning.waves &&
+             t.splits == layers[0]->tuning.splits && t.nontemporal == layers[0]->tuning.nontemporal;
+    }
+    return ok;
 }
 
 rsparse_status check_group(rsparse_layer *const *layers, int32_t n, const void *X, int32_t batch, void *const *Y)
@@ -956,10 +980,13 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
             X_dev = layers[0]->xg;
         }
         if (q4_matrix_cores(layers, n_layers, batch, false)) return linear_q4_matrix_cores(layers, n_layers, X_dev, batch, Y_devs, false, s);
+        bool vector = true;                 // every layer by itself on the vector kernels too
+        for (int i = 0; i < n_layers; ++i) vector = vector && layers[i]->q4() && !q4_matrix_cores(&layers[i], 1, batch, false);
+        if (n_layers > 1 && vector && q4_share_launches(layers, n_layers)) return linear_q4(layers, n_layers, X_dev, batch, Y_devs, false, s);
         for (int i = 0; i < n_layers; ++i) {
             rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch, false)
                                                        ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], false, s)
-                                                       : linear_q4(layers[i], X_dev, batch, Y_devs[i], false, s))
+                                                       : linear_q4(&layers[i], 1, X_dev, batch, &Y_devs[i], false, s))
                                                 : linear_group_impl(&layers[i], 1, X_dev, nullptr, batch, &Y_devs[i], stream);
             if (qs != RSPARSE_OK) return qs;
         }
@@ -1152,7 +1179,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
                 return fail(RSPARSE_EINVAL, "row-dot dense kernel on 4-bit weights needs dense_rowmajor=1, groups >= 32 and batch_tile*d_in*2.125 <= 64 KiB");
             rsparse_status qs = layers[i]->q4() ? (q4_matrix_cores(&layers[i], 1, batch, true)
                                                        ? linear_q4_matrix_cores(&layers[i], 1, X_dev, batch, &Y_devs[i], true, s)
-                                                       : linear_q4(layers[i], X_dev, batch, Y_devs[i], true, s))
+                                                       : linear_q4(&layers[i], 1, X_dev, batch, &Y_devs[i], true, s))
                                                 : rsparse_dense_ref_group(&layers[i], 1, X_dev, batch, &Y_devs[i], stream);
             if (qs != RSPARSE_OK) return qs;
         }

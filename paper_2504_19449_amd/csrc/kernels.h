@@ -166,7 +166,8 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
 // on the same weights).  Y_fused == nullptr: launch_finish completes the layer.  Y_fused != nullptr: the whole
 // layer in this one launch, as launch_fused (not with dense).
 constexpr int kQ4Tile = 1024;
-hipError_t launch_q4(const LayerView &L, const Launch &cfg, const void *X, int batch, bool with_t, bool dense,
+// (one layer); n layers that read the same input share a launch of the first kind.
+hipError_t launch_q4(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, bool with_t, bool dense,
                      void *Y_fused, hipStream_t stream);
 // Second launch: Y = round(yacc + U_r t) (use_rank) or round(yacc); re-zeroes yacc.
 hipError_t launch_finish(const LayerView *L, int n, int batch, void *const *Y, bool use_rank, hipStream_t stream);

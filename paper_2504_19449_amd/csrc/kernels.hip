@@ -1516,41 +1516,47 @@ hipError_t launch_sparse_and_t(const LayerView *L, const Launch *cfg, int n, con
     return hipGetLastError();
 }
 
-hipError_t launch_q4(const LayerView &L, const Launch &cfg, const void *X, int batch, bool with_t, bool dense,
+hipError_t launch_q4(const LayerView *L, const Launch *cfg, int n, const void *X, int batch, bool with_t, bool dense,
                      void *Y_fused, hipStream_t stream)
 {
     const bool fused = Y_fused != nullptr;
-    if (fused && (dense || !with_t || !L.sync || !L.t_pub || (L.rank > 0 && !L.Ut))) return hipErrorInvalidValue;
-    if (!L.Mq || !L.qs || !L.qz || batch < 1 || batch > 32 || L.qshift < 3 || (L.d_in >> L.qshift) < 1 ||
-        ((L.d_in >> L.qshift) << L.qshift) != L.d_in || L.qtiles != (L.d_out + kQ4Tile - 1) / kQ4Tile ||
-        cfg.splits < 1 || cfg.lowrank_rows < 1 || cfg.lowrank_rows > kRowsPerWave * cfg.waves)
-        return hipErrorInvalidValue;
+    if (!same_shape_class(L, n) || batch < 1 || batch > 32) return hipErrorInvalidValue;
+    if (fused && (n != 1 || dense || !with_t || !L[0].sync || !L[0].t_pub || (L[0].rank > 0 && !L[0].Ut))) return hipErrorInvalidValue;
     // batches above 4 tokens run as batch tiles of 4 in the grid's z dimension (the codes are streamed once per tile)
     const int bt = std::min(4, batch_tile(batch));
     const int nz = (batch + bt - 1) / bt;
-    if (bt >= 4 && cfg.waves > 4) return hipErrorInvalidValue;
+    if (bt >= 4 && cfg[0].waves > 4) return hipErrorInvalidValue;
     if (fused && nz > kSyncMaxZ) return hipErrorInvalidValue;
     GroupArgs ga{};
-    ga.n = 1;
-    GatherArgs &a = ga.job[0];
-    a.L = L; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg.splits; a.tiles = L.qtiles;
-    a.cap = gather_cap(L.d_in, cfg.splits, fused ? L.rank : 0);
-    a.lr_rows = cfg.lowrank_rows;
-    a.lr_wgs = (with_t && !dense && L.rank > 0) ? (L.rank + cfg.lowrank_rows - 1) / cfg.lowrank_rows : 0;
-    a.lr_chunk = lowrank_chunk(L.d_in, bt);
-    a.tile_map = 1;
-    a.dense = dense ? 1 : 0;
-    a.Y = Y_fused;
-    a.nz = nz;
-    a.wait_polls = cfg.wait_polls > 0 ? cfg.wait_polls : kWaitLimitPolls;
-    a.skip_stage1 = cfg.skip_stage1;
-    const int total = a.lr_wgs + L.qtiles * cfg.splits;
-    for (int i = 0; i < kMaxGroup; ++i) ga.wg_end[i] = total;
-    size_t lds = gather_lds_bytes(L.d_in, cfg.splits, cfg.waves, bt, fused ? L.rank : 0);
-    if (a.lr_wgs > 0) lds = std::max(lds, lowrank_lds_bytes(L.d_in, bt));
+    ga.n = n;
+    int total = 0;
+    size_t lds = 0;
+    for (int i = 0; i < n; ++i) {
+        const LayerView &l = L[i];
+        if (!l.Mq || !l.qs || !l.qz || l.qshift < 3 || (l.d_in >> l.qshift) < 1 || ((l.d_in >> l.qshift) << l.qshift) != l.d_in ||
+            l.qtiles != (l.d_out + kQ4Tile - 1) / kQ4Tile || cfg[i].splits < 1 || cfg[i].lowrank_rows < 1 || cfg[i].lowrank_rows > kRowsPerWave * cfg[0].waves)
+            return hipErrorInvalidValue;
+        GatherArgs &a = ga.job[i];
+        a.L = l; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = l.qtiles;
+        a.cap = gather_cap(l.d_in, cfg[i].splits, fused ? l.rank : 0);
+        a.lr_rows = cfg[i].lowrank_rows;
+        a.lr_wgs = (with_t && !dense && l.rank > 0) ? (l.rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
+        a.lr_chunk = lowrank_chunk(l.d_in, bt);
+        a.tile_map = 1;
+        a.dense = dense ? 1 : 0;
+        a.Y = Y_fused;
+        a.nz = nz;
+        a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
+        a.skip_stage1 = cfg[i].skip_stage1;
+        total += a.lr_wgs + l.qtiles * cfg[i].splits;
+        ga.wg_end[i] = total;
+        lds = std::max(lds, gather_lds_bytes(l.d_in, cfg[i].splits, cfg[0].waves, bt, fused ? l.rank : 0));
+        if (a.lr_wgs > 0) lds = std::max(lds, lowrank_lds_bytes(l.d_in, bt));
+    }
+    for (int i = n; i < kMaxGroup; ++i) ga.wg_end[i] = total;
     if (lds > 64 * 1024) return hipErrorInvalidValue;
-    dim3 grid(total, 1, nz), block(kWave * cfg.waves);
-    const bool nt = cfg.nontemporal != 0;
+    dim3 grid(total, 1, nz), block(kWave * cfg[0].waves);
+    const bool nt = cfg[0].nontemporal != 0;
 #define RS_Q1(DT, BTV)                                                                                  \
     do {                                                                                                \
         if (fused) {                                                                                    \
@@ -1567,7 +1573,7 @@ hipError_t launch_q4(const LayerView &L, const Launch &cfg, const void *X, int b
     case 2: RS_Q1(DT, 2); break;     \
     default: RS_Q1(DT, 4); break;    \
     }
-    if (L.dtype == F16) { RS_Q(F16) } else { RS_Q(BF16) }
+    if (L[0].dtype == F16) { RS_Q(F16) } else { RS_Q(BF16) }
 #undef RS_Q1
 #undef RS_Q
     return hipGetLastError();
