@@ -98,7 +98,7 @@ typedef struct {
                                 zero): rank * (d_in - k) elements read instead of rank * d_in (k: channels that every token of
                                 the batch tile keeps), summed with fp32 atomics.  Same results within the stated tolerance.
                                 Measured to pay in launches (one layer, or the layers of a grouped call) of about 2^26 weights
-                                or more (28672 -> 8192: 7 %; q/k/v grouped at 8192: 17 %) and at four tokens with the union mask
+                                or more, 2^27 for one layer (28672 -> 8192: 7 %; q/k/v grouped at 8192: 17 %) and at four tokens with the union mask
                                 (few channels are dropped then: 1-7 %), and to cost time in smaller launches at one or two tokens
                                 (t is published later): the library uses the copy in exactly those two cases unless
                                 rsparse_tuning.lowrank_wgs says otherwise.  Ignored by the strip kernel, batches above four, the two-launch

@@ -161,7 +161,7 @@ struct TokenBatch { static constexpr int kGroups = BT >= 8 ? 1 : (BT == 4 ? 2 : 
 // value has it: NaNs made by the ALU are canonical, and NaNs widened from 16-bit inputs have zero
 // low bits; the producer maps it to the canonical NaN anyway.
 constexpr uint32_t kNotReady = 0xffffffffu;
-// How lowrank_rows hands t over: plain stores for a following launch, or -- for the one-launch column-tile kernel,
+// How lowrank_rows hands t over: plain stores for a following launch, or -- for the one-launch 4-bit kernel,
 // which reads t while the launch runs -- entries that hold kNotReady until written (reset at the end of the launch).
 constexpr int kPubPlain = 0, kPubNotReady = 1;
 // Bound on re-reads of an entry that is not ready.  The producers are workgroups with lower
