@@ -1341,7 +1341,7 @@ rsparse_status rsparse_synchronize(rsparse_layer *L)
             // leave the counters and generations usable for the next call
             RS_HIP(hipMemset(sp.sync, 0, sp.sync_n * 4));
             RS_HIP(hipMemset(sp.t_tag, 0, sp.n_t * 8));
-            RS_HIP(hipMemset(sp.t_pub, 0xff, sp.n_t * 4));
+            if (sp.t_pub) RS_HIP(hipMemset(sp.t_pub, 0xff, sp.n_t * 4));      // (the static scratch has none)
             RS_HIP(hipMemset(sp.yacc, 0, sp.n_y * 4));
             return fail(RSPARSE_EHIP, "a cross-workgroup wait of the one-launch kernel ran out; the last result is invalid");
         }
