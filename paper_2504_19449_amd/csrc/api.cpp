@@ -425,6 +425,11 @@ Launch resolve_strip(const rsparse_layer *L, int batch, bool dense, const Launch
     // stage 1: four rows of S_r V_r^T per workgroup while that is one workgroup for every second compute unit or less, else eight
     // (8192 x 8192, rank 512: 40.5 against 45.7 us; q/k/v of 4096, rank 256: 134 against 116)
     int rpw = all.n * ((L->cfg.rank + 3) / 4) <= L->cus / 2 ? 4 : 8;
+    // ... and eight where only so the launch is resident at once (one workgroup per compute unit; us, four tokens, strips of 128: 11008 ->
+    // 4096, rank 512 40.4 - 28.9; q/k/v of 4096 / 1024, rank 512 / 128 26.8 - 21.3)
+    const int nz = (batch + bt - 1) / bt;
+    auto resident = [&](int rows) { return nz * (all.strips * splits + all.n * ((L->cfg.rank + rows - 1) / rows)) <= L->cus; };
+    if (bt > 1 && !resident(4) && resident(8)) rpw = 8;
     if (t.lowrank_rows > 0) {
         rpw = 1;
         while (rpw * 2 <= std::min(t.lowrank_rows, c.waves)) rpw *= 2;

@@ -161,9 +161,9 @@ struct TokenBatch { static constexpr int kGroups = BT >= 8 ? 1 : (BT == 4 ? 2 : 
 // value has it: NaNs made by the ALU are canonical, and NaNs widened from 16-bit inputs have zero
 // low bits; the producer maps it to the canonical NaN anyway.
 constexpr uint32_t kNotReady = 0xffffffffu;
-// How lowrank_rows hands t over: plain stores for a following launch, or -- for the one-launch 4-bit kernel,
-// which reads t while the launch runs -- entries that hold kNotReady until written (reset at the end of the launch).
-constexpr int kPubPlain = 0, kPubNotReady = 1;
+// How lowrank_rows hands t over: plain stores for a following launch, or to the launch that runs -- in the one-launch 4-bit
+// kernel through entries that hold kNotReady until written (reset at the end of the launch), in the others with tags.
+constexpr int kPubPlain = 0, kPubNotReady = 1, kPubTagged = 2;
 // Bound on re-reads of an entry that is not ready.  The producers are workgroups with lower
 // indices (dispatched before the caller), so the wait ends; the bound only turns an impossible
 // schedule into an error flag instead of a hang.
@@ -275,9 +275,15 @@ struct Stage1Args {
     int wgs, t_slots, union_all, skip; // workgroups; token slots of t_tag; test hook: publish nothing
     float tau_ge;
     int waves;
+    int chunk;                         // lowrank_rows: channels of the token(s) in LDS at once; 0: stage1_rows
 };
+inline Stage1Args stage1_args(const LayerView &L, const void *X, int batch, const Launch &cfg, int wgs, int waves, int chunk)
+{
+    return Stage1Args{(const uint16_t *)X, L.SVt, L.sync, L.t_tag, L.d_in, L.rank, batch, cfg.lowrank_rows, wgs, L.t_slots,
+                      L.batch_mask_mode == 1, cfg.skip_stage1, L.tau_ge, waves, chunk};
+}
 template <int BT> struct S1Shape {
-    static constexpr int kRows = BT >= 8 ? 1 : BT >= 4 ? 2 : 4;      // rows that share a token in registers
+    static constexpr int kRows = BT >= 4 ? 2 : 4;      // rows that share a token in registers
 };
 
 template <int DT, int BT, bool EXT>
@@ -419,22 +425,24 @@ __device__ __forceinline__ void stage1_rows(const Stage1Args &args, const LayerV
 // ---------------------------------------------------------------------------------------------
 constexpr int kRowsPerWave = 4;
 
-template <int DT, int BT, int PUB, typename Args, bool EXT = true>
-__device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem, int wg, int z)
+template <int DT, int BT, int PUB, bool EXT = true>
+__device__ __forceinline__ void lowrank_rows(const Stage1Args &a, const LayerView &L, unsigned char *smem, int wg, int z)
 {
     // loads per batch and lane, batches in flight: two batches of six for one token; more tokens keep more of the
     // register file for the token values, and a second batch then spills
     constexpr int LU = BT == 1 ? 6 : 8, kRowBatches = BT == 1 ? 2 : 1;
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = tid >> 6, nw = nthr >> 6;
-    const LayerView &L = a.L;
     const int d_in = L.d_in, r = L.rank;
     const int b0 = z * BT;
     const int nb = min(BT, a.batch - b0);
     const bool union_all = L.batch_mask_mode == 1;
+    int *const line = L.sync + kSyncStage1 + z * kSyncLine;
+    uint32_t gen = 0;
+    if constexpr (PUB == kPubTagged) gen = generation(line);
     TileRules<BT> rules;
     load_rules<BT, EXT>(L, b0, nb, rules);
     uint16_t *s_xm = reinterpret_cast<uint16_t *>(smem);                           // [BT][chunk]
-    const int row_lo = wg * a.lr_rows, row_hi = min(r, row_lo + a.lr_rows);
+    const int row_lo = wg * a.rows, row_hi = min(r, row_lo + a.rows);
 
     float part[kRowsPerWave][BT];
 #pragma unroll
@@ -442,8 +450,8 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
 #pragma unroll
         for (int b = 0; b < BT; ++b) part[sl][b] = 0.f;
 
-    for (int c0 = 0; c0 < d_in; c0 += a.lr_chunk) {
-        const int len = min(a.lr_chunk, d_in - c0);
+    for (int c0 = 0; c0 < d_in; c0 += a.chunk) {
+        const int len = min(a.chunk, d_in - c0);
         const int nq = len / 8;
         if (c0 > 0) __syncthreads();
         constexpr int PB = TokenBatch<BT>::kGroups;
@@ -464,7 +472,7 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
                             if ((m[b] >> e) & 1u) o[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;   // kept -> 0
-                        *reinterpret_cast<u32x4 *>(s_xm + (size_t)b * a.lr_chunk + q * 8) = o;
+                        *reinterpret_cast<u32x4 *>(s_xm + (size_t)b * a.chunk + q * 8) = o;
                     }
                 }
             }
@@ -492,7 +500,7 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
 #pragma unroll
                                 for (int b = 0; b < BT; ++b) {
                                     float xf[8];
-                                    unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_xm + (size_t)b * a.lr_chunk + q * 8), xf);
+                                    unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_xm + (size_t)b * a.chunk + q * 8), xf);
 #pragma unroll
                                     for (int e = 0; e < 8; ++e) part[sl][b] = __builtin_fmaf(f[e], xf[e], part[sl][b]);
                                 }
@@ -529,7 +537,7 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
 #pragma unroll
                                     for (int b = 0; b < BT; ++b) {
                                         float xf[8];
-                                        unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_xm + (size_t)b * a.lr_chunk + q * 8), xf);
+                                        unpack8<DT>(*reinterpret_cast<const u32x4 *>(s_xm + (size_t)b * a.chunk + q * 8), xf);
 #pragma unroll
                                         for (int e = 0; e < 8; ++e) part[sl][b] = __builtin_fmaf(f[e], xf[e], part[sl][b]);
                                     }
@@ -554,8 +562,10 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
             const float v = wave_sum(part[sl][b]);
             if (lane == 0 && i < row_hi) {
                 const size_t at = ((size_t)z * BT + b) * r + i;
-                if (PUB == kPubNotReady) {
-                    if (a.skip_stage1) continue;
+                if (PUB == kPubTagged) {
+                    if (!a.skip) publish_t(L.t_tag + at, gen, v);
+                } else if (PUB == kPubNotReady) {
+                    if (a.skip) continue;
                     uint32_t bits = as_u(v);
                     if (bits == kNotReady) bits = 0x7fc00000u;
                     __hip_atomic_store(L.t_pub + at, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -564,6 +574,28 @@ __device__ __forceinline__ void lowrank_rows(const Args &a, unsigned char *smem,
                 }
             }
         }
+        if (PUB == kPubTagged && lane == 0 && i < row_hi && !a.skip) refresh_unused(L.t_tag, r, a.t_slots, BT, z, gen, i);
+    }
+    if constexpr (PUB == kPubTagged) {
+        __syncthreads();                       // every wave has used the generation
+        if (tid == 0 && __hip_atomic_fetch_add(line, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.wgs - 1) end_of_line(line);
+    }
+}
+
+// Stage 1 of a one-launch kernel of 16-bit weights, in the form that the host chose (stage1_chunk).
+template <int DT, int BT, bool EXT>
+__device__ __forceinline__ void stage1_tagged(const Stage1Args &s, const LayerView &L, unsigned char *smem, int wg, int z)
+{
+    if constexpr (BT >= 8) {
+        lowrank_rows<DT, BT, kPubTagged, EXT>(s, L, smem, wg, z);
+    } else {
+        if constexpr (BT == 4) {
+            if (s.chunk > 0) {
+                lowrank_rows<DT, BT, kPubTagged, EXT>(s, L, smem, wg, z);
+                return;
+            }
+        }
+        stage1_rows<DT, BT, EXT>(s, L, smem, wg, z);
     }
 }
 

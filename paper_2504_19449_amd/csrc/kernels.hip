@@ -156,12 +156,12 @@ struct GatherArgs {
     LayerView L;
     const uint16_t *X;
     int batch, splits, tiles, cap;
-    int lr_wgs, lr_rows, lr_chunk;     // stage-1 workgroups at the front of the grid, rows each, LDS chunk
+    int lr_wgs;                        // stage-1 workgroups at the front of the grid
+    Stage1Args s1;
     int tile_map;
     void *Y;                           // one-launch path only: the output, [batch][d_out]
     int nz;                            // one-launch path only: batch tiles in the grid
     int wait_polls;                    // one-launch path only: bound on re-reads of a t entry that is not ready
-    int skip_stage1;                   // test hook: the stage-1 workgroups publish nothing (exercises the bound)
     int dense;                         // 4-bit kernel only: keep every channel (the dense baseline)
 };
 
@@ -540,7 +540,7 @@ __device__ __forceinline__ void direct_body(const GroupArgs &ga, unsigned char *
                 return;
             }
         }
-        stage1_rows<DT, BT, EXT>(ga.direct[job].s1, L, smem, wg, z);
+        stage1_tagged<DT, BT, EXT>(ga.direct[job].s1, L, smem, wg, z);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), nw = h.waves, nthr = nw * 64;
@@ -882,7 +882,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         // every gather workgroup ends with rows that need t: the stage-1 waves issue ahead of the gather waves they
         // share a compute unit with (measured: q/k/v grouped at 8192 wide 37.0 -> 35.6 us, the other launches unchanged)
         if constexpr (FUSED) __builtin_amdgcn_s_setprio(3);
-        lowrank_rows<DT, BT, FUSED ? kPubNotReady : kPubPlain, GatherArgs, EXT>(a, smem, wg, z);
+        lowrank_rows<DT, BT, FUSED ? kPubNotReady : kPubPlain, EXT>(a.s1, L, smem, wg, z);
         return;
     }
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = tid >> 6, nw = nthr >> 6;
@@ -1460,6 +1460,22 @@ size_t lowrank_lds_bytes(int d_in, int bt)
     return (size_t)bt * lowrank_chunk(d_in, bt) * 2 + 16;
 }
 
+// Unstaged, every set of two rows (four up to two tokens) reads and masks the tokens again: where a workgroup of four tokens has more
+// rows than `unstaged`, and always at eight tokens, they are masked once, in LDS (us per call at 4, 8 and 16 rows a workgroup, unstaged -
+// staged, four tokens, fixed count, 4096 x 4096, rank 256 22.8 - 22.7, 28.7 - 22.7, 40.0 - 24.3; 8192 x 8192, rank 512 40.6 - 42.9,
+// 43.3 - 43.3, 65.2 - 43.6; 28672 -> 8192, rank 1024 8 rows 92.0 - 97.1; eight tokens, default rows: q/k/v of 8192 / 1024, rank
+// 1024 342 - 90, gate and up of 4096 / 11008, rank 512 120 - 76).  The strip kernel, one workgroup per compute unit at four
+// tokens, gains from five rows on (8 rows: 4096 x 4096 20.2 - 16.6, 28672 -> 8192 125 - 107; 4 rows: 16.3 - 16.5, 118 - 116).
+int stage1_chunk(int d_in, int bt, int rows, int unstaged)
+{
+    return bt >= 8 || (bt == 4 && rows > unstaged) ? lowrank_chunk(d_in, bt) : 0;
+}
+
+size_t stage1_lds_bytes(int d_in, int bt, int chunk)
+{
+    return chunk > 0 ? lowrank_lds_bytes(d_in, bt) : (size_t)2 * 8 * 8 * 4;     // stage1_rows: two sums of the waves
+}
+
 #define RS_DISPATCH_BT(BTV, ...)                      \
     switch (BTV) {                                    \
     case 1: { constexpr int BT = 1; __VA_ARGS__; } break; \
@@ -1490,9 +1506,8 @@ hipError_t launch_sparse_and_t(const LayerView *L, const Launch *cfg, int n, con
         const int tiles = (L[i].d_out + kTile - 1) / kTile;
         a.L = L[i]; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = tiles;
         a.cap = gather_cap(L[i].d_in, cfg[i].splits);
-        a.lr_rows = cfg[i].lowrank_rows;
         a.lr_wgs = (with_t && L[i].rank > 0) ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        a.lr_chunk = lowrank_chunk(L[i].d_in, bt);
+        a.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, cfg[0].waves, lowrank_chunk(L[i].d_in, bt));
         a.tile_map = cfg[i].tile_map;
         const int gather_wgs = !with_gather ? 0
                                : cfg[i].tile_map == 2 ? ((tiles + 7) / 8) * 8 * cfg[i].splits : tiles * cfg[i].splits;
@@ -1539,15 +1554,13 @@ hipError_t launch_q4(const LayerView *L, const Launch *cfg, int n, const void *X
         GatherArgs &a = ga.job[i];
         a.L = l; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = l.qtiles;
         a.cap = gather_cap(l.d_in, cfg[i].splits, fused ? l.rank : 0);
-        a.lr_rows = cfg[i].lowrank_rows;
         a.lr_wgs = (with_t && !dense && l.rank > 0) ? (l.rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        a.lr_chunk = lowrank_chunk(l.d_in, bt);
+        a.s1 = stage1_args(l, X, batch, cfg[i], a.lr_wgs, cfg[0].waves, lowrank_chunk(l.d_in, bt));
         a.tile_map = 1;
         a.dense = dense ? 1 : 0;
         a.Y = Y_fused;
         a.nz = nz;
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
-        a.skip_stage1 = cfg[i].skip_stage1;
         total += a.lr_wgs + l.qtiles * cfg[i].splits;
         ga.wg_end[i] = total;
         lds = std::max(lds, gather_lds_bytes(l.d_in, cfg[i].splits, cfg[0].waves, bt, fused ? l.rank : 0));
@@ -1602,9 +1615,10 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
             return hipErrorInvalidValue;
         const int R_all = cfg[i].splits * cfg[0].waves;
         a.cap = direct_cap(L[i].d_in, R_all);
-        a.lr_rows = cfg[i].lowrank_rows;
-        a.lr_wgs = L[i].rank > 0 ? (L[i].rank + a.lr_rows - 1) / a.lr_rows : 0;
-        size_t lr_lds = (size_t)2 * 16 * 8 * 4;
+        a.lr_wgs = L[i].rank > 0 ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
+        if (a.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || (bt >= 4 && cfg[i].lowrank_rows > kRowsPerWave * cfg[0].waves))) return hipErrorInvalidValue;
+        const int chunk = stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, 8);
+        size_t lr_lds = stage1_lds_bytes(L[i].d_in, bt, chunk);
         DirectArgs &h = ga.direct[i];
         h.SVc = nullptr;
         // up to four tokens and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
@@ -1617,13 +1631,11 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
             while (direct_lds(h.cap_s1 = direct_cap(L[i].d_in, a.lr_wgs * cfg[0].waves), cfg[0].waves, bt) > 40 * 1024 && a.lr_wgs < L[i].d_in / 8) a.lr_wgs *= 2;
             lr_lds = direct_lds(h.cap_s1, cfg[0].waves, bt);
         }
-        h.s1 = Stage1Args{a.X, L[i].SVt, L[i].sync, L[i].t_tag, L[i].d_in, L[i].rank, batch, a.lr_rows, a.lr_wgs, L[i].t_slots,
-                          L[i].batch_mask_mode == 1, cfg[i].skip_stage1, L[i].tau_ge, cfg[0].waves};
+        h.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, cfg[0].waves, chunk);
         a.tile_map = cfg[i].tile_map;
         a.Y = Y[i];
         a.nz = nz;
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
-        a.skip_stage1 = cfg[i].skip_stage1;
         const int gather_wgs = cfg[i].tile_map == 2 ? ((tiles + 7) / 8) * 8 * cfg[i].splits : tiles * cfg[i].splits;
         if (cfg[i].tile_map != 2 && (unsigned long long)gather_wgs * tiles >= 1ull << 32) return hipErrorInvalidValue;   // (tiles_inv is exact below)
         h.X = a.X; h.M = L[i].M; h.sync = L[i].sync; h.t_tag = L[i].t_tag; h.yacc = L[i].yacc; h.act_bits = L[i].act_bits;

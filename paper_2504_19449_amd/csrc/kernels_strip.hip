@@ -99,7 +99,7 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     if (FUSED && lr_wgs > 0) {
         const bool lr_last = pin(a.lr_last) != 0;
         if (lr_last ? wg >= n_strip_wgs : wg < lr_wgs) {
-            stage1_rows<DT, BT, true>(a.s1, L, smem, lr_last ? wg - n_strip_wgs : wg, z);
+            stage1_tagged<DT, BT, true>(a.s1, L, smem, lr_last ? wg - n_strip_wgs : wg, z);
             return;
         }
         if (!lr_last) wg -= lr_wgs;
@@ -508,14 +508,13 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
         if (a.cap <= 0) return hipErrorInvalidValue;
         a.dense = dense ? 1 : 0;
         a.lr_wgs = (fused && rank > 0) ? (rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        if (a.lr_wgs > 0 && cfg[i].lowrank_rows < 1) return hipErrorInvalidValue;
-        a.s1 = Stage1Args{a.X, L[i].SVt, L[i].sync, L[i].t_tag, L[i].d_in, rank, batch, cfg[i].lowrank_rows, a.lr_wgs, L[i].t_slots,
-                          L[i].batch_mask_mode == 1, cfg[i].skip_stage1, L[i].tau_ge, waves};
+        if (a.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || (bt >= 4 && cfg[i].lowrank_rows > kRowsPerWave * waves))) return hipErrorInvalidValue;
+        a.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, waves, stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, 4));
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
         total += a.lr_wgs + a.tiles * a.splits;
         ga.wg_end[i] = total;
         lds = std::max(lds, strip_lds_bytes(waves, bt, L[i].strip_w, a.cap));
-        if (a.lr_wgs > 0) lds = std::max(lds, (size_t)2 * 16 * 8 * 4);
+        if (a.lr_wgs > 0) lds = std::max(lds, stage1_lds_bytes(L[i].d_in, bt, a.s1.chunk));
     }
     for (int i = n; i < kMaxGroupLayers; ++i) ga.wg_end[i] = total;
     if (lds > 64 * 1024) return hipErrorInvalidValue;

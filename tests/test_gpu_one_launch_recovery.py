@@ -31,3 +31,31 @@ def test_the_static_entry_reports_the_wait_and_recovers(strip_cols):
             rs.rsparse_synchronize(layer)
             gu.check_outputs(gu._read_out(layer, Y), want["Y"], rs.F32)
     layer.destroy()
+
+
+@pytest.mark.parametrize("strip_cols", [0, 128])
+@pytest.mark.parametrize("B", [3, 4, 7, 8])
+@pytest.mark.parametrize("d_in,rows", [(3080, 5), (3080, 9), (6152, 32), (264, 8)])
+def test_tokens_staged_for_stage_1(d_in, rows, B, strip_cols):
+    """Four tokens and rows enough, eight tokens: the masked tokens lie in LDS, 6144 and 3072 channels at a time.  Chunks that end inside
+    the last one, several rows a wave, waves without rows, own and union masks, calls of other batch sizes between (the tags of all
+    token slots agree), and a wait that runs out."""
+    L = synth.random_layer(d_in, 136, 40, synth.F16, seed=d_in)
+    X16, src = gu.tokens_for(L, 8, linear=3)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    for mode in (0, 1):
+        layer = gu.prepare(L, tau, max_batch=8, out_dtype=rs.F32, strip_cols=strip_cols, batch_mask_mode=mode)
+        forms = dict(launches=1, mfma_min_batch=33, lowrank_rows=rows)
+        for b in (B, 1, B, 2, B):
+            rs.rsparse_set_tuning(layer, **forms)
+            got = gu.run_linear(layer, X16[:b])
+            want = gu.oracle_linear(L, X16[:b], tau, batch_mask_mode=mode)
+            gu.check_lists(got, want)
+            gu.check_outputs(got["Y"], want["Y"], rs.F32)
+        rs.rsparse_set_tuning(layer, **forms, debug_skip_stage1=1, debug_wait_polls=4)
+        with pytest.raises(rs.RSparseError, match="ran out"):
+            gu.run_linear(layer, X16[:B])
+        rs.rsparse_set_tuning(layer, **forms)
+        for _ in range(2):
+            gu.check_outputs(gu.run_linear(layer, X16[:B])["Y"], gu.oracle_linear(L, X16[:B], tau, batch_mask_mode=mode)["Y"], rs.F32)
+        layer.destroy()
