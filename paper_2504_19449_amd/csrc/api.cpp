@@ -285,6 +285,7 @@ int expected_rows(const rsparse_layer *L) { return std::max(8, L->cfg.d_in / 2);
 struct LaunchTotals {
     size_t weights = 0;
     int tiles = 0, strips = 0, n = 1;
+    int rank = 0;                              // of all layers
     bool svc = false;                          // stage 1 reads the channel-major copies of S_r V_r^T by default
     int svc_wgs = 0;                           // ... with this many workgroups
 };
@@ -308,6 +309,7 @@ LaunchTotals totals_of(rsparse_layer *const *layers, int n, int batch)
         t.weights += (size_t)c.d_in * c.d_out;
         t.tiles += layers[i]->tiles;
         t.strips += layers[i]->strips;
+        t.rank += c.rank;
         unions = unions && (c.batch_mask_mode == 1 || (c.batch_mask_mode == 2 && batch >= 4));
         copies = copies && (layers[i]->SVc || c.rank == 0);
         if (layers[i]->SVc) t.svc_wgs += svc_workgroups(layers[i]);
@@ -413,10 +415,16 @@ Launch resolve_strip(const rsparse_layer *L, int batch, bool dense, const Launch
         } else {
             // One number of splits for the layers of a launch, for about 160 workgroups below 2^26 weights, 320 in larger groups and
             // one per compute unit in larger single layers (us per pass at 1 - 2 - 3 - 4 - 5 splits: q/k/v of 4096, strips of 128
-            // 136 - 116 - 126 - 120; of 256 176 - 134 - 122 - 127 - 133; of 64 124 - 126 - 145; q/k/v of 8192 82 - 67 - 66 - 68 - 65,
-            // of 8192 / 1024 118 - 115 - 99 - 95; 2048 93 - 85 - 83 - 91; 8192 x 8192 alone 40 at 4, 45 at 5).
+            // 136 - 116 - 126 - 120; of 256 176 - 134 - 122 - 127 - 133; of 64 124 - 126 - 145; 8192 / 1024 118 - 115 - 99 - 95;
+            // 8192 x 8192 alone 40 at 4, 45 at 5) ...
             const int target = all.weights < ((size_t)1 << 26) ? 5 * L->cus / 8 : group > 1 ? 5 * L->cus / 4 : L->cus;
             splits = std::max(1, (target + all.strips / 2) / std::max(1, all.strips));
+            // ... but in larger groups at one token no more than one per compute unit where that uses half of them and stage 1 is
+            // resident too (us per call, one token, 1 - 2 - 3 - 4 splits: gate and up of 4096 / 11008, strips of 128, 172 of them, 27.4 - 28.3 -
+            // 31.5 - 29.5, of 256 37.2 - 27.0 - 31.9 - 28.6; q/k/v of 8192, of 128 47.9 - 51.8 - 49.1; of 6144, of 128 32.7 - 34.0
+            // - 30.6, of 256 45.8 - 31.6 - 29.1 - 34.2).
+            const int one = L->cus / std::max(1, all.strips);
+            if (bt == 1 && group > 1 && all.weights > ((size_t)1 << 26) && one >= 1 && one * all.strips >= L->cus / 2 && one * all.strips + all.rank / 8 <= 2 * L->cus) splits = one;
         }
     }
     splits = std::max(1, std::min(splits, 4096));

@@ -47,9 +47,9 @@ struct StripArgs {
     int batch;
     int tiles, splits;                 // strips of the layer; workgroups (channel splits) per strip
     int cap;                           // list entries per wave (LDS)
-    int lr_wgs;                        // stage-1 workgroups at the front of the job's range
+    int lr_wgs;                        // stage-1 workgroups at the front of the job's range ...
+    int lr_last;                       // ... or at its END (see launch_strip)
     Stage1Args s1;
-    int lr_last;                       // stage-1 workgroups at the END of the job's range instead (see launch_strip)
     int wait_polls;
     int dense;                         // every channel kept and no low-rank part: the dense product Y = X W^T
 };
@@ -58,6 +58,7 @@ struct StripGroupArgs {
     StripArgs job[kMaxGroupLayers];
     int wg_end[kMaxGroupLayers];
     int n;
+    int s1_end[kMaxGroupLayers];       // the jobs' stage-1 workgroups behind all strips instead (all zero: none)
 };
 
 __device__ __forceinline__ int job_of(const int (&wg_end)[kMaxGroupLayers], int n, int wg, int &local)
@@ -92,14 +93,15 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     static_assert(kUnroll == 8, "a lane reads the row codes of a block as one 16-byte vector");
     const int z = blockIdx.z;
     int wg;
-    const StripArgs &a = ga.job[job_of(ga.wg_end, ga.n, blockIdx.x, wg)];
+    const int n_front = pin(ga.wg_end[kMaxGroupLayers - 1]);
+    const bool behind = FUSED && (int)blockIdx.x >= n_front;
+    const StripArgs &a = ga.job[behind ? job_of(ga.s1_end, ga.n, (int)blockIdx.x - n_front, wg) : job_of(ga.wg_end, ga.n, blockIdx.x, wg)];
     const LayerView &L = a.L;
-    const int lr_wgs = FUSED ? pin(a.lr_wgs) : 0;
-    const int n_strip_wgs = pin(a.tiles) * pin(a.splits);
-    if (FUSED && lr_wgs > 0) {
+    if (FUSED) {
+        const int lr_wgs = pin(a.lr_wgs), n_strip_wgs = pin(a.tiles) * pin(a.splits);
         const bool lr_last = pin(a.lr_last) != 0;
-        if (lr_last ? wg >= n_strip_wgs : wg < lr_wgs) {
-            stage1_tagged<DT, BT, true>(a.s1, L, smem, lr_last ? wg - n_strip_wgs : wg, z);
+        if (behind || (lr_last ? wg >= n_strip_wgs : wg < lr_wgs)) {
+            stage1_tagged<DT, BT, true>(a.s1, L, smem, lr_last && !behind ? wg - n_strip_wgs : wg, z);
             return;
         }
         if (!lr_last) wg -= lr_wgs;
@@ -512,11 +514,9 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
         a.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, waves, stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, 4));
         a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
         total += a.lr_wgs + a.tiles * a.splits;
-        ga.wg_end[i] = total;
         lds = std::max(lds, strip_lds_bytes(waves, bt, L[i].strip_w, a.cap));
         if (a.lr_wgs > 0) lds = std::max(lds, stage1_lds_bytes(L[i].d_in, bt, a.s1.chunk));
     }
-    for (int i = n; i < kMaxGroupLayers; ++i) ga.wg_end[i] = total;
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     // Where the stage-1 workgroups sit.  When every workgroup of the launch is resident at once (two 8-wave
     // workgroups of the one-token kernel per compute unit, one otherwise), they go to the END of each layer's range:
@@ -524,9 +524,27 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
     // stream while the strip workgroups are still compacting -- a time in which the memory system is otherwise
     // idle.  A launch that needs more than one round of workgroups keeps them at the front, so that they are
     // dispatched before any workgroup that will wait for t.
+    // Up to one strip workgroup per compute unit they go behind the strips of all layers, so that no two of those share a compute
+    // unit (one token, us with each layer's behind its own strips - behind all: gate and up of 4096 / 14336 in strips of
+    // 128, 112 + 64 + 112 + 64 workgroups, 38.2 - 28.5; q/k/v of 5120 in strips of 64 28.7 - 24.3); with more strip workgroups t would
+    // come late (gate and up of 4096 / 11008 in strips of 64, 344 of them, 29.3 - 31.0).
     const int resident = cus * (bt == 1 ? 2 : 1);
-    const int lr_last = (long long)total * nz <= resident ? 1 : 0;
-    for (int i = 0; i < n; ++i) ga.job[i].lr_last = lr_last;
+    int strip_wgs = 0;
+    for (int i = 0; i < n; ++i) strip_wgs += ga.job[i].tiles * ga.job[i].splits;
+    const bool lr_last = (long long)total * nz <= resident, behind = lr_last && strip_wgs * nz <= cus;
+    int front = 0, back = 0;
+    for (int i = 0; i < n; ++i) {
+        StripArgs &a = ga.job[i];
+        if (behind) {
+            back += a.lr_wgs;
+            a.lr_wgs = 0;
+        }
+        front += a.tiles * a.splits + a.lr_wgs;
+        a.lr_last = lr_last && !behind;
+        ga.wg_end[i] = front;
+        ga.s1_end[i] = back;
+    }
+    for (int i = n; i < kMaxGroupLayers; ++i) ga.wg_end[i] = front, ga.s1_end[i] = back;
     dim3 grid(total, 1, nz), block(kWave * waves);
 #define RS_S(DT)                                                                                             \
     RS_STRIP_BT(bt, RS_STRIP_W(L[0].strip_w, {                                                                \
