@@ -97,10 +97,12 @@ typedef struct {
                                 the DROPPED channels only (the low-rank part acts on x - sigma_t(x), whose kept channels are
                                 zero): rank * (d_in - k) elements read instead of rank * d_in (k: channels that every token of
                                 the batch tile keeps), summed with fp32 atomics.  Same results within the stated tolerance.
-                                Measured to pay in launches (one layer, or the layers of a grouped call) of about 2^26 weights
-                                or more, 2^27 for one layer (28672 -> 8192: 7 %; q/k/v grouped at 8192: 17 %) and at four tokens with the union mask
-                                (few channels are dropped then: 1-7 %), and to cost time in smaller launches at one or two tokens
-                                (t is published later): the library uses the copy in exactly those two cases unless
+                                Costs time in small launches (t is published later), so the library decides, layer by layer, for
+                                the layers of a call that have the copy: at one and two tokens in launches (one layer, or the
+                                layers of a grouped call) of 9 * 2^23 weights or more whose copies leave 4.5 MB per token of
+                                the batch tile unread at half of the channels kept (28672 -> 8192, rank 1024: 7 %; q/k/v of
+                                8192 / 1024, rank 1024: 11 %, with the copy on k and v only 8 %), and at four tokens with the
+                                union mask from 1.2 MB on (few channels are dropped then: 4-13 %), unless
                                 rsparse_tuning.lowrank_wgs says otherwise.  Ignored by the strip kernel, batches above four, the two-launch
                                 form, rsparse_linear_static and 4-bit weights (those read the row-major copy). */
 } rsparse_config;
@@ -131,10 +133,10 @@ typedef struct {
                                 layers without dense_rowmajor), 1 one launch: keeps 4-bit and such column-major layers off the
                                 matrix cores, which need two (vector kernels, at 5 tokens 125 against 76 us for an MLP of 4096 /
                                 11008), 2 two launches (stage 2 and the rounding in a second kernel).  stages != 0 implies two */
-    int32_t lowrank_wgs;     /* stage-1 workgroups of the channel-major form (cfg.lowrank_channel_major): 0 default (64, or 128
-                                from 16 MB of rows to read, within the resident slots the layer's other workgroups leave free;
-                                128 on skinny layers; the copy is used only where it was measured to pay), > 0: that many,
-                                always, -1: always the row-major copy */
+    int32_t lowrank_wgs;     /* stage-1 workgroups of the channel-major form (cfg.lowrank_channel_major): 0 default (one per
+                                256 KiB of rows it is expected to read, 16 to 64, 8 at four tokens under the union mask; the
+                                copy is used only where it was measured to pay), > 0: that many, always, -1: always the
+                                row-major copy */
     int32_t debug_wait_polls;   /* one-launch kernel: bound on the re-reads of a low-rank intermediate that stage 1 has
                                    not published yet; 0 = default (2^20, or 0.5 s) */
     int32_t debug_skip_stage1;  /* test hook for the error path, needs debug_wait_polls in [1, 64]: stage 1 publishes

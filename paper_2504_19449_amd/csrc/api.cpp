@@ -281,52 +281,80 @@ rsparse_status check_config(const rsparse_config *c)
 // Expected rows of W that a call streams.
 int expected_rows(const rsparse_layer *L) { return std::max(8, L->cfg.d_in / 2); }
 
+// Expected share of the channels that stage 1 over the channel-major copy does not read, at half of the channels kept by every
+// token: those that no token of the tile drops.
+double unread_share(const rsparse_config &c, int batch)
+{
+    const int bt = batch_tile_of(batch);
+    const bool unions = c.batch_mask_mode == 1 || (c.batch_mask_mode == 2 && batch >= 4);
+    return unions ? 1.0 - std::pow(0.5, bt) : std::pow(0.5, bt);
+}
+
+// Stage-1 workgroups over the channel-major copy (each on fixed channels): one per 256 KiB of rows it is expected to read, 16 to
+// 64, and from 8 where it reads hardly any (union mask at four tokens).
+int svc_workgroups(const rsparse_layer *L, int batch)
+{
+    if (L->tuning.lowrank_wgs > 0) return L->tuning.lowrank_wgs;
+    const double read = 1.0 - unread_share(L->cfg, batch), bytes = 2.0 * L->cfg.rank * L->cfg.d_in * read;
+    return std::max(read < 0.1 ? 8 : 16, std::min(64, (int)(bytes / (256 * 1024))));
+}
+
 // The layers of one launch together.
 struct LaunchTotals {
     size_t weights = 0;
     int tiles = 0, strips = 0, n = 1;
-    int rank = 0;                              // of all layers
-    bool svc = false;                          // stage 1 reads the channel-major copies of S_r V_r^T by default
-    int svc_wgs = 0;                           // ... with this many workgroups
+    bool svc[RSPARSE_MAX_GROUP] = {};          // the layer's stage 1 reads the channel-major copy of S_r V_r^T
+    int svc_layers = 0, svc_wgs = 0;           // how many do, with this many workgroups
+    bool svc_idle = false;                     // ... which read hardly anything (union mask at four tokens)
+    int rank = 0, rank_max = 0;                // of all layers
+    int row_wgs = 0, row_rows = 0;             // stage-1 workgroups of the others at four rows per wave; their rows, in whole fours
 };
 
-// Stage-1 workgroups over the channel-major copy (each on fixed channels): one per 256 KiB of rows it is expected to read, 16 to
-// 64; 64 on skinny layers (d_out of the order of the rank: the k / v projections of grouped-query attention), where stage 1 is
-// half or more of what the gather workgroups read.
-int svc_workgroups(const rsparse_layer *L)
-{
-    const double rows = expected_rows(L), s1_bytes = 2.0 * L->cfg.rank * (L->cfg.d_in - rows), gather_bytes = 2.0 * (rows + L->cfg.rank) * L->cfg.d_out;
-    return 2.0 * s1_bytes >= gather_bytes ? 64 : std::max(16, std::min(64, (int)(s1_bytes / (256 * 1024))));
-}
-
-LaunchTotals totals_of(rsparse_layer *const *layers, int n, int batch)
+// copies: the call may use the channel-major copies (one launch, the handle's own scratch).
+LaunchTotals totals_of(rsparse_layer *const *layers, int n, int batch, bool copies = false)
 {
     LaunchTotals t;
     t.n = n;
-    bool unions = true, copies = true;
+    double unread_bytes = 0.0, unread_least = 1.0;
+    bool has[RSPARSE_MAX_GROUP] = {};
     for (int i = 0; i < n; ++i) {
         const rsparse_config &c = layers[i]->cfg;
         t.weights += (size_t)c.d_in * c.d_out;
         t.tiles += layers[i]->tiles;
         t.strips += layers[i]->strips;
         t.rank += c.rank;
-        unions = unions && (c.batch_mask_mode == 1 || (c.batch_mask_mode == 2 && batch >= 4));
-        copies = copies && (layers[i]->SVc || c.rank == 0);
-        if (layers[i]->SVc) t.svc_wgs += svc_workgroups(layers[i]);
+        t.rank_max = std::max(t.rank_max, c.rank);
+        has[i] = copies && batch <= 4 && layers[i]->SVc && lowrank_copy_supported(c.d_in, c.rank);
+        if (!has[i]) continue;
+        unread_bytes += 2.0 * c.rank * c.d_in * unread_share(c, batch);
+        unread_least = std::min(unread_least, unread_share(c, batch));
     }
-    // Where reading only the dropped channels' rows pays: launches of several layers of 2^26 weights or more and of one of 2^27
-    // (t is published three dependent round trips later than by the row dots, which a shorter launch does not hide: 8192 x 8192,
-    // rank 1024 24.3 us with it, 22.2 with the row dots), and at four tokens under the union mask (hardly any channel is
-    // dropped then, so stage 1 reads almost nothing).
-    const int bt = batch_tile_of(batch);
-    t.svc = copies && t.svc_wgs > 0 && (t.weights >= ((size_t)1 << (n > 1 ? 26 : 27)) || (bt == 4 && unions));
+    // Where reading only the dropped channels' rows pays.  t is published three dependent round trips later than by the row dots;
+    // against that stand the rows that are not read, in a launch long enough to hide it (us, row dots - copy, one token, rank d_in / 16
+    // and d_in / 8: gate / up of 4096 / 8192 19.7 - 20.8, 21.6 - 22.9; of 4096 / 11008 23.5 - 24.3, 25.6 - 26.5; of 8192 / 4096 21.5 -
+    // 26.2, 27.1 - 29.2; of 8192 / 8192 33.7 - 33.0, 38.6 - 37.4; 8192 x 8192 19.7 - 22.2, 22.4 - 24.6; q/k/v of 5120 22.3 - 21.7,
+    // 24.7 - 25.0; of 8192 / 1024 25.4 - 24.6, 33.1 - 28.8; 28672 -> 8192 48.8 - 47.3, 53.3 - 51.0; two tokens: q/k/v of 8192 /
+    // 1024 33.3 - 33.6, 42.5 - 39.2; 16384 -> 8192, rank 1024 47.9 - 49.1).  At four tokens hardly any row is left unread
+    // with own masks (28672 -> 8192 91 - 100), and nearly all with the union mask, where few workgroups do: there from
+    // 1.2 MB on (gate / up of 1024 / 8192, rank 128 19.1 - 22.6; 4096 x 4096, rank 256 17.2 - 18.4; 5632 -> 2048, rank 128 18.9 -
+    // 16.8; 5120 x 5120, rank 320 23.0 - 21.5; 11008 -> 4096 29.3 - 26.4).
+    const bool idle = unread_least > 0.9;
+    const bool pays = idle ? unread_bytes >= 1.2e6 : t.weights >= ((size_t)9 << 23) && unread_bytes >= 4.5e6 * batch_tile_of(batch);
+    t.svc_idle = idle;
+    for (int i = 0; i < n; ++i) {
+        const int asked = layers[i]->tuning.lowrank_wgs;
+        t.svc[i] = has[i] && (asked > 0 || (asked == 0 && pays));
+        t.svc_layers += t.svc[i];
+        if (t.svc[i]) t.svc_wgs += svc_workgroups(layers[i], batch);
+        else t.row_wgs += (layers[i]->cfg.rank + 31) / 32, t.row_rows += (layers[i]->cfg.rank + 3) / 4 * 4;
+    }
     return t;
 }
 
-// Launch shape: column tiles x channel splits, the same number of splits for every layer of the launch (they share d_in, so that
-// a workgroup of each has as many rows), each with enough rows to amortise its start, and the staged share small enough
-// for 64 KiB of LDS.  fused: the one-launch kernel.
-Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const LaunchTotals &all, int waves_of_group = 0, bool fused = false)
+// Launch shape of layer i of a launch: column tiles x channel splits, the same number of splits for every layer of the launch (they
+// share d_in, so that a workgroup of each has as many rows), each with enough rows to amortise its start, and the staged share
+// small enough for 64 KiB of LDS.  fused: the one-launch kernel.
+Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const LaunchTotals &all, int i, int waves_of_group = 0, bool fused = false)
 {
     Launch c{};
     const rsparse_tuning &t = L->tuning;
@@ -340,30 +368,36 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const Launc
     c.skip_stage1 = t.debug_skip_stage1 ? 1 : 0;
     c.tile_map = t.tile_map == 0 ? 1 : t.tile_map;
     const int rows = dense ? L->cfg.d_in : expected_rows(L);
-    const int tiles = all.tiles > 0 ? all.tiles : L->tiles, slots = 2 * L->cus;       // two 8-wave workgroups per compute unit
-    const bool svc = fused && !dense && bt <= 4 && L->SVc && L->cfg.rank > 0 && (t.lowrank_wgs > 0 || (t.lowrank_wgs == 0 && all.svc));
+    const int tiles = all.tiles, slots = 2 * L->cus;       // two 8-wave workgroups per compute unit
     int splits = t.splits;
     if (splits <= 0) {
         // one resident round of workgroups for the whole launch: ~1.5 per compute unit, for the 8-wave kernels and for the 4-wave
         // 8-token kernels alike (those hold two workgroups per compute unit at their register count)
         splits = (std::max(tiles, 3 * L->cus / 2) + tiles - 1) / tiles;
+        const int stage1 = all.svc_wgs + all.row_wgs;
+        if (fused && !dense && bt <= 4 && all.svc_layers > 0) {
+            // ... and with stage 1 as close to 15 of 16 slots as they come, within the slots (us, one token, gather workgroups of a
+            // tile: 8192 -> 14336 16: 27.8, 18: 32.8; 20480 -> 8192 24: 37.1, 29: 35.3, 30: 38.7; 28672 -> 8192 24: 52.7, 26: 50.9, 30:
+            // 55.3; gate / up of 8192 / 14336, rank 1024 7: 56.3, 8: 54.9), or all of them where stage 1 is over at once (gate / up of
+            // 4096 / 11008, four tokens, union mask: 10 43.9, 11 41.7).
+            const int fit = (slots - stage1) / tiles;
+            splits = std::max(splits, all.svc_idle ? fit : std::min(fit, (slots * 15 / 16 - stage1 + tiles * 3 / 5) / tiles));
+        } else if (fused && !dense && bt <= 4 && all.weights >= ((size_t)1 << 26) && tiles >= 24) {
+            // with row dots no more than that, and only where it does not make many splits of few tiles, whose sums queue up at the
+            // end (gate / up of 4096 / 8192 12: 19.7, 13: 18.8, 15 - all slots -: 20.8; q/k/v of 8192 / 2048 16: 25.3, 19: 23.9; but of 8192 /
+            // 4096, rank 1024 24: 27.1, 26: 31.3; 8192 x 8192 24: 22.0, 28: 23.0).
+            splits = std::max(splits, (slots * 15 / 16 - stage1) / tiles);
+        }
         // every output receives `splits` same-address atomic adds, which serialise at the end of the
         // kernel: beyond 32 they cost more than the extra workgroups bring, as long as one workgroup
         // per compute unit remains (measured on 11008 -> 4096: 32 splits beat 48)
         if (fused) splits = std::min(splits, std::max(32, (L->cus + tiles - 1) / tiles));
-        if (svc && all.svc) {
-            // How the workgroups spread over the compute units decides more than their number: one whose share of the launch is
-            // stage-1 workgroups idles once t is there.  Few of those and as many gather workgroups as there are slots
-            // left (us per pass, gather workgroups of 512: gate / up of 4096 / 11008 at one token 440: 170, 484: 166,
-            // 528: 178; at four tokens of 4096 / 14336 392: 164, 448: 153, 504: 157; 28672 -> 8192 384: 216, 448: 210, 512: 238;
-            // q/k/v of 8192 / 1024 with 42 + 128 + 128 stage-1 workgroups and as many gather workgroups for each 218, with
-            // 64 each and 16 splits 215).
-            splits = std::max(1, std::min((slots + L->cus / 32 - all.svc_wgs) / tiles, std::max(32, (L->cus + tiles - 1) / tiles)));
-        } else if (fused && bt <= 4) {
+        if (fused && bt <= 4) {
             // Where a wave has few rows (16) anyway, one workgroup per compute unit, stage 1 included, shares the chip evenly
-            // (4096 x 4096, rank 256: 9.5 us with 24 splits and 64 stage-1 workgroups, 9.8 with 32, 9.9 with 16).
-            const int one = (L->cus - all.n * ((L->cfg.rank + 3) / 4)) / tiles;
-            if (one >= 1 && (rows + L->cfg.rank + one - 1) / one <= 16 * c.waves) splits = std::min(splits, one);
+            // (4096 x 4096, rank 256: 9.5 us with 24 splits and 64 stage-1 workgroups, 9.8 with 32, 9.9 with 16; 5120 x 5120, rank 320, four
+            // tokens, union mask: 20.0 with 24 splits and 8, 23.0 with 32, 21.6 with 40).
+            const int one = (L->cus - all.svc_wgs - all.row_rows / 4) / tiles;
+            if (one >= 1 && (rows + all.rank_max + one - 1) / one <= 16 * c.waves) splits = std::min(splits, one);
         }
         const int max_by_rows = std::max(1, rows / (c.waves * 4));          // >= 4 rows per wave
         splits = std::max(1, std::min(splits, max_by_rows));
@@ -379,15 +413,15 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const Launc
     }
     c.lowrank_rows = std::max(1, std::min(lr, 4 * c.waves));                  // at most 4 rows per wave
     // one launch: the gather workgroups end with rows that need t, so stage 1 is cut as fine as the
-    // launch allows: its workgroups get the resident slots (shared by the
-    // layers of a group) that the gather workgroups leave free, with four rows or more.  A launch that needs a
+    // launch allows: its workgroups get the resident slots (shared by the layers of a group that read the rows)
+    // that the others leave free, with four rows or more.  A launch that needs a
     // second round of workgroups loses more than finer stage-1 workgroups gain (measured on 4096 -> 11008 and 28672 -> 8192).
     if (fused && t.lowrank_rows <= 0) {
-        const int free_slots = (slots - tiles * splits) / all.n;
+        const int free_slots = (slots - tiles * splits - all.svc_wgs) / std::max(1, all.n - all.svc_layers);
         const int need = free_slots > 0 ? (L->cfg.rank + free_slots - 1) / free_slots : 4 * c.waves;
         c.lowrank_rows = std::max(std::max(1, c.waves / 2), std::min(4 * c.waves, need));
     }
-    if (svc) c.lowrank_wgs = t.lowrank_wgs > 0 ? t.lowrank_wgs : svc_workgroups(L);
+    if (all.svc[i]) c.lowrank_wgs = svc_workgroups(L, batch);
     return c;
 }
 
@@ -1012,10 +1046,10 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     bool fused = layers[0]->tuning.launches != 2 && stages == 0;
     // (the column kernel reaches M through a 32-bit buffer descriptor; larger layers take two launches)
     for (int i = 0; i < n_layers; ++i) fused = fused && (!layers[i]->M || direct_supported(layers[i]->cfg.d_in, layers[i]->cfg.d_out, layers[i]->cfg.rank));
-    const LaunchTotals all = totals_of(layers, n_layers, batch);
+    const LaunchTotals all = totals_of(layers, n_layers, batch, fused && !ov);
     for (int i = 0; i < n_layers; ++i) {
         v[i] = layers[i]->view(ov, batch);
-        lc[i] = resolve_launch(layers[i], batch, false, all, i ? lc[0].waves : 0, fused);
+        lc[i] = resolve_launch(layers[i], batch, false, all, i, i ? lc[0].waves : 0, fused);
         layers[i]->last_scratch = ov ? *ov : layers[i]->own_scratch();
     }
     MatrixView mv[RSPARSE_MAX_GROUP];
@@ -1118,10 +1152,10 @@ rsparse_status rsparse_mlp_gate_up(rsparse_layer *gate, rsparse_layer *up, const
                        direct_supported(up->cfg.d_in, up->cfg.d_out, up->cfg.rank);
     LayerView v[2];
     Launch lc[2];
-    const LaunchTotals all = totals_of(pair, 2, batch);
+    const LaunchTotals all = totals_of(pair, 2, batch, fused);
     for (int i = 0; i < 2; ++i) {
         v[i] = pair[i]->view(nullptr, batch);
-        lc[i] = resolve_launch(pair[i], batch, false, all, i ? lc[0].waves : 0, fused);
+        lc[i] = resolve_launch(pair[i], batch, false, all, i, i ? lc[0].waves : 0, fused);
     }
     bool mfma = batch >= (gate->tuning.mfma_min_batch > 0 ? gate->tuning.mfma_min_batch : kMfmaDefaultMinBatch);
     for (int i = 0; i < 2; ++i) mfma = mfma && mfma_path_supported(pair[i]->matrix(v[i]), batch) && pair[i]->cfg.topk == 0;
@@ -1204,7 +1238,7 @@ rsparse_status rsparse_dense_ref_group(rsparse_layer *const *layers, int32_t n_l
     const LaunchTotals all = totals_of(layers, n_layers, batch);
     for (int i = 0; i < n_layers; ++i) {
         v[i] = layers[i]->view(nullptr, batch, true);
-        lc[i] = resolve_launch(layers[i], batch, true, all, i ? lc[0].waves : 0);
+        lc[i] = resolve_launch(layers[i], batch, true, all, i, i ? lc[0].waves : 0);
         can_rowdot = can_rowdot && layers[i]->Wtile != nullptr && rowdot_supported(layers[i]->cfg.d_in, batch);
     }
     // The dense product runs on the matrix cores (measured, us, vector ALU -> matrix cores: 4096 x 4096 15.0 -> 8.7 at two

@@ -219,6 +219,7 @@ hipError_t launch_gated_input(const void *G, const void *Up, void *out, size_t n
 size_t gather_lds_bytes(int d_in, int splits, int waves, int bt, int fused_rank = 0);
 size_t direct_lds_bytes(int d_in, int splits, int waves, int bt);   // launch_fused's gather workgroups
 bool direct_supported(int d_in, int d_out, int rank);               // launch_fused: M within its buffer descriptor (2 GiB less 16 MiB)
+bool lowrank_copy_supported(int d_in, int rank);                    // ... and the channel-major copy within its own
 size_t lowrank_lds_bytes(int d_in, int bt);
 // Stage 1 of the one-launch kernels with `rows` rows of S_r V_r^T per workgroup: channels of the token(s) staged in LDS at a time, 0: none.
 int stage1_chunk(int d_in, int bt, int rows, int unstaged);

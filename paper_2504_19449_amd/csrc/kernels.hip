@@ -1455,6 +1455,8 @@ size_t direct_lds_bytes(int d_in, int splits, int waves, int bt) { return direct
 
 bool direct_supported(int d_in, int d_out, int rank) { return (unsigned long long)(d_in + rank) * (unsigned)d_out * 2u <= kMaxBufferBytes; }
 
+bool lowrank_copy_supported(int d_in, int rank) { return (unsigned long long)d_in * rank * 2u <= kMaxBufferBytes; }
+
 size_t lowrank_lds_bytes(int d_in, int bt)
 {
     return (size_t)bt * lowrank_chunk(d_in, bt) * 2 + 16;
@@ -1623,8 +1625,7 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
         h.SVc = nullptr;
         // up to four tokens and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
         const int parts = (L[i].rank + kTile - 1) / kTile;
-        if (bt <= 4 && cfg[i].lowrank_wgs > 0 && L[i].rank > 0 && L[i].SVc && L[i].t_sum && parts <= cfg[0].waves &&
-            (unsigned long long)L[i].d_in * L[i].rank * 2 <= kMaxBufferBytes) {
+        if (bt <= 4 && cfg[i].lowrank_wgs > 0 && L[i].rank > 0 && L[i].SVc && L[i].t_sum && parts <= cfg[0].waves && lowrank_copy_supported(L[i].d_in, L[i].rank)) {
             h.SVc = L[i].SVc;
             a.lr_wgs = std::min(cfg[i].lowrank_wgs, L[i].d_in / 8);
             // a wave's list (all of its channels at worst) has to fit: at least as many workgroups as keep the launch's LDS under 40 KiB

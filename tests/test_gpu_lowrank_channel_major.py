@@ -2,7 +2,7 @@
 four tokens the one-launch column-tile kernel forms t from the rows of the dropped channels only (Sec. 3.4: the
 low-rank part acts on x - sigma_t(x)).  Same oracle, same tolerances, kept lists bit-exact; every other path of a layer
 prepared this way (more tokens, two launches, the dense reference) reads the row-major copy and must be unchanged.
-Left to itself the library uses the copy only in launches of 2^26 weights or more and at four tokens under the union mask;
+Left to itself the library uses the copy only where the rows left unread pay for a later t (rsparse_config, lowrank_channel_major);
 the small layers here force it with an explicit number of stage-1 workgroups."""
 import numpy as np
 import pytest
@@ -255,3 +255,26 @@ def test_random_shapes_and_settings(seed):
         for _ in range(2):
             _check(L, layer, X16, tau, cmp_mode=cmp_mode, batch_mask_mode=1 if union else 0)
         layer.destroy()
+
+
+@pytest.mark.parametrize("flags", [(0, 1, 1), (1, 0, 0), (1, 1, 1)])
+def test_the_copy_on_some_layers_of_a_group(flags):
+    """q/k/v of 8192 / 1024, rank 1024: above the line from which the library uses the copies by itself, each layer that has one
+    its own, beside row dots for the others."""
+    dt = synth.BF16
+    Ls = [synth.random_layer(8192, d_out, 1024, dt, seed=30 + i) for i, d_out in enumerate((8192, 1024, 1024))]
+    src = synth.DModelInput(8192, config=91, linear=40)
+    X16 = synth.encode16(src.tokens(2), dt)
+    tau = gu.calibrated_tau(Ls[0], src, 0.5)
+    layers = [gu.prepare(L, tau, max_batch=2, out_dtype=rs.F32, lowrank_channel_major=f) for L, f in zip(Ls, flags)]
+    for B in (1, 2):
+        Xd = gu.to_dev16(X16[:B])
+        want = [gu.oracle_linear(L, X16[:B], tau)["Y"] for L in Ls]
+        for _ in range(2):
+            Ys = [gu._alloc_out(l, B) for l in layers]
+            rs.rsparse_linear_group(layers, Xd.data_ptr(), B, [y.data_ptr() for y in Ys], gu.stream_ptr())
+            for l, y, w in zip(layers, Ys, want):
+                rs.rsparse_synchronize(l)
+                gu.check_outputs(gu._read_out(l, y), w, rs.F32)
+    for l in layers:
+        l.destroy()
