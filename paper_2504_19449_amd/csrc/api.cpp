@@ -150,7 +150,7 @@ struct rsparse_layer {
     uint16_t *Ms = nullptr;                // strip-major W + U_r^T: [strips][d_in + rank][strip_w]
     int strip_w = 0, strips = 0;
     long long strip_stride = 0;
-    unsigned long long *t_tag = nullptr;   // [t_slots][rank] {generation, t} of the strip kernel
+    unsigned long long *t_tag = nullptr;   // [t_slots][rank] {tag, t} of the one-launch kernels (16-bit weights)
     int t_slots = 0;
     int32_t *act_seg = nullptr;            // [nz_max][d_in / 8] kept channels per channel range (strip kernel)
     bool last_direct = false;              // the last call went through the one-launch column kernel (16-bit weights)
@@ -167,7 +167,7 @@ struct rsparse_layer {
     bool last_mfma = false;
     int32_t *act_list = nullptr, *act_count = nullptr;
     int *sync = nullptr, *t_flags = nullptr;   // t_flags: inside sync
-    uint32_t *t_pub = nullptr;
+    uint32_t *t_pub = nullptr;             // t of the one-launch 4-bit kernel
     ScratchView last_scratch{};            // the per-call scratch the last call used: the handle's own, or the static one
     uint16_t *hy = nullptr;                // [max_batch][d_out] 16-bit output scratch (gate / up results of rsparse_mlp_gate_up's fallback)
     float *bias = nullptr;                 // [d_out] fp32 static bias (rsparse_set_bias), or null
@@ -711,8 +711,10 @@ rsparse_status build_layer(const rsparse_config *cfg, const uint16_t *W, const u
         RS_HIP(hipMalloc((void **)&L->act_seg, (size_t)L->nz_max * (d_in / 8) * 4));
         RS_HIP(hipMemset(L->act_seg, 0, (size_t)L->nz_max * (d_in / 8) * 4));
         L->n_t = n_t;
-        RS_HIP(hipMalloc((void **)&L->t_pub, n_t * 4));
-        RS_HIP(hipMemset(L->t_pub, 0xff, n_t * 4));          // every entry "not ready"
+        if (q4) {
+            RS_HIP(hipMalloc((void **)&L->t_pub, n_t * 4));
+            RS_HIP(hipMemset(L->t_pub, 0xff, n_t * 4));          // every entry "not ready"
+        }
         RS_HIP(hipMemset(L->chan_bits, 0, d_in * 4));
         RS_HIP(hipMemset(L->t, 0, n_t * 4));
         RS_HIP(hipMemset(L->yacc, 0, n_y * 4));
@@ -1021,7 +1023,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     bool any_q4 = false;
     for (int i = 0; i < n_layers; ++i) any_q4 = any_q4 || layers[i]->q4();
     if (any_q4) {
-        // layers with 4-bit weights: together on the matrix cores, or one at a time, each in its own pair of launches
+        // layers with 4-bit weights: together on the matrix cores or on the vector kernels, or one at a time
         if (G_dev) {
             RS_HIP(launch_gated_input(G_dev, X_dev, layers[0]->xg, (size_t)batch * layers[0]->cfg.d_in, layers[0]->cfg.dtype, s));
             X_dev = layers[0]->xg;
@@ -1388,7 +1390,7 @@ rsparse_status rsparse_synchronize(rsparse_layer *L)
             // leave the counters and generations usable for the next call
             RS_HIP(hipMemset(sp.sync, 0, sp.sync_n * 4));
             RS_HIP(hipMemset(sp.t_tag, 0, sp.n_t * 8));
-            if (sp.t_pub) RS_HIP(hipMemset(sp.t_pub, 0xff, sp.n_t * 4));      // (the static scratch has none)
+            if (sp.t_pub) RS_HIP(hipMemset(sp.t_pub, 0xff, sp.n_t * 4));      // (4-bit layers)
             RS_HIP(hipMemset(sp.yacc, 0, sp.n_y * 4));
             return fail(RSPARSE_EHIP, "a cross-workgroup wait of the one-launch kernel ran out; the last result is invalid");
         }

@@ -263,7 +263,7 @@ __device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t rsrc, uint
 // Stage 1 of the low-rank part inside a one-launch kernel: t_i = sum_c (S_r V_r^T)[i, c] (x - sigma_t(x))_c.
 // Everything else in the launch ends with rows that need t, so this is a chain of latencies first: a workgroup takes `rows`
 // rows of S_r V_r^T, its waves share the channels (wave w every nw-th run of 512), and a lane requests its 8 channels of the
-// token(s) and of kS1Rows rows at once -- the rows do not depend on the token --, masks the token in registers (once for all
+// token(s) and of S1Shape::kRows rows at once -- the rows do not depend on the token --, masks the token in registers (once for all
 // rows) and multiplies; the waves meet in LDS and one lane per row and token publishes.  No staging of the token and no barrier
 // before the last product.  (A wave per row over a token staged in LDS published t 1.5 us later at 4096 channels.)
 // ---------------------------------------------------------------------------------------------
@@ -425,8 +425,13 @@ __device__ __forceinline__ void stage1_rows(const Stage1Args &args, const LayerV
 // ---------------------------------------------------------------------------------------------
 constexpr int kRowsPerWave = 4;
 
+struct RowsArgs {
+    const uint16_t *X;
+    int batch, rows, chunk, skip, wgs, t_slots;      // (as in Stage1Args)
+};
+
 template <int DT, int BT, int PUB, bool EXT = true>
-__device__ __forceinline__ void lowrank_rows(const Stage1Args &a, const LayerView &L, unsigned char *smem, int wg, int z)
+__device__ __forceinline__ void lowrank_rows(const RowsArgs &a, const LayerView &L, unsigned char *smem, int wg, int z)
 {
     // loads per batch and lane, batches in flight: two batches of six for one token; more tokens keep more of the
     // register file for the token values, and a second batch then spills
@@ -586,17 +591,13 @@ __device__ __forceinline__ void lowrank_rows(const Stage1Args &a, const LayerVie
 template <int DT, int BT, bool EXT>
 __device__ __forceinline__ void stage1_tagged(const Stage1Args &s, const LayerView &L, unsigned char *smem, int wg, int z)
 {
-    if constexpr (BT >= 8) {
-        lowrank_rows<DT, BT, kPubTagged, EXT>(s, L, smem, wg, z);
-    } else {
-        if constexpr (BT == 4) {
-            if (s.chunk > 0) {
-                lowrank_rows<DT, BT, kPubTagged, EXT>(s, L, smem, wg, z);
-                return;
-            }
+    if constexpr (BT >= 4) {
+        if (BT >= 8 || s.chunk > 0) {
+            lowrank_rows<DT, BT, kPubTagged, EXT>(RowsArgs{s.X, s.batch, s.rows, s.chunk, s.skip, s.wgs, s.t_slots}, L, smem, wg, z);
+            return;
         }
-        stage1_rows<DT, BT, EXT>(s, L, smem, wg, z);
     }
+    if constexpr (BT < 8) stage1_rows<DT, BT, EXT>(s, L, smem, wg, z);
 }
 
 }  // namespace

@@ -37,9 +37,9 @@ struct LayerView {
     int32_t *act_list;      // [nz][d_in] ascending kept channels of batch tile z (union over its tokens)
     uint32_t *act_bits;     // [nz][d_in] per list entry: bit b = token b of the tile keeps it
     int32_t *act_count;     // [nz]
-    int *sync;              // arrival counters of the one-launch path (layout: kSync* below); zero between calls
-    uint32_t *t_pub;        // [nz][BT][rank] one-launch path: t as fp32 bits; all-ones (not ready) between calls
-    unsigned long long *t_tag;  // [t_slots][rank] strip kernel: {generation of the launch that wrote it, t as fp32 bits}
+    int *sync;              // arrival counters (zero between calls) and generations of the one-launch kernels (layout: kSync* below)
+    uint32_t *t_pub;        // [nz][BT][rank] one-launch 4-bit kernel: t as fp32 bits; all-ones (not ready) between calls (or nullptr)
+    unsigned long long *t_tag;  // [t_slots][rank] one-launch kernels of 16-bit weights: {generation + 1 of the launch that wrote it, t as fp32 bits}
     int t_slots;            // token slots of t_tag (max_batch rounded up to whole batch tiles)
     // strip-major W for the strip kernel: strip s holds columns [s * strip_w, (s + 1) * strip_w) of all d_in + rank
     // rows (row c = W[:, c], row d_in + j = U_r[:, j]) contiguously, [strips][d_in + rank][strip_w]; columns past
@@ -115,7 +115,7 @@ struct Launch {
     int splits;        // channel splits per column tile
     int waves;         // waves per workgroup (first launch / dense axpy)
     int lowrank_rows;  // rows of S_r V_r^T per stage-1 workgroup
-    int lowrank_wgs;   // > 0: stage 1 of the one-launch kernel at one token reads the channel-major copy of S_r V_r^T
+    int lowrank_wgs;   // > 0: stage 1 of the one-launch kernel at up to four tokens reads the channel-major copy of S_r V_r^T
                        // (dropped channels' rows only) with this many workgroups, each on a fixed channel range
     int nontemporal;
     int tile_map;      // 1: tile-fastest workgroup order, 2: XCD-aware (a tile's splits share id mod 8)
@@ -127,7 +127,7 @@ struct Launch {
 // its own: the memory system performs atomics on one line one after the other, whatever their words (256 workgroups that add
 // to 8 tiles' sums, count their arrival and store, by itself: 6.6 us with the counters packed into one line, 4.2 with a line each).
 constexpr int kSyncLine = 32;
-constexpr int kSyncTilesDone = 0;              // column tiles (over all batch tiles) whose outputs have been stored
+constexpr int kSyncTilesDone = 0;              // one-launch 4-bit kernel: column tiles (over all batch tiles) whose outputs have been stored
 constexpr int kSyncError = 1 * kSyncLine;      // set when a bounded wait ran out (results of that call are invalid)
 constexpr int kSyncMaxZ = 4;                   // batch tiles per launch
 // {counter, generation} (the hand-off of t, device_stage1.h), a line each:

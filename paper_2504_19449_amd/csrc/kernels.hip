@@ -152,17 +152,18 @@ __device__ __forceinline__ void reduce_to_yacc(float (&acc)[BT][8], float *s_red
     }
 }
 
+// (what every workgroup reads first lies first: the 4-bit kernel of gate, up and down at 4096 / 11008 took 1.3 % longer with it behind L)
 struct GatherArgs {
-    LayerView L;
     const uint16_t *X;
     int batch, splits, tiles, cap;
-    int lr_wgs;                        // stage-1 workgroups at the front of the grid
-    Stage1Args s1;
+    int lr_wgs, lr_rows, lr_chunk;     // stage-1 workgroups at the front of the grid, rows each, LDS chunk
     int tile_map;
-    void *Y;                           // one-launch path only: the output, [batch][d_out]
-    int nz;                            // one-launch path only: batch tiles in the grid
-    int wait_polls;                    // one-launch path only: bound on re-reads of a t entry that is not ready
-    int dense;                         // 4-bit kernel only: keep every channel (the dense baseline)
+    int dense;                         // 4-bit kernels only: keep every channel (the dense baseline)
+    void *Y;                           // one-launch 4-bit kernel only: the output, [batch][d_out]
+    int nz;                            // ... batch tiles in the grid
+    int wait_polls;                    // ... bound on re-reads of a t entry that is not ready
+    int skip_stage1;                   // ... test hook: the stage-1 workgroups publish nothing (exercises the bound)
+    LayerView L;
 };
 
 // What a gather workgroup of the one-launch kernel needs, side by side: it is fetched in a few wide scalar loads, and all of it
@@ -182,7 +183,10 @@ struct DirectArgs {
     int q_base, q_rem, u_base, u_rem;  // balanced shares of d_in / 8 and of the rank over the splits * waves waves of a tile
     int waves;                         // per workgroup
     int cap_s1;                        // list slots of a wave of stage1_gather
+    int wait_polls;                    // bound on re-reads of a t entry that is not there yet
+    void *Y;                           // the output, [batch][d_out]
     Stage1Args s1;
+    LayerView L;
 };
 
 // All of this wave's earlier atomics and stores have been acknowledged by the memory system.
@@ -218,11 +222,15 @@ __device__ __forceinline__ bool map_tile(const GatherArgs &a, int g, int &tile, 
 // [wg_end[i-1], wg_end[i]) of the grid.
 constexpr int kMaxGroup = 4;
 struct GroupArgs {
-    DirectArgs direct[kMaxGroup];   // (one-launch kernel of 16-bit weights)
-    GatherArgs job[kMaxGroup];
     int wg_end[kMaxGroup];
     int n;
-    int gate_up;       // one-launch kernel: jobs 0 and 1 are the gate and up projections of an MLP (same d_out);
+    GatherArgs job[kMaxGroup];
+};
+struct DirectGroupArgs {
+    DirectArgs job[kMaxGroup];
+    int wg_end[kMaxGroup];
+    int n;
+    int gate_up;       // jobs 0 and 1 are the gate and up projections of an MLP (same d_out);
                        // the column tiles are finished jointly and H = round(silu(g) * u) is stored to job[0].Y
 };
 __device__ __forceinline__ int find_job(const int (&wg_end)[kMaxGroup], int n, int wg, int &local)
@@ -515,16 +523,16 @@ __device__ __forceinline__ void stage1_gather(const DirectArgs &h, const LayerVi
 }
 
 template <int DT, int BT, bool NT, bool EXT, int R>
-__device__ __forceinline__ void direct_body(const GroupArgs &ga, unsigned char *smem)
+__device__ __forceinline__ void direct_body(const DirectGroupArgs &ga, unsigned char *smem)
 {
     RS_STAMP_DECL;
     RS_STAMP(1);
     const int z = blockIdx.z;
     int wg;
     const int job = find_job(ga.wg_end, ga.n, blockIdx.x, wg);
-    const GatherArgs &a = ga.job[job];
+    const DirectArgs &a = ga.job[job];
     const LayerView &L = a.L;
-    DirectArgs h = ga.direct[job];
+    DirectArgs h = a;
     __asm__ volatile("" : "+s"(h.X), "+s"(h.M), "+s"(h.sync), "+s"(h.t_tag), "+s"(h.yacc), "+s"(h.act_bits), "+s"(h.d_in), "+s"(h.d_out), "+s"(h.rank),
                      "+s"(h.batch), "+s"(h.tiles), "+s"(h.splits), "+s"(h.cap), "+s"(h.lr_wgs), "+s"(h.tiles_inv), "+s"(h.tile_map), "+s"(h.union_all),
                      "+s"(h.tau_ge), "+s"(h.q_base), "+s"(h.q_rem), "+s"(h.u_base), "+s"(h.u_rem), "+s"(h.waves), "+s"(h.SVc));
@@ -540,7 +548,7 @@ __device__ __forceinline__ void direct_body(const GroupArgs &ga, unsigned char *
                 return;
             }
         }
-        stage1_tagged<DT, BT, EXT>(ga.direct[job].s1, L, smem, wg, z);
+        stage1_tagged<DT, BT, EXT>(a.s1, L, smem, wg, z);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6), nw = h.waves, nthr = nw * 64;
@@ -866,9 +874,11 @@ __device__ __forceinline__ void q4_consume(Q4State<BT> &st, const LayerView &L, 
 // The two groups are independent, so they share one launch.
 // grid.x = lr_wgs + tiles * splits, grid.z = batch tiles of BT tokens, block = 64 * waves.
 // ---------------------------------------------------------------------------------------------
-template <int DT, int BT, bool NT, bool FUSED, bool Q4 = false, bool EXT = true, int R = kUnroll>
+template <int DT, int BT, bool NT, bool FUSED, bool Q4 = false>
 __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *smem)
 {
+    static_assert(Q4 || !FUSED, "16-bit weights in one launch: direct_body");
+    constexpr int R = kUnroll;
     const int z = blockIdx.z;
     int wg;
     const GatherArgs &a = ga.job[find_job(ga.wg_end, ga.n, blockIdx.x, wg)];
@@ -882,7 +892,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         // every gather workgroup ends with rows that need t: the stage-1 waves issue ahead of the gather waves they
         // share a compute unit with (measured: q/k/v grouped at 8192 wide 37.0 -> 35.6 us, the other launches unchanged)
         if constexpr (FUSED) __builtin_amdgcn_s_setprio(3);
-        lowrank_rows<DT, BT, FUSED ? kPubNotReady : kPubPlain, EXT>(a.s1, L, smem, wg, z);
+        lowrank_rows<DT, BT, FUSED ? kPubNotReady : kPubPlain>(RowsArgs{a.X, a.batch, a.lr_rows, a.lr_chunk, a.skip_stage1, lr_wgs, 0}, L, smem, wg, z);
         return;
     }
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, w = tid >> 6, nw = nthr >> 6;
@@ -891,7 +901,7 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
     const int b0 = z * BT;
     const int nb = min(BT, batch - b0);
     TileRules<BT> rules;
-    load_rules<BT, EXT>(L, b0, nb, rules);
+    load_rules<BT, true>(L, b0, nb, rules);
     const GatherLds s = carve(smem, cap, BT, nw);
     const int col = tile * kTile + lane * 8;
     const bool colok = col < d_out;
@@ -1118,25 +1128,19 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         return;
     }
 
-    // ---- arrive at the tile; the last of its `splits` workgroups owns the finish.  For a gate/up pair
-    //      the two layers share the gate layer's counters and the tile is finished once, by the last
-    //      of both layers' workgroups (Sec. 3.1: H = X W_up^T (.) silu(X W_gate^T)).
+    // ---- arrive at the tile; the last of its `splits` workgroups owns the finish
     wait_own_writes();
     __syncthreads();
-    const bool pair = ga.gate_up != 0;
-    int *const sync = pair ? ga.job[0].L.sync : L.sync;    // owner of the counters: the gate layer
-    float *const yacc_g = pair ? ga.job[0].L.yacc : L.yacc;
-    const int arrivals = pair ? ga.job[0].splits + ga.job[1].splits : a.splits;
-    int *tile_ctr = sync + sync_tile(a.tiles, z, tile);
     if (tid == 0) {
-        const int arrived = __hip_atomic_fetch_add(tile_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int *const line = L.sync + sync_tile(a.tiles, z, tile);
+        const int arrived = __hip_atomic_fetch_add(line, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int last_of_layer = 0;
-        if (arrived == arrivals - 1) {
+        if (arrived == a.splits - 1) {
             // every workgroup of this tile has consumed t; when that holds for all tiles, t_pub can go back
-            __hip_atomic_store(tile_ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int done = __hip_atomic_fetch_add(sync + kSyncTilesDone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(line, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int done = __hip_atomic_fetch_add(L.sync + kSyncTilesDone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (done == a.tiles * a.nz - 1) {
-                __hip_atomic_store(sync + kSyncTilesDone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(L.sync + kSyncTilesDone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 last_of_layer = 1;
             }
         }
@@ -1144,50 +1148,24 @@ __device__ __forceinline__ void sparse_body(const GroupArgs &ga, unsigned char *
         s.misc[13] = last_of_layer;
     }
     __syncthreads();
-    if (s.misc[12] != arrivals - 1) return;
+    if (s.misc[12] != a.splits - 1) return;
 
     // ---- Y = round(Y_s + Y_r): swap the sums out (this re-zeroes yacc for the next call), round once
-    constexpr int TW = Q4 ? kQ4Tile : kTile;
-    for (int c = tid; c < TW; c += nthr) {
-        const int o = tile * TW + c;
+    for (int c = tid; c < kQ4Tile; c += nthr) {
+        const int o = tile * kQ4Tile + c;
         if (o < d_out) {
-            float v[BT], vu[BT];
+            float v[BT];
 #pragma unroll
-            for (int b = 0; b < BT; ++b) {
-                const size_t at = (size_t)(b0 + b) * d_out + o;
-                v[b] = b < nb ? __hip_atomic_exchange(yacc_g + at, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
-                vu[b] = (pair && b < nb)
-                            ? __hip_atomic_exchange(ga.job[1].L.yacc + at, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                            : 0.f;
-            }
+            for (int b = 0; b < BT; ++b)
+                v[b] = b < nb ? __hip_atomic_exchange(L.yacc + (size_t)(b0 + b) * d_out + o, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
 #pragma unroll
-            for (int b = 0; b < BT; ++b) {
-                if (b >= nb) continue;
-                const size_t at = (size_t)(b0 + b) * d_out + o;
-                if (!pair) {
-                    store_out(a.Y, at, EXT ? v[b] + bias_at(L, o) : v[b], L.out_dtype);
-                } else {
-                    // g and u are rounded to the storage type first, as the two projections would store them
-                    const float gb = EXT ? v[b] + bias_at(ga.job[0].L, o) : v[b], ub = EXT ? vu[b] + bias_at(ga.job[1].L, o) : vu[b];
-                    const uint16_t g16 = DT == F16 ? to_f16(gb) : to_bf16(gb);
-                    const uint16_t u16 = DT == F16 ? to_f16(ub) : to_bf16(ub);
-                    ((uint16_t *)ga.job[0].Y)[at] = gated1<DT>(g16, u16);
-                }
-            }
+            for (int b = 0; b < BT; ++b)
+                if (b < nb) store_out(a.Y, (size_t)(b0 + b) * d_out + o, v[b] + bias_at(L, o), L.out_dtype);
         }
     }
     if (s.misc[13]) {
-        auto reset_t = [&](uint32_t *t_pub, int rank) {
-            const int words = a.nz * BT * rank;
-            for (int i = tid; i < words; i += nthr)
-                __hip_atomic_store(t_pub + i, kNotReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        if (pair) {
-            reset_t(ga.job[0].L.t_pub, ga.job[0].L.rank);
-            reset_t(ga.job[1].L.t_pub, ga.job[1].L.rank);
-        } else {
-            reset_t(L.t_pub, L.rank);
-        }
+        const int words = a.nz * BT * L.rank;
+        for (int i = tid; i < words; i += nthr) __hip_atomic_store(L.t_pub + i, kNotReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1223,7 +1201,7 @@ __global__ __launch_bounds__(BT >= 8 ? 256 : 512) void k_sparse_and_t(const Grou
 // code for those is left out -- this kernel's once-per-launch code runs from a cold instruction cache.
 // R: rows per batch of loads of a wave: four (two batches of 4 KiB in flight; with eight 0 to 3 % slower).
 template <int DT, int BT, bool NT, bool EXT, int R>
-__global__ __launch_bounds__(BT >= 8 ? 256 : 512, BT >= 8 ? 3 : 4) void k_rsparse_fused(const GroupArgs ga)
+__global__ __launch_bounds__(BT >= 8 ? 256 : 512, BT >= 8 ? 3 : 4) void k_rsparse_fused(const DirectGroupArgs ga)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     direct_body<DT, BT, NT, EXT, R>(ga, smem);
@@ -1509,7 +1487,8 @@ hipError_t launch_sparse_and_t(const LayerView *L, const Launch *cfg, int n, con
         a.L = L[i]; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = tiles;
         a.cap = gather_cap(L[i].d_in, cfg[i].splits);
         a.lr_wgs = (with_t && L[i].rank > 0) ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        a.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, cfg[0].waves, lowrank_chunk(L[i].d_in, bt));
+        a.lr_rows = cfg[i].lowrank_rows;
+        a.lr_chunk = lowrank_chunk(L[i].d_in, bt);
         a.tile_map = cfg[i].tile_map;
         const int gather_wgs = !with_gather ? 0
                                : cfg[i].tile_map == 2 ? ((tiles + 7) / 8) * 8 * cfg[i].splits : tiles * cfg[i].splits;
@@ -1557,7 +1536,9 @@ hipError_t launch_q4(const LayerView *L, const Launch *cfg, int n, const void *X
         a.L = l; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = l.qtiles;
         a.cap = gather_cap(l.d_in, cfg[i].splits, fused ? l.rank : 0);
         a.lr_wgs = (with_t && !dense && l.rank > 0) ? (l.rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        a.s1 = stage1_args(l, X, batch, cfg[i], a.lr_wgs, cfg[0].waves, lowrank_chunk(l.d_in, bt));
+        a.lr_rows = cfg[i].lowrank_rows;
+        a.lr_chunk = lowrank_chunk(l.d_in, bt);
+        a.skip_stage1 = cfg[i].skip_stage1;
         a.tile_map = 1;
         a.dense = dense ? 1 : 0;
         a.Y = Y_fused;
@@ -1604,52 +1585,46 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
     const int bt = batch_tile(batch);
     const int nz = (batch + bt - 1) / bt;
     if (nz > kSyncMaxZ) return hipErrorInvalidValue;
-    GroupArgs ga{};
+    DirectGroupArgs ga{};
     ga.n = n;
     size_t lds = 0;
     int total = 0;
     for (int i = 0; i < n; ++i) {
         if (!L[i].sync || !Y[i]) return hipErrorInvalidValue;
-        GatherArgs &a = ga.job[i];
+        DirectArgs &h = ga.job[i];
         const int tiles = (L[i].d_out + kTile - 1) / kTile;
-        a.L = L[i]; a.X = (const uint16_t *)X; a.batch = batch; a.splits = cfg[i].splits; a.tiles = tiles;
         if (!L[i].M || cfg[i].splits < 1 || !direct_supported(L[i].d_in, L[i].d_out, L[i].rank) || (L[i].rank > 0 && (!L[i].t_tag || L[i].t_slots < nz * bt)))
             return hipErrorInvalidValue;
         const int R_all = cfg[i].splits * cfg[0].waves;
-        a.cap = direct_cap(L[i].d_in, R_all);
-        a.lr_wgs = L[i].rank > 0 ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
-        if (a.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || (bt >= 4 && cfg[i].lowrank_rows > kRowsPerWave * cfg[0].waves))) return hipErrorInvalidValue;
+        h.lr_wgs = L[i].rank > 0 ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
+        if (h.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || (bt >= 4 && cfg[i].lowrank_rows > kRowsPerWave * cfg[0].waves))) return hipErrorInvalidValue;
         const int chunk = stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, 8);
         size_t lr_lds = stage1_lds_bytes(L[i].d_in, bt, chunk);
-        DirectArgs &h = ga.direct[i];
-        h.SVc = nullptr;
         // up to four tokens and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
         const int parts = (L[i].rank + kTile - 1) / kTile;
         if (bt <= 4 && cfg[i].lowrank_wgs > 0 && L[i].rank > 0 && L[i].SVc && L[i].t_sum && parts <= cfg[0].waves && lowrank_copy_supported(L[i].d_in, L[i].rank)) {
             h.SVc = L[i].SVc;
-            a.lr_wgs = std::min(cfg[i].lowrank_wgs, L[i].d_in / 8);
+            h.lr_wgs = std::min(cfg[i].lowrank_wgs, L[i].d_in / 8);
             // a wave's list (all of its channels at worst) has to fit: at least as many workgroups as keep the launch's LDS under 40 KiB
-            while (direct_lds(h.cap_s1 = direct_cap(L[i].d_in, a.lr_wgs * cfg[0].waves), cfg[0].waves, bt) > 40 * 1024 && a.lr_wgs < L[i].d_in / 8) a.lr_wgs *= 2;
+            while (direct_lds(h.cap_s1 = direct_cap(L[i].d_in, h.lr_wgs * cfg[0].waves), cfg[0].waves, bt) > 40 * 1024 && h.lr_wgs < L[i].d_in / 8) h.lr_wgs *= 2;
             lr_lds = direct_lds(h.cap_s1, cfg[0].waves, bt);
         }
-        h.s1 = stage1_args(L[i], X, batch, cfg[i], a.lr_wgs, cfg[0].waves, chunk);
-        a.tile_map = cfg[i].tile_map;
-        a.Y = Y[i];
-        a.nz = nz;
-        a.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
+        h.s1 = stage1_args(L[i], X, batch, cfg[i], h.lr_wgs, cfg[0].waves, chunk);
+        h.L = L[i]; h.Y = Y[i];
+        h.wait_polls = cfg[i].wait_polls > 0 ? cfg[i].wait_polls : kWaitLimitPolls;
         const int gather_wgs = cfg[i].tile_map == 2 ? ((tiles + 7) / 8) * 8 * cfg[i].splits : tiles * cfg[i].splits;
         if (cfg[i].tile_map != 2 && (unsigned long long)gather_wgs * tiles >= 1ull << 32) return hipErrorInvalidValue;   // (tiles_inv is exact below)
-        h.X = a.X; h.M = L[i].M; h.sync = L[i].sync; h.t_tag = L[i].t_tag; h.yacc = L[i].yacc; h.act_bits = L[i].act_bits;
+        h.X = (const uint16_t *)X; h.M = L[i].M; h.sync = L[i].sync; h.t_tag = L[i].t_tag; h.yacc = L[i].yacc; h.act_bits = L[i].act_bits;
         h.waves = cfg[0].waves;
         h.d_in = L[i].d_in; h.d_out = L[i].d_out; h.rank = L[i].rank; h.batch = batch;
-        h.tiles = tiles; h.splits = cfg[i].splits; h.cap = a.cap; h.lr_wgs = a.lr_wgs;
+        h.tiles = tiles; h.splits = cfg[i].splits; h.cap = direct_cap(L[i].d_in, R_all);
         h.tiles_inv = tiles == 1 ? 0u : (uint32_t)((1ull << 32) / tiles + 1);
-        h.tile_map = a.tile_map; h.union_all = L[i].batch_mask_mode == 1; h.tau_ge = L[i].tau_ge;
+        h.tile_map = cfg[i].tile_map; h.union_all = L[i].batch_mask_mode == 1; h.tau_ge = L[i].tau_ge;
         h.q_base = L[i].d_in / 8 / R_all; h.q_rem = L[i].d_in / 8 % R_all;
         h.u_base = L[i].rank / R_all; h.u_rem = L[i].rank % R_all;
-        total += a.lr_wgs + gather_wgs;
+        total += h.lr_wgs + gather_wgs;
         ga.wg_end[i] = total;
-        const size_t need = direct_lds(a.cap, cfg[0].waves, bt);
+        const size_t need = direct_lds(h.cap, cfg[0].waves, bt);
         if (need > 64 * 1024) return hipErrorInvalidValue;
         lds = std::max(lds, need);
         if (lr_lds > 64 * 1024) return hipErrorInvalidValue;

@@ -55,10 +55,11 @@ struct StripArgs {
 };
 
 struct StripGroupArgs {
-    StripArgs job[kMaxGroupLayers];
-    int wg_end[kMaxGroupLayers];
     int n;
+    int n_front;                       // workgroups of the jobs' ranges
+    int wg_end[kMaxGroupLayers];
     int s1_end[kMaxGroupLayers];       // the jobs' stage-1 workgroups behind all strips instead (all zero: none)
+    StripArgs job[kMaxGroupLayers];
 };
 
 __device__ __forceinline__ int job_of(const int (&wg_end)[kMaxGroupLayers], int n, int wg, int &local)
@@ -93,9 +94,8 @@ __device__ __forceinline__ void strip_body(const StripGroupArgs &ga, unsigned ch
     static_assert(kUnroll == 8, "a lane reads the row codes of a block as one 16-byte vector");
     const int z = blockIdx.z;
     int wg;
-    const int n_front = pin(ga.wg_end[kMaxGroupLayers - 1]);
-    const bool behind = FUSED && (int)blockIdx.x >= n_front;
-    const StripArgs &a = ga.job[behind ? job_of(ga.s1_end, ga.n, (int)blockIdx.x - n_front, wg) : job_of(ga.wg_end, ga.n, blockIdx.x, wg)];
+    const bool behind = FUSED && (int)blockIdx.x >= ga.n_front;
+    const StripArgs &a = ga.job[behind ? job_of(ga.s1_end, ga.n, (int)blockIdx.x - ga.n_front, wg) : job_of(ga.wg_end, ga.n, blockIdx.x, wg)];
     const LayerView &L = a.L;
     if (FUSED) {
         const int lr_wgs = pin(a.lr_wgs), n_strip_wgs = pin(a.tiles) * pin(a.splits);
@@ -545,6 +545,7 @@ hipError_t launch_strip(const LayerView *L, const Launch *cfg, int n, const void
         ga.s1_end[i] = back;
     }
     for (int i = n; i < kMaxGroupLayers; ++i) ga.wg_end[i] = front, ga.s1_end[i] = back;
+    ga.n_front = front;
     dim3 grid(total, 1, nz), block(kWave * waves);
 #define RS_S(DT)                                                                                             \
     RS_STRIP_BT(bt, RS_STRIP_W(L[0].strip_w, {                                                                \
