@@ -1045,8 +1045,9 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
     Launch lc[RSPARSE_MAX_GROUP];
     const int stages = layers[0]->tuning.stages;
     // one launch unless asked otherwise (timing a stage alone needs the two-launch form)
-    bool fused = layers[0]->tuning.launches != 2 && stages == 0;
-    // (the column kernel reaches M through a 32-bit buffer descriptor; larger layers take two launches)
+    const bool one_launch = layers[0]->tuning.launches != 2 && stages == 0;
+    // (the column kernel reaches M through a 32-bit buffer descriptor; larger layers take two launches there)
+    bool fused = one_launch;
     for (int i = 0; i < n_layers; ++i) fused = fused && (!layers[i]->M || direct_supported(layers[i]->cfg.d_in, layers[i]->cfg.d_out, layers[i]->cfg.rank));
     const LaunchTotals all = totals_of(layers, n_layers, batch, fused && !ov);
     for (int i = 0; i < n_layers; ++i) {
@@ -1108,7 +1109,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         uint32_t *bits[RSPARSE_MAX_GROUP];
         for (int i = 0; i < n_layers; ++i) bits[i] = layers[i]->chan_bits;
         const rsparse_tuning &t = layers[0]->tuning;
-        if (fused) {
+        if (one_launch) {
             RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 3, false, t.debug_wait_polls, t.debug_skip_stage1, s));
         } else {
             if (stages != 2) RS_HIP(launch_mfma(v, mv, n_layers, X_dev, batch, Y_devs, bits, layers[0]->cus, 1, false, 0, 0, s));
@@ -1129,7 +1130,7 @@ rsparse_status linear_group_impl(rsparse_layer *const *layers, int32_t n_layers,
         layers[i]->last_stream = s;
         layers[i]->last_batch = batch;
         layers[i]->last_mfma = mfma || cols;
-        layers[i]->last_fused = fused;
+        layers[i]->last_fused = mfma ? one_launch : fused;
         layers[i]->last_bt = 0;
         layers[i]->last_strip = false;
         layers[i]->last_direct = fused && !mfma && !cols;

@@ -1,5 +1,6 @@
 """The one-launch kernels after a bounded wait ran out, and which launches a layer gets.  A wait that runs out is forced from the
 host (stage 1 publishes nothing, a few polls), so every kernel ends normally."""
+import numpy as np
 import pytest
 
 import gpu_util as gu
@@ -59,3 +60,40 @@ def test_tokens_staged_for_stage_1(d_in, rows, B, strip_cols):
         for _ in range(2):
             gu.check_outputs(gu.run_linear(layer, X16[:B])["Y"], gu.oracle_linear(L, X16[:B], tau, batch_mask_mode=mode)["Y"], rs.F32)
         layer.destroy()
+
+
+def test_a_layer_above_the_column_kernels_descriptor():
+    """65536 -> 16384: 2 GiB of W.  On the matrix cores, which do not read the column-major copy, it stays one launch: a wait that is
+    made to run out is reported.  At one and four tokens it takes two launches, which have no such wait.  W is zero but for the
+    first and last 64 rows, whose outputs are checked."""
+    d_in, d_out, rank, dt = 65536, 16384, 8, synth.BF16
+    small = synth.random_layer(d_in, 128, rank, dt, seed=12)
+    W = np.zeros((d_out, d_in), dtype=np.uint16)
+    U = np.zeros((d_out, rank), dtype=np.uint16)
+    rows = np.r_[0:64, d_out - 64:d_out]
+    W[rows], U[rows] = small.W16, small.U16
+    X16, src = gu.tokens_for(small, 8, linear=4)
+    tau = gu.calibrated_tau(small, src, 0.5, n_calib=8)
+    cfg = rs.make_config(d_in, d_out, rank, tau, dt, max_batch=8, out_dtype=rs.F32, dense_rowmajor=1)
+    layer = rs.rsparse_prepare_factors(cfg, W, U, small.SV16)
+    del W
+
+    def check(B):
+        got, want = gu.run_linear(layer, X16[:B]), gu.oracle_linear(small, X16[:B], tau)
+        rs.rsparse_synchronize(layer)
+        gu.check_lists(got, want)
+        gu.check_outputs(got["Y"][:, rows], want["Y"], rs.F32)
+
+    for B in (8, 1, 4):
+        check(B)
+    Xd, Y = gu.to_dev16(X16), gu._alloc_out(layer, 8)
+    rs.rsparse_set_tuning(layer, debug_skip_stage1=1, debug_wait_polls=4)
+    rs.rsparse_linear(layer, Xd.data_ptr(), 8, Y.data_ptr(), gu.stream_ptr())
+    with pytest.raises(rs.RSparseError, match="ran out"):
+        rs.rsparse_synchronize(layer)
+    rs.rsparse_linear(layer, Xd.data_ptr(), 1, Y.data_ptr(), gu.stream_ptr())
+    rs.rsparse_synchronize(layer)
+    rs.rsparse_set_tuning(layer)
+    for B in (8, 1):
+        check(B)
+    layer.destroy()
