@@ -403,6 +403,8 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const Launc
         splits = std::max(1, std::min(splits, max_by_rows));
     }
     splits = std::min(splits, 4096);
+    // (the one-launch kernel divides a workgroup's number by the tiles with a 32-bit reciprocal, exact up to here)
+    if (fused && c.tile_map != 2) splits = std::min<long long>(splits, std::max(1ll, 0xffffffffll / ((long long)L->tiles * L->tiles)));
     while ((fused ? direct_lds_bytes(L->cfg.d_in, splits, c.waves, bt) : gather_lds_bytes(L->cfg.d_in, splits, c.waves, bt)) > 60 * 1024 && splits < 65536) splits *= 2;
     c.splits = splits;
     int lr = t.lowrank_rows;

@@ -97,3 +97,16 @@ def test_a_layer_above_the_column_kernels_descriptor():
     for B in (8, 1):
         check(B)
     layer.destroy()
+
+
+def test_more_splits_than_the_kernels_division_covers():
+    """2^20 outputs are 2048 column tiles: from 1024 splits on the workgroup numbers times the tiles pass 2^32."""
+    L = synth.random_layer(8, 1 << 20, 8, synth.F16, seed=13)
+    X16, src = gu.tokens_for(L, 1, linear=5)
+    layer = gu.prepare(L, 0.0, out_dtype=rs.F32)
+    for tuning in (dict(), dict(splits=1100, waves=1), dict(splits=2, waves=1, tile_map=2)):
+        rs.rsparse_set_tuning(layer, **tuning)
+        got, want = gu.run_linear(layer, X16), gu.oracle_linear(L, X16, 0.0)
+        gu.check_lists(got, want)
+        gu.check_outputs(got["Y"], want["Y"], rs.F32)
+    layer.destroy()
