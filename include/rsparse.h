@@ -397,7 +397,9 @@ rsparse_status rsparse_recipe(int32_t d_in, int32_t d_out, double budget_c, doub
  * 8.5 + 2.2 log2(batch) at 3-4 (vector path); dense 6.5 and 3.6 at one token, 6.95 and 4.2 from two on (6 us above 16 tokens)
  * and the tokens' own reads beyond six of them; from 5 tokens on R-Sparse runs on the matrix cores, reads all of W and costs
  * the dense time, 5 us and the factors at 6.0 TB/s.  The estimates land within about 20 % of the measured times
- * on the benchmark shapes.  Host code.  Any output pointer may be NULL.  Errors: RSPARSE_EINVAL.
+ * on the benchmark shapes, but for R-Sparse on small layers at one and two tokens: the fixed costs are kept as they are although the
+ * one-launch kernel has become faster (about 7.0 and 8.2 us now), so that it is estimated up to 25 % and 40 % too slow there
+ * (q/k/v of 2048 / 512) and the decision errs towards the dense product.  Host code.  Any output pointer may be NULL.  Errors: RSPARSE_EINVAL.
  */
 rsparse_status rsparse_plan_layer(int32_t d_in, int32_t d_out, int32_t rank, double keep_fraction, int32_t group,
                                   int32_t batch, double *us_rsparse_out, double *us_dense_out, int32_t *use_rsparse_out);

@@ -374,6 +374,11 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const Launc
         // one resident round of workgroups for the whole launch: ~1.5 per compute unit, for the 8-wave kernels and for the 4-wave
         // 8-token kernels alike (those hold two workgroups per compute unit at their register count)
         splits = (std::max(tiles, 3 * L->cus / 2) + tiles - 1) / tiles;
+        // two launches, up to four tokens, stage 1 a third of the rows of W or more: that number shared out over the layers, not the tiles
+        // -- no workgroup waits for another there, and stage 1 is cut along with the splits (us at 1, 2, 4 and 8 tokens: q/k/v of 8192 /
+        // 1024, rank 1024, 8 + 64 + 64 splits 35.3, 47.6, 65.1, 129, 20 each 38.8, 52.7, 73.5, 111; but of 4096 / 1024, rank 256 /
+        // 128, 15.1, 20.6, 29.4 and 14.6, 19.1, 28.0)
+        if (!fused && !dense && bt <= 4 && (size_t)6 * all.rank * L->cfg.d_in >= all.weights) splits = (std::max(L->tiles, 3 * L->cus / 2 / all.n) + L->tiles - 1) / L->tiles;
         const int stage1 = all.svc_wgs + all.row_wgs;
         if (fused && !dense && bt <= 4 && all.svc_layers > 0) {
             // ... and with stage 1 as close to 15 of 16 slots as they come, within the slots (us, one token, gather workgroups of a
@@ -1313,7 +1318,9 @@ namespace {
 // Times of one linear in a group of `group`, measured on MI355X with this library's kernels (16-bit weights, weights from HBM):
 // fixed cost of the launch(es), which the group shares, plus bytes / rate.  operand_layout: the layer keeps W in the matrix
 // cores' operand layout (dense_rowmajor = 1), otherwise column-major only.  Within 20 % of what was measured from 4096 x 4096
-// to 8192 x 28672 at ranks of 1/16 and 1/8 but for one shape (8192 x 8192 from 17 tokens on: 30.6 for 25.8 us).
+// to 8192 x 28672 at ranks of 1/16 and 1/8 but for one shape (8192 x 8192 from 17 tokens on: 30.6 for 25.8 us) -- and for R-Sparse
+// at one and two tokens on small layers, where the one-launch kernel has become faster than the constants say (fixed cost about 7.0
+// and 8.2 us: estimates of 4096 x 4096 11.7 for 9.3 and 15.9 for 12.1).  The constants stay, callers compare against them.
 void plan_us(int32_t d_in, int32_t d_out, int32_t rank, double keep_fraction, int32_t group, int32_t batch, bool operand_layout,
              double &us_rs, double &us_dense)
 {
