@@ -110,3 +110,61 @@ def test_more_splits_than_the_kernels_division_covers():
         gu.check_lists(got, want)
         gu.check_outputs(got["Y"], want["Y"], rs.F32)
     layer.destroy()
+
+
+@pytest.mark.parametrize("channel_major", [0, 1])
+def test_one_handle_through_all_forms_in_turn(channel_major):
+    """Tags and generations agree whatever a handle is called for in turn: the gate / up pair, either layer by itself, the group,
+    one to three batch tiles, both forms of stage 1, two launches, the dense product, the static entry, and a wait that runs out in
+    between.  512-wide tiles: 1096 outputs are three, the last ragged."""
+    dt, tokens = synth.BF16, 20
+    Ls = [synth.random_layer(1032, 1096, r, dt, seed=50 + r) for r in (40, 264)]
+    X16, src = gu.tokens_for(Ls[0], tokens, linear=6)
+    tau = gu.calibrated_tau(Ls[0], src, 0.5)
+    layers = [gu.prepare(L, tau, max_batch=tokens, lowrank_channel_major=channel_major) for L in Ls]
+    want = [gu.oracle_linear(L, X16, tau)["Y"] for L in Ls]
+    Xd, s = gu.to_dev16(X16), gu.stream_ptr()
+    forms = dict(mfma_min_batch=33, lowrank_wgs=7 * channel_major)
+
+    def one(i, B, fn=rs.rsparse_linear):
+        Y = gu._alloc_out(layers[i], B)
+        fn(layers[i], Xd.data_ptr(), B, Y.data_ptr(), s)
+        rs.rsparse_synchronize(layers[i])
+        gu.check_outputs(gu._read_out(layers[i], Y), want[i][:B], dt)
+
+    def group(B):
+        Ys = [gu._alloc_out(l, B) for l in layers]
+        rs.rsparse_linear_group(layers, Xd.data_ptr(), B, [y.data_ptr() for y in Ys], s)
+        for l, y, w in zip(layers, Ys, want):
+            rs.rsparse_synchronize(l)
+            gu.check_outputs(gu._read_out(l, y), w[:B], dt)
+
+    def pair(B):
+        H = gu._alloc_out(layers[0], B)
+        rs.rsparse_mlp_gate_up(layers[0], layers[1], Xd.data_ptr(), B, H.data_ptr(), s)
+        for l in layers:
+            rs.rsparse_synchronize(l)
+        g, u = (synth.decode16(synth.encode16(w[:B], dt), dt) for w in want)
+        h = g / (1.0 + np.exp(-g)) * u
+        got = gu._read_out(layers[0], H)
+        # one rounding each of g, u and h to bf16, 2^-9 at most; a sum in another order can move each by one step
+        assert np.linalg.norm(got - h) <= 1.5e-2 * np.linalg.norm(h)
+
+    for turn in range(2):
+        for l in layers:
+            rs.rsparse_set_tuning(l, **forms)
+        for step in (lambda: pair(1), lambda: one(0, 1), lambda: group(3), lambda: one(1, 17), lambda: pair(8), lambda: one(1, 1), lambda: one(0, 20),
+                     lambda: group(12), lambda: pair(2), lambda: one(0, 4, rs.rsparse_linear_static), lambda: one(1, 2), lambda: pair(4)):
+            step()
+        for l in layers:
+            rs.rsparse_set_tuning(l, **dict(forms, lowrank_wgs=-1))
+        pair(1), group(9), one(1, 3)
+        rs.rsparse_set_tuning(layers[1], launches=2, mfma_min_batch=33)
+        one(1, 5), one(1, 1)
+        rs.rsparse_set_tuning(layers[1], **forms, debug_skip_stage1=1, debug_wait_polls=4)
+        Y = gu._alloc_out(layers[1], 17)
+        rs.rsparse_linear(layers[1], Xd.data_ptr(), 17, Y.data_ptr(), s)
+        with pytest.raises(rs.RSparseError, match="ran out"):
+            rs.rsparse_synchronize(layers[1])
+    for l in layers:
+        l.destroy()
