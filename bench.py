@@ -33,7 +33,9 @@ HBM_PEAK_GBS = 8000.0
 REPEATS = 10               # timed brackets of `steps` steps each; the median is reported
 K_TOKENS = 32              # tokens per linear for the statistics of k (kept channels)
 STRIP_COLS = 128           # strip width of the strip-layout variant
-CHANNEL_MAJOR_MIN_WEIGHTS = 1 << 26   # column layout: calls that read this many weights keep S_r V_r^T channel-major as well
+# column layout: calls of this many weights that leave this many bytes of S_r V_r^T unread keep it channel-major as well (from
+# there on the library reads that copy at one token: rsparse_config.lowrank_channel_major)
+CHANNEL_MAJOR_MIN_WEIGHTS, CHANNEL_MAJOR_MIN_UNREAD = 9 << 23, 4.5e6
 
 
 def log(msg):
@@ -254,11 +256,11 @@ class Ring:
                 for name in call:
                     _, d_in, d_out, _ = next(l for l in wl["linears"] if l[0] == name)
                     L = self.base[name]
-                    # column layout: the layers of a call (one launch) that reads 2^26 weights or more also keep S_r V_r^T
-                    # channel-major, so that stage 1 reads the dropped channels' rows only (measured to pay from that
-                    # size on -- the launch is then long enough to hide that t is published later -- and to cost time below)
+                    # column layout: the layers of a call (one launch) in which the library reads the channel-major copy of
+                    # S_r V_r^T (the dropped channels' rows only); the others would hold an unused copy
                     call_weights = sum(di * do for n2, di, do, _ in wl["linears"] if n2 in call)
-                    cm = 1 if strip_cols == 0 and rank and call_weights >= CHANNEL_MAJOR_MIN_WEIGHTS else 0
+                    unread = sum(rank * di for n2, di, _, _ in wl["linears"] if n2 in call)       # half of 2 bytes each
+                    cm = 1 if strip_cols == 0 and rank and call_weights >= CHANNEL_MAJOR_MIN_WEIGHTS and unread >= CHANNEL_MAJOR_MIN_UNREAD else 0
                     self.channel_major[name] = cm
                     cfg = rs.make_config(d_in, d_out, rank, self.tau[name][sparsity], dt, max_batch=1,
                                          dense_rowmajor=rowmajor if strip_cols == 0 else 0, strip_cols=strip_cols,
