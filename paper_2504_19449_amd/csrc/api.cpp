@@ -421,13 +421,14 @@ Launch resolve_launch(const rsparse_layer *L, int batch, bool dense, const Launc
     c.lowrank_rows = std::max(1, std::min(lr, 4 * c.waves));                  // at most 4 rows per wave
     // one launch: the gather workgroups end with rows that need t, so stage 1 is cut as fine as the
     // launch allows: its workgroups get the resident slots (shared by the layers of a group that read the rows)
-    // that the others leave free, with four rows or more -- two at four tokens, one set of stage1_rows (us, gate / up of 1160 / 2304, rank
-    // 72, three tokens: four rows 15.6, two 13.9; 4096 x 4096, rank 256, four tokens 22.8 and 22.4).  A launch that needs a
+    // that the others leave free, with four rows or more -- two, one set of stage1_rows, at four tokens where 15 of 16 slots hold them (us, gate / up of 1160 / 2304, rank
+    // 72, three tokens: four rows 15.6, two 13.9; 4096 x 4096, four tokens: rank 256 22.8 and 22.4; rank 512, all slots taken so, 18.8 and 20.4).  A launch that needs a
     // second round of workgroups loses more than finer stage-1 workgroups gain (measured on 4096 -> 11008 and 28672 -> 8192).
     if (fused && t.lowrank_rows <= 0) {
         const int free_slots = (slots - tiles * splits - all.svc_wgs) / std::max(1, all.n - all.svc_layers);
         const int need = free_slots > 0 ? (L->cfg.rank + free_slots - 1) / free_slots : 4 * c.waves;
-        c.lowrank_rows = std::max(bt == 4 ? 2 : std::max(1, c.waves / 2), std::min(4 * c.waves, need));
+        c.lowrank_rows = std::max(std::max(1, c.waves / 2), std::min(4 * c.waves, need));
+        if (bt == 4 && 2 * (free_slots - slots / 16) >= L->cfg.rank) c.lowrank_rows = 2;
     }
     if (all.svc[i]) c.lowrank_wgs = svc_workgroups(L, batch);
     return c;

@@ -1444,7 +1444,9 @@ size_t lowrank_lds_bytes(int d_in, int bt)
 // rows than `unstaged`, and always at eight tokens, they are masked once, in LDS (us per call at 4, 8 and 16 rows a workgroup, unstaged -
 // staged, four tokens, fixed count, 4096 x 4096, rank 256 22.8 - 22.7, 28.7 - 22.7, 40.0 - 24.3; 8192 x 8192, rank 512 40.6 - 42.9,
 // 43.3 - 43.3, 65.2 - 43.6; 28672 -> 8192, rank 1024 8 rows 92.0 - 97.1; eight tokens, default rows: q/k/v of 8192 / 1024, rank
-// 1024 342 - 90, gate and up of 4096 / 11008, rank 512 120 - 76).  The strip kernel, one workgroup per compute unit at four
+// 1024 342 - 90, gate and up of 4096 / 11008, rank 512 120 - 76).  The one-launch kernel of columns masks anew up to eight rows in
+// launches of 2^25 weights or more, which hide it, and up to four in smaller ones (gate / up of 2048 / 5632, rank 256, five
+// rows, fixed count: 32.0 - 27.9).  The strip kernel, one workgroup per compute unit at four
 // tokens, gains from five rows on (8 rows: 4096 x 4096 20.2 - 16.6, 28672 -> 8192 125 - 107; 4 rows: 16.3 - 16.5, 118 - 116).
 int stage1_chunk(int d_in, int bt, int rows, int unstaged)
 {
@@ -1587,7 +1589,8 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
     if (nz > kSyncMaxZ) return hipErrorInvalidValue;
     DirectGroupArgs ga{};
     ga.n = n;
-    size_t lds = 0;
+    size_t lds = 0, weights = 0;
+    for (int i = 0; i < n; ++i) weights += (size_t)L[i].d_in * L[i].d_out;
     int total = 0;
     for (int i = 0; i < n; ++i) {
         if (!L[i].sync || !Y[i]) return hipErrorInvalidValue;
@@ -1598,7 +1601,7 @@ hipError_t launch_fused(const LayerView *L, const Launch *cfg, int n, const void
         const int R_all = cfg[i].splits * cfg[0].waves;
         h.lr_wgs = L[i].rank > 0 ? (L[i].rank + cfg[i].lowrank_rows - 1) / cfg[i].lowrank_rows : 0;
         if (h.lr_wgs > 0 && (cfg[i].lowrank_rows < 1 || (bt >= 4 && cfg[i].lowrank_rows > kRowsPerWave * cfg[0].waves))) return hipErrorInvalidValue;
-        const int chunk = stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, 8);
+        const int chunk = stage1_chunk(L[i].d_in, bt, cfg[i].lowrank_rows, weights >= ((size_t)1 << 25) ? 8 : 4);
         size_t lr_lds = stage1_lds_bytes(L[i].d_in, bt, chunk);
         // up to four tokens and a channel-major copy of S_r V_r^T: stage 1 reads only the dropped channels' rows
         const int parts = (L[i].rank + kTile - 1) / kTile;
