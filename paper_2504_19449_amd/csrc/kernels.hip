@@ -444,15 +444,16 @@ __device__ __forceinline__ void stage1_gather(const DirectArgs &h, const LayerVi
     __syncthreads();
     RS_STAMP(2);
     const int n = uniform(s_misc[0]), col = part * kTile + lane * 8;
-    // (waves past the last whole set of parts have none)
-    const SharedRows sr{s_off, s_cf, n, n, g < ng ? g * R : n, g < ng ? (ng + g) * R : n, s_misc + 1 + part, 0u, 0u};
+    const SharedRows sr{s_off, s_cf, n, n, g * R, (ng + g) * R, s_misc + 1 + part, 0u, 0u};
     float acc[BT][8];
 #pragma unroll
     for (int b = 0; b < BT; ++b)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[b][e] = 0.f;
     auto none = [](int, bool, unsigned long long (&)[BT]) {};
-    const int done = stream_rows<DT, BT, NT, R>(buffer_of(h.SVc, (uint32_t)d_in * pitch), col < r ? (uint32_t)col * 2u : kOutside, sr, acc, none, none);
+    // (waves past the last whole set of parts have none, and must not claim any either: what they claim nobody else streams)
+    int done = 0;
+    if (g < ng) done = stream_rows<DT, BT, NT, R>(buffer_of(h.SVc, (uint32_t)d_in * pitch), col < r ? (uint32_t)col * 2u : kOutside, sr, acc, none, none);
     RS_STAMP(3);
     RS_STAMP_SET(15, done);
     (void)done;

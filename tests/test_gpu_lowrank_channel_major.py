@@ -257,6 +257,37 @@ def test_random_shapes_and_settings(seed):
         layer.destroy()
 
 
+@pytest.mark.parametrize("rank", [1032, 1536, 2056])
+def test_column_parts_that_do_not_divide_the_waves(rank):
+    """Three parts (1032 and 1536 columns, on four and eight waves) and five (2056, on eight): the waves past the last whole set of
+    parts stream nothing, and with lists longer than the batches that the others start with (32 entries at one token, 16 at
+    two to four, on eight waves) none of the claimed batches may go to them."""
+    dt = synth.BF16
+    L = synth.random_layer(2104, 2088, rank, dt, seed=60 + rank)
+    X16, src = gu.tokens_for(L, 4, linear=6)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    layer = gu.prepare(L, tau, max_batch=4, out_dtype=rs.F32, lowrank_channel_major=1)
+    for waves in (8, 4):
+        for wgs in (1, 3, 16):
+            rs.rsparse_set_tuning(layer, waves=waves, lowrank_wgs=wgs)
+            for B in (1, 2, 3, 4):
+                print("case", rank, waves, wgs, B, flush=True)
+                _check(L, layer, X16[:B], tau)
+    layer.destroy()
+
+
+def test_three_column_parts_at_the_default_launch_shape():
+    """8192 -> 28672, rank 1536, one token: 48 stage-1 workgroups with about 85 dropped channels each."""
+    dt = synth.BF16
+    L = synth.random_layer(8192, 28672, 1536, dt, seed=61)
+    X16, src = gu.tokens_for(L, 1, linear=7)
+    tau = gu.calibrated_tau(L, src, 0.5)
+    layer = gu.prepare(L, tau, out_dtype=rs.F32, lowrank_channel_major=1)
+    for _ in range(2):
+        _check(L, layer, X16, tau)
+    layer.destroy()
+
+
 @pytest.mark.parametrize("flags", [(0, 1, 1), (1, 0, 0), (1, 1, 1)])
 def test_the_copy_on_some_layers_of_a_group(flags):
     """q/k/v of 8192 / 1024, rank 1024: above the line from which the library uses the copies by itself, each layer that has one
