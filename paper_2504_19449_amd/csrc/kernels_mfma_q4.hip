@@ -265,17 +265,23 @@ hipError_t launch_mfma_q4(const LayerView *L, const MatrixView *M, int n, const 
         j.t_blocks = (j.rank + 31) / 32 * 2;
         t_blocks += j.t_blocks;
     }
-    // A compute unit holds two workgroups.  The workgroups of t and of the codes together stay within those slots, or the last of them
-    // begin when the others end, and the codes' divide evenly, or some units have twice the work of others: one workgroup per unit, or two
-    // where that is no fewer splits than twice as many and leaves a wave six steps or more (each split adds to every output; between
-    // three and six the same).  us a pass, bf16, nearest to one workgroup per unit with t in four K slices -> this: gate, up and down of
+    // A compute unit holds two workgroups.  The aim is that the workgroups of t and of the codes together stay within those slots, where the
+    // last of them would begin when the others end, and that no few units have twice the work of the others: one workgroup of codes per unit
+    // (rounded down), or two where that is no fewer splits than twice as many and leaves a wave six steps or more (each split adds to every output;
+    // between three and six the same).  us a pass, bf16, nearest to one workgroup per unit with t in four K slices -> this: gate, up and down of
     // 4096 / 11008 (two, rank 512; 264 + 256 workgroups -> 352 + 128) 119.4 at sixteen tokens -> 103.4, 164.8 at 32 -> 154.5, dense 114.2 ->
     // 100.2, 106.7 at four in fp16 -> 96.0; of 4096 / 14336 54.2 -> 52.9; one per unit alone 107.9, 165.0, 100.3, 98.8 and 54.2.  Two per unit with
     // shorter runs: 4096 x 4096 (eight, 16 splits) 112 -> 128, 2048 / 5632 (six) 185 -> 193.
+    // A single split of 129 to 170 workgroups leaves a third of the units or more idle; there all that the slots hold, whatever the runs (two pairs
+    // of layers, rank d_in / 16, 1 - 2 - 3 splits of 144: d_in 1024 39.9 - 40.8 - 39.1, 1536 50.2 - 50.5 - 43.4, 2048 60.2 - 57.4 - 52.0, 3072
+    // 78.8 - 73.7 - 61.7).  And the nearest number to one per unit, a few units with two, where it makes runs of two steps out of three
+    // (down - nearest: 44 a split, d_in 1536 30.2 - 28.5, 68, 1024 30.8 - 29.7, 52, 1280 30.2 - 28.6; but of three out of four 44, 2048 31.7 - 34.5).
     const int slots = 2 * cus, per_split = units * tiles, slices = mfma_t_slices(t_blocks, a.d_in, kQ4Waves, cus), steps = a.d_in / kMfmaK;
-    const int one = cus / per_split, two = std::max(0, slots - t_blocks * std::min(2, slices)) / per_split;
-    const bool twice = two >= std::max(1, 2 * one) && steps >= 6 * kQ4Waves * two;
-    const int splits = std::max(1, std::min(twice ? two : one, steps / kQ4Waves));
+    const int one = cus / per_split, near = (cus + per_split / 2) / per_split, two = std::max(0, slots - t_blocks * std::min(2, slices)) / per_split;
+    auto longest_run = [&](int k) { return ((steps + k - 1) / k + kQ4Waves - 1) / kQ4Waves; };
+    const bool twice = two >= std::max(1, 2 * one) && (steps >= 6 * kQ4Waves * two || (one == 1 && two >= 3));
+    const bool nearest = one > 0 && near > one && longest_run(one) == 3 && longest_run(near) == 2;
+    const int splits = std::max(1, std::min(twice ? two : nearest ? near : one, steps / kQ4Waves));
     a.t_slices = t_blocks > 0 ? std::max(1, std::min(slices, (slots - per_split * splits) / t_blocks)) : 1;
     int t_total = 0, w_total = 0;
     for (int i = 0; i < kMaxGroupLayers; ++i) {

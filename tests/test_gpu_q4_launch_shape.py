@@ -11,8 +11,10 @@ from test_gpu_q4 import Q4Layer
 pytestmark = pytest.mark.gpu
 
 
-# units x token tiles (of 512 slots): 178 (two per compute unit, six steps a wave; with and without t), 516 (more than slots), few (cut to the steps)
-@pytest.mark.parametrize("shape", [(1536, 22536, 40, 128, 17), (1536, 22536, 0, 128, 32), (64, 65800, 8, 32, 17), (96, 648, 72, 32, 3)])
+# units x token tiles (of 512 slots): 178 (two per compute unit, six steps a wave; with and without t), 516 (more than slots), few (cut to the steps),
+# 138 (three splits, short runs), 68 (the nearest to one per unit: runs of two steps)
+@pytest.mark.parametrize("shape", [(1536, 22536, 40, 128, 17), (1536, 22536, 0, 128, 32), (64, 65800, 8, 32, 17), (96, 648, 72, 32, 3),
+                                   (1024, 17416, 16, 128, 20), (1024, 17408, 24, 128, 9)])
 @pytest.mark.parametrize("dt", [synth.F16, synth.BF16])
 def test_division(shape, dt):
     d_in, d_out, rank, group, B = shape
