@@ -122,8 +122,9 @@ typedef struct {
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
                                 dense_rowmajor = 1; 4-bit weights above 2^25: max_batch >= 2): 0 = default (5 for
-                                rsparse_linear; 3 on 4-bit weights, or, where a layer of the call sets splits or waves, 2, 1 up
-                                to 2^24 of them, and up to 2^25 each in a call of several layers; for rsparse_dense_ref 2, 1 above 8192 channels or from 2^27 weights in a call
+                                rsparse_linear; 3 on 4-bit weights, and with launches = 2, stages != 0 or a layer that one
+                                launch does not reach 2, 1 up to 2^24 weights, and up to 2^25 each in a call of several layers;
+                                for rsparse_dense_ref 2, 1 above 8192 channels or from 2^27 weights in a call
                                 (4-bit: 2, 1 up to 2^25 weights), and with dense_kernel set 2, 4 on layers of 2^25 weights or
                                 more), 33 = never (all batches then run in tiles of up to 8 tokens, 4 on 4-bit
                                 weights, on the vector ALU) */

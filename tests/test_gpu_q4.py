@@ -446,26 +446,37 @@ def test_q4_every_layer_of_a_group_runs_by_its_own_tuning():
         l.destroy()
 
 
-def test_q4_one_token_route_by_size_and_group():
-    """One token: a layer by itself runs on the matrix cores up to 2^24 weights, layers of a grouped call up to 2^25 each; above
-    the vector kernel, which skips dropped channels, is the faster one.  One wave per tile, so that bits tell the kernels apart."""
+def test_q4_routes_by_batch_size_and_group():
+    """The vector kernel in one launch at one and two tokens, alone and in a group, whatever launch shape is asked for; the matrix cores
+    from three.  In two launches (launches = 2) the matrix cores from two tokens, at one up to 2^24 weights for a layer by itself and up to
+    2^25 each in a group.  One wave per tile and no low-rank part, so that bits tell the kernels apart."""
     dt = synth.BF16
-    vector = dict(splits=1, waves=1, mfma_min_batch=33)
+    shape = dict(splits=1, waves=1)
     for d_in, d_out, alone in ((4096, 4096, True), (4096, 4224, False)):
         q = Q4Layer(synth.random_layer(d_in, d_out, 0, dt, seed=d_out), 128)
-        X16, src = gu.tokens_for(q.L, 1)
+        X16, src = gu.tokens_for(q.L, 3)
         tau = gu.calibrated_tau(q.L, src, 0.5)
-        layers = [q.prepare(tau, out_dtype=rs.F32) for _ in range(2)]
-        rs.rsparse_set_tuning(layers[0], **vector)
-        want = gu.run_linear(layers[0], X16)["Y"]
-        rs.rsparse_set_tuning(layers[0], splits=1, waves=1)
-        got = gu.run_linear(layers[0], X16)["Y"]
-        assert np.array_equal(got, want) == (not alone)
-        Xd = gu.to_dev16(X16)
-        Ys = [gu._alloc_out(l, 1) for l in layers]
-        rs.rsparse_linear_group(layers, Xd.data_ptr(), 1, [y.data_ptr() for y in Ys], gu.stream_ptr())
-        assert not np.array_equal(gu._read_out(layers[0], Ys[0]), want)
-        for y in (want, got, gu._read_out(layers[1], Ys[1])):
-            gu.check_outputs(y, q.oracle(X16, tau)["Y"], rs.F32)
+        layers = [q.prepare(tau, max_batch=3, out_dtype=rs.F32) for _ in range(2)]
+
+        def run(B, **tuning):
+            """The layer by itself and in a group of two like it."""
+            for l in layers:
+                rs.rsparse_set_tuning(l, **shape, **tuning)
+            one = gu.run_linear(layers[0], X16[:B])["Y"]
+            Xd = gu.to_dev16(X16[:B])
+            Ys = [gu._alloc_out(l, B) for l in layers]
+            rs.rsparse_linear_group(layers, Xd.data_ptr(), B, [y.data_ptr() for y in Ys], gu.stream_ptr())
+            both = [gu._read_out(l, y) for l, y in zip(layers, Ys)]
+            for y in (one, *both):
+                gu.check_outputs(y, q.oracle(X16[:B], tau)["Y"], rs.F32)
+            return one, both
+
+        for launches, mfma_alone, mfma_group in ((0, (False, False, True), (False, False, True)), (2, (alone, True, True), (True, True, True))):
+            for B in (1, 2, 3):
+                vector, _ = run(B, launches=launches, mfma_min_batch=33)
+                one, both = run(B, launches=launches)
+                assert np.array_equal(one, vector) == (not mfma_alone[B - 1]), (launches, B)
+                for y in both:
+                    assert np.array_equal(y, vector) == (not mfma_group[B - 1]), (launches, B)
         for l in layers:
             l.destroy()
