@@ -1,6 +1,6 @@
 """GPU tests of t = (S_r V_r^T) x on the matrix cores at the ends of its range: |t| beyond fp16's largest number, infinite t,
-and t far below fp16's normal numbers, in all three weight forms (column-major, operand layout, 4-bit), next to the oracle and
-next to the vector kernels, which hold t in fp32."""
+and t far below fp16's normal numbers, in all three weight forms (column-major, operand layout, 4-bit: below three tokens with launches = 2),
+next to the oracle and next to the vector kernels, which hold t in fp32."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ from paper_2504_19449_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-FORMS = [("columns", 5), ("columns", 20), ("operand", 5), ("operand", 20), ("q4", 1), ("q4", 2), ("q4", 20)]
+FORMS = [("columns", 5), ("columns", 20), ("operand", 5), ("operand", 20), ("q4", 1), ("q4", 2), ("q4", 5), ("q4", 20)]
 
 
 class _Form:
@@ -81,7 +81,7 @@ def test_infinite_t_gives_infinite_outputs(form, B, dt):
     layer = F.prepare(0.5, B, cmp_mode=2)
     want = F.oracle(X16, 0.5, cmp_mode=2)["Y"]
     assert np.all(np.isneginf(want[0])) and (B <= 2 or np.all(np.isnan(want[2])))
-    for tuning in ({}, dict(mfma_min_batch=33), {}):
+    for tuning in ({}, dict(launches=2), dict(mfma_min_batch=33), {}):
         rs.rsparse_set_tuning(layer, **tuning)
         got = gu.run_linear(layer, X16)["Y"]
         assert np.array_equal(np.isneginf(got), np.isneginf(want)) and np.array_equal(np.isnan(got), np.isnan(want))
@@ -102,7 +102,7 @@ def test_small_t_keeps_its_32_bits(form, B, dt):
     X16 = synth.encode16(rng.standard_normal((B, 320)) * 1e-4, dt)
     layer = F.prepare(1.0, B)
     want = F.oracle(X16, 1.0)["Y"]
-    for tuning in ({}, dict(mfma_min_batch=33)):
+    for tuning in ({}, dict(launches=2), dict(mfma_min_batch=33)):
         rs.rsparse_set_tuning(layer, **tuning)
         got = gu.run_linear(layer, X16)["Y"]
         err = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)

@@ -124,12 +124,12 @@ def test_q4_units(d_in, d_out, rank, group, dt):
         layer = rs.rsparse_prepare_q4(cfg, Q, S16, Z, group, U16, SV16)
         for B in (16, 5, 32, 2, 17):
             want = oracle.rsparse_linear_q4(Q, S16, Z, U16, SV16, X16[:B], dt, tau, group=group, batch_mask_mode=mode)
+            rs.rsparse_set_tuning(layer, mfma_min_batch=1)             # (left alone: from three tokens on)
             got = gu.run_linear(layer, X16[:B])
             gu.check_lists(got, want)
             gu.check_outputs(got["Y"], want["Y"], rs.F32)
             rs.rsparse_set_tuning(layer, mfma_min_batch=33)
             vec = gu.run_linear(layer, X16[:B])
-            rs.rsparse_set_tuning(layer)
             gu.check_lists(got, vec)
             gu.check_outputs(got["Y"], vec["Y"], rs.F32)
         layer.destroy()
@@ -226,6 +226,7 @@ def test_replayed_graphs_of_the_two_launch_forms(form, B):
         Q, S16, Z = synth.quantize_q4(synth.decode16(L.W16, dt), dt, 32)
         cfg = rs.make_config(L.d_in, L.d_out, L.rank, tau, dt, max_batch=32, out_dtype=rs.F32)
         layer = rs.rsparse_prepare_q4(cfg, Q, S16, Z, 32, L.U16, L.SV16)
+        rs.rsparse_set_tuning(layer, mfma_min_batch=1)                 # (left alone: from three tokens on)
         oracle_of = lambda X: oracle.rsparse_linear_q4(Q, S16, Z, L.U16, L.SV16, X, dt, tau, group=32)["Y"]
     else:
         layer = gu.prepare(L, tau, max_batch=32, out_dtype=rs.F32)

@@ -53,17 +53,17 @@ def test_batches_that_waves_claim(waves, rank, B):
             layer.destroy()
 
 
-@pytest.mark.parametrize("B", [1, 3, 9])
+@pytest.mark.parametrize("B,launches", [(1, 0), (3, 0), (9, 0), (1, 2), (3, 2), (9, 2), (20, 0)])
 @pytest.mark.parametrize("dt", [synth.F16, synth.BF16])
-def test_4_bit_layers_share_the_vector_launches(dt, B):
-    """Three 4-bit layers of different widths and ranks on one input, together and one by one: the same results within the
-    oracle's tolerance, and the lists of each."""
+def test_4_bit_layers_share_the_vector_launches(dt, B, launches):
+    """Three 4-bit layers of different widths and ranks on one input, in one launch and in two (which batches above 16 tokens take
+    by themselves): every layer's outputs and lists against the oracle's."""
     qs = [Q4Layer(synth.make_layer(1152, d_out, rank, dt, config=96, linear=i), 128) for i, (d_out, rank) in enumerate(((2120, 40), (72, 8), (1024, 0)))]
     X16, src = gu.tokens_for(qs[0].L, B, config=96)
     tau = gu.calibrated_tau(qs[0].L, src, 0.5)
     layers = [q.prepare(tau, max_batch=B, out_dtype=rs.F32) for q in qs]
     for l in layers:
-        rs.rsparse_set_tuning(l, mfma_min_batch=33)
+        rs.rsparse_set_tuning(l, mfma_min_batch=33, launches=launches)
     Xd = gu.to_dev16(X16)
     for _ in range(2):
         Ys = [gu._alloc_out(l, B) for l in layers]

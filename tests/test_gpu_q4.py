@@ -48,9 +48,10 @@ def _parity(q, X16, tau, out_dtype=None, tuning=None, **kw):
     X16 = np.atleast_2d(X16)
     layer = q.prepare(tau, max_batch=X16.shape[0], out_dtype=out_dtype, **kw)
     want = q.oracle(X16, tau, cmp_mode=kw.get("cmp_mode", 0), batch_mask_mode=kw.get("batch_mask_mode", 0))
-    # the matrix cores, which most sizes here take by themselves, and the vector kernel in two launches, which takes the
-    # launch shape that `tuning` asks for (launches = 1 is the vector kernel already)
-    for form in ({"mfma_min_batch": 33}, {}) if (tuning or {}).get("launches") != 1 else ({},):
+    # the route that the call takes by itself (matrix cores from three tokens on), the matrix cores, and the vector kernel in one launch (in two above
+    # 16 tokens) and in two, each in the launch shape that `tuning` asks for; where it names the launches, with and without the matrix cores
+    forms = ({}, {"mfma_min_batch": 1}, {"mfma_min_batch": 33, "launches": 1}, {"mfma_min_batch": 33, "launches": 2})
+    for form in forms if "launches" not in (tuning or {}) else ({"mfma_min_batch": 33}, {"mfma_min_batch": 1})[:tuning["launches"]]:
         rs.rsparse_set_tuning(layer, **dict(tuning or {}, **form))
         got = gu.run_linear(layer, X16)
         gu.check_lists(got, want)
@@ -74,14 +75,13 @@ def test_q4_ragged_batch1(ragged_q4, dt, out):
 @pytest.mark.parametrize("mask_mode", [0, 1])
 def test_q4_batches(ragged_q4, B, mask_mode):
     """The matrix cores up to 32 tokens; on the vector kernel up to 4 tokens share one pass over the codes and larger batches
-    run as batch tiles of 4, in both launch forms (the one-launch form covers up to 16 tokens and falls back to two launches
+    run as batch tiles of 4, in both launch forms (the one-launch form covers up to 16 tokens and two launches run
     beyond)."""
     q = ragged_q4[synth.BF16]
     X16, src = gu.tokens_for(q.L, B, linear=B)
     tau = gu.calibrated_tau(q.L, src, 0.5)
     _parity(q, X16, tau, out_dtype=rs.F32, batch_mask_mode=mask_mode)
     _parity(q, X16, tau, batch_mask_mode=mask_mode)
-    _parity(q, X16, tau, out_dtype=rs.F32, batch_mask_mode=mask_mode, tuning=dict(launches=1))
 
 
 def test_q4_edge_thresholds_and_sparsities(ragged_q4):
@@ -103,8 +103,7 @@ def test_q4_launch_shapes(ragged_q4, tuning):
     q = ragged_q4[synth.BF16]
     X16, src = gu.tokens_for(q.L, 3, linear=7)
     tau = gu.calibrated_tau(q.L, src, 0.5)
-    _parity(q, X16, tau, out_dtype=rs.F32, tuning=tuning)                       # two launches (and the matrix cores)
-    _parity(q, X16, tau, out_dtype=rs.F32, tuning=dict(tuning, launches=1))     # the whole layer in one launch
+    _parity(q, X16, tau, out_dtype=rs.F32, tuning=tuning)                       # one launch, two, and the matrix cores
 
 
 @pytest.mark.parametrize("group,d_in", [(32, 1056), (64, 1088), (256, 1280), (1024, 2048)])
@@ -136,17 +135,21 @@ def test_q4_extreme_codes_and_zero_points():
     _parity(q, X16, gu.calibrated_tau(L, src, 0.5), out_dtype=rs.F32)
 
 
-@pytest.mark.parametrize("launches", [1, 2, "vector"])
+# the vector kernel in one launch, in two, and the matrix cores
+LAUNCH_FORMS = [dict(launches=1), dict(launches=2, mfma_min_batch=33), dict(mfma_min_batch=1)]
+
+
+@pytest.mark.parametrize("form", LAUNCH_FORMS)
 @pytest.mark.parametrize("B", [1, 4])
-def test_q4_both_launch_forms_on_a_reused_handle(ragged_q4, launches, B):
-    """Back-to-back calls with different kept sets on one handle, in either form of the vector kernel and on the matrix cores
-    (launches = 2): the one-launch form's arrival counters, published intermediates and accumulators must be back in their
-    idle state after every call."""
+def test_q4_launch_forms_on_a_reused_handle(ragged_q4, form, B):
+    """Back-to-back calls with different kept sets on one handle, in either form of the vector kernel and on the matrix cores:
+    the one-launch form's arrival counters, published intermediates and accumulators, and the sums that the first of two launches
+    leaves to the second, must be back in their idle state after every call."""
     q = ragged_q4[synth.F16]
     X16, src = gu.tokens_for(q.L, B, linear=60 + B)
     tau = gu.calibrated_tau(q.L, src, 0.5)
     layer = q.prepare(tau, max_batch=B, out_dtype=rs.F32)
-    rs.rsparse_set_tuning(layer, **(dict(mfma_min_batch=33) if launches == "vector" else dict(launches=launches)))
+    rs.rsparse_set_tuning(layer, **form)
     for t in (tau, -INF, gu.calibrated_tau(q.L, src, 0.8), INF, tau):
         rs.rsparse_set_tau(layer, t)
         got = gu.run_linear(layer, X16)
@@ -263,7 +266,7 @@ def test_q4_mixed_group_call(ragged_q4):
 def test_q4_config1_shapes_as_benchmarked():
     """The MLP shapes of the benchmark workload (4096 -> 11008 and 11008 -> 4096, bf16, r = 512 and the small
     rank of a sparse-heavy recipe) at the default launch shape, captured into a HIP graph and replayed, both
-    launch forms; every output of every replay against the oracle."""
+    launch forms of the vector kernel and the matrix cores; every output of every replay against the oracle."""
     torch = gu.torch_mod()
     dt = synth.BF16
     for d_in, d_out, rank, kind in ((4096, 11008, 512, "dmodel"), (11008, 4096, 64, "down")):
@@ -271,11 +274,11 @@ def test_q4_config1_shapes_as_benchmarked():
         q = Q4Layer(L, 128)
         X16, src = gu.tokens_for(L, 1, kind=kind, linear=rank)
         tau = gu.calibrated_tau(L, src, 0.5)
-        layer = q.prepare(tau, max_batch=1)
+        layer = q.prepare(tau, max_batch=2)                    # (above 2^25 weights the matrix cores need two tokens' room)
         want = q.oracle(X16, tau)
         Xd = gu.to_dev16(X16)
         Y = gu._alloc_out(layer, 1)
-        for form in (dict(launches=1), dict(launches=2), dict(mfma_min_batch=33)):
+        for form in ({}, *LAUNCH_FORMS):
             rs.rsparse_set_tuning(layer, **form)
             got = gu.run_linear(layer, X16)
             gu.check_lists(got, want)
@@ -371,8 +374,8 @@ def test_q4_dense_rowdot_extreme_codes_group_sizes_and_benchmark_shape():
     layer.destroy()
 
 
-@pytest.mark.parametrize("launches", [1, 2, "vector"])
-def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, launches):
+@pytest.mark.parametrize("form", LAUNCH_FORMS)
+def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, form):
     """NaN is never kept and reaches every output through the low-rank part; -0 is 0; a kept +-Inf channel makes that
     token's outputs non-finite (NaN here, where the definition W~ x gives +-Inf or NaN output by output -- the
     documented deviation of the factored group sums)."""
@@ -388,7 +391,7 @@ def test_q4_nan_inf_and_negative_zero_inputs(ragged_q4, launches):
     x[3, 11] = -np.inf
     X16 = synth.encode16(x, dt)
     layer = q.prepare(tau, max_batch=4, out_dtype=rs.F32)
-    rs.rsparse_set_tuning(layer, **(dict(mfma_min_batch=33) if launches == "vector" else dict(launches=launches)))
+    rs.rsparse_set_tuning(layer, **form)
     got = gu.run_linear(layer, X16)
     want = q.oracle(X16, tau)
     gu.check_lists(got, want)
