@@ -41,7 +41,10 @@ hipError_t set_stamp_buffer(void *, int) { return hipErrorNotSupported; }
 #endif
 namespace {
 
-struct StripArgs {
+// (a job of its own lines of memory: where they fall decides how many a workgroup fetches from the host's memory before anything else, 64 bytes
+// each.  us a pass, eager, next to one another and 8 bytes less in LayerView - so: q/k/v and o of 3712 / 1248 (two) 50.3 - 49.5, of
+// 4096 (four) 115.1 - 114.0, 2048 x 2048 (two) 18.4 - 17.9; in graphs alike)
+struct alignas(64) StripArgs {
     LayerView L;
     const uint16_t *X;
     void *Y;
