@@ -232,7 +232,7 @@ struct DirectGroupArgs {
 // exactly.  Measured, a scan of the whole token and one balanced list of all splits per workgroup -> this (us per pass, one token):
 // 4096 x 4096 10.8 -> 9.3, gate / up and down at 4096 / 11008 (four) 172.7 -> 171.0, an 8192 / 28672 block 206.9 -> 202.1, with a fixed count
 // 5128 / 13832 (two) 146.7 -> 138.4; four tokens at 4096 / 14336 (two) 162.9 -> 154.3.  Equal shares of the list -> claimed batches, with
-// the rows form of stage 1 in a kernel of its own (one token: 60 registers, three workgroups to a compute unit, for 86 and two): 9.3 ->
+// the rows form of stage 1 in a kernel of its own (one token: 62 or 63 registers, three workgroups to a compute unit, for 94 and two): 9.3 ->
 // 9.05, 167 -> 158.7, 201.5 -> 197.0, 136.5 -> 133.4; 154.8 -> 147.0.
 // ---------------------------------------------------------------------------------------------
 // What a wave compacts: chunk j of its n_ch chunks holds channels ((j * step + first) * 8 ..) + 7.
