@@ -185,7 +185,8 @@ rsparse_status rsparse_prepare_factors(const rsparse_config *cfg, const void *W_
  * share, and so do the two layers of rsparse_mlp_gate_up.  From 3 tokens on the products run on the matrix cores, codes
  * converted exactly; rsparse_linear and friends run this path as two
  * launches, which layers of a group share, and read both factors in an operand layout of their own (kept beside the plain
- * ones: 4 rank (d_in + d_out) bytes in all; above 2^25 weights only where max_batch >= 2) (tuning launches = 1 selects the one-launch vector kernel, which takes
+ * ones: 4 rank (d_in + d_out) bytes in all; above 2^25 weights only where max_batch >= 2, up to there at max_batch 1 too, where
+ * launches = 2 and mfma_min_batch take them) (tuning launches = 1 selects the one-launch vector kernel, which takes
  * batches above 4 tokens as tiles of 4, the codes streamed once per tile).  rsparse_dense_ref takes such layers one at a time and gives the dense product with W~:
  * with dense_rowmajor = 1 (a second, row-major copy of the codes, scales and zero points: + d_in * d_out / 2 bytes)
  * as a row-dot GEMV over row-major codes, the form a dense 4-bit decoder would use (tuning dense_kernel = 1 forces the
