@@ -75,3 +75,27 @@ def test_4_bit_layers_share_the_vector_launches(dt, B, launches):
             gu.check_outputs(gu._read_out(l, y), want["Y"], rs.F32)
     for l in layers:
         l.destroy()
+
+
+# splits of the plain rule -> with slots left to stage 1: 32 -> 26, 28 -> 26, 22 -> 15
+@pytest.mark.parametrize("shape", [(2048, (2048, 2048, 2048), 256), (2240, (3328, 3328), 280), (5120, (5120, 2048, 2048), 640)])
+def test_groups_that_leave_slots_to_stage_1(shape):
+    """Layers of a group with large ranks at one token, whose launch has fewer splits than its tiles alone would get: outputs and lists
+    of every layer, each call twice on the same handles, and with a launch shape of the caller's in between."""
+    d_in, d_outs, rank = shape
+    Ls = [synth.random_layer(d_in, d_out, rank, synth.BF16, seed=98 + i) for i, d_out in enumerate(d_outs)]
+    X16, src = gu.tokens_for(Ls[0], 1, config=98)
+    tau = gu.calibrated_tau(Ls[0], src, 0.5)
+    layers = [gu.prepare(L, tau, out_dtype=rs.F32) for L in Ls]
+    want = [gu.oracle_linear(L, X16, tau) for L in Ls]
+    Xd = gu.to_dev16(X16)
+    for tuning in ({}, dict(splits=7), {}):
+        for l in layers:
+            rs.rsparse_set_tuning(l, **tuning)
+        Ys = [gu._alloc_out(l, 1) for l in layers]
+        rs.rsparse_linear_group(layers, Xd.data_ptr(), 1, [y.data_ptr() for y in Ys], gu.stream_ptr())
+        for l, y, w in zip(layers, Ys, want):
+            gu.check_lists({"act": [rs.rsparse_last_active(l, 0)], "union": rs.rsparse_last_active(l, -1)}, w)
+            gu.check_outputs(gu._read_out(l, y), w["Y"], rs.F32)
+    for l in layers:
+        l.destroy()
