@@ -122,7 +122,8 @@ typedef struct {
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
                                 dense_rowmajor = 1; 4-bit weights above 2^25: max_batch >= 2): 0 = default (5 for
-                                rsparse_linear; 3 on 4-bit weights, and with launches = 2, stages != 0 or a layer that one
+                                rsparse_linear; 3 on 4-bit weights, 2 in calls of up to 5 * 2^20 of them in all on up to 2048
+                                channels and groups with large ranks, and with launches = 2, stages != 0 or a layer that one
                                 launch does not reach 2, 1 up to 2^24 weights, and up to 2^25 each in a call of several layers;
                                 for rsparse_dense_ref 2, 1 above 8192 channels or from 2^27 weights in a call
                                 (4-bit: 2, 1 up to 2^25 weights), and with dense_kernel set 2, 4 on layers of 2^25 weights or
@@ -182,7 +183,7 @@ rsparse_status rsparse_prepare_factors(const rsparse_config *cfg, const void *W_
  * of two in [32, 1024] that divides d_in.  The library packs the codes channel-major (one kept channel = one
  * contiguous run of d_out / 2 bytes) and dequantises in registers: per quantisation group it accumulates
  * sum x_c q_c and sum x_c and applies scale and zero point once.  Up to 2 tokens this is one launch, which layers of a group
- * share, and so do the two layers of rsparse_mlp_gate_up.  From 3 tokens on the products run on the matrix cores, codes
+ * share, and so do the two layers of rsparse_mlp_gate_up.  From 3 tokens on (2 in small calls and in groups with large ranks) the products run on the matrix cores, codes
  * converted exactly; rsparse_linear and friends run this path as two
  * launches, which layers of a group share, and read both factors in an operand layout of their own (kept beside the plain
  * ones: 4 rank (d_in + d_out) bytes in all; above 2^25 weights only where max_batch >= 2, up to there at max_batch 1 too, where

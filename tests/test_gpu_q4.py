@@ -483,3 +483,50 @@ def test_q4_routes_by_batch_size_and_group():
                     assert np.array_equal(y, vector) == (not mfma_group[B - 1]), (launches, B)
         for l in layers:
             l.destroy()
+
+
+def test_q4_two_tokens_in_small_calls_and_with_large_ranks():
+    """Two tokens: small calls take the matrix cores, alone and in a group, and so do groups with
+    large ranks; one token stays in one launch.  Bits tell the kernels apart where there is no low-rank part and one wave to a tile."""
+    dt = synth.BF16
+    q = Q4Layer(synth.random_layer(1024, 2048, 0, dt, seed=55), 128)
+    X16, src = gu.tokens_for(q.L, 2)
+    tau = gu.calibrated_tau(q.L, src, 0.5)
+    layers = [q.prepare(tau, max_batch=2, out_dtype=rs.F32) for _ in range(3)]
+
+    def run(n, B, **tuning):
+        for l in layers:
+            rs.rsparse_set_tuning(l, splits=1, waves=1, **tuning)
+        Xd = gu.to_dev16(X16[:B])
+        Ys = [gu._alloc_out(l, B) for l in layers[:n]]
+        rs.rsparse_linear_group(layers[:n], Xd.data_ptr(), B, [y.data_ptr() for y in Ys], gu.stream_ptr())
+        got = [gu._read_out(l, y) for l, y in zip(layers, Ys)]
+        for l, y in zip(layers, got):
+            want = q.oracle(X16[:B], tau)
+            gu.check_outputs(y, want["Y"], rs.F32)
+            gu.check_lists({"act": [rs.rsparse_last_active(l, b) for b in range(B)], "union": rs.rsparse_last_active(l, -1)}, want)
+        return got
+
+    for B in (1, 2):
+        vector = run(1, B, launches=1)[0]
+        for n in (1, 2, 3):                                                # (three are beyond the size)
+            assert all(np.array_equal(y, vector) == (B == 1 or n == 3) for y in run(n, B)), (B, n)
+    for l in layers:
+        l.destroy()
+
+    qs = [Q4Layer(synth.random_layer(8192, 1024, 1024, dt, seed=56 + i), 128) for i in range(2)]
+    X16, src = gu.tokens_for(qs[0].L, 2)
+    tau = gu.calibrated_tau(qs[0].L, src, 0.5)
+    layers = [q.prepare(tau, max_batch=2, out_dtype=rs.F32) for q in qs]
+    Xd = gu.to_dev16(X16)
+    for tuning in ({}, dict(mfma_min_batch=33), {}):
+        for l in layers:
+            rs.rsparse_set_tuning(l, **tuning)
+        Ys = [gu._alloc_out(l, 2) for l in layers]
+        rs.rsparse_linear_group(layers, Xd.data_ptr(), 2, [y.data_ptr() for y in Ys], gu.stream_ptr())
+        for q, l, y in zip(qs, layers, Ys):
+            want = q.oracle(X16, tau)
+            gu.check_outputs(gu._read_out(l, y), want["Y"], rs.F32)
+            gu.check_lists({"act": [rs.rsparse_last_active(l, b) for b in range(2)], "union": rs.rsparse_last_active(l, -1)}, want)
+    for l in layers:
+        l.destroy()
