@@ -122,8 +122,8 @@ typedef struct {
                                 2 XCD-aware (all splits of a tile on ids congruent mod 8) */
     int32_t mfma_min_batch;  /* smallest batch that takes the matrix cores (column-major W: needs max_batch >= 5 or
                                 dense_rowmajor = 1; 4-bit weights above 2^25: max_batch >= 2): 0 = default (5 for
-                                rsparse_linear; 3 on 4-bit weights, 2 in calls of up to 5 * 2^20 of them in all on up to 2048
-                                channels and groups with large ranks, and with launches = 2, stages != 0 or a layer that one
+                                rsparse_linear; 3 on 4-bit weights, 2 in calls of up to 5 * 2^20 of them in all on up to
+                                2048 channels, 3072 for one layer, and in groups with large ranks, and with launches = 2, stages != 0 or a layer that one
                                 launch does not reach 2, 1 up to 2^24 weights, and up to 2^25 each in a call of several layers;
                                 for rsparse_dense_ref 2, 1 above 8192 channels or from 2^27 weights in a call
                                 (4-bit: 2, 1 up to 2^25 weights), and with dense_kernel set 2, 4 on layers of 2^25 weights or
